@@ -372,6 +372,16 @@ __device__ __forceinline__ float wave_allsum_f32(float v) {
     return (a + b) + (c + d);
 }
 
+// n / d for n < 2^31, from the reciprocal that recip_of() (mor_launch.h) forms on the host.
+__device__ __forceinline__ uint32_t recip_div(uint32_t n, uint32_t mul, uint32_t shift) { return __umulhi(2u * n, mul) >> shift; }
+// `off` or, when not `live`, the offset that loads zeros and stores nothing.  (The empty asm keeps the compiler from forming the
+// offset under a branch: such branches split a quantization sweep into basic blocks, the error terms of all chunks are then
+// deferred and their scaled values kept: 114 instead of 80 registers in the per-tensor quantize pass.)
+__device__ __forceinline__ uint32_t off_if(bool live, uint32_t off) {
+    asm volatile("" : "+v"(off));
+    return live ? off : 0x80000000u;
+}
+
 // Index of the operand a work unit belongs to, from the running totals of a grouped launch (uniform per wave).
 __device__ __forceinline__ int group_find(const int64_t* end, int n, int64_t v) {
     int i = 0;

@@ -129,25 +129,47 @@ __device__ __forceinline__ uint32_t amax2_of(const u32x4& v, uint32_t a2) {
     return a2;
 }
 
-// Pass A, strided: one workgroup strides over rows; lanes stride over the row's chunks.
 // A partial word of pass A: low half = amax pattern; high half = (smallest non-zero pattern - 1) when the three-way
 // recipe needs it for Eq. (4) (0xFFFF: no non-zero element seen), else 0.
 __device__ __forceinline__ uint32_t block_allmin_u16(uint32_t v, uint32_t* sh4) { return 0xFFFFu - block_allmax_u32(0xFFFFu - v, sh4); }
-__global__ __launch_bounds__(256) void k_tensor_amax_strided(const uint16_t* __restrict__ x, KShape sh,
-                                                             uint32_t* __restrict__ part, uint32_t three) {
-    __shared__ uint32_t sh4[4];
-    uint32_t a2 = 0u, mn2 = 0xFFFFFFFFu;
-    const int64_t cpr = sh.cols / 8;
-    for (int64_t r = blockIdx.x; r < sh.rows; r += gridDim.x)
-        for (int64_t c = threadIdx.x; c < cpr; c += 256) {
-            const u32x4 v = load16(x + r * sh.ld + c * 8);
-            a2 = amax2_of(v, a2);
-            if (three) mn2 = min_nonzero_m1(v, mn2);
-        }
-    const uint32_t a = block_allmax_u32(fold_max16(a2), sh4);
-    uint32_t mn = 0u;
-    if (three) mn = block_allmin_u16(fold_min16(mn2), sh4);
-    if (threadIdx.x == 0) part[blockIdx.x] = a | (mn << 16);
+
+// Operands whose rows are longer than the operand is wide (column slices of a fused buffer, padded rows) go through the same
+// tiles as dense ones: 16-byte chunks numbered row by row, a tile is kTensorChunksPerBlock consecutive chunks.  A tile's first
+// chunk is divided by the chunks per row once (multiplication by a reciprocal, exact below 2^31), a lane's chunks follow by
+// adding 256 and wrapping at the row's end; addresses are 32-bit byte offsets from the tile's first row, used with
+// bounds-checked buffer accesses.  An operand whose tiles span 2 GB or more (a few columns of very long rows), or whose chunk
+// numbers leave those ranges, is `wide`: plain 64-bit arithmetic, one chunk at a time.
+// Bound by HBM like the dense form.  Measured with its 1 x 128 sibling (SubRows) on a pair of 4099 x 5000 column slices of
+// 10 000-element rows in one call with statistics: 58.5 us, against 103.5 us with kernels of one 16-byte chunk per lane that
+// proved no fallback (a third read of the gradient) and took their statistics in launches of their own.
+struct RowMap {
+    int64_t ld;                    // elements, of x
+    uint32_t cpr;                  // chunks per row (0: wide)
+    uint32_t mul, shift;           // reciprocal of cpr, see recip_div
+    uint32_t step_r, step_c;       // 256 chunks further: rows and chunks
+};
+__device__ __forceinline__ uint32_t row_div(const RowMap& m, uint32_t n) { return recip_div(n, m.mul, m.shift); }
+struct RowPos {
+    uint32_t r, c;                 // row inside the tile, chunk inside the row
+};
+__device__ __forceinline__ int64_t row_tile_first(const RowMap& m, int64_t c_first, uint32_t tid, RowPos& p) {
+    const int64_t row0 = c_first < 0x7FFFFFFF ? (int64_t)row_div(m, (uint32_t)c_first) : c_first / m.cpr;      // uniform over the workgroup
+    const uint32_t n = (uint32_t)(c_first - row0 * m.cpr) + tid;
+    p.r = row_div(m, n);
+    p.c = n - p.r * m.cpr;
+    return row0;
+}
+__device__ __forceinline__ void row_step(const RowMap& m, RowPos& p) {
+    p.r += m.step_r;
+    p.c += m.step_c;
+    const bool wrap = p.c >= m.cpr;
+    p.c -= wrap ? m.cpr : 0u;
+    p.r += wrap ? 1u : 0u;
+}
+// Byte offset from the tile's first row of a chunk of CHUNK bytes, rows of `row_bytes` bytes (both factors below 2^24).
+template <int CHUNK>
+__device__ __forceinline__ uint32_t row_off(const RowPos& p, uint32_t row_bytes, bool live) {
+    return off_if(live, __umul24(p.r, row_bytes) + p.c * CHUNK);
 }
 
 __device__ __forceinline__ uint32_t global_amax_bits(const uint32_t* __restrict__ part, int n_part_amax, uint32_t* sh4) {
@@ -238,47 +260,6 @@ __device__ __forceinline__ void tensor_publish(const TensorAcc& a, const TensorP
     }
 }
 
-// Pass B, strided: persistent workgroups stride over 16-row x 128-column tiles, one chunk per thread.
-template <int CRIT, bool FAKE>
-__global__ __launch_bounds__(256) void k_tensor_quant_strided(const uint16_t* __restrict__ x, KShape sh, uint32_t tiles_x,
-                                                              uint32_t n_tiles, KOut o, const uint32_t* __restrict__ amax_part,
-                                                              int n_amax_part, TensorPartials tp, uint32_t mode) {
-    __shared__ uint32_t sh4[4];
-    const uint32_t abits = global_amax_bits(amax_part, n_amax_part, sh4);
-    if (blockIdx.x == 0 && threadIdx.x == 0) tp.abits[0] = abits;
-    // one block = the group: under GAM the block's own mantissa is the group mantissa, the scale is s_b
-    const float s = block_scale(abits, kE4M3Max, mode, group_mantissa_bits(abits, kE4M3Max, mode));
-    const float s5 = (CRIT == kCritEq3) ? block_scale(abits, kE5M2Max, mode, group_mantissa_bits(abits, kE5M2Max, mode)) : 0.0f;
-    const float s_inv = FAKE ? 1.0f / s : 0.0f;
-    TensorAcc acc{0.0f, 0.0f, 0.0f, 0.0f, 0u};
-    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const uint32_t ty = tile / tiles_x, tx = tile - ty * tiles_x;
-        const int64_t r = (int64_t)ty * 16 + (threadIdx.x >> 4);
-        const int64_t c = (int64_t)tx * 128 + (threadIdx.x & 15) * 8;
-        const bool live = r < sh.rows && c < sh.cols;
-        u32x4 raw; raw.x = 0u; raw.y = 0u; raw.z = 0u; raw.w = 0u;
-        if (live) raw = load16(x + r * sh.ld + c);
-        acc.zero2 = zero2_of(raw, acc.zero2);
-        if (abits < fast_amax_limit(mode)) {
-            u32x4 deq;
-            const u32x2 codes = quant8_fast_deq<false, FAKE>(raw, s, s_inv, acc.e0, acc.e1, deq);
-            if (live) {
-                if constexpr (FAKE) store16(o.fake + r * o.ld_fake + c, deq);
-                else store8(o.fp8 + r * o.ld_fp8 + c, codes);
-            }
-            if constexpr (CRIT == kCritEq3) (void)quant8_fast<true>(raw, s5, acc.f0, acc.f1);
-        } else if (live) {
-            acc.e0 += quant8_careful_mem<false>(x + r * sh.ld + c, s, FAKE ? nullptr : o.fp8 + r * o.ld_fp8 + c,
-                                                FAKE ? o.fake + r * o.ld_fake + c : nullptr, s_inv);
-            if constexpr (CRIT == kCritEq3) acc.f0 += quant8_careful_mem<true>(x + r * sh.ld + c, s5, nullptr);
-        }
-    }
-    tensor_publish<CRIT>(acc, tp, blockIdx.x);
-}
-
-// Pass C: every workgroup re-derives the tensor's decision from the per-workgroup partials
-// (binary64 sums in a fixed order, so all workgroups agree), workgroup 0 writes the block outputs
-// (P = 1), and if the decision is BF16 the grid copies the operand into the fallback buffer.
 // A thread's share of the per-workgroup partial sums of pass B (slots threadIdx.x, threadIdx.x + 256, ... in that order).
 // Eight slots' loads are in flight together: the workgroup that does this is on the critical path of the call (one
 // dependent load per slot took 11 round trips for the 2731 slots of an operand of the layer sweep).  A slot beyond the
@@ -309,74 +290,6 @@ __device__ __forceinline__ void tensor_partial_sums(const float* __restrict__ er
         }
     }
 }
-template <int CRIT>
-__global__ __launch_bounds__(256) void k_tensor_finish(TensorPartials tp, int n_slots, unsigned long long n_padded, KOut o, float th,
-                                                       const uint16_t* __restrict__ x, KShape sh, int flat, uint32_t mode,
-                                                       uint32_t three, const uint32_t* __restrict__ amax_part, int n_amax_part) {
-    __shared__ double shd[4];
-    __shared__ unsigned long long shl[4];
-    __shared__ uint32_t sh4[4];
-    double se = 0.0, se5 = 0.0;
-    unsigned long long sz = 0;
-    tensor_partial_sums<CRIT>(tp.err, tp.err5, tp.zero, n_slots, se, se5, sz);
-    se = block_sum_shfl<double>(se, shd);
-    sz = block_sum_shfl<unsigned long long>(sz, shl);
-    if constexpr (CRIT == kCritEq3) se5 = block_sum_shfl<double>(se5, shd);
-    const uint32_t abits = tp.abits[0];
-    const unsigned long long n = n_padded - sz;
-    if (abits >= kInfBits) { se = (double)__builtin_inff(); se5 = se; }
-    uint32_t mask;
-    if constexpr (CRIT == kCritEq3) mask = (se < se5) ? 0u : 1u;
-    else mask = ((n ? se / (double)n : 0.0) < (double)th) ? 0u : 1u;
-    const float s5 = block_scale(abits, kE5M2Max, mode, group_mantissa_bits(abits, kE5M2Max, mode));
-    uint32_t amin_bits = 0u;
-    if (three && mask == 1u) {             // Eq. (4): the operand is kept in E5M2 if its dynamic range fits
-        amin_bits = global_amin_bits(amax_part, n_amax_part, sh4);
-        if (range_fits_e5m2(abits, amin_bits, n ? 1u : 0u)) mask = 2u;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        const uint32_t mg = group_mantissa_bits(abits, kE4M3Max, mode);
-        const float s = mask == 2u ? s5 : block_scale(abits, kE4M3Max, mode, mg);
-        if (three && o.amin) o.amin[0] = __uint_as_float(amin_bits << 16);
-        o.scale[0] = s;
-        if (mode != kScaleFp32 && o.e8m0) o.e8m0[0] = (uint8_t)(__float_as_uint(s) >> 23);
-        if (mode != kScaleFp32 && o.gmant) { o.gmant[0] = mg; o.gmant[1] = group_mantissa_bits(abits, kE5M2Max, mode); }
-        o.amax[0] = __uint_as_float(abits << 16);
-        o.err_sum[0] = (float)se;
-        o.nnz[0] = n > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)n;
-        if constexpr (CRIT == kCritEq3) o.err5_sum[0] = (float)se5;
-        o.mask[0] = (uint8_t)mask;
-    }
-    if (mask == 2u) {
-        const bool fast = abits < fast_amax_limit(mode);
-        const float s_inv = o.fake ? 1.0f / s5 : 0.0f;
-        const int64_t cpr = sh.cols / 8;
-        for (int64_t r = blockIdx.x; r < sh.rows; r += gridDim.x)
-            for (int64_t c = threadIdx.x; c < cpr; c += 256)
-                requant_chunk_e5m2(x + r * sh.ld + c * 8, o.fake ? nullptr : o.fp8 + r * o.ld_fp8 + c * 8,
-                                   o.fake ? o.fake + r * o.ld_fake + c * 8 : nullptr, s5, s_inv, fast);
-        return;
-    }
-    if (mask == 0u || o.bf16 == nullptr) return;
-    if (flat) {
-        const int64_t n_chunks = sh.rows * sh.cols / 8;
-        const int64_t stride = (int64_t)gridDim.x * 256;
-        int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-        for (; c + 3 * stride < n_chunks; c += 4 * stride) {
-            u32x4 v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = load16(x + (c + u * stride) * 8);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) store16(o.bf16 + (c + u * stride) * 8, v[u]);
-        }
-        for (; c < n_chunks; c += stride) store16(o.bf16 + c * 8, load16(x + c * 8));
-    } else {
-        const int64_t cpr = sh.cols / 8;
-        for (int64_t r = blockIdx.x; r < sh.rows; r += gridDim.x)
-            for (int64_t c = threadIdx.x; c < cpr; c += 256) store16(o.bf16 + r * o.ld_bf16 + c * 8, load16(x + r * sh.ld + c * 8));
-    }
-}
-
 // Copies `n_chunks` 16-byte chunks from x to dst with workgroup `b` of `nb`: tiles of 1024 consecutive chunks (16 KB),
 // four 16-byte loads in flight per lane.
 __device__ __forceinline__ void copy_chunk_tiles(const uint16_t* __restrict__ x, uint16_t* __restrict__ dst, int64_t n_chunks, int b, int nb) {
@@ -772,9 +685,9 @@ __global__ void k_histogram_update(uint32_t* __restrict__ hist, const StatsDev* 
 constexpr int kMaxGroup = 8;           // per-tensor operands / GAM pre-pass per launch (their table shares the 4 KB
                                        // kernel-argument segment with the statistics riders)
 
-template <int CRIT, bool FAKE>
+template <int CRIT, bool FAKE, bool ROWS>
 __global__ __launch_bounds__(256) void k_sub1x128_group(GroupSub g) {
-    sub_group_body<CRIT, FAKE>(g, (int64_t)blockIdx.x, (int64_t)gridDim.x);
+    sub_group_body<CRIT, FAKE, false, ROWS>(g, (int64_t)blockIdx.x, (int64_t)gridDim.x, nullptr, 0.0f);
 }
 
 // Statistics of sub-tensor operands of a group: pass 1 writes one partial record per workgroup into
@@ -1006,20 +919,22 @@ struct SoloStats {
     StatsRec* rec;         // [gridDim.x]: 128 bytes apart, the first kSoloRecWords dwords used
     StatsDev* out;
     int64_t n_part;
+    unsigned long long total_elems;
+    uint32_t edge_missing;     // elements that a block of the last column lacks (ragged operands)
     float near_tol;
     int n_rec;
 };
 // (Six workgroups per compute unit as for the kernel without statistics: the second launch bound makes the compiler fit
 // Eq. 2's variants into 80 registers, which it does without spilling; Eq. 3's variants need more either way.)
-template <int CRIT, bool FAKE>
-__global__ __launch_bounds__(256, CRIT == kCritEq3 ? 4 : 6) void k_sub1x128_solo_stats(SubRiders g, SoloStats s) {
+template <int CRIT, bool FAKE, bool ROWS>
+__global__ __launch_bounds__(256, CRIT == kCritEq3 || ROWS ? 4 : 6) void k_sub1x128_solo_stats(SubRiders g, SoloStats s) {
     __shared__ SubStatsShared ssh;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (threadIdx.x < 17) reinterpret_cast<uint32_t*>(&ssh)[threadIdx.x] = 0u;      // c[16], n
     ssh.e_lane[threadIdx.x] = 0.0;
     ssh.n_lane[threadIdx.x] = 0u;
     __syncthreads();
-    sub_group_body<CRIT, FAKE, true>(g, (int64_t)blockIdx.x, (int64_t)gridDim.x, &ssh, s.near_tol);
+    sub_group_body<CRIT, FAKE, true, ROWS>(g, (int64_t)blockIdx.x, (int64_t)gridDim.x, &ssh, s.near_tol);
     const double e_w = wave_allsum_f64(ssh.e_lane[threadIdx.x]);
     const uint32_t n_w = wave_allsum_u32(ssh.n_lane[threadIdx.x]);
     if (lane == 0) { ssh.e[w] = e_w; atomicAdd(&ssh.n, n_w); }
@@ -1059,15 +974,17 @@ __global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStat
         tot.e += __longlong_as_double((long long)q[j][8]);
         tot.n += (uint32_t)q[j][9];
     }
-    tot.eb = 128ull * tot.c[12];          // (per lane; the sums below add the lanes' products)
+    tot.eb = 128ull * tot.c[12] - (unsigned long long)s.edge_missing * tot.c[14];      // (per lane; the sums below add the lanes' products)
+    tot.c[14] = 0u;                       // (no E5M2 blocks here: the slot counted BF16 blocks of a ragged last column)
     stats_fast_reduce(tot, fin);
-    stats_emit(tot, s.out, s.n_part, (unsigned long long)s.n_part * 128ull, nullptr);
+    stats_emit(tot, s.out, s.n_part, s.total_elems, nullptr);
 }
 
 // Per-tensor operands of a group share three launches (amax, quantize, finish + fallback copy).
 struct TensorOp {
     const uint16_t* x;
     int64_t n_chunks, n_tiles;
+    int64_t chunks_per_row;              // STRIDED kernels
     KOut o;
     float th;
     uint32_t mode;                       // scaling algorithm
@@ -1080,6 +997,7 @@ struct TensorOp {
     uint32_t* flush_part;                // [n_amax] lower bounds on the number of elements certain to flush to zero
     unsigned long long flush_need;       // that many certain flushes prove the BF16 decision (0 = proof not attempted)
     StatsDev* stats;                     // optional
+    RowMap rm;                           // operands with padded leading dimensions (STRIDED kernels)
 };
 struct GroupTensor {
     int n;
@@ -1087,6 +1005,13 @@ struct GroupTensor {
     float near_tol;
     TensorOp op[kMaxGroup];
 };
+// Element offset of 16-byte chunk `c` in a matrix with rows of `ld` elements, any size (paths that are not bound by it).
+template <bool STRIDED>
+__device__ __forceinline__ int64_t tensor_chunk_off(const TensorOp& t, int64_t c, int64_t ld) {
+    if constexpr (!STRIDED) return c * 8;
+    const int64_t cpr = t.chunks_per_row, r = c / cpr;
+    return r * ld + (c - r * cpr) * 8;
+}
 // Pass A also gathers a PROOF of the BF16 decision where one exists.  Section 4.1.3 observes that a
 // per-tensor scale falls back as soon as ~2.4 % of the values flush to zero; each flushed non-zero
 // element contributes exactly 1 to the error sum of Eq. (1)-(2), so "flushed >= th * N" already implies
@@ -1097,6 +1022,7 @@ struct GroupTensor {
 // pass (2 more bytes read per element) is skipped.  The outputs are the same either way.
 // Workgroups from `stats_first` on do not belong to pass A: they compute the partial statistics records of the batch's
 // sub-tensor operands (whose kernels have already run), in the shadow of this bandwidth-bound pass.
+template <bool STRIDED>
 __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupStats riders, int stats_first) {
     if ((int)blockIdx.x >= stats_first) { stats_partial_body(riders, (int)blockIdx.x - stats_first); return; }
     __shared__ uint32_t sh4[4];
@@ -1109,10 +1035,19 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
     uint32_t mn2 = 0xFFFFFFFFu;                   // three-way recipe: smallest non-zero pattern, minus one, per half-word
     for (int64_t tile = b; tile < t.n_tiles; tile += t.n_amax) {
         const int64_t c0 = tile * kTensorChunksPerBlock + threadIdx.x;
-        if (c0 + 7 * 256 < t.n_chunks) {
+        if (c0 + 7 * 256 < t.n_chunks && !(STRIDED && t.rm.cpr == 0u)) {
             u32x4 v[8];
+            if constexpr (STRIDED) {
+                RowPos pos;
+                const int64_t row0 = row_tile_first(t.rm, tile * kTensorChunksPerBlock, threadIdx.x, pos);
+                const BufRsrc rx = make_buf(t.x + row0 * t.rm.ld);
+                const uint32_t row_bytes = (uint32_t)t.rm.ld * 2u;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = load16(t.x + (c0 + u * 256) * 8);
+                for (int u = 0; u < 8; ++u) { v[u] = buf_load16(rx, row_off<16>(pos, row_bytes, true), 0u); row_step(t.rm, pos); }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = load16(t.x + (c0 + u * 256) * 8);
+            }
 #pragma unroll
             for (int u = 0; u < 8; ++u) a2 = amax2_of(v[u], a2);
             if (three) {
@@ -1135,7 +1070,7 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
         } else {
             for (int u = 0; u < 8; ++u)
                 if (c0 + u * 256 < t.n_chunks) {
-                    const u32x4 v = load16(t.x + (c0 + u * 256) * 8);
+                    const u32x4 v = load16(t.x + tensor_chunk_off<STRIDED>(t, c0 + u * 256, t.rm.ld));
                     a2 = amax2_of(v, a2);
                     if (three) mn2 = min_nonzero_m1(v, mn2);
                 }
@@ -1161,7 +1096,8 @@ __device__ __forceinline__ bool tensor_fallback_proven(const TensorOp& t, unsign
     f = block_sum_shfl<unsigned long long>(f, shl);
     return f >= t.flush_need;
 }
-template <int CRIT, bool FAKE>
+// STRIDED: operands with padded leading dimensions (see RowMap).
+template <int CRIT, bool FAKE, bool STRIDED>
 __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
     __shared__ uint32_t sh4[4];
     const int op = group_find32(g.slot_end, g.n, blockIdx.x);
@@ -1171,8 +1107,22 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
     uint8_t* __restrict__ fp8 = t.o.fp8;
     const int64_t n_chunks = t.n_chunks, n_tiles = t.n_tiles, G = t.n_slots;
     u32x4 bufA[kTensorChunksPerThread];
+    const bool wide = STRIDED && t.rm.cpr == 0u;             // chunk by chunk, in the careful path below
     auto load_tile = [&](u32x4* raw, int64_t tile) {
         const int64_t c0 = tile * kTensorChunksPerBlock + threadIdx.x;
+        if constexpr (STRIDED) {
+            // (wide: a null window, so all chunks read as zeros here; the careful path reads them itself)
+            RowPos pos;
+            const int64_t row0 = wide ? 0 : row_tile_first(t.rm, tile * kTensorChunksPerBlock, threadIdx.x, pos);
+            const BufRsrc rx = make_buf_window(x + row0 * t.rm.ld, wide ? 0u : 0x7FFFFFFFu);
+            const uint32_t row_bytes = (uint32_t)t.rm.ld * 2u;
+#pragma unroll
+            for (int u = 0; u < kTensorChunksPerThread; ++u) {
+                raw[u] = buf_load16(rx, row_off<16>(pos, row_bytes, c0 + u * 256 < n_chunks), 0u);
+                row_step(t.rm, pos);
+            }
+            return;
+        }
 #pragma unroll
         for (int u = 0; u < kTensorChunksPerThread; ++u) {
             const int64_t c = c0 + u * 256;
@@ -1191,7 +1141,7 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
     const uint32_t mode = t.mode;
     const float s = block_scale(abits, kE4M3Max, mode, group_mantissa_bits(abits, kE4M3Max, mode));
     const float s5 = (CRIT == kCritEq3) ? block_scale(abits, kE5M2Max, mode, group_mantissa_bits(abits, kE5M2Max, mode)) : 0.0f;
-    const bool fast = abits < fast_amax_limit(mode);
+    const bool fast = abits < fast_amax_limit(mode) && !wide;
     const bool dual = CRIT == kCritEq3 && s5 == 128.0f * s;
     const bool emit = !(proven && t.lean != 0u);             // lean payload: the codes of a proven BF16 operand are not stored
     const float s_inv = FAKE ? 1.0f / s : 0.0f;
@@ -1206,15 +1156,36 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
         const int64_t c0 = c_first + threadIdx.x;
         const int64_t left = n_chunks - c_first;
         const uint32_t valid = (uint32_t)(left < kTensorChunksPerBlock ? left : kTensorChunksPerBlock);      // chunks of this tile
-        const BufRsrc r8 = make_buf_window(fp8 + c_first * 8, (FAKE || !emit) ? 0u : valid * 8u);
-        const BufRsrc rb = make_buf_window(bf16 + c_first * 8, proven ? valid * 16u : 0u);
-        const BufRsrc rf = make_buf_window(fakep + c_first * 8, (FAKE && !proven) ? valid * 16u : 0u);
+        int64_t row0 = 0;
+        RowPos pos0{0u, 0u};
+        if constexpr (STRIDED) row0 = wide ? 0 : row_tile_first(t.rm, c_first, threadIdx.x, pos0);
+        const int64_t at8 = STRIDED ? row0 * t.o.ld_fp8 : c_first * 8, atb = STRIDED ? row0 * t.o.ld_bf16 : c_first * 8,
+                      atf = STRIDED ? row0 * t.o.ld_fake : c_first * 8;
+        const BufRsrc r8 = make_buf_window(fp8 + at8, (FAKE || !emit) ? 0u : (STRIDED ? 0x7FFFFFFFu : valid * 8u));
+        const BufRsrc rb = make_buf_window(bf16 + atb, proven && !wide ? (STRIDED ? 0x7FFFFFFFu : valid * 16u) : 0u);
+        const BufRsrc rf = make_buf_window(fakep + atf, (FAKE && !proven) ? (STRIDED ? 0x7FFFFFFFu : valid * 16u) : 0u);
         const uint32_t off8 = threadIdx.x * 8u, off16 = threadIdx.x * 16u;
+        // byte offsets of chunk u in the payload and in the BF16 output; STRIDED lanes beyond the last chunk get none
+        RowPos pos = pos0;
+        auto at_fp8 = [&](int u) -> uint32_t {
+            if constexpr (!STRIDED) return off8 + u * 2048u;
+            const uint32_t v = row_off<8>(pos, (uint32_t)t.o.ld_fp8, threadIdx.x + u * 256u < valid);
+            row_step(t.rm, pos);
+            return v;
+        };
+        auto at_16 = [&](int u, int64_t ld) -> uint32_t {
+            if constexpr (!STRIDED) return off16 + u * 4096u;
+            const uint32_t v = row_off<16>(pos, (uint32_t)ld * 2u, threadIdx.x + u * 256u < valid);
+            row_step(t.rm, pos);
+            return v;
+        };
 #pragma unroll
         for (int u = 0; u < kTensorChunksPerThread; ++u) acc.zero2 = zero2_of(raw[u], acc.zero2);
         asm volatile("" : "+v"(acc.zero2));      // counted here, not sunk below the sweep (which would keep the masked words alive)
 #pragma unroll
-        for (int u = 0; u < kTensorChunksPerThread; ++u) buf_store16(rb, off16 + u * 4096u, raw[u]);       // proven fallback
+        for (int u = 0; u < kTensorChunksPerThread; ++u) buf_store16(rb, at_16(u, t.o.ld_bf16), raw[u]);       // proven fallback
+        pos = pos0;
+        if constexpr (STRIDED) asm volatile("" : "+v"(pos.r), "+v"(pos.c));      // the sweep's offsets are formed chunk by chunk, not kept from here
         if (fast && FAKE && proven) {
             // fake quantization of an operand already proven to stay in BF16: the output is the input (stored above);
             // only the error sums are still needed
@@ -1230,8 +1201,8 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
             for (int u = 0; u < kTensorChunksPerThread; ++u) {
                 u32x4 deq;
                 const u32x2 codes = quant8_dual<FAKE>(raw[u], s, s_inv, acc.e0, acc.e1, acc.f0, acc.f1, deq);
-                if constexpr (FAKE) buf_store16(rf, off16 + u * 4096u, deq);
-                else buf_store8(r8, off8 + u * 2048u, 0u, codes);
+                if constexpr (FAKE) buf_store16(rf, at_16(u, t.o.ld_fake), deq);
+                else buf_store8(r8, at_fp8(u), 0u, codes);
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else if (fast) {
@@ -1239,8 +1210,8 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
             for (int u = 0; u < kTensorChunksPerThread; ++u) {
                 u32x4 deq;
                 const u32x2 codes = quant8_fast_deq<false, FAKE>(raw[u], s, s_inv, acc.e0, acc.e1, deq);
-                if constexpr (FAKE) buf_store16(rf, off16 + u * 4096u, deq);
-                else buf_store8(r8, off8 + u * 2048u, 0u, codes);
+                if constexpr (FAKE) buf_store16(rf, at_16(u, t.o.ld_fake), deq);
+                else buf_store8(r8, at_fp8(u), 0u, codes);
                 if constexpr (CRIT == kCritEq3) (void)quant8_fast<true>(raw[u], s5, acc.f0, acc.f1);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -1249,9 +1220,15 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
             for (int u = 0; u < kTensorChunksPerThread; ++u) {
                 const int64_t c = c0 + u * 256;
                 if (c < n_chunks) {
-                    acc.e0 += quant8_careful_mem<false>(x + c * 8, s, (FAKE || !emit) ? nullptr : fp8 + c * 8,
-                                                        (FAKE && !proven) ? fakep + c * 8 : nullptr, s_inv);
-                    if constexpr (CRIT == kCritEq3) acc.f0 += quant8_careful_mem<true>(x + c * 8, s5, nullptr);
+                    const uint16_t* __restrict__ src = x + tensor_chunk_off<STRIDED>(t, c, t.rm.ld);
+                    acc.e0 += quant8_careful_mem<false>(src, s, (FAKE || !emit) ? nullptr : fp8 + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fp8),
+                                                        (FAKE && !proven) ? fakep + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fake) : nullptr, s_inv);
+                    if constexpr (CRIT == kCritEq3) acc.f0 += quant8_careful_mem<true>(src, s5, nullptr);
+                    if (wide) {
+                        const u32x4 v = load16(src);
+                        acc.zero2 = pk_sub_u16(zero2_of(v, acc.zero2), 0x00040004u);       // counted as eight zeros above
+                        if (proven) store16(bf16 + tensor_chunk_off<STRIDED>(t, c, t.o.ld_bf16), v);
+                    }
                 }
             }
         }
@@ -1266,7 +1243,7 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
     tensor_publish<CRIT>(acc, tp, b);
 }
 // Workgroups from `stats_first` on combine the riders' partial statistics records (one workgroup per operand).
-template <int CRIT>
+template <int CRIT, bool STRIDED>
 __global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, GroupStats riders, int stats_first) {
     if ((int)blockIdx.x >= stats_first) { stats_final_body(riders, (int)blockIdx.x - stats_first); return; }
     const int op = group_find32(g.copy_end, g.n, blockIdx.x);
@@ -1321,7 +1298,7 @@ __global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, Grou
             const bool near = fabs((double)metric - (double)t.th) <= (double)g.near_tol * (double)t.th;
             const unsigned long long total = (unsigned long long)t.n_chunks * 8ull;
             stats_finish(st, 1, total, (double)err_f, nnz32, mask == 1u ? 1ull : 0ull, near ? 1ull : 0ull, mask == 2u ? 1ull : 0ull,
-                         mask == 1u ? total : 0ull, mask == 2u ? total : 0ull, proven ? 1u : 0u);
+                         mask == 1u ? total : 0ull, mask == 2u ? total : 0ull, proven && !STRIDED ? 1u : 0u);
         }
     }
     if (mask == 2u) {
@@ -1329,11 +1306,26 @@ __global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, Grou
         uint16_t* __restrict__ fakep = t.o.fake;
         const float s_inv = fakep ? 1.0f / s5 : 0.0f;
         for (int64_t c = (int64_t)b * 256 + threadIdx.x; c < t.n_chunks; c += (int64_t)nb * 256)
-            requant_chunk_e5m2(t.x + c * 8, fakep ? nullptr : t.o.fp8 + c * 8, fakep ? fakep + c * 8 : nullptr, s5, s_inv, fast);
+            requant_chunk_e5m2(t.x + tensor_chunk_off<STRIDED>(t, c, t.rm.ld), fakep ? nullptr : t.o.fp8 + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fp8),
+                               fakep ? fakep + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fake) : nullptr, s5, s_inv, fast);
         return;
     }
     if (proven || mask == 0u || t.o.bf16 == nullptr) return;
-    copy_chunk_tiles(t.x, t.o.bf16, t.n_chunks, b, nb);
+    if constexpr (STRIDED) {
+        const int64_t stride = (int64_t)nb * 256;
+        int64_t c = (int64_t)b * 256 + threadIdx.x;
+        for (; c + 3 * stride < t.n_chunks; c += 4 * stride) {
+            u32x4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = load16(t.x + tensor_chunk_off<true>(t, c + u * stride, t.rm.ld));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) store16(t.o.bf16 + tensor_chunk_off<true>(t, c + u * stride, t.o.ld_bf16), v[u]);
+        }
+        for (; c < t.n_chunks; c += stride)
+            store16(t.o.bf16 + tensor_chunk_off<true>(t, c, t.o.ld_bf16), load16(t.x + tensor_chunk_off<true>(t, c, t.rm.ld)));
+    } else {
+        copy_chunk_tiles(t.x, t.o.bf16, t.n_chunks, b, nb);
+    }
 }
 
 // Group loop of Algorithm 1 for sub-tensor operands: the operand's amax (partials of pass A) gives the
@@ -1442,6 +1434,7 @@ constexpr int64_t kSubFlatMaxBlocks = 1536;   // workgroups of 4 waves, each wav
                                               // registers let be resident, so no workgroup waits for another to end (one 64 MiB operand, cold
                                               // caches: 21.0 us at 1536 against 23.2 us at 2048 (one unit per wave); 112 MiB: 32.1 against 34.5 us;
                                               // 224 MiB: 65 us either way)
+constexpr int64_t kSubRowsMaxBlocks = 1280;   // the ROWS form's registers (90) let five be resident per compute unit
 static_assert(kSubFlatMaxBlocks <= 2 * kSoloFinalThreads, "k_solo_stats_final takes two records per lane");
 static int clamp_grid_y(int64_t v) { return (int)(v < 1 ? 1 : (v > 65535 ? 65535 : v)); }
 
@@ -1467,41 +1460,19 @@ static hipError_t launch_sub1x128(const uint16_t* x, const KShape& sh, const KOu
     return hipGetLastError();
 }
 
-static hipError_t launch_tensor(const uint16_t* x, const KShape& sh, const KOut& o, int crit, float th, uint32_t mode, uint32_t three,
-                                void* ws, hipStream_t st, KProf* prof) {
-    const TensorPlan pl = plan_tensor(sh.rows, sh.cols);
-    char* w = static_cast<char*>(ws);
-    uint32_t* amax_part = reinterpret_cast<uint32_t*>(w + pl.off_amax_part);
-    TensorPartials tp{reinterpret_cast<float*>(w + pl.off_err_part), reinterpret_cast<float*>(w + pl.off_err5_part),
-                      reinterpret_cast<uint32_t*>(w + pl.off_nnz_part), reinterpret_cast<uint32_t*>(w + pl.off_decision)};
-    const int n_amax = (int)(sh.rows < kMaxAmaxBlocks ? sh.rows : kMaxAmaxBlocks);
-    { ProfScope ps(prof, kKernTensorAmax, st); k_tensor_amax_strided<<<dim3(n_amax), dim3(256), 0, st>>>(x, sh, amax_part, three); }
-    const int64_t gx = (sh.cols + 127) / 128, gy = (sh.rows + 15) / 16;
-    if (gx * gy > 0x7FFFFFFF) return hipErrorInvalidValue;
-    // 16-bit zero counters per lane: at most 8 zeros per tile and lane, so 4096 tiles per workgroup are safe
-    const int64_t min_blocks = (gx * gy + 4095) / 4096;
-    if (min_blocks > kMaxQuantBlocks) return hipErrorInvalidValue;
-    const int n_slots = (int)(gx * gy < kMaxQuantBlocks ? gx * gy : kMaxQuantBlocks);
-    const unsigned long long n_padded = (unsigned long long)(gx * gy) * 2048ull;
-    {
-        ProfScope ps(prof, kKernTensorQuant, st);
-        const uint32_t tx = (uint32_t)gx, nt = (uint32_t)(gx * gy);
-        if (o.fake) {
-            if (crit == kCritEq3) k_tensor_quant_strided<kCritEq3, true><<<dim3(n_slots), dim3(256), 0, st>>>(x, sh, tx, nt, o, amax_part, n_amax, tp, mode);
-            else k_tensor_quant_strided<kCritEq2, true><<<dim3(n_slots), dim3(256), 0, st>>>(x, sh, tx, nt, o, amax_part, n_amax, tp, mode);
-        } else {
-            if (crit == kCritEq3) k_tensor_quant_strided<kCritEq3, false><<<dim3(n_slots), dim3(256), 0, st>>>(x, sh, tx, nt, o, amax_part, n_amax, tp, mode);
-            else k_tensor_quant_strided<kCritEq2, false><<<dim3(n_slots), dim3(256), 0, st>>>(x, sh, tx, nt, o, amax_part, n_amax, tp, mode);
-        }
-    }
-    {
-        ProfScope ps(prof, kKernFallbackCopy, st);
-        const int grid = (o.bf16 || three) ? 2048 : 1;
-        const int flat = (sh.ld == sh.cols && o.ld_bf16 == sh.cols) ? 1 : 0;
-        if (crit == kCritEq3) k_tensor_finish<kCritEq3><<<dim3(grid), dim3(256), 0, st>>>(tp, n_slots, n_padded, o, th, x, sh, flat, mode, three, amax_part, n_amax);
-        else k_tensor_finish<kCritEq2><<<dim3(grid), dim3(256), 0, st>>>(tp, n_slots, n_padded, o, th, x, sh, flat, mode, three, amax_part, n_amax);
-    }
-    return hipGetLastError();
+// Fills the chunk layout of a per-tensor operand (or of the amax pass of one): rows of sh.ld elements, outputs as in o.
+static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o) {
+    const int64_t cpr = sh.cols / 8;
+    t.n_chunks = sh.rows * cpr;
+    t.n_tiles = (t.n_chunks + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
+    t.chunks_per_row = cpr;
+    t.rm = RowMap{};
+    t.rm.ld = sh.ld;
+    if (cpr >= (1 << 28) || !row_map_fits(longest_row(sh, o), kTensorChunksPerBlock / cpr + 2)) return;      // wide: cpr stays 0
+    t.rm.cpr = (uint32_t)cpr;
+    recip_of(cpr, &t.rm.mul, &t.rm.shift);
+    t.rm.step_r = (uint32_t)(256 / cpr);
+    t.rm.step_c = (uint32_t)(256 % cpr);
 }
 
 // ---- batches ---------------------------------------------------------------------------------
@@ -1510,10 +1481,10 @@ constexpr int kStatsMaxWg = 256;
 
 // Which kernels take an operand.
 enum Route {
-    kRouteTensorGroup,      // per-tensor, dense: grouped three-pass kernels
-    kRouteTensorStrided,    // per-tensor, padded leading dimensions
-    kRouteSubFlat,          // 1 x 128, dense, whole blocks, two types, FP8 payload: the persistent grouped kernel
-    kRouteSubGeneral,       // 1 x 128, everything else
+    kRouteTensorGroup,      // per-tensor: grouped three-pass kernels (dense operands and padded leading dimensions in launches of their own)
+    kRouteSubFlat,          // 1 x 128, two types, dense, a whole number of 32-block units: the persistent grouped kernel
+    kRouteSubRows,          // 1 x 128, two types, padded leading dimensions or ragged edges: the ROWS form of the same kernel
+    kRouteSubGeneral,       // 1 x 128, three types, or rows too long for 32-bit offsets inside a unit
     kRouteTeam,             // 128 x 128, 64 x 64, per-channel rows: a team of lanes keeps the block in registers
     kRouteSubCol,           // 128 x 1
     kRouteChannelCol        // per-channel columns
@@ -1522,20 +1493,23 @@ bool item_is_flat(const BatchItem& it) { return is_flat(it.sh, it.o); }
 Route route_of(const BatchItem& it) {
     const bool plain = !it.three;
     switch (it.gran) {
-    case kGranTensor: return item_is_flat(it) ? kRouteTensorGroup : kRouteTensorStrided;
-    case kGranSub:      // (with bands of rows as GAM groups the flat kernel takes whole 32-block units only: no renumbered tail)
-        return (plain && item_is_flat(it) && it.sh.cols % 128 == 0 && (it.group_rows == 0 || (it.sh.rows * (it.sh.cols / 128)) % 32 == 0))
-                   ? kRouteSubFlat : kRouteSubGeneral;
+    case kGranTensor: return kRouteTensorGroup;
+    case kGranSub: {
+        const int64_t bpr = (it.sh.cols + 127) / 128;
+        if (!plain) return kRouteSubGeneral;
+        if (item_is_flat(it) && it.sh.cols % 128 == 0 && (it.sh.rows * bpr) % 32 == 0) return kRouteSubFlat;
+        return bpr < (1 << 24) && row_map_fits(longest_row(it.sh, it.o), 32 / bpr + 2) ? kRouteSubRows : kRouteSubGeneral;
+    }
     case kGranBlock: case kGranBlock64: case kGranRow: return kRouteTeam;
     case kGranSubCol: return kRouteSubCol;
     default: return kRouteChannelCol;
     }
 }
 int64_t item_parts(const BatchItem& it) { return geom_parts(make_geom(it.gran, it.sh.rows, it.sh.cols)); }
-// A dense 1 x 128 operand of whole 32-block units whose blocks are decided one by one can gather its statistics in its own
-// kernel (k_sub1x128_solo_stats) when it is alone in its launch and the batch has no per-tensor launch they could ride on.
+// A 1 x 128 operand whose blocks are decided one by one can gather its statistics in its own kernel (k_sub1x128_solo_stats)
+// when it is alone in its launch and the batch has no per-tensor launch they could ride on.
 bool solo_stats_candidate(const BatchItem& it) {
-    return it.stats && it.scope == 0 && route_of(it) == kRouteSubFlat && item_parts(it) % 32 == 0;
+    return it.stats && it.scope == 0 && (route_of(it) == kRouteSubFlat || route_of(it) == kRouteSubRows);
 }
 int stats_wgs(int64_t n_part) {                        // riding in a launch of 256-lane workgroups
     if (n_part <= 4096) return 1;                       // one workgroup writes the result directly
@@ -1679,9 +1653,10 @@ void BatchRun::group_mantissas() {
     for (int base = 0; base < cnt && err == hipSuccess; base += kMaxGroupTensor) {
         const int m = cnt - base < kMaxGroupTensor ? cnt - base : kMaxGroupTensor;
         GroupGam gg; gg.n = m;
-        GroupTensor ga; ga.n = 0; ga.near_tol = near_tol;
-        int slot_of[kMaxGroupTensor];
-        int64_t total_tiles = 0;
+        GroupTensor ga[2];                                // dense operands, padded leading dimensions
+        int64_t total_tiles[2] = {0, 0};
+        int slot_of[kMaxGroupTensor];                     // 2 * slot + layout
+        for (int l = 0; l < 2; ++l) { ga[l].n = 0; ga[l].near_tol = near_tol; }
         for (int k = 0; k < m; ++k) {
             const int i = idx[base + k];
             const BatchItem& it = items[i];
@@ -1701,37 +1676,68 @@ void BatchRun::group_mantissas() {
             }
             uint32_t* part = reinterpret_cast<uint32_t*>(carve(2 * sizeof(uint32_t) * kProveMaxWg));
             q.amax_part = part;
-            if (it.sh.ld == it.sh.cols) {
-                TensorOp& t = ga.op[ga.n];
-                t = TensorOp{};
-                t.x = it.x;
-                t.n_chunks = it.sh.rows * it.sh.cols / 8;
-                t.n_tiles = (t.n_chunks + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
-                t.amax_part = part;
-                total_tiles += t.n_tiles;
-                slot_of[k] = ga.n++;
-            } else if (err == hipSuccess) {
-                q.n_amax = (int)(it.sh.rows < kMaxAmaxBlocks ? it.sh.rows : kMaxAmaxBlocks);
-                ProfScope ps(prof, kKernGroupAmax, st);
-                k_tensor_amax_strided<<<dim3(q.n_amax), dim3(256), 0, st>>>(it.x, it.sh, part, 0u);
+            const int l = it.sh.ld == it.sh.cols ? 0 : 1;
+            TensorOp& t = ga[l].op[ga[l].n];
+            t = TensorOp{};
+            t.x = it.x;
+            set_tensor_layout(t, it.sh, KOut{});
+            t.amax_part = part;
+            total_tiles[l] += t.n_tiles;
+            slot_of[k] = 2 * ga[l].n++ + l;
+        }
+        int a_end[2] = {0, 0};
+        for (int l = 0; l < 2; ++l)
+            for (int j = 0; j < ga[l].n; ++j) {
+                TensorOp& t = ga[l].op[j];
+                t.n_amax = share(t.n_tiles, total_tiles[l], kMaxAmaxBlocks, t.n_tiles);
+                a_end[l] += t.n_amax;
+                ga[l].amax_end[j] = a_end[l];
             }
-        }
-        int a_end = 0;
-        for (int j = 0; j < ga.n; ++j) {
-            TensorOp& t = ga.op[j];
-            t.n_amax = share(t.n_tiles, total_tiles, kMaxAmaxBlocks, t.n_tiles);
-            a_end += t.n_amax;
-            ga.amax_end[j] = a_end;
-        }
         for (int k = 0; k < m; ++k)
-            if (slot_of[k] >= 0) gg.op[k].n_amax = ga.op[slot_of[k]].n_amax;
+            if (slot_of[k] >= 0) gg.op[k].n_amax = ga[slot_of[k] & 1].op[slot_of[k] >> 1].n_amax;
         if (err != hipSuccess) return;
-        if (ga.n) {
-            GroupStats none; none.n = 0; none.near_tol = near_tol;
+        GroupStats none; none.n = 0; none.near_tol = near_tol;
+        if (ga[0].n) {
             ProfScope ps(prof, kKernGroupAmax, st);
-            k_tensor_amax_group<<<dim3(a_end), dim3(256), kResidency3, st>>>(ga, none, a_end);
+            k_tensor_amax_group<false><<<dim3(a_end[0]), dim3(256), kResidency3, st>>>(ga[0], none, a_end[0]);
+        }
+        if (ga[1].n) {
+            ProfScope ps(prof, kKernGroupAmax, st);
+            k_tensor_amax_group<true><<<dim3(a_end[1]), dim3(256), kResidency3, st>>>(ga[1], none, a_end[1]);
         }
         { ProfScope ps(prof, kKernGroupMantissa, st); k_gam_prepare<<<dim3(m), dim3(256), 0, st>>>(gg); }
+    }
+}
+
+// Adds an operand to the table of a 1 x 128 launch (all but its running total of units).
+template <class G>
+void sub_table_add(G& g, const BatchItem& it, const uint32_t* gam) {
+    const int k = g.n++;
+    const int64_t bpr = (it.sh.cols + 127) / 128;
+    g.x[k] = it.x; g.o[k] = it.o; g.th[k] = it.th; g.defer[k] = it.scope == 1;
+    g.mode[k] = (uint8_t)it.scaling; g.gam[k] = gam; g.prove[k] = scope_proof_applies(it) ? 1 : 0;
+    g.group_rows[k] = (uint32_t)it.group_rows; g.bpr[k] = (uint32_t)bpr;
+    g.ld[k] = it.sh.ld; g.cols[k] = it.sh.cols; g.n_part[k] = it.sh.rows * bpr;
+    recip_of(bpr < 1 << 24 ? bpr : 1, &g.mul[k], &g.shift[k]);      // (used by the ROWS form only, whose rows are shorter)
+}
+template <bool ROWS>
+void launch_sub_group(const dim3& grid, int crit, bool fake, const GroupSub& g, hipStream_t st) {
+    if (fake) {
+        if (crit == kCritEq3) k_sub1x128_group<kCritEq3, true, ROWS><<<grid, dim3(256), 0, st>>>(g);
+        else k_sub1x128_group<kCritEq2, true, ROWS><<<grid, dim3(256), 0, st>>>(g);
+    } else {
+        if (crit == kCritEq3) k_sub1x128_group<kCritEq3, false, ROWS><<<grid, dim3(256), 0, st>>>(g);
+        else k_sub1x128_group<kCritEq2, false, ROWS><<<grid, dim3(256), 0, st>>>(g);
+    }
+}
+template <bool ROWS>
+void launch_solo_stats(const dim3& grid, int crit, bool fake, const SubRiders& one, const SoloStats& ss, hipStream_t st) {
+    if (fake) {
+        if (crit == kCritEq3) k_sub1x128_solo_stats<kCritEq3, true, ROWS><<<grid, dim3(256), 0, st>>>(one, ss);
+        else k_sub1x128_solo_stats<kCritEq2, true, ROWS><<<grid, dim3(256), 0, st>>>(one, ss);
+    } else {
+        if (crit == kCritEq3) k_sub1x128_solo_stats<kCritEq3, false, ROWS><<<grid, dim3(256), 0, st>>>(one, ss);
+        else k_sub1x128_solo_stats<kCritEq2, false, ROWS><<<grid, dim3(256), 0, st>>>(one, ss);
     }
 }
 
@@ -1745,37 +1751,36 @@ void BatchRun::sub_tensor_operands(int crit) {
     bool team_has[2] = {false, false};
     for (int i = 0; i < n; ++i)
         if (route[i] == kRouteTeam && items[i].crit == crit && team_kind_of(items[i]) == 0) team_has[items[i].o.fake ? 1 : 0] = true;
-    // ---- 1x128 sub-channel operands, persistent grouped kernel (FP8 payload, then fake quantization)
-    for (int fake = 0; fake < 2 && err == hipSuccess; ++fake) {
+    // ---- 1x128 sub-channel operands, persistent grouped kernel (FP8 payload, then fake quantization; flat, then ROWS form)
+    for (int variant = 0; variant < 4 && err == hipSuccess; ++variant) {
+        const bool fake = (variant & 1) != 0, rows_form = (variant & 2) != 0;
         GroupSub g; g.n = 0;
         int64_t total = 0;
         int newest = -1;                                  // the item added to the table last
         auto flush = [&]() {
             if (g.n == 0 || err != hipSuccess) { g.n = 0; total = 0; return; }
             int64_t blocks = (total + 3) / 4;
-            if (blocks > kSubFlatMaxBlocks) blocks = kSubFlatMaxBlocks;
+            const int64_t max_blocks = rows_form ? kSubRowsMaxBlocks : kSubFlatMaxBlocks;
+            if (blocks > max_blocks) blocks = max_blocks;
             if (g.n == 1 && !will_ride && solo_stats_candidate(items[newest])) {
                 // a lone operand: its kernel gathers the statistics as well
                 SoloStats ss;
                 ss.rec = reinterpret_cast<StatsRec*>(carve(sizeof(StatsRec) * (size_t)blocks));
                 ss.out = static_cast<StatsDev*>(items[newest].stats);
                 ss.n_part = item_parts(items[newest]);
+                ss.total_elems = (unsigned long long)(items[newest].sh.rows * items[newest].sh.cols);
+                ss.edge_missing = (uint32_t)((128 - items[newest].sh.cols % 128) % 128);
                 ss.near_tol = near_tol;
                 ss.n_rec = (int)blocks;
                 if (err != hipSuccess) { g.n = 0; total = 0; return; }
-                SubRiders one; one.n = 1;
-                one.unit_end[0] = g.unit_end[0]; one.x[0] = g.x[0]; one.o[0] = g.o[0]; one.th[0] = g.th[0]; one.defer[0] = g.defer[0];
-                one.mode[0] = g.mode[0]; one.prove[0] = g.prove[0]; one.gam[0] = g.gam[0]; one.group_rows[0] = g.group_rows[0]; one.bpr[0] = g.bpr[0];
+                SubRiders one; one.n = 0;
+                sub_table_add(one, items[newest], gam_of[newest]);
+                one.unit_end[0] = total;
                 {
                     ProfScope ps(prof, kKernSub1x128, st);
                     const dim3 grid((unsigned)blocks);
-                    if (fake) {
-                        if (crit == kCritEq3) k_sub1x128_solo_stats<kCritEq3, true><<<grid, dim3(256), 0, st>>>(one, ss);
-                        else k_sub1x128_solo_stats<kCritEq2, true><<<grid, dim3(256), 0, st>>>(one, ss);
-                    } else {
-                        if (crit == kCritEq3) k_sub1x128_solo_stats<kCritEq3, false><<<grid, dim3(256), 0, st>>>(one, ss);
-                        else k_sub1x128_solo_stats<kCritEq2, false><<<grid, dim3(256), 0, st>>>(one, ss);
-                    }
+                    if (rows_form) launch_solo_stats<true>(grid, crit, fake, one, ss, st);
+                    else launch_solo_stats<false>(grid, crit, fake, one, ss, st);
                 }
                 { ProfScope ps2(prof, kKernStatsFinal, st); k_solo_stats_final<<<dim3(1), dim3(kSoloFinalThreads), 0, st>>>(ss); }
                 stats_done[newest] = true;
@@ -1783,50 +1788,28 @@ void BatchRun::sub_tensor_operands(int crit) {
                 return;
             }
             ProfScope ps(prof, kKernSub1x128, st);
-            if (fake) {
-                if (crit == kCritEq3) k_sub1x128_group<kCritEq3, true><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(g);
-                else k_sub1x128_group<kCritEq2, true><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(g);
-            } else {
-                if (crit == kCritEq3) k_sub1x128_group<kCritEq3, false><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(g);
-                else k_sub1x128_group<kCritEq2, false><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(g);
-            }
+            if (rows_form) launch_sub_group<true>(dim3((unsigned)blocks), crit, fake, g, st);
+            else launch_sub_group<false>(dim3((unsigned)blocks), crit, fake, g, st);
             g.n = 0; total = 0;
         };
         for (int i = 0; i < n; ++i) {
             const BatchItem& it = items[i];
-            if (route[i] != kRouteSubFlat || it.crit != crit || (it.o.fake != nullptr) != (fake != 0)) continue;
-            const int64_t n_part = item_parts(it), n_units = n_part / 32, n_full = n_units * 32, n_tail = n_part - n_full;
-            if (n_units > 0 && n_units <= kSubRiderMaxUnits && team_has[fake] && riders.table.n < kMaxSubRiders &&
-                (riders.table.n == 0 || riders.fake == (fake != 0))) {
+            if (route[i] != (rows_form ? kRouteSubRows : kRouteSubFlat) || it.crit != crit || (it.o.fake != nullptr) != fake) continue;
+            const int64_t n_units = (item_parts(it) + 31) / 32;
+            if (!rows_form && n_units <= kSubRiderMaxUnits && team_has[fake] && riders.table.n < kMaxSubRiders &&
+                (riders.table.n == 0 || riders.fake == fake)) {
                 SubRiders& r = riders.table;
                 rider_units += n_units;
-                r.unit_end[r.n] = rider_units; r.x[r.n] = it.x; r.o[r.n] = it.o; r.th[r.n] = it.th; r.defer[r.n] = it.scope == 1;
-                r.mode[r.n] = (uint8_t)it.scaling; r.gam[r.n] = gam_of[i]; r.prove[r.n] = scope_proof_applies(it) ? 1 : 0;
-                r.group_rows[r.n] = (uint32_t)it.group_rows; r.bpr[r.n] = (uint32_t)(it.sh.cols / 128);
-                ++r.n;
-                riders.fake = fake != 0;
+                sub_table_add(r, it, gam_of[i]);
+                r.unit_end[r.n - 1] = rider_units;
+                riders.fake = fake;
                 riders.blocks = (rider_units + 3) / 4 < kSubFlatMaxBlocks ? (rider_units + 3) / 4 : kSubFlatMaxBlocks;
-            } else if (n_units > 0) {
+            } else {
                 total += n_units;
-                g.unit_end[g.n] = total; g.x[g.n] = it.x; g.o[g.n] = it.o; g.th[g.n] = it.th; g.defer[g.n] = it.scope == 1;
-                g.mode[g.n] = (uint8_t)it.scaling; g.gam[g.n] = gam_of[i]; g.prove[g.n] = scope_proof_applies(it) ? 1 : 0;
-                g.group_rows[g.n] = (uint32_t)it.group_rows; g.bpr[g.n] = (uint32_t)(it.sh.cols / 128);
+                sub_table_add(g, it, gam_of[i]);
+                g.unit_end[g.n - 1] = total;
                 newest = i;
-                if (++g.n == kMaxGroupSub) flush();
-            }
-            if (n_tail > 0) {     // fewer than 32 blocks left: the general kernel takes them
-                KShape ts{n_tail, 128, 128};
-                KOut to = it.o;
-                if (to.fp8) to.fp8 += n_full * 128;
-                to.ld_fp8 = 128;
-                if (to.fake) { to.fake += n_full * 128; to.ld_fake = 128; }
-                if (to.bf16) to.bf16 += n_full * 128;
-                to.ld_bf16 = 128;
-                to.scale += n_full; to.amax += n_full; to.err_sum += n_full; to.nnz += n_full; to.mask += n_full;
-                if (to.err5_sum) to.err5_sum += n_full;
-                if (to.e8m0) to.e8m0 += n_full;
-                // (the tail's rows are renumbered from 0; an operand with bands of rows as GAM groups has no tail, see route_of)
-                if (err == hipSuccess) err = launch_sub1x128(it.x + n_full * 128, ts, to, crit, it.scope == 1, it.th, (uint32_t)it.scaling, gam_of[i], 0u, 0u, st, nullptr);
+                if (g.n == kMaxGroupSub) flush();
             }
         }
         flush();
@@ -1854,14 +1837,7 @@ void BatchRun::sub_tensor_operands(int crit) {
             g.mode[k] = r.mode[k]; g.gam[k] = r.gam[k]; g.prove[k] = r.prove[k]; g.group_rows[k] = r.group_rows[k]; g.bpr[k] = r.bpr[k];
         }
         ProfScope ps(prof, kKernSub1x128, st);
-        const dim3 grid((unsigned)riders.blocks);
-        if (riders.fake) {
-            if (crit == kCritEq3) k_sub1x128_group<kCritEq3, true><<<grid, dim3(256), 0, st>>>(g);
-            else k_sub1x128_group<kCritEq2, true><<<grid, dim3(256), 0, st>>>(g);
-        } else {
-            if (crit == kCritEq3) k_sub1x128_group<kCritEq3, false><<<grid, dim3(256), 0, st>>>(g);
-            else k_sub1x128_group<kCritEq2, false><<<grid, dim3(256), 0, st>>>(g);
-        }
+        launch_sub_group<false>(dim3((unsigned)riders.blocks), crit, riders.fake, g, st);
         riders.used = true;
     }
     // ---- 128x1 sub-columns
@@ -1951,10 +1927,32 @@ void BatchRun::collect_statistics() {
     }
 }
 
+// The three launches of a group of per-tensor operands; statistics of sub-tensor operands ride in extra workgroups.
+template <bool STRIDED>
+void launch_tensor_passes(const GroupTensor& g, const GroupStats& riders, int a_end, int ride_partial, int s_end, int c_end, int ride_final,
+                          int crit, bool fake, int lds, hipStream_t st, KProf* prof) {
+    { ProfScope ps(prof, kKernTensorAmax, st); k_tensor_amax_group<STRIDED><<<dim3(a_end + ride_partial), dim3(256), lds, st>>>(g, riders, a_end); }
+    {
+        ProfScope ps(prof, kKernTensorQuant, st);
+        if (fake) {
+            if (crit == kCritEq3) k_tensor_quant_group<kCritEq3, true, STRIDED><<<dim3(s_end), dim3(256), lds, st>>>(g);
+            else k_tensor_quant_group<kCritEq2, true, STRIDED><<<dim3(s_end), dim3(256), lds, st>>>(g);
+        } else {
+            if (crit == kCritEq3) k_tensor_quant_group<kCritEq3, false, STRIDED><<<dim3(s_end), dim3(256), lds, st>>>(g);
+            else k_tensor_quant_group<kCritEq2, false, STRIDED><<<dim3(s_end), dim3(256), lds, st>>>(g);
+        }
+    }
+    {
+        ProfScope ps(prof, kKernFallbackCopy, st);
+        if (crit == kCritEq3) k_tensor_finish_group<kCritEq3, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
+        else k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
+    }
+}
 void BatchRun::per_tensor_operands(int crit) {
     // ---- per-tensor operands: amax pass, quantize pass, finish (+ fallback copy) pass; FP8 payload and fake
-    //      quantization are different kernels
-    for (int fake = 0; fake < 2 && err == hipSuccess; ++fake) {
+    //      quantization are different kernels, and so are dense operands and padded leading dimensions
+    for (int variant = 0; variant < 4 && err == hipSuccess; ++variant) {
+        const bool fake = (variant & 1) != 0, strided = (variant & 2) != 0;
         int idx[kMaxGroupTensor];
         int cnt = 0;
         auto flush = [&]() {
@@ -1979,8 +1977,7 @@ void BatchRun::per_tensor_operands(int crit) {
                 const BatchItem& it = items[idx[k]];
                 TensorOp& t = g.op[k];
                 t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u; t.lean = it.lean ? 1u : 0u;
-                t.n_chunks = it.sh.rows * it.sh.cols / 8;
-                t.n_tiles = (t.n_chunks + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
+                set_tensor_layout(t, it.sh, it.o);
                 t.n_amax = share(t.n_tiles, total_tiles, amax_cap, t.n_tiles);
                 t.n_slots = share(t.n_tiles, total_tiles, quant_cap, t.n_tiles);
                 const TensorPlan pl = plan_tensor(it.sh.rows, it.sh.cols);
@@ -2008,43 +2005,19 @@ void BatchRun::per_tensor_operands(int crit) {
                 ride_final = ride_partial > riders.n ? riders.n : 0;      // single-workgroup operands are final already
                 riders_used = true;
             }
-            { ProfScope ps(prof, kKernTensorAmax, st); k_tensor_amax_group<<<dim3(a_end + ride_partial), dim3(256), pass_lds, st>>>(g, riders, a_end); }
-            {
-                ProfScope ps(prof, kKernTensorQuant, st);
-                if (fake) {
-                    if (crit == kCritEq3) k_tensor_quant_group<kCritEq3, true><<<dim3(s_end), dim3(256), pass_lds, st>>>(g);
-                    else k_tensor_quant_group<kCritEq2, true><<<dim3(s_end), dim3(256), pass_lds, st>>>(g);
-                } else {
-                    if (crit == kCritEq3) k_tensor_quant_group<kCritEq3, false><<<dim3(s_end), dim3(256), pass_lds, st>>>(g);
-                    else k_tensor_quant_group<kCritEq2, false><<<dim3(s_end), dim3(256), pass_lds, st>>>(g);
-                }
-            }
-            {
-                ProfScope ps(prof, kKernFallbackCopy, st);
-                if (crit == kCritEq3) k_tensor_finish_group<kCritEq3><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
-                else k_tensor_finish_group<kCritEq2><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
-            }
+            if (strided) launch_tensor_passes<true>(g, riders, a_end, ride_partial, s_end, c_end, ride_final, crit, fake, pass_lds, st, prof);
+            else launch_tensor_passes<false>(g, riders, a_end, ride_partial, s_end, c_end, ride_final, crit, fake, pass_lds, st, prof);
             cnt = 0;
         };
         for (int i = 0; i < n; ++i) {
             const BatchItem& it = items[i];
-            if (route[i] != kRouteTensorGroup || it.crit != crit || (it.o.fake != nullptr) != (fake != 0)) continue;
+            if (route[i] != kRouteTensorGroup || it.crit != crit || (it.o.fake != nullptr) != fake || item_is_flat(it) == strided) continue;
             const int64_t n_tiles = (it.sh.rows * it.sh.cols / 8 + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
             if (n_tiles > 2000ll * kMaxQuantBlocks) { err = hipErrorInvalidValue; return; }   // 16-bit per-lane zero counters
             idx[cnt] = i;
             if (++cnt == kMaxGroupTensor) flush();
         }
         flush();
-    }
-    // ---- per-tensor operands with padded leading dimensions, one at a time
-    for (int i = 0; i < n && err == hipSuccess; ++i) {
-        const BatchItem& it = items[i];
-        if (route[i] != kRouteTensorStrided || it.crit != crit) continue;
-        char* w = carve(plan_tensor(it.sh.rows, it.sh.cols).bytes);
-        if (err != hipSuccess) return;
-        err = launch_tensor(it.x, it.sh, it.o, it.crit, it.th, (uint32_t)it.scaling, it.three ? 1u : 0u, w, st, prof);
-        if (err == hipSuccess && it.stats)
-            err = launch_select_stats(make_geom(it.gran, it.sh.rows, it.sh.cols), it.o.err_sum, it.o.nnz, it.o.mask, it.th, near_tol, it.stats, st);
     }
 }
 

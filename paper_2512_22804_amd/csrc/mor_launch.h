@@ -50,6 +50,26 @@ inline StatsGeom make_geom(int gran, int64_t rows, int64_t cols) {
 }
 inline int64_t geom_parts(const StatsGeom& g) { return ((g.rows + g.pr - 1) / g.pr) * g.gc; }
 
+// Reciprocal of d (1 <= d < 2^31) for n / d == mulhi(2n, mul) >> shift, n < 2^31: with l = ceil(log2 d) and
+// mul = floor(2^(31+l) / d) + 1, mul * d exceeds 2^(31+l) by at most d <= 2^l, so the quotient is off by less than 1 / d.
+inline void recip_of(int64_t d, uint32_t* mul, uint32_t* shift) {
+    uint32_t l = 0;
+    while ((1ll << l) < d) ++l;
+    *mul = (uint32_t)((1ull << (31 + l)) / (unsigned long long)d + 1ull);
+    *shift = l;
+}
+// Leading dimensions up to which the kernels for padded rows form 32-bit byte offsets inside a tile, and the same for the tile's
+// span (`rows` of the longest row); beyond them the general paths are taken.
+constexpr int64_t kRowMapMaxLd = 1 << 22;
+inline int64_t longest_row(const KShape& sh, const KOut& o) {
+    int64_t ld = sh.ld;
+    if (o.fp8 && o.ld_fp8 > ld) ld = o.ld_fp8;
+    if (o.bf16 && o.ld_bf16 > ld) ld = o.ld_bf16;
+    if (o.fake && o.ld_fake > ld) ld = o.ld_fake;
+    return ld;
+}
+inline bool row_map_fits(int64_t ld, int64_t rows) { return ld < kRowMapMaxLd && rows * ld * 2 < 0x7FFFFFFFll; }
+
 // Workspace layout for the passes that need one (all offsets 16-byte aligned).
 struct TensorPlan {
     int     amax_blocks;     // grid of the amax pass

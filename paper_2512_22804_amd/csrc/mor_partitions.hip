@@ -335,7 +335,7 @@ template <int TEAM, int CRIT, bool FAKE, bool EDGE, bool RIDE>
 __global__ __launch_bounds__(TEAM == kTeamBigRow ? 1024 : 256) void k_team_group(GroupTeam g, SubRiders riders, int64_t sub_first) {
     if constexpr (RIDE) {
         if ((int64_t)blockIdx.x >= sub_first) {
-            sub_group_body<CRIT, FAKE>(riders, (int64_t)blockIdx.x - sub_first, (int64_t)gridDim.x - sub_first);
+            sub_group_body<CRIT, FAKE, false, false>(riders, (int64_t)blockIdx.x - sub_first, (int64_t)gridDim.x - sub_first, nullptr, 0.0f);
             return;
         }
     }

@@ -1,0 +1,114 @@
+"""Operands whose rows are longer than the operand is wide, and 1x128 operands with ragged edges: the chunk and block
+addresses of these kernels come from divisions by the row's length, so the sizes are those where a tile (2048 16-byte chunks)
+or a unit (32 blocks) ends inside a row, spans many rows, or ends at the operand's last element.  Everything is compared with
+the oracle, bit for bit but for the error sums; outputs with padded rows of their own must leave the padding alone."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_22804_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# rows, cols, ld: one chunk per row; rows shorter and longer than the 256 chunks of one step; a tile that ends with a row;
+# one element more than a tile; rows longer than a tile
+SHAPES = [(5000, 8, 16), (700, 24, 40), (1030, 136, 272), (257, 2040, 4096), (256, 2048, 2056), (9, 2056, 2064), (33, 16384, 16392),
+          (3, 40000, 40008)]
+
+
+def _operand(rows, cols, ld, kind, seed=5):
+    width = -(-ld // 128) * 128
+    if kind == "grad":
+        return W.gradient(rows, width, seed)[:, :ld].copy()
+    if kind == "half":
+        return W.gradient(rows, width, seed, tiny_frac=0.3, tiny_half=True)[:, :ld].copy()
+    x = W.outlier_normal(rows, ld, seed)
+    if kind == "large":                    # amax >= 2^25: the element path that needs no assumption
+        x[rows // 2, cols // 2] = 0x4D00
+    if kind == "inf":
+        x[0, cols - 1] = 0x7F80
+    return x
+
+
+@pytest.mark.parametrize("gran", ["tensor", "sub1x128"])
+@pytest.mark.parametrize("rows, cols, ld", SHAPES)
+def test_padded_rows(gran, rows, cols, ld):
+    import parity
+    ragged = gran == "sub1x128" and cols % 128 != 0
+    for kind in ("normal", "grad", "half", "large", "inf"):
+        parity.compare(_operand(rows, cols, ld, kind), gran, cols=cols, ragged=ragged, label=kind)
+    parity.compare(_operand(rows, cols, ld, "half"), gran, crit="e4m3_vs_e5m2", cols=cols, ragged=ragged, scaling="gam")
+    parity.compare_fake(_operand(rows, cols, ld, "half"), gran, cols=cols, ragged=ragged)
+
+
+@pytest.mark.parametrize("rows, cols", [(1, 8), (1, 136), (31, 128), (33, 128), (3, 1400), (65, 4104), (127, 16)])
+def test_ragged_sub_rows(rows, cols):
+    """Dense 1x128 operands whose last block or last unit is not whole, with bands of rows as GAM groups too."""
+    import parity
+    for kind in ("half", "large"):
+        x = _operand(rows, cols, cols, kind)
+        parity.compare(x, "sub1x128", cols=cols, ragged=cols % 128 != 0, label=kind)
+        parity.compare(x, "sub1x128", scope="tensor", cols=cols, ragged=cols % 128 != 0, scaling="gam", gam_group_rows=7)
+
+
+@pytest.mark.parametrize("gran", ["tensor", "sub1x128"])
+@pytest.mark.parametrize("cols, ld", [(8, 4194304), (8, 2097152), (136, 3000000)])
+def test_rows_too_long_for_tile_offsets(gran, cols, ld):
+    """A few columns of very long rows: a tile of the operand spans 2 GB or more, or a row is 2^22 elements."""
+    import parity
+    rows = 5 if ld == 4194304 else 520
+    dev = torch.device("cuda:0")
+    from paper_2512_22804_amd import binding as B
+    small = _operand(rows, cols, cols, "half")
+    buf = torch.zeros(rows * ld, dtype=torch.int16, device=dev).view(rows, ld)
+    buf[:, :cols] = parity.to_dev(small)
+    p = B.make_params(rows, cols, gran, ld=ld, ragged=gran == "sub1x128")
+    q = B.make_params(rows, cols, gran, ld=cols, ragged=gran == "sub1x128")
+    a, b = (B.alloc_outputs(x, dev, bf16_fill=parity.FILL) for x in (p, q))
+    B.mor_analyze_quantize(p, buf, a)
+    B.mor_analyze_quantize(q, parity.to_dev(small), b)
+    torch.cuda.synchronize()
+    for f in ("fp8", "bf16", "scale", "amax", "nnz", "mask"):
+        assert torch.equal(getattr(a, f), getattr(b, f)), f
+    assert torch.allclose(a.err_sum, b.err_sum, rtol=1e-5, atol=0)      # the error sums' own bound
+
+
+@pytest.mark.parametrize("gran", ["tensor", "sub1x128"])
+@pytest.mark.parametrize("rows, cols", [(300, 200), (70, 3000)])
+def test_padded_outputs_and_statistics(oracle, gran, rows, cols):
+    """Payload and fallback buffers with rows of their own length; statistics of the lone operand (ragged blocks counted with
+    their real sizes) and of two operands in one call."""
+    import parity
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    near = 1e-2
+    entries, keep = [], []
+    for seed in (1, 2):
+        xb = _operand(rows, cols, cols + 24, "half", seed)
+        p = B.make_params(rows, cols, gran, ld=cols + 24, ragged=True)
+        out = B.alloc_outputs(p, dev)
+        wide8 = torch.full((rows, cols + 8), 0xA5, dtype=torch.uint8, device=dev)
+        wideb = torch.full((rows, cols + 16), 0x5A5A, dtype=torch.int16, device=dev)
+        out.fp8, out.bf16 = wide8[:, :cols], wideb[:, :cols]
+        st = torch.full((B.STATS_BYTES,), 0xEE, dtype=torch.uint8, device=dev)
+        entries.append((p, parity.to_dev(xb), out, st))
+        keep.append((xb, wide8, wideb))
+    for group in ([0], [0, 1]):
+        items = B.make_batch([entries[i] for i in group])
+        ws = torch.full((max(16, B.mor_batch_workspace_bytes(items)),), 0xA7, dtype=torch.uint8, device=dev)
+        for i in group:
+            keep[i][1].fill_(0xA5); keep[i][2].fill_(0x5A5A); entries[i][3].fill_(0xEE)
+        B.mor_analyze_quantize_batch(items, near, ws)
+        torch.cuda.synchronize()
+        for i in group:
+            xb, wide8, wideb = keep[i]
+            p, x, out, st = entries[i]
+            a = oracle.analyze_quantize(xb, gran, "partition", "mean_rel_err", 0.045, bf16_fill=0x5A5A, ld=cols + 24, cols=cols, ragged=True)
+            assert np.array_equal(out.mask.cpu().numpy(), a.mask)
+            assert np.array_equal(wide8[:, :cols].cpu().numpy(), a.fp8) and bool((wide8[:, cols:] == 0xA5).all())
+            assert np.array_equal(wideb[:, :cols].cpu().numpy().view(np.uint16), a.bf16) and bool((wideb[:, cols:] == 0x5A5A).all())
+            got = B.read_stats(st)
+            want = oracle.select_stats(out.err_sum.cpu().numpy(), a.nnz, a.mask, rows, cols, gran, 0.045, near, ragged=True)
+            for k in ("n_part", "n_fp8_part", "n_bf16_part", "n_e5m2_part", "n_elem_fp8", "n_elem_bf16", "n_elem_e5m2", "nnz_total", "hist"):
+                if k in want:
+                    assert got[k] == want[k], (k, got[k], want[k])
