@@ -252,8 +252,9 @@ static mor_status dequantize_any(const mor_params* p, const uint8_t* fp8, int64_
     mor_status gs;
     const int64_t group_rows = group_rows_of(p, &gs);
     if (e8m0 && gs != MOR_OK) return gs;
-    hipError_t e = mor::launch_dequantize(mor::make_geom(p->granularity, p->rows, p->cols), fp8, ld_fp8, scale, mask, bf16, ld_bf16,
-                                          y, ld_y, e8m0, gmant, e8m0 ? group_rows : 0, static_cast<hipStream_t>(stream));
+    const mor::DeqItem it{mor::make_geom(p->granularity, p->rows, p->cols), fp8, ld_fp8, scale, mask, bf16, ld_bf16, y, ld_y, e8m0, gmant,
+                          e8m0 ? group_rows : 0};
+    hipError_t e = mor::launch_dequantize_batch(&it, 1, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? MOR_OK : MOR_ERR_HIP;
 }
 

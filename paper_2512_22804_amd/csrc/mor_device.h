@@ -154,10 +154,14 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-// Finite values only (the branch-free paths never see NaN).
-__device__ __forceinline__ uint32_t f32_to_bf16_rne_finite(float f) {
-    const uint32_t u = __float_as_uint(f);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+// Two values at once, no NaN but the default one (0x7FC00000, either sign): v_cvt_pk_bf16_f32, which agrees with the function above
+// on every binary32 pattern that is not a NaN, subnormals included (checked over all of them), and truncates a NaN's payload.
+// One instruction instead of seven per pair: fake quantization of an 8192 x 4096 operand 28.9 -> 28.1 us at 128x128, 25.6 -> 24.9
+// at 1x128, 47.5 -> 43.7 per tensor.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_bf16_rne(float lo, float hi) {
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
 // The same as quant8_fast, optionally (FAKE) also producing the eight de-quantized values
@@ -176,7 +180,7 @@ __device__ __forceinline__ u32x2 quant8_fast_deq(const u32x4& raw, float s, floa
         if (j == 3) { w1 = cvt_pk8<E5M2>(y0, y1, w1, true);  q = cvt_pk_f32<E5M2>(w1, true); }
         err0 += rel_term(y0, q.x);
         err1 += rel_term(y1, q.y);
-        if constexpr (FAKE) deq[j] = f32_to_bf16_rne_finite(q.x * s_inv) | (f32_to_bf16_rne_finite(q.y * s_inv) << 16);
+        if constexpr (FAKE) deq[j] = pk_bf16_rne(q.x * s_inv, q.y * s_inv);
     }
     u32x2 r; r.x = (uint32_t)w0; r.y = (uint32_t)w1;
     return r;
@@ -209,7 +213,7 @@ __device__ __forceinline__ u32x2 quant8_dual(const u32x4& raw, float s, float s_
         const f32x2 q5 = __builtin_amdgcn_cvt_scalef32_pk_f32_bf8((uint32_t)(uint16_t)c5.x, kInv128, false);
         f0 += __builtin_amdgcn_fmed3f(__builtin_fabsf(y0 - q5.x) * r0, 0.0f, 1.0f);
         f1 += __builtin_amdgcn_fmed3f(__builtin_fabsf(y1 - q5.y) * r1, 0.0f, 1.0f);
-        if constexpr (FAKE) deq[j] = f32_to_bf16_rne_finite(q.x * s_inv) | (f32_to_bf16_rne_finite(q.y * s_inv) << 16);
+        if constexpr (FAKE) deq[j] = pk_bf16_rne(q.x * s_inv, q.y * s_inv);
     }
     u32x2 r; r.x = (uint32_t)w0; r.y = (uint32_t)w1;
     return r;
@@ -229,7 +233,7 @@ __device__ __forceinline__ u32x2 quant8_cols(const u32x4& raw, const float (&s)[
         if (j == 3) { w1 = cvt_pk8<E5M2>(y0, y1, w1, true);  q = cvt_pk_f32<E5M2>(w1, true); }
         err[2 * j] += rel_term(y0, q.x);
         err[2 * j + 1] += rel_term(y1, q.y);
-        if constexpr (FAKE) deq[j] = f32_to_bf16_rne_finite(q.x * s_inv[2 * j]) | (f32_to_bf16_rne_finite(q.y * s_inv[2 * j + 1]) << 16);
+        if constexpr (FAKE) deq[j] = pk_bf16_rne(q.x * s_inv[2 * j], q.y * s_inv[2 * j + 1]);
     }
     u32x2 r; r.x = (uint32_t)w0; r.y = (uint32_t)w1;
     return r;
@@ -433,6 +437,9 @@ __device__ __forceinline__ BufRsrc make_buf_window(const void* base, uint32_t by
 }
 __device__ __forceinline__ u32x4 buf_load16(BufRsrc r, uint32_t voff, uint32_t soff) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, kBufAux);
+}
+__device__ __forceinline__ u32x2 buf_load8(BufRsrc r, uint32_t voff, uint32_t soff) {
+    return __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
 }
 // 16-byte stores never take a register in the scalar-offset field: the compiler assumes that form needs no wait
 // states before the data registers are overwritten and reuses them in the very next instruction, but on gfx950 the

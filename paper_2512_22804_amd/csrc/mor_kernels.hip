@@ -399,6 +399,12 @@ __device__ __forceinline__ float dequant_scale(const float* __restrict__ scale, 
     // stored GAM form (Algorithm 1): the scale is rebuilt from the group's shared mantissa and the block's E8M0 byte
     return e8m0 ? __uint_as_float(((uint32_t)e8m0[p] << 23) | gmant[2 * band + (mk == 2u ? 1 : 0)]) : scale[p];
 }
+// 1 / s, correctly rounded; a NaN scale gives the default NaN, so that products with it convert as pk_bf16_rne expects (the
+// decoded NaN codes are default NaNs too).
+__device__ __forceinline__ float dequant_inverse(float s) {
+    const float v = 1.0f / s;
+    return v != v ? __uint_as_float((__float_as_uint(v) & 0x80000000u) | 0x7FC00000u) : v;
+}
 template <bool E5M2>
 __device__ __forceinline__ u32x4 dequant8(const u32x2& q, float s_inv) {
     u32x4 out;
@@ -406,10 +412,11 @@ __device__ __forceinline__ u32x4 dequant8(const u32x2& q, float s_inv) {
     for (int j = 0; j < 4; ++j) {
         const int word = (int)(j < 2 ? q.x : q.y);
         const f32x2 v = (j & 1) ? cvt_pk_f32<E5M2>(word, true) : cvt_pk_f32<E5M2>(word, false);
-        out[j] = f32_to_bf16_rne(v.x * s_inv) | (f32_to_bf16_rne(v.y * s_inv) << 16);
+        out[j] = pk_bf16_rne(v.x * s_inv, v.y * s_inv);
     }
     return out;
 }
+// One chunk at a time, any leading dimensions (rows too long for the tiles below).
 __global__ __launch_bounds__(256) void k_dequant(StatsGeom g, int pr_log2, int pc_log2, const uint8_t* __restrict__ fp8, int64_t ld_fp8,
                                                  const float* __restrict__ scale, const uint8_t* __restrict__ mask,
                                                  const uint16_t* __restrict__ bf16, int64_t ld_bf16, uint16_t* __restrict__ y,
@@ -424,63 +431,121 @@ __global__ __launch_bounds__(256) void k_dequant(StatsGeom g, int pr_log2, int p
             if (bf16) store16(y + r * ld_y + c, load16(bf16 + r * ld_bf16 + c));
             continue;
         }
-        const float s_inv = 1.0f / dequant_scale(scale, e8m0, gmant, p, mk, group_rows ? r / group_rows : 0);     // correctly rounded IEEE division
+        const float s_inv = dequant_inverse(dequant_scale(scale, e8m0, gmant, p, mk, group_rows ? r / group_rows : 0));
         const u32x2 q = *reinterpret_cast<const u32x2*>(fp8 + r * ld_fp8 + c);
         store16(y + r * ld_y + c, mk == 2u ? dequant8<true>(q, s_inv) : dequant8<false>(q, s_inv));
     }
 }
-// Grouped form for many operands (blocks whose width is a multiple of 8): a workgroup takes 64 rows x 128 columns of
-// one operand, four 8-byte payload loads in flight per lane.
+// Blocks whose width is a multiple of 8: tiles of 1024 consecutive 16-byte output chunks (see RowMap) of one operand per
+// workgroup, four per lane.  Bound by HBM (1 byte read and 2 written per element, 2 and 2 in BF16 blocks), so what counts is that
+// no load waits for another one: the masks and scales are loaded together, then the payload chunks (FP8 or BF16 as the mask says;
+// the other form's load has no address and moves nothing).  8192 x 14336 at 1x128, a tenth of the blocks in BF16: 60 us =
+// 6.1 TB/s, against 93 us with one chunk in flight per lane; eight chunks per lane 63 us (101 registers), two 60 us.  14336 x 4096
+// without BF16 blocks: 27.0 us; 30.9 us with non-temporal payload loads (the FP8 bytes may still lie in the Infinity Cache,
+// where such loads do not look after them), 28.4 us before.
+constexpr int kDeqChunks = 4;
 constexpr int kMaxGroupDeq = 16;
 struct DeqOp {
-    StatsGeom g;
+    RowMap rm;                      // of y; rm.ld is not used
+    int64_t n_chunks, gc;
     int32_t pr_log2, pc_log2;
-    int64_t strips_x;
-    const uint8_t* fp8; int64_t ld_fp8;
+    const uint8_t* fp8;
     const float* scale; const uint8_t* mask;
-    const uint16_t* bf16; int64_t ld_bf16;
-    uint16_t* y; int64_t ld_y;
+    const uint16_t* bf16;
+    uint16_t* y;
     const uint8_t* e8m0; const uint32_t* gmant;
-    int64_t group_rows;
+    uint32_t ld_fp8, ld_bf16, ld_y;
+    uint32_t group_rows, group_mul, group_shift;      // stored GAM form with bands of rows as groups (group_rows = 0: one group)
 };
 struct GroupDeq {
     int n;
-    int64_t unit_end[kMaxGroupDeq];
+    int32_t tile_end[kMaxGroupDeq];
     DeqOp op[kMaxGroupDeq];
 };
 __global__ __launch_bounds__(256) void k_dequant_group(GroupDeq gd) {
-    const int op = group_find(gd.unit_end, gd.n, blockIdx.x);
+    constexpr int N = kDeqChunks, kTile = 256 * N;
+    const int op = group_find32(gd.tile_end, gd.n, blockIdx.x);
     const DeqOp& t = gd.op[op];
-    const int64_t unit = (int64_t)blockIdx.x - (op ? gd.unit_end[op - 1] : 0);
-    const int64_t rg = unit / t.strips_x, strip = unit - rg * t.strips_x;
-    const int64_t c = strip * 128 + (threadIdx.x & 15) * 8;
-    if (c >= t.g.cols) return;
-    const int64_t r0 = rg * 64 + (threadIdx.x >> 4);
-    u32x2 q[4];
-    uint32_t mk[4];
-    float s[4];
+    const int64_t c_first = (int64_t)(blockIdx.x - (op ? gd.tile_end[op - 1] : 0)) * kTile;
+    const int64_t left = t.n_chunks - c_first;
+    const uint32_t valid = (uint32_t)(left < kTile ? left : kTile);
+    RowPos pos0;
+    const int64_t row0 = row_tile_first(t.rm, c_first, threadIdx.x, pos0);
+    const int64_t br0 = row0 >> t.pr_log2;                                // block row of the tile's first row
+    const uint8_t* __restrict__ mask = t.mask + br0 * t.gc;
+    const float* __restrict__ scale = t.scale ? t.scale + br0 * t.gc : nullptr;
+    const uint8_t* __restrict__ e8m0 = t.e8m0 ? t.e8m0 + br0 * t.gc : nullptr;
+    uint32_t mk[N];
+    float s[N];
+    RowPos pos = pos0;
+    uint32_t pp[N];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t r = r0 + 16 * k;
-        mk[k] = 1u; s[k] = 1.0f; q[k].x = 0u; q[k].y = 0u;
-        if (r < t.g.rows) {
-            const int64_t p = (r >> t.pr_log2) * t.g.gc + (c >> t.pc_log2);
-            mk[k] = t.mask[p];
-            s[k] = dequant_scale(t.scale, t.e8m0, t.gmant, p, mk[k], t.group_rows ? r / t.group_rows : 0);
-            if (mk[k] != 1u) q[k] = *reinterpret_cast<const u32x2*>(t.fp8 + r * t.ld_fp8 + c);
-        }
+    for (int u = 0; u < N; ++u) {
+        const bool live = threadIdx.x + u * 256u < valid;
+        const uint32_t br = (uint32_t)(((row0 + pos.r) >> t.pr_log2) - br0);
+        pp[u] = live ? br * (uint32_t)t.gc + ((pos.c * 8u) >> t.pc_log2) : 0u;      // (block 0 of the tile exists)
+        mk[u] = mask[pp[u]];
+        row_step(t.rm, pos);
     }
+    if (e8m0) {
+        pos = pos0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t r = r0 + 16 * k;
-        if (r >= t.g.rows) continue;
-        if (mk[k] == 1u) {
-            if (t.bf16) store16(t.y + r * t.ld_y + c, load16(t.bf16 + r * t.ld_bf16 + c));
-            continue;
+        for (int u = 0; u < N; ++u) {
+            const uint64_t row = (uint64_t)row0 + (threadIdx.x + u * 256u < valid ? pos.r : 0u);
+            const uint64_t band = t.group_rows ? (row < 0x7FFFFFFFu ? recip_div((uint32_t)row, t.group_mul, t.group_shift) : row / t.group_rows) : 0u;
+            s[u] = __uint_as_float(((uint32_t)e8m0[pp[u]] << 23) | t.gmant[2 * band + (mk[u] == 2u ? 1 : 0)]);
+            row_step(t.rm, pos);
         }
-        const float s_inv = 1.0f / s[k];                                   // correctly rounded IEEE division
-        store16(t.y + r * t.ld_y + c, mk[k] == 2u ? dequant8<true>(q[k], s_inv) : dequant8<false>(q[k], s_inv));
+    } else {
+#pragma unroll
+        for (int u = 0; u < N; ++u) s[u] = scale[pp[u]];
     }
+    const BufRsrc r8 = make_buf(t.fp8 + row0 * t.ld_fp8), ry = make_buf(t.y + row0 * t.ld_y);
+    const BufRsrc rb = make_buf_window(t.bf16 + row0 * t.ld_bf16, t.bf16 ? 0x7FFFFFFFu : 0u);
+    u32x2 q[N];
+    u32x4 keep[N];
+    bool some_keep = false, some_e5 = false;
+    pos = pos0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const bool live = threadIdx.x + u * 256u < valid;
+        q[u] = buf_load8(r8, row_off<8>(pos, t.ld_fp8, live && mk[u] != 1u), 0u);
+        some_keep |= live && mk[u] == 1u;
+        some_e5 |= live && mk[u] == 2u;
+        row_step(t.rm, pos);
+    }
+    if (__any(some_keep)) {
+        pos = pos0;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            keep[u] = buf_load16(rb, row_off<16>(pos, t.ld_bf16 * 2u, threadIdx.x + u * 256u < valid && mk[u] == 1u), 0u);
+            row_step(t.rm, pos);
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < N; ++u) keep[u] = u32x4{0u, 0u, 0u, 0u};
+    }
+    auto emit = [&](auto mixed) {
+        pos = pos0;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const float s_inv = dequant_inverse(s[u]);
+            u32x4 out = dequant8<false>(q[u], s_inv);
+            if constexpr (decltype(mixed)::value) {
+                const u32x4 out5 = dequant8<true>(q[u], s_inv);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) out[j] = mk[u] == 2u ? out5[j] : out[j];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) out[j] = mk[u] == 1u ? keep[u][j] : out[j];
+            const bool put = threadIdx.x + u * 256u < valid && (mk[u] != 1u || t.bf16 != nullptr);
+            buf_store16(ry, row_off<16>(pos, t.ld_y * 2u, put), out);
+            row_step(t.rm, pos);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if (__any(some_e5)) emit(std::true_type{});
+    else emit(std::false_type{});
 }
 __global__ __launch_bounds__(256) void k_dequant_columns(StatsGeom g, int pr_log2, const uint8_t* __restrict__ fp8, int64_t ld_fp8,
                                                          const float* __restrict__ scale, const uint8_t* __restrict__ mask,
@@ -1186,16 +1251,7 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
         for (int u = 0; u < kTensorChunksPerThread; ++u) buf_store16(rb, at_16(u, t.o.ld_bf16), raw[u]);       // proven fallback
         pos = pos0;
         if constexpr (STRIDED) asm volatile("" : "+v"(pos.r), "+v"(pos.c));      // the sweep's offsets are formed chunk by chunk, not kept from here
-        if (fast && FAKE && proven) {
-            // fake quantization of an operand already proven to stay in BF16: the output is the input (stored above);
-            // only the error sums are still needed
-#pragma unroll
-            for (int u = 0; u < kTensorChunksPerThread; ++u) {
-                (void)quant8_fast<false>(raw[u], s, acc.e0, acc.e1);
-                if constexpr (CRIT == kCritEq3) (void)quant8_fast<true>(raw[u], s5, acc.f0, acc.f1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else if (CRIT == kCritEq3 && fast && dual) {
+        if (CRIT == kCritEq3 && fast && dual) {
             // both formats in one sweep with one reciprocal per element (see quant8_dual)
 #pragma unroll
             for (int u = 0; u < kTensorChunksPerThread; ++u) {
@@ -2071,39 +2127,38 @@ hipError_t launch_dequantize_batch(const DeqItem* items, int n, hipStream_t st) 
     };
     for (int i = 0; i < n; ++i) {
         const DeqItem& it = items[i];
-        if (it.geom.pc == 1 && it.geom.cols > 1) {       // one column per block: its own kernel
-            hipError_t e = launch_dequantize(it.geom, it.fp8, it.ld_fp8, it.scale, it.mask, it.bf16, it.ld_bf16, it.y, it.ld_y, it.e8m0,
-                                             it.gmant, it.group_rows, st);
-            if (e != hipSuccess) return e;
+        const StatsGeom& geom = it.geom;
+        const int prl = log2_or_whole(geom.pr, geom.rows), pcl = log2_or_whole(geom.pc, geom.cols);
+        if (geom.pc == 1 && geom.cols > 1) {       // one column per block: its own kernel
+            const dim3 grid((unsigned)((geom.cols + 127) / 128), (unsigned)clamp_grid_y((geom.rows + 127) / 128));
+            k_dequant_columns<<<grid, dim3(256), 0, st>>>(geom, prl, it.fp8, it.ld_fp8, it.scale, it.mask, it.bf16, it.ld_bf16, it.y, it.ld_y,
+                                                          it.e8m0, it.gmant, it.group_rows);
             continue;
         }
-        const int64_t strips_x = (it.geom.cols + 127) / 128, units = strips_x * ((it.geom.rows + 63) / 64);
-        if (units > 0x7FFFFFFF) return hipErrorInvalidValue;
-        if (total + units > 0x7FFFFFFF) flush();
+        TensorOp layout;
+        KOut o{};
+        o.fake = it.y; o.ld_fake = it.ld_y;
+        if (it.bf16) { o.bf16 = const_cast<uint16_t*>(it.bf16); o.ld_bf16 = it.ld_bf16; }
+        set_tensor_layout(layout, KShape{geom.rows, geom.cols, it.ld_fp8}, o);
+        layout.n_tiles = (layout.n_chunks + 256 * kDeqChunks - 1) / (256 * kDeqChunks);
+        if (layout.rm.cpr == 0u || layout.n_tiles > 0x7FFFFFFF || it.group_rows > 0x7FFFFFFF) {      // 64-bit addresses, one chunk at a time
+            const dim3 grid((unsigned)((geom.cols + 127) / 128), (unsigned)clamp_grid_y((geom.rows + 15) / 16));
+            k_dequant<<<grid, dim3(256), 0, st>>>(geom, prl, pcl, it.fp8, it.ld_fp8, it.scale, it.mask, it.bf16, it.ld_bf16, it.y, it.ld_y, it.e8m0,
+                                                  it.gmant, it.group_rows);
+            continue;
+        }
+        if (total + layout.n_tiles > 0x7FFFFFFF) flush();
         DeqOp& t = g.op[g.n];
-        t.g = it.geom; t.pr_log2 = log2_or_whole(it.geom.pr, it.geom.rows); t.pc_log2 = log2_or_whole(it.geom.pc, it.geom.cols);
-        t.strips_x = strips_x;
-        t.fp8 = it.fp8; t.ld_fp8 = it.ld_fp8; t.scale = it.scale; t.mask = it.mask; t.bf16 = it.bf16; t.ld_bf16 = it.ld_bf16;
-        t.y = it.y; t.ld_y = it.ld_y; t.e8m0 = it.e8m0; t.gmant = it.gmant; t.group_rows = it.group_rows;
-        total += units;
-        g.unit_end[g.n] = total;
+        t.rm = layout.rm; t.n_chunks = layout.n_chunks; t.gc = geom.gc; t.pr_log2 = prl; t.pc_log2 = pcl;
+        t.fp8 = it.fp8; t.scale = it.scale; t.mask = it.mask; t.bf16 = it.bf16; t.y = it.y; t.e8m0 = it.e8m0; t.gmant = it.gmant;
+        t.ld_fp8 = (uint32_t)it.ld_fp8; t.ld_bf16 = (uint32_t)it.ld_bf16; t.ld_y = (uint32_t)it.ld_y;
+        t.group_rows = (uint32_t)it.group_rows;
+        recip_of(it.group_rows ? it.group_rows : 1, &t.group_mul, &t.group_shift);
+        total += layout.n_tiles;
+        g.tile_end[g.n] = (int32_t)total;
         if (++g.n == kMaxGroupDeq) flush();
     }
     flush();
-    return hipGetLastError();
-}
-
-hipError_t launch_dequantize(const StatsGeom& geom, const uint8_t* fp8, int64_t ld_fp8, const float* scale,
-                             const uint8_t* mask, const uint16_t* bf16, int64_t ld_bf16, uint16_t* y, int64_t ld_y,
-                             const uint8_t* e8m0, const uint32_t* gmant, int64_t group_rows, hipStream_t st) {
-    const int prl = log2_or_whole(geom.pr, geom.rows), pcl = log2_or_whole(geom.pc, geom.cols);
-    if (geom.pc == 1 && geom.cols > 1) {
-        const dim3 grid((unsigned)((geom.cols + 127) / 128), (unsigned)clamp_grid_y((geom.rows + 127) / 128));
-        k_dequant_columns<<<grid, dim3(256), 0, st>>>(geom, prl, fp8, ld_fp8, scale, mask, bf16, ld_bf16, y, ld_y, e8m0, gmant, group_rows);
-    } else {
-        const dim3 grid((unsigned)((geom.cols + 127) / 128), (unsigned)clamp_grid_y((geom.rows + 15) / 16));
-        k_dequant<<<grid, dim3(256), 0, st>>>(geom, prl, pcl, fp8, ld_fp8, scale, mask, bf16, ld_bf16, y, ld_y, e8m0, gmant, group_rows);
-    }
     return hipGetLastError();
 }
 

@@ -209,9 +209,6 @@ uint32_t* column_tensor_proven_word(char* column_workspace, int64_t rows, int64_
 hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int cnt, int crit, const uint32_t* const* gam_of,
                                     char* const* ws_of, hipStream_t st, KProf* prof);
 
-hipError_t launch_dequantize(const StatsGeom& geom, const uint8_t* fp8, int64_t ld_fp8, const float* scale,
-                             const uint8_t* mask, const uint16_t* bf16, int64_t ld_bf16, uint16_t* y, int64_t ld_y,
-                             const uint8_t* e8m0, const uint32_t* gmant, int64_t group_rows, hipStream_t st);
 // One operand of a de-quantize batch (validated by the caller).
 struct DeqItem {
     StatsGeom geom;
