@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace mor {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -376,6 +378,24 @@ __device__ __forceinline__ float wave_allsum_f32(float v) {
     return (a + b) + (c + d);
 }
 
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
+    return ((unsigned long long)dpp_u32<CTRL>((uint32_t)(v >> 32)) << 32) | dpp_u32<CTRL>((uint32_t)v);
+}
+__device__ __forceinline__ unsigned long long readlane_u64(unsigned long long v, int lane) {
+    return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+__device__ __forceinline__ unsigned long long wave_allsum_u64(unsigned long long v) {
+    v += dpp_u64<kDppXor1>(v); v += dpp_u64<kDppXor2>(v); v += dpp_u64<kDppHalfMirror>(v); v += dpp_u64<kDppMirror>(v);
+    return (readlane_u64(v, 0) + readlane_u64(v, 16)) + (readlane_u64(v, 32) + readlane_u64(v, 48));
+}
+__device__ __forceinline__ double wave_allsum_f64(double v) {      // fixed order: deterministic
+    auto sh = [](double x, auto ctrl) { return __longlong_as_double((long long)dpp_u64<decltype(ctrl)::value>((unsigned long long)__double_as_longlong(x))); };
+    v += sh(v, std::integral_constant<int, kDppXor1>{}); v += sh(v, std::integral_constant<int, kDppXor2>{});
+    v += sh(v, std::integral_constant<int, kDppHalfMirror>{}); v += sh(v, std::integral_constant<int, kDppMirror>{});
+    auto rl = [&](int lane) { return __longlong_as_double((long long)readlane_u64((unsigned long long)__double_as_longlong(v), lane)); };
+    return (rl(0) + rl(16)) + (rl(32) + rl(48));
+}
 // n / d for n < 2^31, from the reciprocal that recip_of() (mor_launch.h) forms on the host.
 __device__ __forceinline__ uint32_t recip_div(uint32_t n, uint32_t mul, uint32_t shift) { return __umulhi(2u * n, mul) >> shift; }
 // `off` or, when not `live`, the offset that loads zeros and stores nothing.  (The empty asm keeps the compiler from forming the
@@ -421,10 +441,8 @@ __device__ __forceinline__ uint32_t decide_eq3(float err4, float err5) { return 
 // zeros and stores nothing, so ragged edges need no per-lane branches.  Offsets are bytes from `base`
 // (32 bits; callers keep them below 2^31).
 constexpr int kBufAux = 2;      // cache-policy field of the buffer loads: non-temporal
-constexpr int kBufStoreAux = 18; // of the buffer stores: non-temporal and written through at system scope (nt sc1).  Measured
-                                 // against nt alone, alternating runs on one box: the per-tensor quantize pass of the layer
-                                 // sweep (2 bytes read, 3 written per element) takes 211.4-212.2 us instead of 213.9-214.0 us;
-                                 // the amax pass that runs before it reads 1.6 us longer, the step time is the same within 0.1 %
+constexpr int kBufStoreAux = 2;  // of the buffer stores: non-temporal.  Written through at system scope as well (nt sc1) they cost the
+                                 // per-tensor quantize pass 2.3 us of 84 us where its operand comes from the Infinity Cache
 typedef __amdgpu_buffer_rsrc_t BufRsrc;
 constexpr uint32_t kBufOutside = 0x80000000u;
 __device__ __forceinline__ BufRsrc make_buf(const void* base) {
@@ -437,6 +455,12 @@ __device__ __forceinline__ BufRsrc make_buf_window(const void* base, uint32_t by
 }
 __device__ __forceinline__ u32x4 buf_load16(BufRsrc r, uint32_t voff, uint32_t soff) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, kBufAux);
+}
+// The load of a pass whose operand another pass reads again (KEEP): without the non-temporal hint the lines stay in the 256 MB
+// Infinity Cache, which non-temporal reads look up but do not fill.
+template <bool KEEP>
+__device__ __forceinline__ u32x4 buf_load16_first(BufRsrc r, uint32_t voff, uint32_t soff) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, KEEP ? 0 : kBufAux);
 }
 __device__ __forceinline__ u32x2 buf_load8(BufRsrc r, uint32_t voff, uint32_t soff) {
     return __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);

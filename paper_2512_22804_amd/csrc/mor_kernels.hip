@@ -112,7 +112,9 @@ __global__ __launch_bounds__(256) void k_sub1x128_strided(const uint16_t* __rest
 // ======================================================================================
 constexpr int kTensorChunksPerThread = 8;                       // 16-byte chunks per thread in pass B
 constexpr int kTensorChunksPerBlock = 256 * kTensorChunksPerThread;
-constexpr int kMaxAmaxBlocks = 2048;     // pass A of the six gradient operands: 78 us at 2048 workgroups, 86 us at 1024, 84 us at 4096
+constexpr int kMaxAmaxBlocks = 512;      // pass A of several operands, all its workgroups resident.  The two parts of the six gradients of
+                                         // a layer (256 and 235 MB) take 45 + 39 us at 512, 49 + 39 us at 2048 with three resident per
+                                         // compute unit; the whole layer 409 us at 512, 411 at 384, 413 at 768, 428 at 2048
 constexpr int kProveMaxWg = 8192;      // workgroups of one launch (and partial records per operand) of the block-shaped GAM pre-pass
 
 __device__ __forceinline__ uint32_t block_allmax_u32(uint32_t v, uint32_t* sh4) {
@@ -206,7 +208,7 @@ struct TensorPartials {   // one slot per pass-B workgroup (at most kMaxQuantBlo
     uint32_t* abits;       // [0] = global amax bits, published by workgroup 0 of pass B
 };
 constexpr int kMaxQuantBlocks = 16384;
-constexpr int kSoloAmaxBlocks = 768, kSoloQuantBlocks = 1536;     // launch shape of a per-tensor operand that is alone in its launches
+constexpr int kSoloAmaxBlocks = 512, kSoloQuantBlocks = 1280;     // launch shape of a per-tensor operand that is alone in its launches
 
 template <typename T>
 __device__ __forceinline__ T block_sum_256(T v, T* sh) {
@@ -828,24 +830,6 @@ __device__ __forceinline__ void stats_final_body(const GroupStats& g, int op) {
 constexpr int kStatsFastThreads = 1024;
 constexpr int kStatsFastPerLane = 4;                   // blocks per lane of a partial workgroup
 constexpr int64_t kStatsDirectParts = 16384;           // one workgroup, 16 blocks per lane at most: packed 16-bit counters cannot overflow
-template <int CTRL>
-__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
-    return ((unsigned long long)dpp_u32<CTRL>((uint32_t)(v >> 32)) << 32) | dpp_u32<CTRL>((uint32_t)v);
-}
-__device__ __forceinline__ unsigned long long readlane_u64(unsigned long long v, int lane) {
-    return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
-}
-__device__ __forceinline__ unsigned long long wave_allsum_u64(unsigned long long v) {
-    v += dpp_u64<kDppXor1>(v); v += dpp_u64<kDppXor2>(v); v += dpp_u64<kDppHalfMirror>(v); v += dpp_u64<kDppMirror>(v);
-    return (readlane_u64(v, 0) + readlane_u64(v, 16)) + (readlane_u64(v, 32) + readlane_u64(v, 48));
-}
-__device__ __forceinline__ double wave_allsum_f64(double v) {      // fixed order: deterministic
-    auto sh = [](double x, auto ctrl) { return __longlong_as_double((long long)dpp_u64<decltype(ctrl)::value>((unsigned long long)__double_as_longlong(x))); };
-    v += sh(v, std::integral_constant<int, kDppXor1>{}); v += sh(v, std::integral_constant<int, kDppXor2>{});
-    v += sh(v, std::integral_constant<int, kDppHalfMirror>{}); v += sh(v, std::integral_constant<int, kDppMirror>{});
-    auto rl = [&](int lane) { return __longlong_as_double((long long)readlane_u64((unsigned long long)__double_as_longlong(v), lane)); };
-    return (rl(0) + rl(16)) + (rl(32) + rl(48));
-}
 struct StatsPacked {
     double e;
     unsigned long long n, eb, e5;
@@ -1062,6 +1046,7 @@ struct TensorOp {
     uint32_t* flush_part;                // [n_amax] lower bounds on the number of elements certain to flush to zero
     unsigned long long flush_need;       // that many certain flushes prove the BF16 decision (0 = proof not attempted)
     StatsDev* stats;                     // optional
+    int64_t keep_from;                   // pass A: tiles from this one on are read without the non-temporal hint
     RowMap rm;                           // operands with padded leading dimensions (STRIDED kernels)
 };
 struct GroupTensor {
@@ -1088,12 +1073,13 @@ __device__ __forceinline__ int64_t tensor_chunk_off(const TensorOp& t, int64_t c
 // Workgroups from `stats_first` on do not belong to pass A: they compute the partial statistics records of the batch's
 // sub-tensor operands (whose kernels have already run), in the shadow of this bandwidth-bound pass.
 template <bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupStats riders, int stats_first) {
+__global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupStats riders, int stats_first, int block0) {
     if ((int)blockIdx.x >= stats_first) { stats_partial_body(riders, (int)blockIdx.x - stats_first); return; }
     __shared__ uint32_t sh4[4];
-    const int op = group_find32(g.amax_end, g.n, blockIdx.x);
+    const int block = (int)blockIdx.x + block0;              // block0: the launch covers a part of the table's operands
+    const int op = group_find32(g.amax_end, g.n, block);
     const TensorOp& t = g.op[op];
-    const int b = blockIdx.x - (op ? g.amax_end[op - 1] : 0);
+    const int b = block - (op ? g.amax_end[op - 1] : 0);
     const bool prove = t.flush_need != 0ull;
     const bool three = t.three != 0u;
     uint32_t a2 = 0u, keep2 = 0u, seen = 0u;      // keep2: per half-word count of elements NOT certain to flush
@@ -1107,11 +1093,26 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
                 const int64_t row0 = row_tile_first(t.rm, tile * kTensorChunksPerBlock, threadIdx.x, pos);
                 const BufRsrc rx = make_buf(t.x + row0 * t.rm.ld);
                 const uint32_t row_bytes = (uint32_t)t.rm.ld * 2u;
+                uint32_t off[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) { v[u] = buf_load16(rx, row_off<16>(pos, row_bytes, true), 0u); row_step(t.rm, pos); }
+                for (int u = 0; u < 8; ++u) { off[u] = row_off<16>(pos, row_bytes, true); row_step(t.rm, pos); }
+                if (tile >= t.keep_from) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = buf_load16_first<true>(rx, off[u], 0u);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = buf_load16_first<false>(rx, off[u], 0u);
+                }
             } else {
+                // (buffer loads: plain loads that differ in the hint only would be merged into one without it)
+                const BufRsrc rx = make_buf(t.x + tile * (kTensorChunksPerBlock * 8));
+                if (tile >= t.keep_from) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = load16(t.x + (c0 + u * 256) * 8);
+                    for (int u = 0; u < 8; ++u) v[u] = buf_load16_first<true>(rx, threadIdx.x * 16u + u * 4096u, 0u);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = buf_load16_first<false>(rx, threadIdx.x * 16u + u * 4096u, 0u);
+                }
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) a2 = amax2_of(v[u], a2);
@@ -1153,21 +1154,42 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
         if (threadIdx.x == 0) t.flush_part[b] = (sh4[0] + sh4[1]) + (sh4[2] + sh4[3]);
     }
 }
-// Sum of the certain-flush lower bounds of an operand; same value in every workgroup that calls it.
-__device__ __forceinline__ bool tensor_fallback_proven(const TensorOp& t, unsigned long long* shl) {
-    if (t.flush_need == 0ull) return false;
-    unsigned long long f = 0;
-    for (int i = threadIdx.x; i < t.n_amax; i += 256) f += t.flush_part[i];
-    f = block_sum_shfl<unsigned long long>(f, shl);
-    return f >= t.flush_need;
+// What pass A found out about the operand: its amax, and whether the sum of the certain-flush lower bounds proves the BF16
+// decision.  Same values in every workgroup that calls it.  All partials are loaded together and one barrier exchanges the wave
+// results: every workgroup of pass B waits for this before it can scale anything.
+__device__ __forceinline__ uint32_t tensor_pass_a_result(const TensorOp& t, bool& proven) {
+    __shared__ uint32_t sha[4];
+    __shared__ unsigned long long shf[4];
+    const bool prove = t.flush_need != 0ull;
+    uint32_t a = 0u;
+    unsigned long long f = 0ull;
+    for (int i0 = threadIdx.x; i0 < t.n_amax; i0 += 4 * 256) {
+        uint32_t av[4], fv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool ok = i0 + u * 256 < t.n_amax;
+            const int ic = ok ? i0 + u * 256 : i0;           // always a valid slot: the loads need no branch
+            av[u] = t.amax_part[ic];
+            fv[u] = prove ? t.flush_part[ic] : 0u;
+            fv[u] = ok ? fv[u] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { a = max(a, av[u] & 0xFFFFu); f += fv[u]; }
+    }
+    a = wave_allmax_u32(a);
+    if (prove) f = wave_allsum_u64(f);
+    if ((threadIdx.x & 63) == 0) { sha[threadIdx.x >> 6] = a; shf[threadIdx.x >> 6] = f; }
+    __syncthreads();
+    proven = prove && (shf[0] + shf[1]) + (shf[2] + shf[3]) >= t.flush_need;
+    return max(max(sha[0], sha[1]), max(sha[2], sha[3]));
 }
 // STRIDED: operands with padded leading dimensions (see RowMap).
 template <int CRIT, bool FAKE, bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
-    __shared__ uint32_t sh4[4];
-    const int op = group_find32(g.slot_end, g.n, blockIdx.x);
+__global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int block0) {
+    const int block = (int)blockIdx.x + block0;
+    const int op = group_find32(g.slot_end, g.n, block);
     const TensorOp& t = g.op[op];
-    const int b = blockIdx.x - (op ? g.slot_end[op - 1] : 0);
+    const int b = block - (op ? g.slot_end[op - 1] : 0);
     const uint16_t* __restrict__ x = t.x;
     uint8_t* __restrict__ fp8 = t.o.fp8;
     const int64_t n_chunks = t.n_chunks, n_tiles = t.n_tiles, G = t.n_slots;
@@ -1197,9 +1219,8 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g) {
     };
     int64_t tl = b;
     load_tile(bufA, tl);
-    __shared__ unsigned long long shl4[4];
-    const uint32_t abits = global_amax_bits(t.amax_part, t.n_amax, sh4);
-    const bool proven = tensor_fallback_proven(t, shl4);     // then the BF16 fallback is written in this sweep
+    bool proven;                                             // then the BF16 fallback is written in this sweep
+    const uint32_t abits = tensor_pass_a_result(t, proven);
     uint16_t* __restrict__ bf16 = t.o.bf16;
     if (b == 0 && threadIdx.x == 0) { t.abits[0] = abits; t.abits[1] = proven ? 1u : 0u; }
     // one block = the group: under GAM the block's own mantissa is the group mantissa and the scale is s_b
@@ -1401,28 +1422,48 @@ struct GroupGam {
     int n;
     GamOp op[kMaxGroup];
 };
-__global__ __launch_bounds__(256) void k_gam_prepare(GroupGam g) {
-    __shared__ uint32_t sh4[4];
-    __shared__ unsigned long long shl[4];
+// One workgroup per operand, on the critical path of the call: 1024 lanes, four partials of each kind in flight per lane (an
+// operand of 2048 partials took 8.7 us with 256 lanes and one load at a time).
+constexpr int kGamThreads = 1024;
+__global__ __launch_bounds__(kGamThreads) void k_gam_prepare(GroupGam g) {
+    __shared__ uint32_t sha[kGamThreads / 64];
+    __shared__ unsigned long long shl[kGamThreads / 64];
     const GamOp& t = g.op[blockIdx.x];
     if (t.skip) return;                  // uniform over the workgroup
-    const uint32_t gbits = global_amax_bits(t.amax_part, t.n_amax, sh4);
-    unsigned long long fl = 0ull;
-    if (t.flush_part)
-        for (int i = threadIdx.x; i < t.n_amax; i += 256) fl += t.flush_part[i];
-    fl = block_sum_shfl<unsigned long long>(fl, shl);
-    if (threadIdx.x == 0) {
-        t.gam[2] = (t.flush_part && fl >= t.flush_need) ? 1u : 0u;
-        const uint32_t mg = group_mantissa_bits(gbits, kE4M3Max, t.mode);
-        t.gam[0] = mg;
-        const uint32_t mg5 = group_mantissa_bits(gbits, kE5M2Max, t.mode);
-        t.gam[1] = mg5;
-        if (t.gmant) { t.gmant[0] = mg; t.gmant[1] = mg5; }
+    uint32_t a = 0u;
+    unsigned long long fl_wg = 0ull;
+    for (int i0 = threadIdx.x; i0 < t.n_amax; i0 += 4 * kGamThreads) {
+        uint32_t av[4], fv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kGamThreads;
+            const int ic = i < t.n_amax ? i : i0;          // always a valid slot: the loads need no branch
+            av[u] = t.amax_part[ic];
+            fv[u] = t.flush_part ? t.flush_part[ic] : 0u;
+            if (i >= t.n_amax) fv[u] = 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { a = max(a, av[u] & 0xFFFFu); fl_wg += fv[u]; }
     }
+    a = wave_allmax_u32(a);
+    fl_wg = wave_allsum_u64(fl_wg);
+    if ((threadIdx.x & 63) == 0) { sha[threadIdx.x >> 6] = a; shl[threadIdx.x >> 6] = fl_wg; }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    unsigned long long flushes = 0ull;
+#pragma unroll
+    for (int w = 0; w < kGamThreads / 64; ++w) { a = max(a, sha[w]); flushes += shl[w]; }
+    t.gam[2] = (t.flush_part && flushes >= t.flush_need) ? 1u : 0u;
+    const uint32_t mg = group_mantissa_bits(a, kE4M3Max, t.mode);
+    t.gam[0] = mg;
+    const uint32_t mg5 = group_mantissa_bits(a, kE5M2Max, t.mode);
+    t.gam[1] = mg5;
+    if (t.gmant) { t.gmant[0] = mg; t.gmant[1] = mg5; }
 }
 
 // Group loop of Algorithm 1 with bands of rows as groups: workgroup (band, w) scans its share of the band's 16-byte chunks,
 // then one lane per band turns the band's amax into its two mantissas (table behind the four header words of `gam`).
+template <bool KEEP>
 __global__ __launch_bounds__(256) void k_band_amax(const uint16_t* __restrict__ x, KShape sh, int64_t group_rows, int wpb,
                                                    uint32_t* __restrict__ part) {
     __shared__ uint32_t sh4[4];
@@ -1434,7 +1475,8 @@ __global__ __launch_bounds__(256) void k_band_amax(const uint16_t* __restrict__ 
     uint32_t a2 = 0u;
     for (int64_t c = (int64_t)w * 256 + threadIdx.x; c < n_chunks; c += (int64_t)wpb * 256) {
         const int64_t r = c / cpr, cc = c - r * cpr;
-        a2 = amax2_of(load16(x + (r_first + r) * sh.ld + cc * 8), a2);
+        const uint16_t* p = x + (r_first + r) * sh.ld + cc * 8;
+        a2 = amax2_of(KEEP ? *reinterpret_cast<const u32x4*>(p) : load16(p), a2);
     }
     const uint32_t a = block_allmax_u32(fold_max16(a2), sh4);
     if (threadIdx.x == 0) part[blockIdx.x] = a;
@@ -1522,6 +1564,7 @@ static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o) {
     t.n_chunks = sh.rows * cpr;
     t.n_tiles = (t.n_chunks + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
     t.chunks_per_row = cpr;
+    t.keep_from = keep_for_second_pass(sh) ? 0 : t.n_tiles;
     t.rm = RowMap{};
     t.rm.ld = sh.ld;
     if (cpr >= (1 << 28) || !row_map_fits(longest_row(sh, o), kTensorChunksPerBlock / cpr + 2)) return;      // wide: cpr stays 0
@@ -1629,6 +1672,8 @@ struct BatchRun {
     bool will_ride = false;                      // the batch has grouped per-tensor launches for statistics to ride on
     bool riders_used = false;                    // the first statistics group went along with a per-tensor launch
     bool stats_done[kBatchMax] = {};             // the operand's block kernel has written its statistics already
+    int wave_of[kBatchMax] = {};                 // operands that Algorithm 1 reads twice: group of at most kKeepGroupBytes; others 0
+    int n_waves = 1;
 
     size_t ws_bytes = 0;
     // Next `bytes` of the caller's workspace.  The phases below carve exactly what item_workspace() adds up; should the
@@ -1641,8 +1686,9 @@ struct BatchRun {
         ws_off += need;
         return p;
     }
-    void group_mantissas();
-    void sub_tensor_operands(int crit);
+    void assign_waves();
+    void group_mantissas(int wave);
+    void sub_tensor_operands(int crit, int wave);
     void tensor_level_decisions();
     void collect_statistics();
     void per_tensor_operands(int crit);
@@ -1651,15 +1697,26 @@ struct BatchRun {
 
 // ---- Algorithm 1, group loop: operands with sub-tensor blocks and GAM / E8M0 scaling get their group
 //      mantissas first (GAM: one more read of the operand for its amax)
-void BatchRun::group_mantissas() {
+void BatchRun::assign_waves() {
+    int64_t bytes = 0;
+    for (int i = 0; i < n; ++i) {
+        const BatchItem& it = items[i];
+        if (it.gran == kGranTensor || it.gran == kGranCol || it.scaling != kScaleGam) continue;      // (those two group themselves)
+        const int64_t b = it.sh.rows * it.sh.cols * 2;
+        if (bytes > 0 && bytes + b > kKeepGroupBytes) { ++n_waves; bytes = 0; }
+        bytes += b;
+        wave_of[i] = n_waves - 1;
+    }
+}
+void BatchRun::group_mantissas(int wave) {
     int idx[kBatchMax];
     int cnt = 0;
     for (int i = 0; i < n; ++i)
-        if (items[i].gran != kGranTensor && items[i].scaling != kScaleFp32 && items[i].group_rows == 0) idx[cnt++] = i;
+        if (wave_of[i] == wave && items[i].gran != kGranTensor && items[i].scaling != kScaleFp32 && items[i].group_rows == 0) idx[cnt++] = i;
     // operands whose groups are bands of rows: one mantissa pair per band, in a table behind the four header words
     for (int i = 0; i < n && err == hipSuccess; ++i) {
         const BatchItem& it = items[i];
-        if (it.group_rows == 0) continue;
+        if (wave_of[i] != wave || it.group_rows == 0) continue;
         const int64_t n_groups = (it.sh.rows + it.group_rows - 1) / it.group_rows;
         const int wpb = band_wgs(it);
         if (n_groups * wpb > 0x7FFFFFFF) { err = hipErrorInvalidValue; return; }
@@ -1667,7 +1724,9 @@ void BatchRun::group_mantissas() {
         uint32_t* part = reinterpret_cast<uint32_t*>(carve(sizeof(uint32_t) * (size_t)n_groups * (size_t)wpb));
         if (err != hipSuccess) return;
         gam_of[i] = gam;
-        { ProfScope ps(prof, kKernGroupAmax, st); k_band_amax<<<dim3((unsigned)(n_groups * wpb)), dim3(256), 0, st>>>(it.x, it.sh, it.group_rows, wpb, part); }
+        { ProfScope ps(prof, kKernGroupAmax, st); 
+            if (keep_for_second_pass(it.sh)) k_band_amax<true><<<dim3((unsigned)(n_groups * wpb)), dim3(256), 0, st>>>(it.x, it.sh, it.group_rows, wpb, part);
+            else k_band_amax<false><<<dim3((unsigned)(n_groups * wpb)), dim3(256), 0, st>>>(it.x, it.sh, it.group_rows, wpb, part); }
         { ProfScope ps(prof, kKernGroupMantissa, st); k_gam_prepare_bands<<<dim3((unsigned)((n_groups + 255) / 256)), dim3(256), 0, st>>>(part, wpb, n_groups, gam, it.o.gmant); }
     }
     // operands whose tensor-level decision the pre-pass may prove: block-shaped pre-pass (group amax and, per block,
@@ -1699,7 +1758,7 @@ void BatchRun::group_mantissas() {
             if (!scope_proof_applies(it)) continue;
             pv_part[i] = reinterpret_cast<uint32_t*>(carve(sizeof(uint32_t) * kProveMaxWg));
             pv_flush[i] = reinterpret_cast<uint32_t*>(carve(sizeof(uint32_t) * kProveMaxWg));
-            pv[n_pv] = BlockProveItem{it.x, it.sh.rows, it.sh.cols, it.sh.ld, pv_part[i], pv_flush[i], 0, scope_proof_kind(it)};
+            pv[n_pv] = BlockProveItem{it.x, it.sh.rows, it.sh.cols, it.sh.ld, pv_part[i], pv_flush[i], 0, scope_proof_kind(it), keep_for_second_pass(it.sh) ? 1 : 0};
             pv_units += scope_proof_units(it);
             pv_item[n_pv] = i;
             if (++n_pv == kProveGroup) flush();
@@ -1755,13 +1814,13 @@ void BatchRun::group_mantissas() {
         GroupStats none; none.n = 0; none.near_tol = near_tol;
         if (ga[0].n) {
             ProfScope ps(prof, kKernGroupAmax, st);
-            k_tensor_amax_group<false><<<dim3(a_end[0]), dim3(256), kResidency3, st>>>(ga[0], none, a_end[0]);
+            k_tensor_amax_group<false><<<dim3(a_end[0]), dim3(256), 0, st>>>(ga[0], none, a_end[0], 0);
         }
         if (ga[1].n) {
             ProfScope ps(prof, kKernGroupAmax, st);
-            k_tensor_amax_group<true><<<dim3(a_end[1]), dim3(256), kResidency3, st>>>(ga[1], none, a_end[1]);
+            k_tensor_amax_group<true><<<dim3(a_end[1]), dim3(256), 0, st>>>(ga[1], none, a_end[1], 0);
         }
-        { ProfScope ps(prof, kKernGroupMantissa, st); k_gam_prepare<<<dim3(m), dim3(256), 0, st>>>(gg); }
+        { ProfScope ps(prof, kKernGroupMantissa, st); k_gam_prepare<<<dim3(m), dim3(kGamThreads), 0, st>>>(gg); }
     }
 }
 
@@ -1798,7 +1857,7 @@ void launch_solo_stats(const dim3& grid, int crit, bool fake, const SubRiders& o
 }
 
 // ---- operands with sub-tensor blocks of one criterion
-void BatchRun::sub_tensor_operands(int crit) {
+void BatchRun::sub_tensor_operands(int crit, int wave) {
     // ---- small flat 1x128 operands ride on the first 128x128 team launch of the same criterion and output kind
     // (extra workgroups of that launch) instead of paying the ramp and tail of a launch of their own
     TeamRiders riders;
@@ -1806,7 +1865,7 @@ void BatchRun::sub_tensor_operands(int crit) {
     int64_t rider_units = 0;
     bool team_has[2] = {false, false};
     for (int i = 0; i < n; ++i)
-        if (route[i] == kRouteTeam && items[i].crit == crit && team_kind_of(items[i]) == 0) team_has[items[i].o.fake ? 1 : 0] = true;
+        if (wave_of[i] == wave && route[i] == kRouteTeam && items[i].crit == crit && team_kind_of(items[i]) == 0) team_has[items[i].o.fake ? 1 : 0] = true;
     // ---- 1x128 sub-channel operands, persistent grouped kernel (FP8 payload, then fake quantization; flat, then ROWS form)
     for (int variant = 0; variant < 4 && err == hipSuccess; ++variant) {
         const bool fake = (variant & 1) != 0, rows_form = (variant & 2) != 0;
@@ -1850,7 +1909,7 @@ void BatchRun::sub_tensor_operands(int crit) {
         };
         for (int i = 0; i < n; ++i) {
             const BatchItem& it = items[i];
-            if (route[i] != (rows_form ? kRouteSubRows : kRouteSubFlat) || it.crit != crit || (it.o.fake != nullptr) != fake) continue;
+            if (wave_of[i] != wave || route[i] != (rows_form ? kRouteSubRows : kRouteSubFlat) || it.crit != crit || (it.o.fake != nullptr) != fake) continue;
             const int64_t n_units = (item_parts(it) + 31) / 32;
             if (!rows_form && n_units <= kSubRiderMaxUnits && team_has[fake] && riders.table.n < kMaxSubRiders &&
                 (riders.table.n == 0 || riders.fake == fake)) {
@@ -1873,7 +1932,7 @@ void BatchRun::sub_tensor_operands(int crit) {
     // ---- 1x128 sub-channel operands, general kernel
     for (int i = 0; i < n && err == hipSuccess; ++i) {
         const BatchItem& it = items[i];
-        if (route[i] != kRouteSubGeneral || it.crit != crit) continue;
+        if (wave_of[i] != wave || route[i] != kRouteSubGeneral || it.crit != crit) continue;
         err = launch_sub1x128(it.x, it.sh, it.o, crit, it.scope == 1, it.th, (uint32_t)it.scaling, gam_of[i], (uint32_t)it.three,
                               (uint32_t)it.group_rows, st, prof);
     }
@@ -1882,7 +1941,7 @@ void BatchRun::sub_tensor_operands(int crit) {
         int idx[kBatchMax];
         int cnt = 0;
         for (int i = 0; i < n; ++i)
-            if (route[i] == kRouteTeam && items[i].crit == crit && team_kind_of(items[i]) == kind) idx[cnt++] = i;
+            if (wave_of[i] == wave && route[i] == kRouteTeam && items[i].crit == crit && team_kind_of(items[i]) == kind) idx[cnt++] = i;
         if (cnt) err = launch_team_items(items, idx, cnt, kind, crit, gam_of, &riders, st, prof);
     }
     if (err == hipSuccess && riders.table.n > 0 && !riders.used) {      // no team launch took them: a launch of their own
@@ -1901,7 +1960,7 @@ void BatchRun::sub_tensor_operands(int crit) {
         int idx[kBatchMax];
         int cnt = 0;
         for (int i = 0; i < n; ++i)
-            if (route[i] == kRouteSubCol && items[i].crit == crit) idx[cnt++] = i;
+            if (wave_of[i] == wave && route[i] == kRouteSubCol && items[i].crit == crit) idx[cnt++] = i;
         if (cnt) err = launch_subcol_items(items, idx, cnt, crit, gam_of, st, prof);
     }
     // ---- per-channel columns
@@ -1910,7 +1969,7 @@ void BatchRun::sub_tensor_operands(int crit) {
         char* ws_of[kBatchMax];
         int cnt = 0;
         for (int i = 0; i < n; ++i)
-            if (route[i] == kRouteChannelCol && items[i].crit == crit) {
+            if (wave_of[i] == wave && route[i] == kRouteChannelCol && items[i].crit == crit) {
                 ws_of[cnt] = carve(column_workspace_bytes(items[i].sh.rows, items[i].sh.cols));
                 col_ws[i] = ws_of[cnt];
                 idx[cnt++] = i;
@@ -1983,19 +2042,31 @@ void BatchRun::collect_statistics() {
     }
 }
 
-// The three launches of a group of per-tensor operands; statistics of sub-tensor operands ride in extra workgroups.
+// The launches of a table of per-tensor operands: pass A and pass B over one part of the table after the other (see
+// kKeepGroupBytes), then one finish pass for all.  Statistics of sub-tensor operands ride in extra workgroups of the first and
+// the last one.
+struct TensorPart {
+    int a0, a1, s0, s1;      // workgroups of pass A and pass B
+    int lds;                 // residency cap
+};
 template <bool STRIDED>
-void launch_tensor_passes(const GroupTensor& g, const GroupStats& riders, int a_end, int ride_partial, int s_end, int c_end, int ride_final,
-                          int crit, bool fake, int lds, hipStream_t st, KProf* prof) {
-    { ProfScope ps(prof, kKernTensorAmax, st); k_tensor_amax_group<STRIDED><<<dim3(a_end + ride_partial), dim3(256), lds, st>>>(g, riders, a_end); }
-    {
+void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_parts, const GroupStats& riders, int ride_partial, int c_end,
+                          int ride_final, int crit, bool fake, hipStream_t st, KProf* prof) {
+    for (int k = 0; k < n_parts; ++k) {
+        const TensorPart& p = parts[k];
+        const int ride = k == 0 ? ride_partial : 0;
+        {
+            ProfScope ps(prof, kKernTensorAmax, st);
+            k_tensor_amax_group<STRIDED><<<dim3(p.a1 - p.a0 + ride), dim3(256), 0, st>>>(g, riders, p.a1 - p.a0, p.a0);
+        }
         ProfScope ps(prof, kKernTensorQuant, st);
+        const dim3 grid(p.s1 - p.s0);
         if (fake) {
-            if (crit == kCritEq3) k_tensor_quant_group<kCritEq3, true, STRIDED><<<dim3(s_end), dim3(256), lds, st>>>(g);
-            else k_tensor_quant_group<kCritEq2, true, STRIDED><<<dim3(s_end), dim3(256), lds, st>>>(g);
+            if (crit == kCritEq3) k_tensor_quant_group<kCritEq3, true, STRIDED><<<grid, dim3(256), p.lds, st>>>(g, p.s0);
+            else k_tensor_quant_group<kCritEq2, true, STRIDED><<<grid, dim3(256), p.lds, st>>>(g, p.s0);
         } else {
-            if (crit == kCritEq3) k_tensor_quant_group<kCritEq3, false, STRIDED><<<dim3(s_end), dim3(256), lds, st>>>(g);
-            else k_tensor_quant_group<kCritEq2, false, STRIDED><<<dim3(s_end), dim3(256), lds, st>>>(g);
+            if (crit == kCritEq3) k_tensor_quant_group<kCritEq3, false, STRIDED><<<grid, dim3(256), p.lds, st>>>(g, p.s0);
+            else k_tensor_quant_group<kCritEq2, false, STRIDED><<<grid, dim3(256), p.lds, st>>>(g, p.s0);
         }
     }
     {
@@ -2014,28 +2085,13 @@ void BatchRun::per_tensor_operands(int crit) {
         auto flush = [&]() {
             if (cnt == 0 || err != hipSuccess) { cnt = 0; return; }
             GroupTensor g; g.n = cnt; g.near_tol = near_tol;
-            int64_t total_tiles = 0;
-            for (int k = 0; k < cnt; ++k) {
-                const BatchItem& it = items[idx[k]];
-                const int64_t n_chunks = it.sh.rows * it.sh.cols / 8;
-                total_tiles += (n_chunks + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
-            }
-            int a_end = 0, s_end = 0, c_end = 0;
-            // Launch shape.  Several operands in the launch: one 32 KB tile per workgroup of pass B (up to 16384), at most three
-            // workgroups resident per compute unit.  One operand alone does better with persistent workgroups that are all
-            // resident from the start (measured with cold caches: 112 MiB, E4M3 kept: 57 us against 77 us per call; 336 MiB:
-            // 148 against 195 us; 224 MiB falling back: 146 against 157 us), whereas the six gradients of the layer sweep
-            // lose with that shape (333 against 294 us for the three launches).
-            const bool solo = cnt == 1 && total_tiles <= 2000ll * kSoloQuantBlocks;
-            const int amax_cap = solo ? kSoloAmaxBlocks : kMaxAmaxBlocks, quant_cap = solo ? kSoloQuantBlocks : kMaxQuantBlocks;
-            const int pass_lds = solo ? 0 : kResidency3;
+            int64_t all_tiles = 0;
             for (int k = 0; k < cnt; ++k) {
                 const BatchItem& it = items[idx[k]];
                 TensorOp& t = g.op[k];
                 t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u; t.lean = it.lean ? 1u : 0u;
                 set_tensor_layout(t, it.sh, it.o);
-                t.n_amax = share(t.n_tiles, total_tiles, amax_cap, t.n_tiles);
-                t.n_slots = share(t.n_tiles, total_tiles, quant_cap, t.n_tiles);
+                all_tiles += t.n_tiles;
                 const TensorPlan pl = plan_tensor(it.sh.rows, it.sh.cols);
                 char* w = carve(pl.bytes);
                 t.amax_part = reinterpret_cast<uint32_t*>(w + pl.off_amax_part);
@@ -2048,11 +2104,42 @@ void BatchRun::per_tensor_operands(int crit) {
                 if (crit == kCritEq2 && it.o.bf16 && !it.three && it.th > 0.0f && it.th < 0.9f)
                     t.flush_need = flush_need_of(it.th, it.sh.rows * it.sh.cols);
                 t.stats = static_cast<StatsDev*>(it.stats);
-                a_end += t.n_amax; s_end += t.n_slots;
-                c_end += (it.o.bf16 || it.three) ? share(t.n_tiles, total_tiles, 2048, 2048) : 1;
-                g.amax_end[k] = a_end; g.slot_end[k] = s_end; g.copy_end[k] = c_end;
             }
             if (err != hipSuccess) { cnt = 0; return; }      // the workspace ran out while carving
+            TensorPart parts[kMaxGroupTensor];
+            int n_parts = 0, a_end = 0, s_end = 0, c_end = 0;
+            for (int first = 0; first < cnt;) {
+                int64_t bytes = 0, total_tiles = 0;
+                int last = first;                            // operands first .. last - 1 form a part
+                for (; last < cnt; ++last) {
+                    const BatchItem& it = items[idx[last]];
+                    const int64_t b = it.sh.rows * it.sh.cols * 2;
+                    if (last > first && bytes + b > kKeepGroupBytes) break;
+                    bytes += b;
+                    total_tiles += g.op[last].n_tiles;
+                }
+                // Launch shape.  Several operands in the launch: one 32 KB tile per workgroup of pass B (up to 16384), at most
+                // three workgroups resident per compute unit.  One operand alone does better with persistent workgroups that are
+                // all resident from the start (224 MiB falling back: 129 us per call with 512 workgroups in pass A and 1280 in
+                // pass B, 130 with 768 and 1536, 135 with one tile per workgroup; the six gradients of a layer 409 us against 414 the
+                // other way round).
+                const bool solo = last - first == 1 && total_tiles <= 2000ll * kSoloQuantBlocks;
+                const int amax_cap = solo ? kSoloAmaxBlocks : kMaxAmaxBlocks, quant_cap = solo ? kSoloQuantBlocks : kMaxQuantBlocks;
+                TensorPart& p = parts[n_parts++];
+                p.lds = solo ? 0 : kResidency3;
+                p.a0 = a_end; p.s0 = s_end;
+                for (int k = first; k < last; ++k) {
+                    TensorOp& t = g.op[k];
+                    t.n_amax = share(t.n_tiles, total_tiles, amax_cap, t.n_tiles);
+                    t.n_slots = share(t.n_tiles, total_tiles, quant_cap, t.n_tiles);
+                    t.keep_from = bytes > kKeepTensorBytes ? t.n_tiles - t.n_tiles * (kKeepTensorBytes >> 15) / total_tiles : 0;
+                    a_end += t.n_amax; s_end += t.n_slots;
+                    c_end += (t.o.bf16 || t.three) ? share(t.n_tiles, all_tiles, 2048, 2048) : 1;
+                    g.amax_end[k] = a_end; g.slot_end[k] = s_end; g.copy_end[k] = c_end;
+                }
+                p.a1 = a_end; p.s1 = s_end;
+                first = last;
+            }
             GroupStats riders; riders.n = 0; riders.near_tol = near_tol;
             int ride_partial = 0, ride_final = 0;
             if (!riders_used && n_stats_groups > 0) {
@@ -2061,8 +2148,8 @@ void BatchRun::per_tensor_operands(int crit) {
                 ride_final = ride_partial > riders.n ? riders.n : 0;      // single-workgroup operands are final already
                 riders_used = true;
             }
-            if (strided) launch_tensor_passes<true>(g, riders, a_end, ride_partial, s_end, c_end, ride_final, crit, fake, pass_lds, st, prof);
-            else launch_tensor_passes<false>(g, riders, a_end, ride_partial, s_end, c_end, ride_final, crit, fake, pass_lds, st, prof);
+            if (strided) launch_tensor_passes<true>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
+            else launch_tensor_passes<false>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             cnt = 0;
         };
         for (int i = 0; i < n; ++i) {
@@ -2099,8 +2186,11 @@ hipError_t launch_batch(const BatchItem* items, int n, float near_tol, void* ws,
     run.ws_bytes = ws_bytes;
     for (int i = 0; i < n; ++i) run.route[i] = route_of(items[i]);
     for (int i = 0; i < n; ++i) run.will_ride |= run.route[i] == kRouteTensorGroup;
-    run.group_mantissas();
-    for (int crit = 0; crit < 2 && run.err == hipSuccess; ++crit) run.sub_tensor_operands(crit);
+    run.assign_waves();
+    for (int wave = 0; wave < run.n_waves && run.err == hipSuccess; ++wave) {
+        run.group_mantissas(wave);
+        for (int crit = 0; crit < 2 && run.err == hipSuccess; ++crit) run.sub_tensor_operands(crit, wave);
+    }
     if (run.err == hipSuccess) run.tensor_level_decisions();
     // the statistics of the sub-tensor operands are collected after their kernels (and tensor-level decisions)
     if (run.err == hipSuccess) run.collect_statistics();

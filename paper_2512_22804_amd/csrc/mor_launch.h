@@ -116,9 +116,8 @@ struct ProfScope {
 
 // Residency caps: bytes of dynamic LDS a launch reserves (and never touches) so that only 3 or 5 workgroups of 256
 // lanes fit the 160 KB of a compute unit.  The streaming passes run faster with FEWER workgroups in flight than
-// their register use would allow (measured on MI355X: pass B of the per-tensor path 214 us at 3 per unit, 226 us at 4,
-// 237 us at 6, 223 us at 2; pass A 79 us at 3 against 81 us uncapped; the 128x128 team kernel 114 us at 4 or 5 against
-// 116 us at 7; the quantize pass of the per-channel columns 0.609 ms per twelve-operand pass at 4 against 0.620 ms
+// their register use would allow (measured on MI355X: pass B of the per-tensor path over several operands, whole layer call,
+// 413.5 us at 3 per unit, 417 us at 4, 419 us at 5 and uncapped; the 128x128 team kernel 114 us at 4 or 5 against 116 us at 7; the quantize pass of the per-channel columns 0.609 ms per twelve-operand pass at 4 against 0.620 ms
 // uncapped): fewer concurrent streams keep the accesses of each HBM channel closer together.  Kernels that need many
 // waves to hide latency (de-quantization, 128x1 sub-columns) lose with a cap and have none.
 constexpr int kResidency3 = 52000;
@@ -126,6 +125,21 @@ constexpr int kResidency4 = 39000;
 constexpr int kResidency5 = 31000;
 
 constexpr int kBatchMax = 64;     // operands per batch call
+
+// Operands that are read twice (amax first, then quantize).  The first pass reads them without the non-temporal hint, so that
+// they stay in the Infinity Cache (256 MB) for the second one, and a batch takes them in groups of at most kKeepGroupBytes,
+// both passes of one group before the next group's.  Measured with bare passes (2 bytes read; 2 read and 3 written per
+// element): 64 MB 39 -> 32 us, 224 MB 135 -> 114, 480 MB 295 -> 260 in one group and 228 in two, 960 MB 597 -> 566 in one.
+// The first pass itself is up to 15 % slower that way (6.0 instead of 7.0 TB/s), which an operand far larger than the cache does
+// not get back: above kKeepMaxBytes the hint stays.
+constexpr int64_t kKeepGroupBytes = 256ll << 20;
+constexpr int64_t kKeepMaxBytes = 1ll << 30;
+// Per-tensor operands, whose quantize pass may also write a BF16 copy, keep at most the last kKeepTensorBytes of a group.  More
+// pays in calls that follow each other (224 MiB falling back to BF16, us per call: none 146.4, 64 MB 138, 96 MB 134.8, 128 MB 132.2, all
+// 128.9; the six gradients of a layer 429, 412, 407.9, 406.6, 408), but a call whose output buffers have just been filled by
+// others finds their unwritten lines in the cache and has them evicted: 179, 184.6, 185.8, 188.9, 203 us for its first pass.
+constexpr int64_t kKeepTensorBytes = 96ll << 20;
+inline bool keep_for_second_pass(const KShape& sh) { return sh.rows * sh.cols * 2 <= kKeepMaxBytes; }
 
 // One operand of a batch (validated by the caller).
 struct BatchItem {
@@ -188,6 +202,7 @@ struct BlockProveItem {
     uint32_t* flush_part;    // [n_wg]
     int n_wg;
     int kind;                // kProveKind*
+    int keep;                // keep_for_second_pass
 };
 hipError_t launch_block_amax_prove(const BlockProveItem* ops, int n, hipStream_t st);
 

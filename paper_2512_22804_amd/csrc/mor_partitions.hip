@@ -361,6 +361,7 @@ struct ProveOp {
     uint32_t* amax_part;
     uint32_t* flush_part;
     int32_t kind;            // kProveBlock128, kProveRows, kProveBlock64
+    int32_t keep;            // the operand stays in the Infinity Cache for the block kernel (see keep_for_second_pass)
 };
 enum { kProveBlock128 = kProveKindBlock128, kProveRows = kProveKindRows, kProveBlock64 = kProveKindBlock64,
        kProveSubRow = kProveKindSubRow,       // 1 x 128 sub-rows: the 16 lanes of a DPP row hold one whole block per chunk
@@ -384,14 +385,28 @@ __device__ __forceinline__ void prove_tiles(const ProveOp& t, int b, int nb, uin
             const int64_t piece = unit * 4 + w, row = piece / t.units_x, c0 = (piece - row * t.units_x) * kProvePiece;
             const BufRsrc rx = make_buf(t.x + row * t.ld + c0);
             const bool inside = piece < t.n_units;
+            if (t.keep) {
 #pragma unroll
-            for (int i = 0; i < kChunks; ++i)
-                raw[i] = buf_load16(rx, (inside && c0 + (i * 64 + lane) * 8 < t.cols) ? (uint32_t)(lane * 16) : kBufOutside, i * 1024);
+                for (int i = 0; i < kChunks; ++i)
+                    raw[i] = buf_load16_first<true>(rx, (inside && c0 + (i * 64 + lane) * 8 < t.cols) ? (uint32_t)(lane * 16) : kBufOutside, i * 1024);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kChunks; ++i)
+                    raw[i] = buf_load16_first<false>(rx, (inside && c0 + (i * 64 + lane) * 8 < t.cols) ? (uint32_t)(lane * 16) : kBufOutside, i * 1024);
+            }
         } else {
             const int64_t tr = unit / t.units_x, tc = unit - tr * t.units_x;
-            const uint16_t* __restrict__ src = t.x + (tr * 128 + (tid >> 4)) * t.ld + tc * 128 + (tid & 15) * 8;
+            if (t.keep) {
+                // (buffer loads, see above: their policies stay apart; a tile's rows span less than 2 GB where keep is set)
+                const BufRsrc rx = make_buf(t.x + tr * 128 * t.ld + tc * 128);
+                const uint32_t off = (uint32_t)(((tid >> 4) * t.ld + (tid & 15) * 8) * 2), step = (uint32_t)(16 * t.ld * 2);
 #pragma unroll
-            for (int i = 0; i < kChunks; ++i) raw[i] = load16(src + (int64_t)i * 16 * t.ld);
+                for (int i = 0; i < kChunks; ++i) raw[i] = buf_load16_first<true>(rx, off, i * step);
+            } else {
+                const uint16_t* __restrict__ src = t.x + (tr * 128 + (tid >> 4)) * t.ld + tc * 128 + (tid & 15) * 8;
+#pragma unroll
+                for (int i = 0; i < kChunks; ++i) raw[i] = load16(src + (int64_t)i * 16 * t.ld);
+            }
         }
     };
     const int64_t n_wg_units = KIND == kProveRows ? (t.n_units + 3) / 4 : t.n_units;
@@ -536,6 +551,7 @@ struct ColOp {
     uint32_t group_rows;        // 128 x 1 blocks under GAM with bands of rows as groups (0: one group)
     uint8_t defer, mode, three, prove;   // prove: count certain flushes in the amax pass (see below)
     uint8_t derive_gam;
+    uint8_t keep;               // column-amax pass: the operand stays in the Infinity Cache for the quantize pass
     const uint32_t* gam;
     // per-channel columns: workspace, [n_strips x cols_padded] each, cols_padded = tiles_x * 128
     uint16_t* part_amax;
@@ -660,10 +676,15 @@ __device__ __forceinline__ void col_strip(const ColOp& t, int64_t unit, ColShare
         // (the next tile's loads are not started early: with 32 more registers fewer workgroups fit, and the quantize pass
         // of the per-channel columns took 407 us instead of 396 us)
         u32x4 raw[kChunks];
+        if (MODE == kColAmax && t.keep) {
 #pragma unroll
-        for (int i = 0; i < kChunks; ++i) {
-            if constexpr (EDGE) raw[i] = buf_load16(rx, is_valid(i) ? xoff : kBufOutside, i * xstep);
-            else raw[i] = load16(src + (int64_t)i * 16 * t.ld);
+            for (int i = 0; i < kChunks; ++i) raw[i] = buf_load16_first<true>(rx, is_valid(i) ? xoff : kBufOutside, i * xstep);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kChunks; ++i) {
+                if constexpr (EDGE) raw[i] = buf_load16(rx, is_valid(i) ? xoff : kBufOutside, i * xstep);
+                else raw[i] = load16(src + (int64_t)i * 16 * t.ld);
+            }
         }
         // one sweep over the chunks for everything that reads the magnitudes (column amax, zero counts, smallest
         // non-zero magnitude), so that no masked copy of the tile stays in registers
@@ -1314,6 +1335,7 @@ hipError_t launch_block_amax_prove(const BlockProveItem* ops, int n, hipStream_t
         for (int k = base; k < n && k < base + kMaxTeamGroup; ++k) {
             ProveOp& t = g.op[g.n];
             t.x = ops[k].x; t.ld = ops[k].ld; t.cols = ops[k].cols; t.kind = ops[k].kind;
+            t.keep = ops[k].keep && (t.kind == kProveRows || 128 * ops[k].ld * 2 < 0x7FFFFFFFll) ? 1 : 0;
             if (t.kind == kProveRows) { t.units_x = (ops[k].cols + kProvePiece - 1) / kProvePiece; t.n_units = ops[k].rows * t.units_x; }
             else { t.units_x = ops[k].cols / 128; t.n_units = (ops[k].rows / 128) * t.units_x; }
             t.amax_part = ops[k].amax_part; t.flush_part = ops[k].flush_part;
@@ -1424,7 +1446,9 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
         GroupCol g; g.n = 0;
         int64_t total = 0;
         int comb = 0, copy = 0;
+        int64_t group_bytes = 0;
         auto flush = [&]() {
+            group_bytes = 0;
             if (g.n == 0) return;
             // fallback-column pass: about kColCopyBudget workgroups over all operands of the launch (a workgroup that finds
             // every kept column already written costs a few nanoseconds of dispatch, which adds up over 12 000 of them)
@@ -1456,7 +1480,10 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
             const int64_t tiles_x = (it.sh.cols + 127) / 128;
             const int64_t units = (int64_t)pl.n_strips * tiles_x;
             if (units > 0x3FFFFFFF || tiles_x * kColCopyRowGroups > 0x3FFFFFFF) return hipErrorInvalidValue;
-            if (total + units > 0x7FFFFFFF || (int64_t)copy + tiles_x * kColCopyRowGroups > 0x7FFFFFFF) flush();
+            const int64_t bytes = it.sh.rows * it.sh.cols * 2;
+            if (total + units > 0x7FFFFFFF || (int64_t)copy + tiles_x * kColCopyRowGroups > 0x7FFFFFFF ||
+                (group_bytes > 0 && group_bytes + bytes > kKeepGroupBytes)) flush();
+            group_bytes += bytes;
             ColOp& t = g.op[g.n];
             fill_col_op(t, it, gam_of[idx[k]]);
             char* w = ws_of[k];
@@ -1476,6 +1503,7 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
             t.wg = reinterpret_cast<uint32_t*>(w + pl.off_wg);
             t.derive_gam = it.scaling == kScaleGam ? 1 : 0;
             t.gmant = it.o.gmant;
+            t.keep = keep_for_second_pass(it.sh) ? 1 : 0;
             total += units;
             comb += (int)((pl.cols_padded + 255) / 256);
             copy += (int)(tiles_x * kColCopyRowGroups);          // upper bound, for the overflow check above; set in flush()
