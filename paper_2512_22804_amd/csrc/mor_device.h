@@ -67,6 +67,10 @@ constexpr int kGamHeaderWords = 4;
 __device__ __forceinline__ const uint32_t* gam_words(const uint32_t* gam, uint32_t group_rows, int64_t r0) {
     return group_rows ? gam + kGamHeaderWords + 2 * (r0 / group_rows) : gam;
 }
+// E8M0-only scaling: the caller's group-mantissa output, written once per operand by the lane that owns its first block.
+__device__ __forceinline__ void zero_group_mantissa(uint32_t* gmant) {
+    if (gmant) { gmant[0] = 0u; gmant[1] = 0u; }
+}
 // With a scale of up to one binade below s_b, the smallest BF16 subnormal times the scale can round to a
 // binary32 zero one binade of amax earlier, so the branch-free path ends at 2^24 instead of 2^25.
 __device__ __forceinline__ uint32_t fast_amax_limit(uint32_t mode) { return mode == kScaleFp32 ? kFastAmaxBits : kFastAmaxBits - 0x80u; }
@@ -441,8 +445,12 @@ __device__ __forceinline__ uint32_t decide_eq3(float err4, float err5) { return 
 // zeros and stores nothing, so ragged edges need no per-lane branches.  Offsets are bytes from `base`
 // (32 bits; callers keep them below 2^31).
 constexpr int kBufAux = 2;      // cache-policy field of the buffer loads: non-temporal
-constexpr int kBufStoreAux = 2;  // of the buffer stores: non-temporal.  Written through at system scope as well (nt sc1) they cost the
-                                 // per-tensor quantize pass 2.3 us of 84 us where its operand comes from the Infinity Cache
+// Cache policies of the buffer stores.  kBufStoreAux: non-temporal and written through at system scope (nt sc1); the de-quantize
+// kernel takes 60.5 us with it where nt alone takes 61.2, fake quantization at 128x1 with columns kept in BF16 (stored over the
+// de-quantized values) 76.5 against 81.9 us.  kBufStoreNt: nt alone, for the per-tensor quantize pass, which reads its operand
+// partly from the Infinity Cache (130.3 against 131.4 us per call of 8192 x 14336), and for 1x128 operands with padded rows (a
+// pair of 4099 x 5000 slices 51.7 against 53.9 us).
+constexpr int kBufStoreAux = 18, kBufStoreNt = 2;
 typedef __amdgpu_buffer_rsrc_t BufRsrc;
 constexpr uint32_t kBufOutside = 0x80000000u;
 __device__ __forceinline__ BufRsrc make_buf(const void* base) {
@@ -469,14 +477,16 @@ __device__ __forceinline__ u32x2 buf_load8(BufRsrc r, uint32_t voff, uint32_t so
 // states before the data registers are overwritten and reuses them in the very next instruction, but on gfx950 the
 // first data dword of some lanes was then stored with its NEW contents (seen as rare, timing-dependent corruption of
 // fake-quantized rows).  With a constant scalar offset the compiler inserts the wait states and the data is intact.
+template <int AUX = kBufStoreAux>
 __device__ __forceinline__ void buf_store16(BufRsrc r, uint32_t voff, const u32x4& v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, kBufStoreAux);
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, AUX);
 }
 // No other code may issue a 16-byte buffer store (a register scalar offset would bring the hazard back): any later use
 // of the builtin's name is a compile error.
 #pragma GCC poison __builtin_amdgcn_raw_buffer_store_b128
+template <int AUX = kBufStoreAux>
 __device__ __forceinline__ void buf_store8(BufRsrc r, uint32_t voff, uint32_t soff, const u32x2& v) {
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, kBufStoreAux);
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, AUX);
 }
 
 // Streaming accesses: every operand byte is touched once per pass, so loads and stores carry the

@@ -76,6 +76,7 @@ __device__ __forceinline__ void sub_block_body(const u32x4& raw, const uint16_t*
         if constexpr (CRIT == kCritEq3) o.err5_sum[p] = err5;
         if constexpr (!DEFER) o.mask[p] = (uint8_t)mask;
         if (mode != kScaleFp32 && o.e8m0) o.e8m0[p] = (uint8_t)(__float_as_uint(s) >> 23);
+        if (mode == kScaleE8M0 && p == 0) zero_group_mantissa(o.gmant);
         if (three && o.amin) o.amin[p] = __uint_as_float(amin_bits << 16);
     }
     if constexpr (!DEFER) {
@@ -97,7 +98,7 @@ __global__ __launch_bounds__(256) void k_sub1x128_strided(const uint16_t* __rest
         u32x4 raw; raw.x = 0u; raw.y = 0u; raw.z = 0u; raw.w = 0u;
         if (valid) raw = load16(src);
         uint32_t mg = 0u, mg5 = 0u;
-        if (mode) { const uint32_t* gw = gam_words(gam, group_rows, r); mg = gw[0]; mg5 = gw[1]; }
+        if (mode == kScaleGam) { const uint32_t* gw = gam_words(gam, group_rows, r); mg = gw[0]; mg5 = gw[1]; }
         sub_block_body<CRIT, DEFER, FAKE>(raw, src, valid, l, r * cpr + cb, o, FAKE ? nullptr : o.fp8 + r * o.ld_fp8 + c,
                                           o.bf16 ? o.bf16 + r * o.ld_bf16 + c : nullptr, FAKE ? o.fake + r * o.ld_fake + c : nullptr,
                                           th, mode, mg, mg5, three != 0u);
@@ -112,7 +113,9 @@ __global__ __launch_bounds__(256) void k_sub1x128_strided(const uint16_t* __rest
 // ======================================================================================
 constexpr int kTensorChunksPerThread = 8;                       // 16-byte chunks per thread in pass B
 constexpr int kTensorChunksPerBlock = 256 * kTensorChunksPerThread;
-constexpr int kMaxAmaxBlocks = 512;      // pass A of several operands, all its workgroups resident.  The two parts of the six gradients of
+constexpr int kAmaxOneTile = 768;        // tiles of a pass-A launch up to which every one gets a workgroup (three per compute unit); also the size of
+                                         // the partials' arrays.  1251 tiles of padded rows: 51.6 us per call at 512 workgroups, 53.3 at 1251
+constexpr int kMaxAmaxBlocks = 512;      // pass A of larger launches, all its workgroups resident.  The two parts of the six gradients of
                                          // a layer (256 and 235 MB) take 45 + 39 us at 512, 49 + 39 us at 2048 with three resident per
                                          // compute unit; the whole layer 409 us at 512, 411 at 384, 413 at 768, 428 at 2048
 constexpr int kProveMaxWg = 8192;      // workgroups of one launch (and partial records per operand) of the block-shaped GAM pre-pass
@@ -208,7 +211,8 @@ struct TensorPartials {   // one slot per pass-B workgroup (at most kMaxQuantBlo
     uint32_t* abits;       // [0] = global amax bits, published by workgroup 0 of pass B
 };
 constexpr int kMaxQuantBlocks = 16384;
-constexpr int kSoloAmaxBlocks = 512, kSoloQuantBlocks = 1280;     // launch shape of a per-tensor operand that is alone in its launches
+constexpr int kSoloQuantBlocks = 1280;     // pass B of a per-tensor operand that is alone in its launches: persistent workgroups
+constexpr int kQuantOneTile = 1536;        // ... unless its tiles all fit the chip at once (six workgroups per compute unit)
 
 template <typename T>
 __device__ __forceinline__ T block_sum_256(T v, T* sh) {
@@ -308,85 +312,6 @@ __device__ __forceinline__ void copy_chunk_tiles(const uint16_t* __restrict__ x,
             for (int u = 0; u < 4; ++u)
                 if (c0 + u * 256 < n_chunks) store16(dst + (c0 + u * 256) * 8, load16(x + (c0 + u * 256) * 8));
         }
-    }
-}
-
-// ======================================================================================
-// Tensor-level decision over sub-tensor scaling (Section 3.1): the deferred block kernels wrote
-// err_sum / nnz per block; aggregate sum(err_sum) / sum(nnz), decide once, broadcast the mask.
-// ======================================================================================
-// Grouped: every operand with a tensor-level decision shares two launches -- partial sums per workgroup, then the decision
-// (re-derived by every workgroup of the operand from the partials in a fixed order, so all agree) with the mask
-// broadcast and the conditional copy of the BF16 fallback.
-constexpr int kScopeBlocks = 256;       // partial records per operand
-constexpr int kMaxGroupScope = 16;
-struct ScopeOp {
-    const float* err_sum; const float* err5_sum; const uint32_t* nnz; uint8_t* mask;
-    int64_t n_part;
-    double* part_err; double* part_err5; unsigned long long* part_nnz;     // [kScopeBlocks] each
-    uint32_t* decision;                                                    // [1]
-    const uint32_t* proven;                                                // non-null and [0] != 0: the block kernel wrote the fallback
-    float th;
-    int32_t crit;
-    int32_t n_red;                                                         // workgroups of the reduce pass (<= kScopeBlocks)
-    // fallback copy
-    const uint16_t* x; uint16_t* bf16;
-    int64_t rows, cols, ld, ld_bf16;
-};
-struct GroupScope {
-    int n;
-    int32_t red_end[kMaxGroupScope], copy_end[kMaxGroupScope];
-    ScopeOp op[kMaxGroupScope];
-};
-__global__ __launch_bounds__(256) void k_scope_reduce_group(GroupScope g) {
-    __shared__ double shd[4];
-    __shared__ unsigned long long shl[4];
-    const int op = group_find32(g.red_end, g.n, blockIdx.x);
-    const ScopeOp& t = g.op[op];
-    const int b = blockIdx.x - (op ? g.red_end[op - 1] : 0);
-    double e = 0.0, e5 = 0.0;
-    unsigned long long n = 0;
-    const int64_t stride = (int64_t)t.n_red * 256;
-    for (int64_t p = (int64_t)b * 256 + threadIdx.x; p < t.n_part; p += stride) {
-        e += (double)t.err_sum[p];
-        n += t.nnz[p];
-        if (t.crit == kCritEq3) e5 += (double)t.err5_sum[p];
-    }
-    e = block_sum_shfl<double>(e, shd);
-    n = block_sum_shfl<unsigned long long>(n, shl);
-    e5 = block_sum_shfl<double>(e5, shd);
-    if (threadIdx.x == 0) { t.part_err[b] = e; t.part_nnz[b] = n; t.part_err5[b] = e5; }
-}
-// Same decision in every workgroup that calls it (fixed summation order over the operand's partial records).
-__device__ __forceinline__ uint32_t scope_decision(const ScopeOp& t, double* shd, unsigned long long* shl) {
-    double e = 0.0, e5 = 0.0;
-    unsigned long long n = 0;
-    if ((int)threadIdx.x < t.n_red) { e = t.part_err[threadIdx.x]; n = t.part_nnz[threadIdx.x]; e5 = t.part_err5[threadIdx.x]; }
-    e = block_sum_shfl<double>(e, shd);
-    n = block_sum_shfl<unsigned long long>(n, shl);
-    e5 = block_sum_shfl<double>(e5, shd);
-    if (t.crit == kCritEq3) return (e < e5) ? 0u : 1u;
-    return ((n ? e / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
-}
-// Decision (every workgroup re-derives it from the partial records: the same value everywhere), mask broadcast over the
-// operand's workgroups, then the copy of a BF16 tensor that no earlier pass has proven and written.
-__global__ __launch_bounds__(256) void k_scope_copy_group(GroupScope g) {
-    __shared__ double shd[4];
-    __shared__ unsigned long long shl[4];
-    const int op = group_find32(g.copy_end, g.n, blockIdx.x);
-    const ScopeOp& t = g.op[op];
-    const int b = blockIdx.x - (op ? g.copy_end[op - 1] : 0);
-    const int nb = g.copy_end[op] - (op ? g.copy_end[op - 1] : 0);
-    const uint32_t m = scope_decision(t, shd, shl);
-    if (b == 0 && threadIdx.x == 0) t.decision[0] = m;
-    for (int64_t p = (int64_t)b * 256 + threadIdx.x; p < t.n_part; p += (int64_t)nb * 256) t.mask[p] = (uint8_t)m;
-    if (t.bf16 == nullptr || m == 0u || (t.proven && t.proven[0] != 0u)) return;
-    if (t.ld == t.cols && t.ld_bf16 == t.cols) {
-        copy_chunk_tiles(t.x, t.bf16, t.rows * t.cols / 8, b, nb);
-    } else {
-        const int64_t cpr = t.cols / 8;
-        for (int64_t r = b; r < t.rows; r += nb)
-            for (int64_t c = threadIdx.x; c < cpr; c += 256) store16(t.bf16 + r * t.ld_bf16 + c * 8, load16(t.x + r * t.ld + c * 8));
     }
 }
 
@@ -956,6 +881,140 @@ __global__ __launch_bounds__(256) void k_stats_group_final(GroupStats g) {
     stats_emit(tot, t.out, t.n_part, (unsigned long long)(t.geom.rows * t.geom.cols), nullptr);
 }
 
+// ======================================================================================
+// Tensor-level decision over sub-tensor scaling (Section 3.1): the deferred block kernels wrote
+// err_sum / nnz per block; aggregate sum(err_sum) / sum(nnz), decide once, broadcast the mask.
+// ======================================================================================
+// Grouped: every operand with a tensor-level decision shares two launches -- partial sums per workgroup, then the decision
+// (re-derived by every workgroup of the operand from the partials in a fixed order, so all agree) with the mask
+// broadcast and the conditional copy of the BF16 fallback.
+constexpr int kScopeBlocks = 256;       // partial records per operand
+constexpr int kMaxGroupScope = 16;
+struct ScopeOp {
+    const float* err_sum; const float* err5_sum; const uint32_t* nnz; uint8_t* mask;
+    int64_t n_part;
+    double* part_err; double* part_err5; unsigned long long* part_nnz;     // [kScopeBlocks] each
+    uint32_t* decision;                                                    // [1]
+    const uint32_t* proven;                                                // non-null and [0] != 0: the block kernel wrote the fallback
+    float th;
+    int32_t crit;
+    int32_t n_red;                                                         // workgroups of the reduce pass (<= kScopeBlocks)
+    // fallback copy
+    const uint16_t* x; uint16_t* bf16;
+    int64_t rows, cols, ld, ld_bf16;
+    // selection statistics: all blocks get one decision, so the reduce pass can count everything that does not depend on it
+    StatsDev* stats;                                                       // optional
+    StatsRec* rec;                                                         // [n_red]
+    float near_tol;
+};
+struct GroupScope {
+    int n;
+    int32_t red_end[kMaxGroupScope], copy_end[kMaxGroupScope];
+    ScopeOp op[kMaxGroupScope];
+};
+// Four blocks' loads in flight per lane.  With statistics the same sweep also fills the workgroup's record (histogram bins,
+// near-threshold blocks), so no statistics launch follows.  Per-channel operands of one linear layer, 67 + 50 MB: 88.3 us per call
+// against 103.4 us with statistics launches, three barriers per sum and an empty fallback-column launch.
+__global__ __launch_bounds__(256) void k_scope_reduce_group(GroupScope g) {
+    __shared__ double shd[4];
+    __shared__ StatsFastShared<4> sh;
+    const int op = group_find32(g.red_end, g.n, blockIdx.x);
+    const ScopeOp& t = g.op[op];
+    const int b = blockIdx.x - (op ? g.red_end[op - 1] : 0);
+    const bool eq3 = t.crit == kCritEq3, want = t.stats != nullptr;
+    double e5 = 0.0;
+    StatsPacked acc;
+    acc.e = 0.0; acc.n = 0ull; acc.eb = 0ull; acc.e5 = 0ull;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc.pk[k] = 0u;
+    const int64_t stride = (int64_t)t.n_red * 256;
+    for (int64_t p0 = (int64_t)b * 256 + threadIdx.x; p0 < t.n_part; p0 += 4 * stride) {
+        float es[4], es5[4];
+        uint32_t nz[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool ok = p0 + u * stride < t.n_part;
+            const int64_t p = ok ? p0 + u * stride : p0;       // always a valid block: the loads need no branch
+            es[u] = t.err_sum[p]; nz[u] = t.nnz[p]; es5[u] = eq3 ? t.err5_sum[p] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (p0 + u * stride >= t.n_part) continue;
+            e5 += (double)es5[u];
+            if (want) stats_accumulate_packed(es[u], nz[u], 0u, 0ull, t.th, t.near_tol, acc);
+            else { acc.e += (double)es[u]; acc.n += nz[u]; }
+        }
+    }
+    StatsTotals tot;
+    tot.e = acc.e; tot.n = acc.n; tot.eb = 0ull; tot.e5 = 0ull;
+#pragma unroll
+    for (int k = 0; k < kStatCnt; ++k) tot.c[k] = (k & 1) ? acc.pk[k >> 1] >> 16 : acc.pk[k >> 1] & 0xFFFFu;
+    e5 = block_sum_shfl<double>(e5, shd);
+    stats_fast_reduce(tot, sh);                                // the totals arrive in wave 0
+    if (threadIdx.x == 0) { t.part_err[b] = tot.e; t.part_nnz[b] = tot.n; t.part_err5[b] = e5; }
+    if (want) stats_emit(tot, nullptr, 0, 0ull, t.rec + b);
+}
+// Same decision in every wave that calls it (fixed summation order over the operand's partial records), no barrier.
+__device__ __forceinline__ uint32_t scope_decision(const ScopeOp& t) {
+    const int lane = threadIdx.x & 63;
+    double e = 0.0, e5 = 0.0;
+    unsigned long long n = 0;
+#pragma unroll
+    for (int k = 0; k < kScopeBlocks / 64; ++k) {
+        const bool ok = lane + 64 * k < t.n_red;
+        const int i = ok ? lane + 64 * k : 0;
+        const double ev = t.part_err[i], e5v = t.part_err5[i];
+        const unsigned long long nv = t.part_nnz[i];
+        e += ok ? ev : 0.0; e5 += ok ? e5v : 0.0; n += ok ? nv : 0ull;
+    }
+    e = wave_allsum_f64(e);
+    if (t.crit == kCritEq3) return (e < wave_allsum_f64(e5)) ? 0u : 1u;
+    n = wave_allsum_u64(n);
+    return ((n ? e / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
+}
+// Decision (every workgroup re-derives it from the partial records: the same value everywhere), mask broadcast over the
+// operand's workgroups, statistics by its first one, then the copy of a BF16 tensor that no earlier pass has proven and written.
+__global__ __launch_bounds__(256) void k_scope_copy_group(GroupScope g) {
+    __shared__ StatsFastShared<4> sh;
+    const int op = group_find32(g.copy_end, g.n, blockIdx.x);
+    const ScopeOp& t = g.op[op];
+    const int b = blockIdx.x - (op ? g.copy_end[op - 1] : 0);
+    const int nb = g.copy_end[op] - (op ? g.copy_end[op - 1] : 0);
+    const uint32_t m = scope_decision(t);
+    if (b == 0 && threadIdx.x == 0) t.decision[0] = m;
+    for (int64_t p = (int64_t)b * 256 + threadIdx.x; p < t.n_part; p += (int64_t)nb * 256) t.mask[p] = (uint8_t)m;
+    if (b == 0 && t.stats) {                                   // uniform over the workgroup
+        StatsTotals tot;
+        tot.e = 0.0; tot.n = 0ull; tot.eb = 0ull; tot.e5 = 0ull;
+#pragma unroll
+        for (int k = 0; k < kStatCnt; ++k) tot.c[k] = 0u;
+        if ((int)threadIdx.x < t.n_red) {
+            const StatsRec& r = t.rec[threadIdx.x];
+            tot.e = r.e; tot.n = r.n;
+#pragma unroll
+            for (int k = 0; k < kStatCnt; ++k) tot.c[k] = r.cnt[k];
+        }
+        stats_fast_reduce(tot, sh);
+        const unsigned long long total = (unsigned long long)(t.rows * t.cols);
+        tot.c[12] = 0u;
+        if (m) tot.eb = total;
+        if (threadIdx.x < 64) {
+            const uint32_t mine = stats_pick(tot, (int)threadIdx.x < kStatCnt ? (int)threadIdx.x : 0);
+            if (threadIdx.x < 12) t.stats->hist[threadIdx.x] = mine;
+            if (threadIdx.x == 0)
+                stats_finish(t.stats, t.n_part, total, tot.e, tot.n, m ? (unsigned long long)t.n_part : 0ull, tot.c[13], 0ull, tot.eb, 0ull, 0u);
+        }
+    }
+    if (t.bf16 == nullptr || m == 0u || (t.proven && t.proven[0] != 0u)) return;
+    if (t.ld == t.cols && t.ld_bf16 == t.cols) {
+        copy_chunk_tiles(t.x, t.bf16, t.rows * t.cols / 8, b, nb);
+    } else {
+        const int64_t cpr = t.cols / 8;
+        for (int64_t r = b; r < t.rows; r += nb)
+            for (int64_t c = threadIdx.x; c < cpr; c += 256) store16(t.bf16 + r * t.ld_bf16 + c * 8, load16(t.x + r * t.ld + c * 8));
+    }
+}
+
 // ---- a lone dense 1 x 128 operand: the block kernel gathers the statistics of its workgroups itself (one record per
 //      workgroup), so that the call needs one small combine launch afterwards instead of two statistics launches that
 //      read the per-block outputs again.  (Combining the records inside the block kernel as well -- the workgroup that
@@ -1269,7 +1328,7 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
         for (int u = 0; u < kTensorChunksPerThread; ++u) acc.zero2 = zero2_of(raw[u], acc.zero2);
         asm volatile("" : "+v"(acc.zero2));      // counted here, not sunk below the sweep (which would keep the masked words alive)
 #pragma unroll
-        for (int u = 0; u < kTensorChunksPerThread; ++u) buf_store16(rb, at_16(u, t.o.ld_bf16), raw[u]);       // proven fallback
+        for (int u = 0; u < kTensorChunksPerThread; ++u) buf_store16<kBufStoreNt>(rb, at_16(u, t.o.ld_bf16), raw[u]);       // proven fallback
         pos = pos0;
         if constexpr (STRIDED) asm volatile("" : "+v"(pos.r), "+v"(pos.c));      // the sweep's offsets are formed chunk by chunk, not kept from here
         if (CRIT == kCritEq3 && fast && dual) {
@@ -1278,8 +1337,8 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
             for (int u = 0; u < kTensorChunksPerThread; ++u) {
                 u32x4 deq;
                 const u32x2 codes = quant8_dual<FAKE>(raw[u], s, s_inv, acc.e0, acc.e1, acc.f0, acc.f1, deq);
-                if constexpr (FAKE) buf_store16(rf, at_16(u, t.o.ld_fake), deq);
-                else buf_store8(r8, at_fp8(u), 0u, codes);
+                if constexpr (FAKE) buf_store16<kBufStoreNt>(rf, at_16(u, t.o.ld_fake), deq);
+                else buf_store8<kBufStoreNt>(r8, at_fp8(u), 0u, codes);
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else if (fast) {
@@ -1287,8 +1346,8 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
             for (int u = 0; u < kTensorChunksPerThread; ++u) {
                 u32x4 deq;
                 const u32x2 codes = quant8_fast_deq<false, FAKE>(raw[u], s, s_inv, acc.e0, acc.e1, deq);
-                if constexpr (FAKE) buf_store16(rf, at_16(u, t.o.ld_fake), deq);
-                else buf_store8(r8, at_fp8(u), 0u, codes);
+                if constexpr (FAKE) buf_store16<kBufStoreNt>(rf, at_16(u, t.o.ld_fake), deq);
+                else buf_store8<kBufStoreNt>(r8, at_fp8(u), 0u, codes);
                 if constexpr (CRIT == kCritEq3) (void)quant8_fast<true>(raw[u], s5, acc.f0, acc.f1);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -1407,7 +1466,7 @@ __global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, Grou
 
 // Group loop of Algorithm 1 for sub-tensor operands: the operand's amax (partials of pass A) gives the
 // group mantissas for E4M3 and E5M2, which the block kernels read; also written to the caller's output.
-// E8M0-only operands have no amax pass (n_amax = 0) and a zero mantissa.
+// (E8M0-only operands have a zero mantissa, which their block kernels know.)
 struct GamOp {
     const uint32_t* amax_part; int n_amax;
     uint32_t mode;
@@ -1508,7 +1567,7 @@ static int band_wgs(const BatchItem& it) {
 
 TensorPlan plan_tensor(int64_t, int64_t) {
     TensorPlan pl;
-    pl.amax_blocks = kMaxAmaxBlocks;
+    pl.amax_blocks = kAmaxOneTile;
     pl.quant_blocks = kMaxQuantBlocks;
     size_t off = 0;
     pl.off_amax_part = off; off = align16(off + sizeof(uint32_t) * (size_t)pl.amax_blocks);
@@ -1532,6 +1591,9 @@ constexpr int64_t kSubFlatMaxBlocks = 1536;   // workgroups of 4 waves, each wav
                                               // registers let be resident, so no workgroup waits for another to end (one 64 MiB operand, cold
                                               // caches: 21.0 us at 1536 against 23.2 us at 2048 (one unit per wave); 112 MiB: 32.1 against 34.5 us;
                                               // 224 MiB: 65 us either way)
+constexpr int64_t kSubRowsAlone = 98304;      // 1121 x 704 beside eleven other operands: 33.6 us per call with the general kernel, 37.7 in the
+                                              // ROWS form; 68 000 blocks alone 11.5 against 11.7; 164 000 blocks 24.6 against 18 us; twelve
+                                              // operands of 64 to 2048 rows 53 to 78 us against 19 to 39
 constexpr int64_t kSubRowsMaxBlocks = 1280;   // the ROWS form's registers (90) let five be resident per compute unit
 static_assert(kSubFlatMaxBlocks <= 2 * kSoloFinalThreads, "k_solo_stats_final takes two records per lane");
 static int clamp_grid_y(int64_t v) { return (int)(v < 1 ? 1 : (v > 65535 ? 65535 : v)); }
@@ -1577,6 +1639,9 @@ static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o) {
 // ---- batches ---------------------------------------------------------------------------------
 namespace {
 constexpr int kStatsMaxWg = 256;
+static_assert(kScopeBlocks <= kStatsMaxWg, "a tensor-level decision leaves one statistics record per reduce workgroup");
+constexpr int kScopeCopyWg = 1024;      // workgroups of a decision / mask / copy launch (per-channel operands of one linear layer, none of them
+                                        // copied: 88.3 us per call, 89.9 at 4096; 8192 x 14336 copied: 145.7 against 145.4 us)
 
 // Which kernels take an operand.
 enum Route {
@@ -1712,7 +1777,7 @@ void BatchRun::group_mantissas(int wave) {
     int idx[kBatchMax];
     int cnt = 0;
     for (int i = 0; i < n; ++i)
-        if (wave_of[i] == wave && items[i].gran != kGranTensor && items[i].scaling != kScaleFp32 && items[i].group_rows == 0) idx[cnt++] = i;
+        if (wave_of[i] == wave && items[i].gran != kGranTensor && items[i].scaling == kScaleGam && items[i].group_rows == 0) idx[cnt++] = i;
     // operands whose groups are bands of rows: one mantissa pair per band, in a table behind the four header words
     for (int i = 0; i < n && err == hipSuccess; ++i) {
         const BatchItem& it = items[i];
@@ -1781,7 +1846,6 @@ void BatchRun::group_mantissas(int wave) {
             q.amax_part = nullptr; q.n_amax = 0; q.mode = (uint32_t)it.scaling; q.gam = gam; q.gmant = it.o.gmant;
             q.flush_part = nullptr; q.flush_need = 0ull; q.skip = 0u;
             slot_of[k] = -1;
-            if (it.scaling != kScaleGam) continue;
             if (it.gran == kGranCol) { q.skip = 1u; continue; }      // the group amax comes out of the column-amax pass
             if (pv_part[i]) {
                 q.amax_part = pv_part[i]; q.n_amax = pv_wg[i];
@@ -1804,7 +1868,7 @@ void BatchRun::group_mantissas(int wave) {
         for (int l = 0; l < 2; ++l)
             for (int j = 0; j < ga[l].n; ++j) {
                 TensorOp& t = ga[l].op[j];
-                t.n_amax = share(t.n_tiles, total_tiles[l], kMaxAmaxBlocks, t.n_tiles);
+                t.n_amax = share(t.n_tiles, total_tiles[l], total_tiles[l] <= kAmaxOneTile ? kAmaxOneTile : kMaxAmaxBlocks, t.n_tiles);
                 a_end[l] += t.n_amax;
                 ga[l].amax_end[j] = a_end[l];
             }
@@ -1820,7 +1884,9 @@ void BatchRun::group_mantissas(int wave) {
             ProfScope ps(prof, kKernGroupAmax, st);
             k_tensor_amax_group<true><<<dim3(a_end[1]), dim3(256), 0, st>>>(ga[1], none, a_end[1], 0);
         }
-        { ProfScope ps(prof, kKernGroupMantissa, st); k_gam_prepare<<<dim3(m), dim3(kGamThreads), 0, st>>>(gg); }
+        bool any = false;
+        for (int k = 0; k < m; ++k) any |= gg.op[k].skip == 0u;
+        if (any) { ProfScope ps(prof, kKernGroupMantissa, st); k_gam_prepare<<<dim3(m), dim3(kGamThreads), 0, st>>>(gg); }
     }
 }
 
@@ -2006,11 +2072,15 @@ void BatchRun::tensor_level_decisions() {
         if (column_tensor_proof_applies(it)) t.proven = column_tensor_proven_word(col_ws[i], it.sh.rows, it.sh.cols);
         int64_t want = (t.n_part + 1023) / 1024;
         t.n_red = (int)(want < 1 ? 1 : (want > kScopeBlocks ? kScopeBlocks : want));
+        t.stats = static_cast<StatsDev*>(it.stats);
+        t.rec = it.stats ? reinterpret_cast<StatsRec*>(carve(sizeof(StatsRec) * kStatsMaxWg)) : nullptr;
+        t.near_tol = near_tol;
+        stats_done[i] = true;
         t.x = it.x; t.bf16 = it.o.bf16;
         t.rows = it.sh.rows; t.cols = it.sh.cols; t.ld = it.sh.ld; t.ld_bf16 = it.o.ld_bf16;
         red += t.n_red;
         {   // workgroups of the decision / mask / copy launch: enough for the copy, and never fewer than the reduce pass had
-            const int c = it.o.bf16 ? share(it.sh.rows * it.sh.cols, total_elems, 4096, 4096) : 1;
+            const int c = it.o.bf16 ? share(it.sh.rows * it.sh.cols, total_elems, kScopeCopyWg, kScopeCopyWg) : 1;
             copy += c > t.n_red ? c : t.n_red;
         }
         g.red_end[g.n] = red; g.copy_end[g.n] = copy;
@@ -2124,7 +2194,9 @@ void BatchRun::per_tensor_operands(int crit) {
                 // pass B, 130 with 768 and 1536, 135 with one tile per workgroup; the six gradients of a layer 409 us against 414 the
                 // other way round).
                 const bool solo = last - first == 1 && total_tiles <= 2000ll * kSoloQuantBlocks;
-                const int amax_cap = solo ? kSoloAmaxBlocks : kMaxAmaxBlocks, quant_cap = solo ? kSoloQuantBlocks : kMaxQuantBlocks;
+                // Up to kAmaxOneTile tiles, and what fits the chip at once in pass B, a workgroup takes one tile.
+                const int amax_cap = total_tiles <= kAmaxOneTile ? kAmaxOneTile : kMaxAmaxBlocks;
+                const int quant_cap = !solo ? kMaxQuantBlocks : (total_tiles <= kQuantOneTile ? kQuantOneTile : kSoloQuantBlocks);
                 TensorPart& p = parts[n_parts++];
                 p.lds = solo ? 0 : kResidency3;
                 p.a0 = a_end; p.s0 = s_end;
@@ -2185,6 +2257,13 @@ hipError_t launch_batch(const BatchItem* items, int n, float near_tol, void* ws,
     run.wsp = static_cast<char*>(ws);
     run.ws_bytes = ws_bytes;
     for (int i = 0; i < n; ++i) run.route[i] = route_of(items[i]);
+    {   // A single 1 x 128 operand that needs the ROWS form gets it from kSubRowsAlone blocks on: a wave works through 32 blocks
+        // there, which a small operand alone pays as latency, but several operands share the launch.
+        int rows_form = 0, last = 0;
+        for (int i = 0; i < n; ++i)
+            if (run.route[i] == kRouteSubRows) { ++rows_form; last = i; }
+        if (rows_form == 1 && item_parts(items[last]) < kSubRowsAlone) run.route[last] = kRouteSubGeneral;
+    }
     for (int i = 0; i < n; ++i) run.will_ride |= run.route[i] == kRouteTensorGroup;
     run.assign_waves();
     for (int wave = 0; wave < run.n_waves && run.err == hipSuccess; ++wave) {

@@ -206,7 +206,7 @@ __device__ __forceinline__ void team_block(const TeamOp& t, int64_t unit, TeamSh
     const uint32_t abits = team_allmax<TEAM>(fold_max16(sc.amax2), sh);
     const uint32_t mode = t.mode;
     uint32_t mg = 0u, mg5 = 0u;
-    if (mode) { const uint32_t* gw = gam_words(t.gam, t.group_rows, r0); mg = gw[0]; mg5 = gw[1]; }
+    if (mode == kScaleGam) { const uint32_t* gw = gam_words(t.gam, t.group_rows, r0); mg = gw[0]; mg5 = gw[1]; }
     float s = block_scale(abits, kE4M3Max, mode, mg);
     float s5 = 0.0f;                                       // only Eq. 3 and the three-way recipe look at E5M2
     if (CRIT == kCritEq3 || t.three) s5 = block_scale(abits, kE5M2Max, mode, mg5);
@@ -312,6 +312,7 @@ __device__ __forceinline__ void team_block(const TeamOp& t, int64_t unit, TeamSh
         if constexpr (CRIT == kCritEq3) o.err5_sum[p] = err5;
         if (!defer) o.mask[p] = (uint8_t)mask;
         if (mode != kScaleFp32 && o.e8m0) o.e8m0[p] = (uint8_t)(__float_as_uint(s) >> 23);
+        if (mode == kScaleE8M0 && p == 0) zero_group_mantissa(o.gmant);
         if (t.three && o.amin) o.amin[p] = __uint_as_float(amin_bits << 16);
     }
     const bool keep = mask == 1u || proven;                // (a deferred decision has mask 0 here)
@@ -631,7 +632,7 @@ __device__ __forceinline__ void col_strip(const ColOp& t, int64_t unit, ColShare
     const int64_t cols_padded = t.tiles_x * 128;
     const uint32_t mode = t.mode;
     uint32_t mg = 0u, mg5 = 0u;
-    if (mode) {      // (bands of rows as groups only occur with 128 x 1 blocks, where a strip is one tile)
+    if (mode == kScaleGam) {      // (bands of rows as groups only occur with 128 x 1 blocks, where a strip is one tile)
         const uint32_t* gw = gam_words(t.gam, MODE == kColLocal ? t.group_rows : 0u, strip * t.tiles_per_strip * 128);
         mg = gw[0]; mg5 = gw[1];
     }
@@ -898,6 +899,7 @@ __device__ __forceinline__ void col_strip(const ColOp& t, int64_t unit, ColShare
                     if constexpr (CRIT == kCritEq3) o.err5_sum[p] = e5;
                     if (!defer) o.mask[p] = (uint8_t)mk;
                     if (mode != kScaleFp32 && o.e8m0) o.e8m0[p] = (uint8_t)(__float_as_uint(s_out) >> 23);
+                    if (mode == kScaleE8M0 && p == 0) zero_group_mantissa(o.gmant);
                     if (t.three && o.amin) o.amin[p] = __uint_as_float(amin_bits << 16);
                 }
             }
@@ -1078,8 +1080,6 @@ __global__ __launch_bounds__(256) void k_col_scales(GroupCol g) {
             gam_out[0] = mg; gam_out[1] = mg5;
             if (t.gmant) { t.gmant[0] = mg; t.gmant[1] = mg5; }
         }
-    } else if (t.mode) {
-        mg = t.gam[0]; mg5 = t.gam[1];
     }
     bool all_proven = false;
     if (t.prove && t.tensor_need) {                        // uniform over the workgroup
@@ -1121,6 +1121,7 @@ __global__ __launch_bounds__(256) void k_col_scales(GroupCol g) {
         t.o.amax[c] = __uint_as_float(a << 16);
         t.o.scale[c] = s;
         if (t.mode != kScaleFp32 && t.o.e8m0) t.o.e8m0[c] = (uint8_t)(__float_as_uint(s) >> 23);
+        if (t.mode == kScaleE8M0 && c == 0) zero_group_mantissa(t.gmant);
     }
 }
 // Second combine: column error sums over the strips (binary64, fixed order), non-zero counts, decision.
@@ -1470,7 +1471,9 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
                 if (crit == kCritEq3) k_col_finish<kCritEq3><<<dim3((unsigned)comb), dim3(256), 0, st>>>(g);
                 else k_col_finish<kCritEq2><<<dim3((unsigned)comb), dim3(256), 0, st>>>(g);
             }
-            { ProfScope ps(prof, kKernFallbackCopy, st); k_col_fallback<<<dim3((unsigned)copy), dim3(256), 0, st>>>(g); }
+            bool copies = false;      // some operand keeps columns in BF16 or E5M2 by decisions of their own
+            for (int k = 0; k < g.n; ++k) copies |= !g.op[k].defer && (g.op[k].o.bf16 != nullptr || g.op[k].three);
+            if (copies) { ProfScope ps(prof, kKernFallbackCopy, st); k_col_fallback<<<dim3((unsigned)copy), dim3(256), 0, st>>>(g); }
             g.n = 0; total = 0; comb = 0; copy = 0;
         };
         for (int k = 0; k < cnt; ++k) {

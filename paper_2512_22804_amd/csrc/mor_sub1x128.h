@@ -217,8 +217,8 @@ __device__ __forceinline__ void sub_unit_process(const u32x4 (&raw)[8], const ui
                 }                                                                          \
             }                                                                              \
             if constexpr (ROWS) {                                                          \
-                if constexpr (FAKE) buf_store16(rf, sub_off<2>(sr, pos, l, o.ld_fake), deq); \
-                else buf_store8(r8, sub_off<1>(sr, pos, l, o.ld_fp8), 0u, codes);          \
+                if constexpr (FAKE) buf_store16<kBufStoreNt>(rf, sub_off<2>(sr, pos, l, o.ld_fake), deq); \
+                else buf_store8<kBufStoreNt>(r8, sub_off<1>(sr, pos, l, o.ld_fp8), 0u, codes); \
                 sub_step(sr, pos);                                                         \
             } else if constexpr (FAKE) store16(ff + K * 128, deq);                         \
             else store8(fl + K * 128, codes);                                              \
@@ -269,7 +269,7 @@ __device__ __forceinline__ void sub_unit_process(const u32x4 (&raw)[8], const ui
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     const uint32_t at = sub_off<2>(sr, pos, l, o.ld_bf16);
-                    buf_store16(rb, (bits >> k) & 1u ? at : kBufOutside, raw[k]);
+                    buf_store16<kBufStoreNt>(rb, (bits >> k) & 1u ? at : kBufOutside, raw[k]);
                     sub_step(sr, pos);
                 }
             } else {
@@ -310,7 +310,7 @@ struct GroupSubT {
     uint8_t defer[N];          // 1: tensor-level decision follows, write no mask / fallback here
     uint8_t mode[N];           // scaling algorithm
     uint8_t prove[N];          // 1: gam[2] != 0 says that the tensor-level BF16 decision is already proven (fallback stored here)
-    const uint32_t* gam[N];    // mode != 0: {mantissa for E4M3, mantissa for E5M2, proven flag} of the operand's group
+    const uint32_t* gam[N];    // GAM: {mantissa for E4M3, mantissa for E5M2, proven flag} of the operand's group; null otherwise
     uint32_t group_rows[N];    // GAM with bands of rows as groups (0: one group): the band's mantissas come from the table behind gam
     uint32_t bpr[N];           // blocks per row, to find a block's row
     int64_t ld[N], cols[N], n_part[N];      // ROWS form (padded leading dimensions, ragged edges)
@@ -359,7 +359,7 @@ __device__ __forceinline__ void sub_group_body(const G& g, int64_t block, int64_
     auto process = [&](const u32x4 (&raw)[8], int op, int64_t local) {
         const uint32_t mode = g.mode[op];
         uint32_t mg = 0u, mg5 = 0u;
-        if (mode) { mg = g.gam[op][0]; if constexpr (CRIT == kCritEq3) mg5 = g.gam[op][1]; }
+        if (__builtin_expect(mode == kScaleGam, 0)) { mg = g.gam[op][0]; if constexpr (CRIT == kCritEq3) mg5 = g.gam[op][1]; }
         const bool proven = g.prove[op] != 0 && g.gam[op][2] != 0u;
         sub_unit_process<CRIT, FAKE, STATS, ROWS>(raw, g.x[op], g.o[op], local, lane, g.th[op], g.defer[op] != 0, mode, mg, mg5, proven,
                                             g.gam[op], mode == kScaleGam ? g.group_rows[op] : 0u, g.bpr[op], rows_of(op), ssh, near_tol);
@@ -367,6 +367,9 @@ __device__ __forceinline__ void sub_group_body(const G& g, int64_t block, int64_
     int opA;
     int64_t locA;
     load_unit(bufA, u, opA, locA);
+    if (block == 0 && threadIdx.x == 0)                    // (in the shadow of the first unit's loads)
+        for (int op = 0; op < g.n; ++op)
+            if (g.mode[op] == kScaleE8M0) zero_group_mantissa(g.o[op].gmant);
     for (;;) {
         process(bufA, opA, locA);
         u += W;

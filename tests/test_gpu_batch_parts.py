@@ -51,3 +51,27 @@ def test_parts_equal_single_calls(scaling, scope):
                 assert got[k] == want[k], (gran, rows, cols, k)
         kept += int((b.mask == 1).sum())
     assert kept > 0
+
+
+@pytest.mark.parametrize("crit", ["mean_rel_err", "e4m3_vs_e5m2"])
+@pytest.mark.parametrize("rows, cols", [(1, 128), (255, 128), (256, 128), (257, 128), (1025, 128), (2048, 128 * 129)])
+def test_tensor_level_statistics(crit, rows, cols):
+    """Statistics gathered by the reduce pass of a tensor-level decision: one block, a last lane or wave that is not full, one and
+    more than one workgroup, more blocks than one round of all workgroups."""
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    for seed in (0, 1):                    # kept in E4M3 and in BF16 under Eq. 2
+        x = _operand(rows, cols, seed, dev)
+        p = B.make_params(rows, cols, "sub1x128", "tensor", crit, 0.0238)
+        out = B.alloc_outputs(p, dev, bf16_fill=0x5A5A)
+        st = [torch.full((B.STATS_BYTES,), 0xEE, dtype=torch.uint8, device=dev) for _ in range(2)]
+        items = B.make_batch([(p, x, out, st[0])])
+        ws = torch.full((B.mor_batch_workspace_bytes(items),), 0xA7, dtype=torch.uint8, device=dev)
+        B.mor_analyze_quantize_batch(items, 0.05, ws)
+        B.mor_select_stats(p, out.err_sum, out.nnz, out.mask, 0.05, st[1])
+        got, want = (B.read_stats(s) for s in st)
+        for k in want:
+            if k in ("err_sum_total", "mean_err"):       # binary64 sums of the same terms in another order
+                assert got[k] == pytest.approx(want[k], rel=1e-12)
+            else:
+                assert got[k] == want[k], (k, got[k], want[k])

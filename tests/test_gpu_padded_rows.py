@@ -112,3 +112,54 @@ def test_padded_outputs_and_statistics(oracle, gran, rows, cols):
             for k in ("n_part", "n_fp8_part", "n_bf16_part", "n_e5m2_part", "n_elem_fp8", "n_elem_bf16", "n_elem_e5m2", "nnz_total", "hist"):
                 if k in want:
                     assert got[k] == want[k], (k, got[k], want[k])
+
+
+@pytest.mark.parametrize("rows, cols, ld", SHAPES + [(1, 8, 8), (33, 128, 128), (65, 4104, 4104), (31, 1400, 1400)])
+def test_rows_form_of_the_unit_kernel(rows, cols, ld):
+    """Two or more such 1x128 operands in a call share launches of the kernel that works through units of 32 blocks (a small
+    operand alone takes the general kernel); payload with both criteria, fake quantization, bands of rows as GAM groups."""
+    import parity
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    for kind in ("half", "large", "inf"):
+        xb = _operand(rows, cols, ld, kind)
+        for kw in ({}, {"crit": "e4m3_vs_e5m2"}, {"scaling": "gam", "gam_group_rows": 5}, {"scaling": "e8m0", "scope": "tensor"}):
+            p = B.make_params(rows, cols, "sub1x128", ld=ld, ragged=cols % 128 != 0, threshold=0.045, **kw)
+            outs = [parity.guarded_outputs(p, dev, bf16_fill=parity.FILL) for _ in range(2)]
+            fakes = [parity.guarded_outputs(p, dev, want_bf16=False, want_fp8=False) for _ in range(2)]
+            ys = [torch.full((rows, cols), 0x5A5A, dtype=torch.int16, device=dev) for _ in range(2)]
+            x = parity.to_dev(xb)
+            items = B.make_batch([(p, x, o, None) for o, _ in outs] + [(p, x, o, None, y) for (o, _), y in zip(fakes, ys)])
+            ws = torch.full((max(16, B.mor_batch_workspace_bytes(items)),), 0xFF, dtype=torch.uint8, device=dev)
+            B.mor_analyze_quantize_batch(items, 1e-2, ws)
+            torch.cuda.synchronize()
+            for _, guards in outs + fakes:
+                guards.check()
+            parity.compare(xb, "sub1x128", cols=cols, ragged=cols % 128 != 0, label=kind, gpu=(p, outs[1][0]), **kw)
+            o, f = outs[0][0], fakes[1][0]
+            y = torch.full_like(ys[0], 0x1111)
+            B.mor_dequantize(p, o.fp8, o.scale, o.mask, o.bf16, y)
+            assert torch.equal(ys[1], y) and torch.equal(f.mask, o.mask) and torch.equal(f.err_sum, o.err_sum)
+
+
+def test_rows_form_alone_with_statistics(oracle):
+    """One operand large enough for that kernel alone, ragged, with statistics (BF16 blocks of the last column are narrower)."""
+    import parity
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    rows, cols = 24581, 520
+    xb = _operand(rows, cols, cols, "half")
+    p = B.make_params(rows, cols, "sub1x128", ragged=True)
+    out = B.alloc_outputs(p, dev, bf16_fill=parity.FILL)
+    st = torch.full((B.STATS_BYTES,), 0xEE, dtype=torch.uint8, device=dev)
+    items = B.make_batch([(p, parity.to_dev(xb), out, st)])
+    ws = torch.full((B.mor_batch_workspace_bytes(items),), 0xA7, dtype=torch.uint8, device=dev)
+    B.mor_analyze_quantize_batch(items, 1e-2, ws)
+    torch.cuda.synchronize()
+    r = parity.compare(xb, "sub1x128", cols=cols, ragged=True, gpu=(p, out))
+    got, a = B.read_stats(st), r["oracle"]
+    assert 0 < got["n_bf16_part"] < got["n_part"]
+    want = oracle.select_stats(out.err_sum.cpu().numpy(), a.nnz, out.mask.cpu().numpy(), rows, cols, "sub1x128", 0.045, 1e-2, ragged=True)
+    for k in ("n_part", "n_fp8_part", "n_bf16_part", "n_e5m2_part", "n_elem_fp8", "n_elem_bf16", "n_elem_e5m2", "nnz_total", "hist"):
+        if k in want:
+            assert got[k] == want[k], (k, got[k], want[k])
