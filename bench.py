@@ -494,12 +494,13 @@ def main() -> int:
                 rec["launches"] += 1
                 if args.per_operand:
                     rec["bytes"] += algorithmic_bytes(kname, o["n"], o["P"], o["fallback_frac"], o["fused_fallback"])
-                else:      # a grouped launch covers every operand of that granularity
+                else:      # the grouped launches of a kernel cover every operand of that granularity, in parts of at most 256 MB
+                    parts = sum(1 for j in range(pr.count) if B.KERNEL_NAMES[pr.kernel[j]] == kname)
                     for q in ops:
                         if kname.startswith("stats"):
-                            rec["bytes"] += algorithmic_bytes(kname, q["n"], q["P"], 0.0) if q["gran"] != "tensor" else 0.0
+                            rec["bytes"] += algorithmic_bytes(kname, q["n"], q["P"], 0.0) / parts if q["gran"] != "tensor" else 0.0
                         elif KERNEL_GRAN.get(kname) == q["gran"] or (sub_rides and kname == "team_block" and q["gran"] == "sub1x128"):
-                            rec["bytes"] += algorithmic_bytes(kname, q["n"], q["P"], q["fallback_frac"], q["fused_fallback"])
+                            rec["bytes"] += algorithmic_bytes(kname, q["n"], q["P"], q["fallback_frac"], q["fused_fallback"]) / parts
             if not args.per_operand:
                 break
     ev.destroy()

@@ -2159,7 +2159,7 @@ void BatchRun::per_tensor_operands(int crit) {
             for (int k = 0; k < cnt; ++k) {
                 const BatchItem& it = items[idx[k]];
                 TensorOp& t = g.op[k];
-                t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u; t.lean = it.lean ? 1u : 0u;
+                t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u; t.lean = it.lean && !strided ? 1u : 0u;      // (padded rows always get their payload, and report no proof)
                 set_tensor_layout(t, it.sh, it.o);
                 all_tiles += t.n_tiles;
                 const TensorPlan pl = plan_tensor(it.sh.rows, it.sh.cols);
