@@ -211,6 +211,9 @@ struct TensorPartials {   // one slot per pass-B workgroup (at most kMaxQuantBlo
     uint32_t* abits;       // [0] = global amax bits, published by workgroup 0 of pass B
 };
 constexpr int kMaxQuantBlocks = 16384;
+constexpr int64_t kMaxTensorTiles = 2000ll * kMaxQuantBlocks;      // of one operand: pass B's zero counters (16 bits per lane, 32 a tile) last 2047
+static_assert((kMaxTensorTiles / kMaxAmaxBlocks + 1) * kTensorChunksPerBlock * 8 <= 0xFFFFFFFFll,
+              "the flush count of a pass-A workgroup is 32 bits wide");
 constexpr int kSoloQuantBlocks = 1280;     // pass B of a per-tensor operand that is alone in its launches: persistent workgroups
 constexpr int kQuantOneTile = 1536;        // ... unless its tiles all fit the chip at once (six workgroups per compute unit)
 
@@ -1141,7 +1144,7 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
     const int b = block - (op ? g.amax_end[op - 1] : 0);
     const bool prove = t.flush_need != 0ull;
     const bool three = t.three != 0u;
-    uint32_t a2 = 0u, keep2 = 0u, seen = 0u;      // keep2: per half-word count of elements NOT certain to flush
+    uint32_t a2 = 0u, flushed = 0u;
     uint32_t mn2 = 0xFFFFFFFFu;                   // three-way recipe: smallest non-zero pattern, minus one, per half-word
     for (int64_t tile = b; tile < t.n_tiles; tile += t.n_amax) {
         const int64_t c0 = tile * kTensorChunksPerBlock + threadIdx.x;
@@ -1183,6 +1186,7 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
                 // t = running amax with 20 taken off the exponent (0 if that underflows); 1 <= m < t  <=>  m-1 < t-1
                 const uint32_t t2 = pk_sub_sat_u16(a2, 0x0A000A00u);
                 const uint32_t tm1 = pk_sub_sat_u16(t2, 0x00010001u);
+                uint32_t keep2 = 0u;                       // per half-word: elements of this tile NOT certain to flush
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
 #pragma unroll
@@ -1190,7 +1194,7 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
                         const uint32_t mm1 = pk_sub_u16(v[u][j] & 0x7FFF7FFFu, 0x00010001u);     // wraps to 0xFFFF for zeros
                         keep2 = pk_add_u16(keep2, pk_is_zero_u16(pk_sub_sat_u16(tm1, mm1)));
                     }
-                seen += 64u;
+                flushed += 64u - fold_add16(keep2);        // widened tile by tile: 16 bits would hold 2047 tiles of a workgroup
             }
         } else {
             for (int u = 0; u < 8; ++u)
@@ -1206,7 +1210,7 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
     if (three) mn = block_allmin_u16(fold_min16(mn2), sh4);
     if (threadIdx.x == 0) t.amax_part[b] = a | (mn << 16);
     if (prove) {
-        const uint32_t wf = wave_allsum_u32(seen - fold_add16(keep2));
+        const uint32_t wf = wave_allsum_u32(flushed);
         __syncthreads();
         if ((threadIdx.x & 63) == 0) sh4[threadIdx.x >> 6] = wf;
         __syncthreads();
@@ -2228,7 +2232,7 @@ void BatchRun::per_tensor_operands(int crit) {
             const BatchItem& it = items[i];
             if (route[i] != kRouteTensorGroup || it.crit != crit || (it.o.fake != nullptr) != fake || item_is_flat(it) == strided) continue;
             const int64_t n_tiles = (it.sh.rows * it.sh.cols / 8 + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
-            if (n_tiles > 2000ll * kMaxQuantBlocks) { err = hipErrorInvalidValue; return; }   // 16-bit per-lane zero counters
+            if (n_tiles > kMaxTensorTiles) { err = hipErrorInvalidValue; return; }
             idx[cnt] = i;
             if (++cnt == kMaxGroupTensor) flush();
         }
