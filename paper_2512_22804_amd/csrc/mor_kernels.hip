@@ -2283,12 +2283,6 @@ hipError_t launch_batch(const BatchItem* items, int n, float near_tol, void* ws,
     return hipGetLastError();
 }
 
-static int log2_or_whole(int64_t block, int64_t dim) {
-    if (block >= dim) return 62;                 // one block spans the dimension: index >> 62 == 0
-    int l = 0;
-    while ((1ll << l) < block) ++l;
-    return l;
-}
 hipError_t launch_dequantize_batch(const DeqItem* items, int n, hipStream_t st) {
     static_assert(sizeof(GroupDeq) <= 3800, "kernel-argument segment is 4 KB");
     GroupDeq g; g.n = 0;
@@ -2301,7 +2295,7 @@ hipError_t launch_dequantize_batch(const DeqItem* items, int n, hipStream_t st) 
     for (int i = 0; i < n; ++i) {
         const DeqItem& it = items[i];
         const StatsGeom& geom = it.geom;
-        const int prl = log2_or_whole(geom.pr, geom.rows), pcl = log2_or_whole(geom.pc, geom.cols);
+        const int prl = block_shift(geom.pr, geom.rows, 64), pcl = block_shift(geom.pc, geom.cols, 64);
         if (geom.pc == 1 && geom.cols > 1) {       // one column per block: its own kernel
             const dim3 grid((unsigned)((geom.cols + 127) / 128), (unsigned)clamp_grid_y((geom.rows + 127) / 128));
             k_dequant_columns<<<grid, dim3(256), 0, st>>>(geom, prl, it.fp8, it.ld_fp8, it.scale, it.mask, it.bf16, it.ld_bf16, it.y, it.ld_y,
@@ -2322,7 +2316,7 @@ hipError_t launch_dequantize_batch(const DeqItem* items, int n, hipStream_t st) 
         }
         if (total + layout.n_tiles > 0x7FFFFFFF) flush();
         DeqOp& t = g.op[g.n];
-        t.rm = layout.rm; t.n_chunks = layout.n_chunks; t.gc = geom.gc; t.pr_log2 = prl; t.pc_log2 = pcl;
+        t.rm = layout.rm; t.n_chunks = layout.n_chunks; t.gc = geom.gc; t.pr_log2 = prl; t.pc_log2 = block_shift(geom.pc, geom.cols, 32);
         t.fp8 = it.fp8; t.scale = it.scale; t.mask = it.mask; t.bf16 = it.bf16; t.y = it.y; t.e8m0 = it.e8m0; t.gmant = it.gmant;
         t.ld_fp8 = (uint32_t)it.ld_fp8; t.ld_bf16 = (uint32_t)it.ld_bf16; t.ld_y = (uint32_t)it.ld_y;
         t.group_rows = (uint32_t)it.group_rows;

@@ -50,6 +50,14 @@ inline StatsGeom make_geom(int gran, int64_t rows, int64_t cols) {
 }
 inline int64_t geom_parts(const StatsGeom& g) { return ((g.rows + g.pr - 1) / g.pr) * g.gc; }
 
+// Shift that takes a row or column, held in `bits` bits, to its block of a dimension of `dim` elements.  One block that spans the
+// dimension need not be a power of two: shifting out all but the sign bit leaves 0 for every non-negative index.
+inline int block_shift(int64_t block, int64_t dim, int bits) {
+    if (block >= dim) return bits - 1;
+    int l = 0;
+    while ((1ll << l) < block) ++l;
+    return l;
+}
 // Reciprocal of d (1 <= d < 2^31) for n / d == mulhi(2n, mul) >> shift, n < 2^31: with l = ceil(log2 d) and
 // mul = floor(2^(31+l) / d) + 1, mul * d exceeds 2^(31+l) by at most d <= 2^l, so the quotient is off by less than 1 / d.
 inline void recip_of(int64_t d, uint32_t* mul, uint32_t* shift) {
