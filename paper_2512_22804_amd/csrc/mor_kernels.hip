@@ -1658,8 +1658,6 @@ static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o) {
 namespace {
 constexpr int kStatsMaxWg = 256;
 static_assert(kScopeBlocks <= kStatsMaxWg, "a tensor-level decision leaves one statistics record per reduce workgroup");
-constexpr int kScopeCopyWg = 1024;      // workgroups of a decision / mask / copy launch (per-channel operands of one linear layer, none of them
-                                        // copied: 88.3 us per call, 89.9 at 4096; 8192 x 14336 copied: 145.7 against 145.4 us)
 
 // Which kernels take an operand.
 enum Route {
@@ -2072,9 +2070,17 @@ void BatchRun::tensor_level_decisions() {
         { ProfScope ps(prof, kKernFallbackCopy, st); k_scope_copy_group<<<dim3(copy), dim3(256), 0, st>>>(g); }
         g.n = 0; red = 0; copy = 0;
     };
-    int64_t total_elems = 0;
-    for (int i = 0; i < n; ++i)
-        if (items[i].gran != kGranTensor && items[i].scope == 1) total_elems += items[i].sh.rows * items[i].sh.cols;
+    int64_t total_elems = 0, unproven_bytes = 0;
+    int n_unproven = 0;                                    // operands whose BF16 payload, if any, is left to the copy launch
+    for (int i = 0; i < n; ++i) {
+        const BatchItem& it = items[i];
+        if (it.gran == kGranTensor || it.scope != 1) continue;
+        total_elems += it.sh.rows * it.sh.cols;
+        if (it.o.bf16 == nullptr || scope_proof_applies(it) || column_tensor_proof_applies(it)) continue;
+        ++n_unproven;
+        unproven_bytes += it.sh.rows * it.sh.cols * 2;
+    }
+    const int budget = scope_copy_budget(n_unproven, unproven_bytes);
     for (int i = 0; i < n; ++i) {
         const BatchItem& it = items[i];
         if (it.gran == kGranTensor || it.scope != 1) continue;
@@ -2098,7 +2104,7 @@ void BatchRun::tensor_level_decisions() {
         t.rows = it.sh.rows; t.cols = it.sh.cols; t.ld = it.sh.ld; t.ld_bf16 = it.o.ld_bf16;
         red += t.n_red;
         {   // workgroups of the decision / mask / copy launch: enough for the copy, and never fewer than the reduce pass had
-            const int c = it.o.bf16 ? share(it.sh.rows * it.sh.cols, total_elems, kScopeCopyWg, kScopeCopyWg) : 1;
+            const int c = it.o.bf16 ? share(it.sh.rows * it.sh.cols, total_elems, budget, budget) : 1;
             copy += c > t.n_red ? c : t.n_red;
         }
         g.red_end[g.n] = red; g.copy_end[g.n] = copy;

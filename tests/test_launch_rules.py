@@ -40,8 +40,14 @@ static bool reciprocals() {
     }
     return true;
 }
+// Several large operands without a proof get more workgroups for their copies than one does; small ones and proven ones do not.
+static bool copy_budget() {
+    const int64_t mb = 1 << 20;
+    return scope_copy_budget(0, 0) == 1024 && scope_copy_budget(1, 224 * mb) == 1024 && scope_copy_budget(2, 224 * mb) == 2048 &&
+           scope_copy_budget(12, 960 * mb) == 4096 && scope_copy_budget(12, 100 * mb) == 1600 && scope_copy_budget(64, mb) == 1024;
+}
 int main() {
-    printf("shifts=%d reciprocals=%d\n", shifts(), reciprocals());
+    printf("shifts=%d reciprocals=%d copy_budget=%d\n", shifts(), reciprocals(), copy_budget());
     return 0;
 }
 """
@@ -58,6 +64,6 @@ def answers(tmp_path_factory):
     return dict(kv.split("=") for kv in out.split())
 
 
-@pytest.mark.parametrize("rule", ["shifts", "reciprocals"])
+@pytest.mark.parametrize("rule", ["shifts", "reciprocals", "copy_budget"])
 def test_rule(answers, rule):
     assert answers[rule] == "1"
