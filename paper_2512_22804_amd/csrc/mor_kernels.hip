@@ -952,12 +952,17 @@ __global__ __launch_bounds__(256) void k_scope_reduce_group(GroupScope g) {
             else { acc.e += (double)es[u]; acc.n += nz[u]; }
         }
     }
+    e5 = block_sum_shfl<double>(e5, shd);
     StatsTotals tot;
     tot.e = acc.e; tot.n = acc.n; tot.eb = 0ull; tot.e5 = 0ull;
+    if (!want) {                                               // the sums alone (uniform over the workgroup)
+        tot.e = block_sum_shfl<double>(tot.e, shd);
+        tot.n = block_sum_shfl<unsigned long long>(tot.n, sh.n);
+    } else {
 #pragma unroll
-    for (int k = 0; k < kStatCnt; ++k) tot.c[k] = (k & 1) ? acc.pk[k >> 1] >> 16 : acc.pk[k >> 1] & 0xFFFFu;
-    e5 = block_sum_shfl<double>(e5, shd);
-    stats_fast_reduce(tot, sh);                                // the totals arrive in wave 0
+        for (int k = 0; k < kStatCnt; ++k) tot.c[k] = (k & 1) ? acc.pk[k >> 1] >> 16 : acc.pk[k >> 1] & 0xFFFFu;
+        stats_fast_reduce(tot, sh);                            // the totals arrive in wave 0
+    }
     if (threadIdx.x == 0) { t.part_err[b] = tot.e; t.part_nnz[b] = tot.n; t.part_err5[b] = e5; }
     if (want) stats_emit(tot, nullptr, 0, 0ull, t.rec + b);
 }
