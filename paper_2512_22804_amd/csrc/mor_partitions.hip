@@ -1439,7 +1439,10 @@ hipError_t launch_subcol_items(const BatchItem* items, const int* idx, int cnt, 
 }
 
 // Per-channel columns: all operands of one criterion share five launches per kernel variant (amax, scales, quantize,
-// finish, fallback columns).  ws_of[k] is the workspace of operand idx[k] (column_workspace_bytes).
+// finish, fallback columns), however large they are together: in parts of 256 MB, as other operands that are read twice, the
+// five launches of each part cost more than its second read gains (the twelve operands of a layer 561 us per call in one go,
+// 637 in four parts, 591 in one go without the first pass leaving its operands in the Infinity Cache).  ws_of[k] is the
+// workspace of operand idx[k] (column_workspace_bytes).
 hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int cnt, int crit, const uint32_t* const* gam_of,
                                     char* const* ws_of, hipStream_t st, KProf* prof) {
     for (int variant = 0; variant < 4; ++variant) {
@@ -1447,9 +1450,7 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
         GroupCol g; g.n = 0;
         int64_t total = 0;
         int comb = 0, copy = 0;
-        int64_t group_bytes = 0;
         auto flush = [&]() {
-            group_bytes = 0;
             if (g.n == 0) return;
             // fallback-column pass: about kColCopyBudget workgroups over all operands of the launch (a workgroup that finds
             // every kept column already written costs a few nanoseconds of dispatch, which adds up over 12 000 of them)
@@ -1483,10 +1484,7 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
             const int64_t tiles_x = (it.sh.cols + 127) / 128;
             const int64_t units = (int64_t)pl.n_strips * tiles_x;
             if (units > 0x3FFFFFFF || tiles_x * kColCopyRowGroups > 0x3FFFFFFF) return hipErrorInvalidValue;
-            const int64_t bytes = it.sh.rows * it.sh.cols * 2;
-            if (total + units > 0x7FFFFFFF || (int64_t)copy + tiles_x * kColCopyRowGroups > 0x7FFFFFFF ||
-                (group_bytes > 0 && group_bytes + bytes > kKeepGroupBytes)) flush();
-            group_bytes += bytes;
+            if (total + units > 0x7FFFFFFF || (int64_t)copy + tiles_x * kColCopyRowGroups > 0x7FFFFFFF) flush();
             ColOp& t = g.op[g.n];
             fill_col_op(t, it, gam_of[idx[k]]);
             char* w = ws_of[k];
