@@ -1758,8 +1758,9 @@ struct BatchRun {
     bool will_ride = false;                      // the batch has grouped per-tensor launches for statistics to ride on
     bool riders_used = false;                    // the first statistics group went along with a per-tensor launch
     bool stats_done[kBatchMax] = {};             // the operand's block kernel has written its statistics already
-    int wave_of[kBatchMax] = {};                 // operands that Algorithm 1 reads twice: group of at most kKeepGroupBytes; others 0
+    int wave_of[kBatchMax] = {};                 // operands that Algorithm 1 reads twice: the group they are taken in; others 0
     int n_waves = 1;
+    bool first_read_keeps[kBatchMax] = {};       // ... and whether the amax pass leaves them in the Infinity Cache
 
     size_t ws_bytes = 0;
     // Next `bytes` of the caller's workspace.  The phases below carve exactly what item_workspace() adds up; should the
@@ -1783,16 +1784,35 @@ struct BatchRun {
 
 // ---- Algorithm 1, group loop: operands with sub-tensor blocks and GAM / E8M0 scaling get their group
 //      mantissas first (GAM: one more read of the operand for its amax)
+// Under a tensor-level decision the operands of these granularities gain less from the second read than the launches of every part
+// and a slower first pass cost (twelve operands of a layer, us per call in parts of 256 MB; in one go, kept; in one go, not kept):
+// per-channel rows 527, 514, 507 (fake quantization 526, 510, 508), 64 x 64 blocks 537, 509, 525 (536, 525, 526), 1 x 128 sub-rows
+// with payload 477, 478, 464.  Up to 256 MB they are kept like the others (8192 x 4096 per-channel rows: 51 against 66 us).
+bool taken_whole(const BatchItem& it) {
+    return scope_proof_applies(it) && (it.gran == kGranRow || it.gran == kGranBlock64 || (it.gran == kGranSub && it.o.fake == nullptr));
+}
 void BatchRun::assign_waves() {
-    int64_t bytes = 0;
+    int64_t bytes = 0, whole_bytes = 0;
+    for (int i = 0; i < n; ++i)
+        if (taken_whole(items[i])) whole_bytes += items[i].sh.rows * items[i].sh.cols * 2;
+    const bool whole = whole_bytes > kKeepGroupBytes;
     for (int i = 0; i < n; ++i) {
         const BatchItem& it = items[i];
+        first_read_keeps[i] = keep_for_second_pass(it.sh);
         if (it.gran == kGranTensor || it.gran == kGranCol || it.scaling != kScaleGam) continue;      // (those two group themselves)
+        if (whole && taken_whole(it)) continue;
         const int64_t b = it.sh.rows * it.sh.cols * 2;
         if (bytes > 0 && bytes + b > kKeepGroupBytes) { ++n_waves; bytes = 0; }
         bytes += b;
         wave_of[i] = n_waves - 1;
     }
+    if (!whole) return;
+    if (bytes > 0) ++n_waves;
+    for (int i = 0; i < n; ++i)
+        if (taken_whole(items[i])) {
+            wave_of[i] = n_waves - 1;
+            first_read_keeps[i] &= items[i].gran == kGranBlock64;
+        }
 }
 void BatchRun::group_mantissas(int wave) {
     int idx[kBatchMax];
@@ -1844,7 +1864,7 @@ void BatchRun::group_mantissas(int wave) {
             if (!scope_proof_applies(it)) continue;
             pv_part[i] = reinterpret_cast<uint32_t*>(carve(sizeof(uint32_t) * kProveMaxWg));
             pv_flush[i] = reinterpret_cast<uint32_t*>(carve(sizeof(uint32_t) * kProveMaxWg));
-            pv[n_pv] = BlockProveItem{it.x, it.sh.rows, it.sh.cols, it.sh.ld, pv_part[i], pv_flush[i], 0, scope_proof_kind(it), keep_for_second_pass(it.sh) ? 1 : 0};
+            pv[n_pv] = BlockProveItem{it.x, it.sh.rows, it.sh.cols, it.sh.ld, pv_part[i], pv_flush[i], 0, scope_proof_kind(it), first_read_keeps[i] ? 1 : 0};
             pv_units += scope_proof_units(it);
             pv_item[n_pv] = i;
             if (++n_pv == kProveGroup) flush();

@@ -38,3 +38,32 @@ THREE = [(4096, 14336)] * 3          # 117 MB each
 def test_columns_share_their_launches(scaling):
     got = _kernels("channel_col", "partition", scaling, THREE)
     assert got == {"column_tile": 2, "column_combine": 2, "fallback_copy": 1}
+
+
+@pytest.mark.parametrize("gran, fake, parts", [("channel_row", False, 1), ("channel_row", True, 1), ("block64", False, 1), ("block64", True, 1),
+                                               ("sub1x128", False, 1), ("sub1x128", True, 2), ("block128", False, 2), ("sub128x1", True, 2)])
+def test_parts_under_a_tensor_level_decision(gran, fake, parts):
+    got = _kernels(gran, "tensor", "gam", THREE, fake)
+    assert got["group_amax"] == parts and got["group_mantissa"] == parts
+
+
+def test_a_batch_with_both_kinds():
+    """Operands taken whole stay out of the parts of the others: 128 x 128 blocks in two parts, 64 x 64 blocks in a third."""
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    entries = []
+    for gran in ("block128", "block64"):
+        for rows, cols in THREE:
+            p = B.make_params(rows, cols, gran, "tensor", "mean_rel_err", 0.045, scaling="gam")
+            entries.append((p, torch.ones((rows, cols), dtype=torch.bfloat16, device=dev), B.alloc_outputs(p, dev), None))
+    items = B.make_batch(entries)
+    ws = torch.empty(B.mor_batch_workspace_bytes(items), dtype=torch.uint8, device=dev)
+    ev = B.HipEvents()
+    prof = ev.new_profile(B.MOR_PROFILE_MAX)
+    B.mor_analyze_quantize_batch(items, 1e-5, ws, prof)
+    torch.cuda.synchronize()
+    names = collections.Counter(B.KERNEL_NAMES[prof.kernel[k]] for k in range(prof.count))
+    ev.destroy()
+    assert names["group_amax"] == 3 and names["team_block"] == 3
+    for p, x, out, _ in entries:
+        assert not bool(out.mask.any()) and bool((out.amax == 1.0).all())
