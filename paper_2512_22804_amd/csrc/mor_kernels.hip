@@ -1614,9 +1614,10 @@ constexpr int64_t kSubFlatMaxBlocks = 1536;   // workgroups of 4 waves, each wav
                                               // registers let be resident, so no workgroup waits for another to end (one 64 MiB operand, cold
                                               // caches: 21.0 us at 1536 against 23.2 us at 2048 (one unit per wave); 112 MiB: 32.1 against 34.5 us;
                                               // 224 MiB: 65 us either way)
-constexpr int64_t kSubRowsAlone = 98304;      // 1121 x 704 beside eleven other operands: 33.6 us per call with the general kernel, 37.7 in the
-                                              // ROWS form; 68 000 blocks alone 11.5 against 11.7; 164 000 blocks 24.6 against 18 us; twelve
-                                              // operands of 64 to 2048 rows 53 to 78 us against 19 to 39
+constexpr int64_t kSubRowsAlone = 81920;      // us per call, general kernel / ROWS form: 33 000 blocks 6.1 / 7.8 (dense with a tail), 6.1 / 6.8
+                                              // (padded), 7.0 / 8.2 (ragged); 66 000 blocks 9.7 / 10.5, 9.5 / 8.8, 11.4 / 11.2; 77 000 blocks 10.9 / 11.2
+                                              // (padded); 82 500 blocks 11.6 / 11.1 (tail); 93 000 blocks 12.9 / 11.5, 12.7 / 11.5, 15.6 / 12.1.  Several
+                                              // operands share the launch: twelve of 64 to 2048 rows 53 to 78 us per call / 19 to 39
 constexpr int64_t kSubRowsMaxBlocks = 1280;   // the ROWS form's registers (90) let five be resident per compute unit
 static_assert(kSubFlatMaxBlocks <= 2 * kSoloFinalThreads, "k_solo_stats_final takes two records per lane");
 static int clamp_grid_y(int64_t v) { return (int)(v < 1 ? 1 : (v > 65535 ? 65535 : v)); }

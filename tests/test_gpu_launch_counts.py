@@ -8,7 +8,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-def _kernels(gran, scope, scaling, shapes, fake=False):
+def _kernels(gran, scope, scaling, shapes, fake=False, stats=False):
     from paper_2512_22804_amd import binding as B
     dev = torch.device("cuda:0")
     gen = torch.Generator(device=dev)
@@ -18,7 +18,8 @@ def _kernels(gran, scope, scaling, shapes, fake=False):
         x = torch.randn((rows, cols), generator=gen, device=dev).to(torch.bfloat16)
         p = B.make_params(rows, cols, gran, scope, "mean_rel_err", 0.045, scaling=scaling)
         out = B.alloc_outputs(p, dev, want_bf16=not fake, want_fp8=not fake)
-        entries.append((p, x, out, None, torch.empty_like(x) if fake else None))
+        st = torch.empty(B.STATS_BYTES, dtype=torch.uint8, device=dev) if stats else None
+        entries.append((p, x, out, st, torch.empty_like(x) if fake else None))
     items = B.make_batch(entries)
     ws = torch.empty(max(16, B.mor_batch_workspace_bytes(items)), dtype=torch.uint8, device=dev)
     ev = B.HipEvents()
@@ -45,6 +46,14 @@ def test_columns_share_their_launches(scaling):
 def test_parts_under_a_tensor_level_decision(gran, fake, parts):
     got = _kernels(gran, "tensor", "gam", THREE, fake)
     assert got["group_amax"] == parts and got["group_mantissa"] == parts
+
+
+@pytest.mark.parametrize("rows, unit_kernel", [(2401, False), (2501, True)])
+def test_lone_sub_rows_with_a_tail(rows, unit_kernel):
+    """Dense 1x128 operands of 79 000 and 82 500 blocks, no whole number of units: the second is large enough alone for the kernel that
+    works through units of 32 blocks and gathers the statistics itself."""
+    got = _kernels("sub1x128", "partition", "fp32_amax", [(rows, 4224)], stats=True)
+    assert got["sub1x128"] == 1 and ("stats_partial" in got) != unit_kernel
 
 
 def test_a_batch_with_both_kinds():
