@@ -76,7 +76,6 @@ __device__ __forceinline__ void sub_block_body(const u32x4& raw, const uint16_t*
         if constexpr (CRIT == kCritEq3) o.err5_sum[p] = err5;
         if constexpr (!DEFER) o.mask[p] = (uint8_t)mask;
         if (mode != kScaleFp32 && o.e8m0) o.e8m0[p] = (uint8_t)(__float_as_uint(s) >> 23);
-        if (mode == kScaleE8M0 && p == 0) zero_group_mantissa(o.gmant);
         if (three && o.amin) o.amin[p] = __uint_as_float(amin_bits << 16);
     }
     if constexpr (!DEFER) {
@@ -93,6 +92,7 @@ __global__ __launch_bounds__(256) void k_sub1x128_strided(const uint16_t* __rest
     const int64_t cb = blockIdx.x, cpr = (sh.cols + 127) / 128;
     const int64_t c = cb * 128 + l * 8;
     const bool valid = c < sh.cols;
+    if (mode == kScaleE8M0 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) zero_group_mantissa(o.gmant);
     for (int64_t r = (int64_t)blockIdx.y * 16 + (threadIdx.x >> 6) * 4 + g; r < sh.rows; r += (int64_t)gridDim.y * 16) {
         const uint16_t* src = x + r * sh.ld + c;
         u32x4 raw; raw.x = 0u; raw.y = 0u; raw.z = 0u; raw.w = 0u;
