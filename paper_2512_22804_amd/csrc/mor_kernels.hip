@@ -113,6 +113,7 @@ __global__ __launch_bounds__(256) void k_sub1x128_strided(const uint16_t* __rest
 // ======================================================================================
 constexpr int kTensorChunksPerThread = 8;                       // 16-byte chunks per thread in pass B
 constexpr int kTensorChunksPerBlock = 256 * kTensorChunksPerThread;
+constexpr int kSmallChunksPerThread = 2;                        // ... of a small operand with padded rows that is alone (see kOneTensorMaxChunks)
 constexpr int kAmaxOneTile = 768;        // tiles of a pass-A launch up to which every one gets a workgroup (three per compute unit); also the size of
                                          // the partials' arrays.  1251 tiles of padded rows: 51.6 us per call at 512 workgroups, 53.3 at 1251
 constexpr int kMaxAmaxBlocks = 512;      // pass A of larger launches, all its workgroups resident.  The two parts of the six gradients of
@@ -1120,12 +1121,15 @@ struct TensorOp {
     int64_t keep_from;                   // pass A: tiles from this one on are read without the non-temporal hint
     RowMap rm;                           // operands with padded leading dimensions (STRIDED kernels)
 };
-struct GroupTensor {
+template <int N>
+struct GroupTensorT {
     int n;
-    int32_t amax_end[kMaxGroup], slot_end[kMaxGroup], copy_end[kMaxGroup];   // running workgroup totals per pass
+    int32_t amax_end[N], slot_end[N], copy_end[N];   // running workgroup totals per pass
     float near_tol;
-    TensorOp op[kMaxGroup];
+    TensorOp op[N];
 };
+using GroupTensor = GroupTensorT<kMaxGroup>;
+using OneTensor = GroupTensorT<1>;
 // Element offset of 16-byte chunk `c` in a matrix with rows of `ld` elements, any size (paths that are not bound by it).
 template <bool STRIDED>
 __device__ __forceinline__ int64_t tensor_chunk_off(const TensorOp& t, int64_t c, int64_t ld) {
@@ -1143,11 +1147,10 @@ __device__ __forceinline__ int64_t tensor_chunk_off(const TensorOp& t, int64_t c
 // pass (2 more bytes read per element) is skipped.  The outputs are the same either way.
 // Workgroups from `stats_first` on do not belong to pass A: they compute the partial statistics records of the batch's
 // sub-tensor operands (whose kernels have already run), in the shadow of this bandwidth-bound pass.
-template <bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupStats riders, int stats_first, int block0) {
-    if ((int)blockIdx.x >= stats_first) { stats_partial_body(riders, (int)blockIdx.x - stats_first); return; }
+template <bool STRIDED, int CH, class G>
+__device__ __forceinline__ void tensor_amax_body(const G& g, int block) {
+    constexpr int kTile = 256 * CH;
     __shared__ uint32_t sh4[4];
-    const int block = (int)blockIdx.x + block0;              // block0: the launch covers a part of the table's operands
     const int op = group_find32(g.amax_end, g.n, block);
     const TensorOp& t = g.op[op];
     const int b = block - (op ? g.amax_end[op - 1] : 0);
@@ -1156,40 +1159,40 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
     uint32_t a2 = 0u, flushed = 0u;
     uint32_t mn2 = 0xFFFFFFFFu;                   // three-way recipe: smallest non-zero pattern, minus one, per half-word
     for (int64_t tile = b; tile < t.n_tiles; tile += t.n_amax) {
-        const int64_t c0 = tile * kTensorChunksPerBlock + threadIdx.x;
-        if (c0 + 7 * 256 < t.n_chunks && !(STRIDED && t.rm.cpr == 0u)) {
-            u32x4 v[8];
+        const int64_t c0 = tile * kTile + threadIdx.x;
+        if (c0 + (CH - 1) * 256 < t.n_chunks && !(STRIDED && t.rm.cpr == 0u)) {
+            u32x4 v[CH];
             if constexpr (STRIDED) {
                 RowPos pos;
-                const int64_t row0 = row_tile_first(t.rm, tile * kTensorChunksPerBlock, threadIdx.x, pos);
+                const int64_t row0 = row_tile_first(t.rm, tile * kTile, threadIdx.x, pos);
                 const BufRsrc rx = make_buf(t.x + row0 * t.rm.ld);
                 const uint32_t row_bytes = (uint32_t)t.rm.ld * 2u;
-                uint32_t off[8];
+                uint32_t off[CH];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) { off[u] = row_off<16>(pos, row_bytes, true); row_step(t.rm, pos); }
+                for (int u = 0; u < CH; ++u) { off[u] = row_off<16>(pos, row_bytes, true); row_step(t.rm, pos); }
                 if (tile >= t.keep_from) {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = buf_load16_first<true>(rx, off[u], 0u);
+                    for (int u = 0; u < CH; ++u) v[u] = buf_load16_first<true>(rx, off[u], 0u);
                 } else {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = buf_load16_first<false>(rx, off[u], 0u);
+                    for (int u = 0; u < CH; ++u) v[u] = buf_load16_first<false>(rx, off[u], 0u);
                 }
             } else {
                 // (buffer loads: plain loads that differ in the hint only would be merged into one without it)
-                const BufRsrc rx = make_buf(t.x + tile * (kTensorChunksPerBlock * 8));
+                const BufRsrc rx = make_buf(t.x + tile * (kTile * 8));
                 if (tile >= t.keep_from) {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = buf_load16_first<true>(rx, threadIdx.x * 16u + u * 4096u, 0u);
+                    for (int u = 0; u < CH; ++u) v[u] = buf_load16_first<true>(rx, threadIdx.x * 16u + u * 4096u, 0u);
                 } else {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = buf_load16_first<false>(rx, threadIdx.x * 16u + u * 4096u, 0u);
+                    for (int u = 0; u < CH; ++u) v[u] = buf_load16_first<false>(rx, threadIdx.x * 16u + u * 4096u, 0u);
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a2 = amax2_of(v[u], a2);
+            for (int u = 0; u < CH; ++u) a2 = amax2_of(v[u], a2);
             if (three) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) mn2 = min_nonzero_m1(v[u], mn2);
+                for (int u = 0; u < CH; ++u) mn2 = min_nonzero_m1(v[u], mn2);
             }
             if (prove) {
                 // t = running amax with 20 taken off the exponent (0 if that underflows); 1 <= m < t  <=>  m-1 < t-1
@@ -1197,16 +1200,16 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
                 const uint32_t tm1 = pk_sub_sat_u16(t2, 0x00010001u);
                 uint32_t keep2 = 0u;                       // per half-word: elements of this tile NOT certain to flush
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
+                for (int u = 0; u < CH; ++u)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const uint32_t mm1 = pk_sub_u16(v[u][j] & 0x7FFF7FFFu, 0x00010001u);     // wraps to 0xFFFF for zeros
                         keep2 = pk_add_u16(keep2, pk_is_zero_u16(pk_sub_sat_u16(tm1, mm1)));
                     }
-                flushed += 64u - fold_add16(keep2);        // widened tile by tile: 16 bits would hold 2047 tiles of a workgroup
+                flushed += 8u * CH - fold_add16(keep2);        // widened tile by tile: 16 bits would hold 2047 tiles of a workgroup
             }
         } else {
-            for (int u = 0; u < 8; ++u)
+            for (int u = 0; u < CH; ++u)
                 if (c0 + u * 256 < t.n_chunks) {
                     const u32x4 v = load16(t.x + tensor_chunk_off<STRIDED>(t, c0 + u * 256, t.rm.ld));
                     a2 = amax2_of(v, a2);
@@ -1226,6 +1229,12 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
         if (threadIdx.x == 0) t.flush_part[b] = (sh4[0] + sh4[1]) + (sh4[2] + sh4[3]);
     }
 }
+template <bool STRIDED>
+__global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupStats riders, int stats_first, int block0) {
+    if ((int)blockIdx.x >= stats_first) { stats_partial_body(riders, (int)blockIdx.x - stats_first); return; }
+    tensor_amax_body<STRIDED, kTensorChunksPerThread>(g, (int)blockIdx.x + block0);      // block0: the launch covers a part of the table's operands
+}
+__global__ __launch_bounds__(256) void k_tensor_amax_one(OneTensor g) { tensor_amax_body<true, kSmallChunksPerThread>(g, (int)blockIdx.x); }
 // What pass A found out about the operand: its amax, and whether the sum of the certain-flush lower bounds proves the BF16
 // decision.  Same values in every workgroup that calls it.  All partials are loaded together and one barrier exchanges the wave
 // results: every workgroup of pass B waits for this before it can scale anything.
@@ -1256,34 +1265,34 @@ __device__ __forceinline__ uint32_t tensor_pass_a_result(const TensorOp& t, bool
     return max(max(sha[0], sha[1]), max(sha[2], sha[3]));
 }
 // STRIDED: operands with padded leading dimensions (see RowMap).
-template <int CRIT, bool FAKE, bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int block0) {
-    const int block = (int)blockIdx.x + block0;
+template <int CRIT, bool FAKE, bool STRIDED, int CH, class G>
+__device__ __forceinline__ void tensor_quant_body(const G& g, int block) {
+    constexpr int kTile = 256 * CH;
     const int op = group_find32(g.slot_end, g.n, block);
     const TensorOp& t = g.op[op];
     const int b = block - (op ? g.slot_end[op - 1] : 0);
     const uint16_t* __restrict__ x = t.x;
     uint8_t* __restrict__ fp8 = t.o.fp8;
-    const int64_t n_chunks = t.n_chunks, n_tiles = t.n_tiles, G = t.n_slots;
-    u32x4 bufA[kTensorChunksPerThread];
+    const int64_t n_chunks = t.n_chunks, n_tiles = t.n_tiles, n_slots = t.n_slots;
+    u32x4 bufA[CH];
     const bool wide = STRIDED && t.rm.cpr == 0u;             // chunk by chunk, in the careful path below
     auto load_tile = [&](u32x4* raw, int64_t tile) {
-        const int64_t c0 = tile * kTensorChunksPerBlock + threadIdx.x;
+        const int64_t c0 = tile * kTile + threadIdx.x;
         if constexpr (STRIDED) {
             // (wide: a null window, so all chunks read as zeros here; the careful path reads them itself)
             RowPos pos;
-            const int64_t row0 = wide ? 0 : row_tile_first(t.rm, tile * kTensorChunksPerBlock, threadIdx.x, pos);
+            const int64_t row0 = wide ? 0 : row_tile_first(t.rm, tile * kTile, threadIdx.x, pos);
             const BufRsrc rx = make_buf_window(x + row0 * t.rm.ld, wide ? 0u : 0x7FFFFFFFu);
             const uint32_t row_bytes = (uint32_t)t.rm.ld * 2u;
 #pragma unroll
-            for (int u = 0; u < kTensorChunksPerThread; ++u) {
+            for (int u = 0; u < CH; ++u) {
                 raw[u] = buf_load16(rx, row_off<16>(pos, row_bytes, c0 + u * 256 < n_chunks), 0u);
                 row_step(t.rm, pos);
             }
             return;
         }
 #pragma unroll
-        for (int u = 0; u < kTensorChunksPerThread; ++u) {
+        for (int u = 0; u < CH; ++u) {
             const int64_t c = c0 + u * 256;
             if (c < n_chunks) raw[u] = load16(x + c * 8);
             else { raw[u].x = 0u; raw[u].y = 0u; raw[u].z = 0u; raw[u].w = 0u; }
@@ -1315,10 +1324,10 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
         // tiles, 3.5e-8 with a chain per tile, at the same time per call.  Padded rows start a chain per chunk as well, 2.4e-8 (the
         // rounding of the result is 2.3e-8; 0.5 % of the time): their former kernel, one chunk per lane and tile, had that.
         TileSums sum{0.0f, 0.0f, 0.0f, 0.0f};
-        const int64_t c_first = tile * kTensorChunksPerBlock;
+        const int64_t c_first = tile * kTile;
         const int64_t c0 = c_first + threadIdx.x;
         const int64_t left = n_chunks - c_first;
-        const uint32_t valid = (uint32_t)(left < kTensorChunksPerBlock ? left : kTensorChunksPerBlock);      // chunks of this tile
+        const uint32_t valid = (uint32_t)(left < kTile ? left : kTile);      // chunks of this tile
         int64_t row0 = 0;
         RowPos pos0{0u, 0u};
         if constexpr (STRIDED) row0 = wide ? 0 : row_tile_first(t.rm, c_first, threadIdx.x, pos0);
@@ -1343,16 +1352,16 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
             return v;
         };
 #pragma unroll
-        for (int u = 0; u < kTensorChunksPerThread; ++u) acc.zero2 = zero2_of(raw[u], acc.zero2);
+        for (int u = 0; u < CH; ++u) acc.zero2 = zero2_of(raw[u], acc.zero2);
         asm volatile("" : "+v"(acc.zero2));      // counted here, not sunk below the sweep (which would keep the masked words alive)
 #pragma unroll
-        for (int u = 0; u < kTensorChunksPerThread; ++u) buf_store16<kBufStoreNt>(rb, at_16(u, t.o.ld_bf16), raw[u]);       // proven fallback
+        for (int u = 0; u < CH; ++u) buf_store16<kBufStoreNt>(rb, at_16(u, t.o.ld_bf16), raw[u]);       // proven fallback
         pos = pos0;
         if constexpr (STRIDED) asm volatile("" : "+v"(pos.r), "+v"(pos.c));      // the sweep's offsets are formed chunk by chunk, not kept from here
         if (CRIT == kCritEq3 && fast && dual) {
             // both formats in one sweep with one reciprocal per element (see quant8_dual)
 #pragma unroll
-            for (int u = 0; u < kTensorChunksPerThread; ++u) {
+            for (int u = 0; u < CH; ++u) {
                 u32x4 deq;
                 TileSums c = STRIDED ? TileSums{0.0f, 0.0f, 0.0f, 0.0f} : sum;
                 const u32x2 codes = quant8_dual<FAKE>(raw[u], s, s_inv, c.e0, c.e1, c.f0, c.f1, deq);
@@ -1363,7 +1372,7 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
             }
         } else if (fast) {
 #pragma unroll
-            for (int u = 0; u < kTensorChunksPerThread; ++u) {
+            for (int u = 0; u < CH; ++u) {
                 u32x4 deq;
                 TileSums c = STRIDED ? TileSums{0.0f, 0.0f, 0.0f, 0.0f} : sum;
                 const u32x2 codes = quant8_fast_deq<false, FAKE>(raw[u], s, s_inv, c.e0, c.e1, deq);
@@ -1375,7 +1384,7 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
             }
         } else {
 #pragma clang loop unroll(disable)
-            for (int u = 0; u < kTensorChunksPerThread; ++u) {
+            for (int u = 0; u < CH; ++u) {
                 const int64_t c = c0 + u * 256;
                 if (c < n_chunks) {
                     const uint16_t* __restrict__ src = x + tensor_chunk_off<STRIDED>(t, c, t.rm.ld);
@@ -1394,20 +1403,26 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
     };
     for (;;) {
         process(bufA, tl);
-        tl += G;
+        tl += n_slots;
         if (tl >= n_tiles) break;
         load_tile(bufA, tl);
     }
     TensorPartials tp{t.err, t.err5, t.zero, t.abits};
     tensor_publish<CRIT>(acc, tp, b);
 }
-// Workgroups from `stats_first` on combine the riders' partial statistics records (one workgroup per operand).
-template <int CRIT, bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, GroupStats riders, int stats_first) {
-    if ((int)blockIdx.x >= stats_first) { stats_final_body(riders, (int)blockIdx.x - stats_first); return; }
-    const int op = group_find32(g.copy_end, g.n, blockIdx.x);
+template <int CRIT, bool FAKE, bool STRIDED>
+__global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int block0) {
+    tensor_quant_body<CRIT, FAKE, STRIDED, kTensorChunksPerThread>(g, (int)blockIdx.x + block0);
+}
+template <int CRIT, bool FAKE>
+__global__ __launch_bounds__(256) void k_tensor_quant_one(OneTensor g) {
+    tensor_quant_body<CRIT, FAKE, true, kSmallChunksPerThread>(g, (int)blockIdx.x);
+}
+template <int CRIT, bool STRIDED, int CH, class G>
+__device__ __forceinline__ void tensor_finish_body(const G& g, int block) {
+    const int op = group_find32(g.copy_end, g.n, block);
     const TensorOp& t = g.op[op];
-    const int b = blockIdx.x - (op ? g.copy_end[op - 1] : 0);
+    const int b = block - (op ? g.copy_end[op - 1] : 0);
     const int nb = g.copy_end[op] - (op ? g.copy_end[op - 1] : 0);
     const bool proven = t.abits[1] != 0u;                     // pass B already wrote the fallback
     if (proven && b != 0) return;                             // only the operand's first workgroup has work left
@@ -1420,7 +1435,7 @@ __global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, Grou
     sz = block_sum_shfl<unsigned long long>(sz, shl);
     if constexpr (CRIT == kCritEq3) se5 = block_sum_shfl<double>(se5, shd);
     const uint32_t abits = t.abits[0];
-    const unsigned long long n_padded = (unsigned long long)t.n_tiles * kTensorChunksPerBlock * 8;
+    const unsigned long long n_padded = (unsigned long long)t.n_tiles * (256 * CH) * 8;
     const unsigned long long n = n_padded - sz;
     if (abits >= kInfBits) { se = (double)__builtin_inff(); se5 = se; }
     uint32_t mask;
@@ -1460,13 +1475,20 @@ __global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, Grou
                          mask == 1u ? total : 0ull, mask == 2u ? total : 0ull, proven && !STRIDED ? 1u : 0u);
         }
     }
+    // Small operands find their rows without a 64-bit division, whose latency counts there (0.2 us of 12.7); larger ones lose by the
+    // branch (2048 x 4096 copied under Eq. 3: 26.3 against 24.5 us per call).
+    auto chunk_off = [&](int64_t c, int64_t ld) -> int64_t {
+        if (CH != kSmallChunksPerThread || t.rm.cpr == 0u || c >= 0x7FFFFFFF) return tensor_chunk_off<STRIDED>(t, c, ld);
+        const uint32_t r = row_div(t.rm, (uint32_t)c);
+        return (int64_t)r * ld + (int64_t)((uint32_t)c - r * t.rm.cpr) * 8;
+    };
     if (mask == 2u) {
         const bool fast = abits < fast_amax_limit(t.mode);
         uint16_t* __restrict__ fakep = t.o.fake;
         const float s_inv = fakep ? 1.0f / s5 : 0.0f;
         for (int64_t c = (int64_t)b * 256 + threadIdx.x; c < t.n_chunks; c += (int64_t)nb * 256)
-            requant_chunk_e5m2(t.x + tensor_chunk_off<STRIDED>(t, c, t.rm.ld), fakep ? nullptr : t.o.fp8 + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fp8),
-                               fakep ? fakep + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fake) : nullptr, s5, s_inv, fast);
+            requant_chunk_e5m2(t.x + chunk_off(c, t.rm.ld), fakep ? nullptr : t.o.fp8 + chunk_off(c, t.o.ld_fp8),
+                               fakep ? fakep + chunk_off(c, t.o.ld_fake) : nullptr, s5, s_inv, fast);
         return;
     }
     if (proven || mask == 0u || t.o.bf16 == nullptr) return;
@@ -1476,15 +1498,25 @@ __global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, Grou
         for (; c + 3 * stride < t.n_chunks; c += 4 * stride) {
             u32x4 v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = load16(t.x + tensor_chunk_off<true>(t, c + u * stride, t.rm.ld));
+            for (int u = 0; u < 4; ++u) v[u] = load16(t.x + chunk_off(c + u * stride, t.rm.ld));
 #pragma unroll
-            for (int u = 0; u < 4; ++u) store16(t.o.bf16 + tensor_chunk_off<true>(t, c + u * stride, t.o.ld_bf16), v[u]);
+            for (int u = 0; u < 4; ++u) store16(t.o.bf16 + chunk_off(c + u * stride, t.o.ld_bf16), v[u]);
         }
         for (; c < t.n_chunks; c += stride)
-            store16(t.o.bf16 + tensor_chunk_off<true>(t, c, t.o.ld_bf16), load16(t.x + tensor_chunk_off<true>(t, c, t.rm.ld)));
+            store16(t.o.bf16 + chunk_off(c, t.o.ld_bf16), load16(t.x + chunk_off(c, t.rm.ld)));
     } else {
         copy_chunk_tiles(t.x, t.o.bf16, t.n_chunks, b, nb);
     }
+}
+// Workgroups from `stats_first` on combine the riders' partial statistics records (one workgroup per operand).
+template <int CRIT, bool STRIDED>
+__global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, GroupStats riders, int stats_first) {
+    if ((int)blockIdx.x >= stats_first) { stats_final_body(riders, (int)blockIdx.x - stats_first); return; }
+    tensor_finish_body<CRIT, STRIDED, kTensorChunksPerThread>(g, (int)blockIdx.x);
+}
+template <int CRIT>
+__global__ __launch_bounds__(256) void k_tensor_finish_one(OneTensor g) {
+    tensor_finish_body<CRIT, true, kSmallChunksPerThread>(g, (int)blockIdx.x);
 }
 
 // Group loop of Algorithm 1 for sub-tensor operands: the operand's amax (partials of pass A) gives the
@@ -1645,10 +1677,10 @@ static hipError_t launch_sub1x128(const uint16_t* x, const KShape& sh, const KOu
 }
 
 // Fills the chunk layout of a per-tensor operand (or of the amax pass of one): rows of sh.ld elements, outputs as in o.
-static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o) {
+static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o, int tile_chunks = kTensorChunksPerBlock) {
     const int64_t cpr = sh.cols / 8;
     t.n_chunks = sh.rows * cpr;
-    t.n_tiles = (t.n_chunks + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
+    t.n_tiles = (t.n_chunks + tile_chunks - 1) / tile_chunks;
     t.chunks_per_row = cpr;
     t.keep_from = keep_for_second_pass(sh) ? 0 : t.n_tiles;
     t.rm = RowMap{};
@@ -2195,6 +2227,34 @@ void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_p
         else k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
     }
 }
+// A small operand with padded rows that is alone: the same three passes over tiles of two chunks per lane, from a table of one operand,
+// with a finish workgroup for every 1024 chunks that may have to be copied.  Such a call is a chain of launches, so what counts is
+// what the host spends on each (3.8 KB of kernel arguments for a table of eight operands and the statistics' riders, 0.4 KB here)
+// and the depth of a workgroup's work.  us per call, these kernels / the grouped ones: 256 x 4096 11.5 / 14.9 kept in E4M3, 11.7 / 14.0
+// kept in BF16; 1024 x 4096 13.6 / 16.1 and 13.9 / 14.5; four chunks per lane 12.0 at 256 x 4096, one 13.1.
+constexpr int64_t kOneTensorMaxChunks = 1 << 19;      // (1280 x 4096, beyond it: 18.2 and 16.6 us, 18.3 and 20.8 with the kernels of one chunk per lane
+                                                      // that the grouped ones replaced)
+void launch_one_tensor(const GroupTensor& g, int a_end, int s_end, int c_end, int crit, bool fake, hipStream_t st, KProf* prof) {
+    OneTensor o;
+    o.n = 1; o.near_tol = g.near_tol; o.op[0] = g.op[0];
+    o.amax_end[0] = a_end; o.slot_end[0] = s_end; o.copy_end[0] = c_end;
+    const dim3 block(256);
+    { ProfScope ps(prof, kKernTensorAmax, st); k_tensor_amax_one<<<dim3(a_end), block, 0, st>>>(o); }
+    {
+        ProfScope ps(prof, kKernTensorQuant, st);
+        const dim3 grid(s_end);
+        if (fake) {
+            if (crit == kCritEq3) k_tensor_quant_one<kCritEq3, true><<<grid, block, 0, st>>>(o);
+            else k_tensor_quant_one<kCritEq2, true><<<grid, block, 0, st>>>(o);
+        } else {
+            if (crit == kCritEq3) k_tensor_quant_one<kCritEq3, false><<<grid, block, 0, st>>>(o);
+            else k_tensor_quant_one<kCritEq2, false><<<grid, block, 0, st>>>(o);
+        }
+    }
+    ProfScope ps(prof, kKernFallbackCopy, st);
+    if (crit == kCritEq3) k_tensor_finish_one<kCritEq3><<<dim3(c_end), block, 0, st>>>(o);
+    else k_tensor_finish_one<kCritEq2><<<dim3(c_end), block, 0, st>>>(o);
+}
 void BatchRun::per_tensor_operands(int crit) {
     // ---- per-tensor operands: amax pass, quantize pass, finish (+ fallback copy) pass; FP8 payload and fake
     //      quantization are different kernels, and so are dense operands and padded leading dimensions
@@ -2205,12 +2265,15 @@ void BatchRun::per_tensor_operands(int crit) {
         auto flush = [&]() {
             if (cnt == 0 || err != hipSuccess) { cnt = 0; return; }
             GroupTensor g; g.n = cnt; g.near_tol = near_tol;
+            const bool ride = !riders_used && n_stats_groups > 0;
+            const KShape& sh0 = items[idx[0]].sh;
+            const bool one = strided && cnt == 1 && !ride && sh0.rows * (sh0.cols / 8) <= kOneTensorMaxChunks;
             int64_t all_tiles = 0;
             for (int k = 0; k < cnt; ++k) {
                 const BatchItem& it = items[idx[k]];
                 TensorOp& t = g.op[k];
                 t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u; t.lean = it.lean && !strided ? 1u : 0u;      // (padded rows always get their payload, and report no proof)
-                set_tensor_layout(t, it.sh, it.o);
+                set_tensor_layout(t, it.sh, it.o, one ? 256 * kSmallChunksPerThread : kTensorChunksPerBlock);
                 all_tiles += t.n_tiles;
                 const TensorPlan pl = plan_tensor(it.sh.rows, it.sh.cols);
                 char* w = carve(pl.bytes);
@@ -2245,7 +2308,7 @@ void BatchRun::per_tensor_operands(int crit) {
                 // other way round).
                 const bool solo = last - first == 1 && total_tiles <= 2000ll * kSoloQuantBlocks;
                 // Up to kAmaxOneTile tiles, and what fits the chip at once in pass B, a workgroup takes one tile.
-                const int amax_cap = total_tiles <= kAmaxOneTile ? kAmaxOneTile : kMaxAmaxBlocks;
+                const int amax_cap = one || total_tiles <= kAmaxOneTile ? kAmaxOneTile : kMaxAmaxBlocks;
                 const int quant_cap = !solo ? kMaxQuantBlocks : (total_tiles <= kQuantOneTile ? kQuantOneTile : kSoloQuantBlocks);
                 TensorPart& p = parts[n_parts++];
                 p.lds = solo ? 0 : kResidency3;
@@ -2256,7 +2319,7 @@ void BatchRun::per_tensor_operands(int crit) {
                     t.n_slots = share(t.n_tiles, total_tiles, quant_cap, t.n_tiles);
                     t.keep_from = bytes > kKeepTensorBytes ? t.n_tiles - t.n_tiles * (kKeepTensorBytes >> 15) / total_tiles : 0;
                     a_end += t.n_amax; s_end += t.n_slots;
-                    c_end += (t.o.bf16 || t.three) ? share(t.n_tiles, all_tiles, 2048, 2048) : 1;
+                    c_end += (t.o.bf16 || t.three) ? share(t.n_tiles, all_tiles, 2048, one ? (t.n_chunks + 1023) / 1024 : 2048) : 1;
                     g.amax_end[k] = a_end; g.slot_end[k] = s_end; g.copy_end[k] = c_end;
                 }
                 p.a1 = a_end; p.s1 = s_end;
@@ -2264,13 +2327,14 @@ void BatchRun::per_tensor_operands(int crit) {
             }
             GroupStats riders; riders.n = 0; riders.near_tol = near_tol;
             int ride_partial = 0, ride_final = 0;
-            if (!riders_used && n_stats_groups > 0) {
+            if (ride) {
                 riders = stats_groups[0];
                 ride_partial = riders.wg_end[riders.n - 1];
                 ride_final = ride_partial > riders.n ? riders.n : 0;      // single-workgroup operands are final already
                 riders_used = true;
             }
-            if (strided) launch_tensor_passes<true>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
+            if (one) launch_one_tensor(g, a_end, s_end, c_end, crit, fake, st, prof);
+            else if (strided) launch_tensor_passes<true>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             else launch_tensor_passes<false>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             cnt = 0;
         };

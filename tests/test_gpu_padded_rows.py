@@ -163,3 +163,31 @@ def test_rows_form_alone_with_statistics(oracle):
     for k in ("n_part", "n_fp8_part", "n_bf16_part", "n_e5m2_part", "n_elem_fp8", "n_elem_bf16", "n_elem_e5m2", "nnz_total", "hist"):
         if k in want:
             assert got[k] == want[k], (k, got[k], want[k])
+
+
+@pytest.mark.parametrize("rows, cols, ld", [(1, 8, 16), (63, 8, 16), (64, 8, 16), (65, 64, 72), (1, 4096, 8192), (1, 4104, 8208), (2, 4088, 4096),
+                                            (512, 8192, 8200), (513, 8192, 8200)])
+def test_small_lone_operands(rows, cols, ld):
+    """Per-tensor operands with padded rows up to 2^19 chunks have kernels of their own where they are alone in the call: tiles of 512
+    chunks, one chunk to many tiles, the largest of the range and the next larger one; with and without statistics."""
+    import parity
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    for kind, kw in (("normal", {}), ("grad", {}), ("half", {"crit": "e4m3_vs_e5m2", "formats": "e4m3|e5m2|bf16"}), ("large", {"scaling": "gam"}),
+                     ("half", {"crit": "e4m3_vs_e5m2"}), ("inf", {"scaling": "e8m0"})):
+        x = _operand(rows, cols, ld, kind)
+        r = parity.compare(x, "tensor", cols=cols, label=kind, **kw)
+        if "formats" not in kw:
+            parity.compare_fake(x, "tensor", cols=cols, **kw)
+        p = r["params"]
+        out = B.alloc_outputs(p, dev, bf16_fill=parity.FILL)
+        st = [torch.full((B.STATS_BYTES,), 0xEE, dtype=torch.uint8, device=dev) for _ in range(2)]
+        xd = parity.to_dev(x)
+        items = B.make_batch([(p, xd, out, st[0])])
+        ws = torch.full((B.mor_batch_workspace_bytes(items),), 0xA7, dtype=torch.uint8, device=dev)
+        B.mor_analyze_quantize_batch(items, 1e-2, ws)
+        B.mor_select_stats(p, out.err_sum, out.nnz, out.mask, 1e-2, st[1])
+        got, want = (B.read_stats(s) for s in st)
+        assert got == want
+        for f in ("fp8", "bf16", "scale", "amax", "err_sum", "nnz", "mask"):
+            assert torch.equal(getattr(out, f), getattr(r["gpu"], f)), (kind, f)
