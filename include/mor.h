@@ -191,7 +191,7 @@ typedef struct mor_stats {
 /* Set by mor_analyze_quantize_batch for a per-tensor operand whose BF16 decision was already proven
  * by the amax pass (enough elements certain to flush to zero), so that the fallback payload was
  * written by the quantize pass and the separate copy pass was skipped.  Informational only: the
- * outputs do not depend on it.  Operands with padded leading dimensions always report 0. */
+ * outputs do not depend on it.  Operands with padded leading dimensions report 0, whether it happened or not. */
 #define MOR_STATS_FLAG_FUSED_FALLBACK 1u
 
 /* Number of blocks for a shape made of whole blocks, or -1 if the shape is invalid for the granularity. */

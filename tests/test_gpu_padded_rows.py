@@ -191,3 +191,23 @@ def test_small_lone_operands(rows, cols, ld):
         assert got == want
         for f in ("fp8", "bf16", "scale", "amax", "err_sum", "nnz", "mask"):
             assert torch.equal(getattr(out, f), getattr(r["gpu"], f)), (kind, f)
+
+
+@pytest.mark.parametrize("rows, cols, ld, frac, proven", [(520, 1024, 1032, 0.2, 1), (520, 1024, 1032, 0.0, 0), (4096, 2048, 2056, 0.2, 1),
+                                                          (4096, 2048, 2056, 0.0, 0)])
+def test_padded_rows_prove_their_decision(rows, cols, ld, frac, proven):
+    """The statistics of operands with padded rows do not report whether the BF16 decision was proven by the amax pass, so the
+    workspace is looked at: behind its partial records stand the operand's amax pattern and the outcome of the proof."""
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(int(frac * 10))
+    v = np.exp2(rng.uniform(-3.0, 3.0, size=(rows, ld))).astype(np.float32)
+    v[rng.random((rows, ld)) < frac] = np.float32(2.0 ** -40)
+    v[3, 5] = 8.0
+    x = torch.from_numpy(W.f32_to_bf16_bits(v).view(np.int16)).to(dev)
+    p = B.make_params(rows, cols, "tensor", ld=ld)
+    out = B.alloc_outputs(p, dev, bf16_fill=0x5A5A)
+    B.mor_analyze_quantize(p, x[:, :cols], out)
+    at = (4 * 768 + 3 * 4 * 16384) // 4                    # 768 amax records, 16 384 of each of three sums
+    words = out.workspace.view(torch.int32)[at:at + 2].tolist()
+    assert words == [0x4100, proven] and int(out.mask[0]) == proven
