@@ -107,8 +107,8 @@ __global__ __launch_bounds__(256) void k_sub1x128_strided(const uint16_t* __rest
 
 // ======================================================================================
 // Per-tensor granularity (Section 4.1.1 "Per-Tensor"): pass A = global amax, pass B = quantize
-// with the global scale; the last workgroup of pass B to finish sums the per-workgroup error
-// partials in binary64 and takes the decision; then a conditional copy of the BF16 fallback.
+// with the global scale, pass C = sums of the per-workgroup error partials in binary64, the decision,
+// and the copy of a BF16 fallback that pass B has not already written.
 // Everything is stream-ordered; the host never waits.
 // ======================================================================================
 constexpr int kTensorChunksPerThread = 8;                       // 16-byte chunks per thread in pass B
@@ -146,7 +146,7 @@ __device__ __forceinline__ uint32_t block_allmin_u16(uint32_t v, uint32_t* sh4) 
 // bounds-checked buffer accesses.  An operand whose tiles span 2 GB or more (a few columns of very long rows), or whose chunk
 // numbers leave those ranges, is `wide`: plain 64-bit arithmetic, one chunk at a time.
 // Bound by HBM like the dense form.  Measured with its 1 x 128 sibling (SubRows) on a pair of 4099 x 5000 column slices of
-// 10 000-element rows in one call with statistics: 58.5 us, against 103.5 us with kernels of one 16-byte chunk per lane that
+// 10 000-element rows in one call with statistics: 51.6 us, against 103.5 us with kernels of one 16-byte chunk per lane that
 // proved no fallback (a third read of the gradient) and took their statistics in launches of their own.
 struct RowMap {
     int64_t ld;                    // elements, of x
@@ -178,11 +178,6 @@ __device__ __forceinline__ uint32_t row_off(const RowPos& p, uint32_t row_bytes,
     return off_if(live, __umul24(p.r, row_bytes) + p.c * CHUNK);
 }
 
-__device__ __forceinline__ uint32_t global_amax_bits(const uint32_t* __restrict__ part, int n_part_amax, uint32_t* sh4) {
-    uint32_t a = 0u;
-    for (int i = threadIdx.x; i < n_part_amax; i += 256) a = max(a, part[i] & 0xFFFFu);
-    return block_allmax_u32(a, sh4);
-}
 // Smallest non-zero magnitude pattern of the operand from the partial words (0 when it has no non-zero element).
 __device__ __forceinline__ uint32_t global_amin_bits(const uint32_t* __restrict__ part, int n_part_amax, uint32_t* sh4) {
     uint32_t m = 0xFFFFu;
@@ -209,7 +204,6 @@ struct TensorPartials {   // one slot per pass-B workgroup (at most kMaxQuantBlo
     float* err;
     float* err5;
     uint32_t* zero;        // zero elements seen by the workgroup (padding chunks count as zeros)
-    uint32_t* abits;       // [0] = global amax bits, published by workgroup 0 of pass B
 };
 constexpr int kMaxQuantBlocks = 16384;
 constexpr int64_t kMaxTensorTiles = 2000ll * kMaxQuantBlocks;      // of one operand: pass B's zero counters (16 bits per lane, 32 a tile) last 2047
@@ -218,19 +212,6 @@ static_assert((kMaxTensorTiles / kMaxAmaxBlocks + 1) * kTensorChunksPerBlock * 8
 constexpr int kSoloQuantBlocks = 1280;     // pass B of a per-tensor operand that is alone in its launches: persistent workgroups
 constexpr int kQuantOneTile = 1536;        // ... unless its tiles all fit the chip at once (six workgroups per compute unit)
 
-template <typename T>
-__device__ __forceinline__ T block_sum_256(T v, T* sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-#pragma unroll
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    const T r = sh[0];
-    __syncthreads();
-    return r;
-}
 // Same result on every thread, two barriers, fixed summation order.
 template <typename T>
 __device__ __forceinline__ T block_sum_shfl(T v, T* sh4) {
@@ -324,10 +305,10 @@ __device__ __forceinline__ void copy_chunk_tiles(const uint16_t* __restrict__ x,
 }
 
 // ======================================================================================
-// De-quantize / de-scale (Section 4, Figure 4).  Blocks whose width is a multiple of 8 (or the whole
-// row): grid.x = 128-column strip, grid.y strides over groups of 16 rows, one 8-element chunk per
-// thread and row.  Blocks one column wide: one workgroup per 128 x 128 tile, so that a thread's 8
-// column scales are inverted once per tile.
+// De-quantize / de-scale (Section 4, Figure 4).  Blocks whose width is a multiple of 8 (or the whole row): tiles of consecutive
+// 16-byte output chunks, several operands in a launch; where rows are too long for the tiles' 32-bit offsets, grid.x =
+// 128-column strip, grid.y strides over groups of 16 rows, one chunk per thread and row.  Blocks one column wide: one workgroup
+// per 128 x 128 tile, so that a thread's 8 column scales are inverted once per tile.
 // ======================================================================================
 __device__ __forceinline__ float dequant_scale(const float* __restrict__ scale, const uint8_t* __restrict__ e8m0,
                                                const uint32_t* __restrict__ gmant, int64_t p, uint32_t mk, int64_t band) {
@@ -1275,12 +1256,12 @@ __device__ __forceinline__ void tensor_quant_body(const G& g, int block) {
     uint8_t* __restrict__ fp8 = t.o.fp8;
     const int64_t n_chunks = t.n_chunks, n_tiles = t.n_tiles, n_slots = t.n_slots;
     u32x4 bufA[CH];
-    const bool wide = STRIDED && t.rm.cpr == 0u;             // chunk by chunk, in the careful path below
+    const bool wide = STRIDED && t.rm.cpr == 0u;             // chunk by chunk, in the careful path below; pass A proves nothing then
     auto load_tile = [&](u32x4* raw, int64_t tile) {
         const int64_t c0 = tile * kTile + threadIdx.x;
         if constexpr (STRIDED) {
             // (wide: a null window, so all chunks read as zeros here; the careful path reads them itself)
-            RowPos pos;
+            RowPos pos{0u, 0u};
             const int64_t row0 = wide ? 0 : row_tile_first(t.rm, tile * kTile, threadIdx.x, pos);
             const BufRsrc rx = make_buf_window(x + row0 * t.rm.ld, wide ? 0u : 0x7FFFFFFFu);
             const uint32_t row_bytes = (uint32_t)t.rm.ld * 2u;
@@ -1334,7 +1315,7 @@ __device__ __forceinline__ void tensor_quant_body(const G& g, int block) {
         const int64_t at8 = STRIDED ? row0 * t.o.ld_fp8 : c_first * 8, atb = STRIDED ? row0 * t.o.ld_bf16 : c_first * 8,
                       atf = STRIDED ? row0 * t.o.ld_fake : c_first * 8;
         const BufRsrc r8 = make_buf_window(fp8 + at8, (FAKE || !emit) ? 0u : (STRIDED ? 0x7FFFFFFFu : valid * 8u));
-        const BufRsrc rb = make_buf_window(bf16 + atb, proven && !wide ? (STRIDED ? 0x7FFFFFFFu : valid * 16u) : 0u);
+        const BufRsrc rb = make_buf_window(bf16 + atb, proven ? (STRIDED ? 0x7FFFFFFFu : valid * 16u) : 0u);
         const BufRsrc rf = make_buf_window(fakep + atf, (FAKE && !proven) ? (STRIDED ? 0x7FFFFFFFu : valid * 16u) : 0u);
         const uint32_t off8 = threadIdx.x * 8u, off16 = threadIdx.x * 16u;
         // byte offsets of chunk u in the payload and in the BF16 output; STRIDED lanes beyond the last chunk get none
@@ -1391,11 +1372,7 @@ __device__ __forceinline__ void tensor_quant_body(const G& g, int block) {
                     sum.e0 += quant8_careful_mem<false>(src, s, (FAKE || !emit) ? nullptr : fp8 + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fp8),
                                                         (FAKE && !proven) ? fakep + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fake) : nullptr, s_inv);
                     if constexpr (CRIT == kCritEq3) sum.f0 += quant8_careful_mem<true>(src, s5, nullptr);
-                    if (wide) {
-                        const u32x4 v = load16(src);
-                        acc.zero2 = pk_sub_u16(zero2_of(v, acc.zero2), 0x00040004u);       // counted as eight zeros above
-                        if (proven) store16(bf16 + tensor_chunk_off<STRIDED>(t, c, t.o.ld_bf16), v);
-                    }
+                    if (wide) acc.zero2 = pk_sub_u16(zero2_of(load16(src), acc.zero2), 0x00040004u);       // counted as eight zeros above
                 }
             }
         }
@@ -1407,7 +1384,7 @@ __device__ __forceinline__ void tensor_quant_body(const G& g, int block) {
         if (tl >= n_tiles) break;
         load_tile(bufA, tl);
     }
-    TensorPartials tp{t.err, t.err5, t.zero, t.abits};
+    TensorPartials tp{t.err, t.err5, t.zero};
     tensor_publish<CRIT>(acc, tp, b);
 }
 template <int CRIT, bool FAKE, bool STRIDED>
@@ -1746,7 +1723,7 @@ size_t item_workspace(const BatchItem& it) {
     if (it.gran == kGranCol) b += column_workspace_bytes(it.sh.rows, it.sh.cols);
     if (it.stats && it.gran != kGranTensor) b += align16(sizeof(StatsRec) * (solo_stats_candidate(it) ? kSubFlatMaxBlocks : kStatsMaxWg));
     if (it.gran != kGranTensor && it.scaling != kScaleFp32) {
-        b += 16;                                                                   // group mantissa words
+        b += 16;                                                                   // group mantissa words (E8M0 uses none; the size stays)
         if (it.scaling == kScaleGam && it.group_rows == 0) b += 2 * align16(sizeof(uint32_t) * kProveMaxWg);   // amax and flush partials of the pre-pass
         if (it.scaling == kScaleGam && it.group_rows != 0) {                       // bands of rows as groups: mantissa table, amax partials
             const size_t n_groups = (size_t)((it.sh.rows + it.group_rows - 1) / it.group_rows);
