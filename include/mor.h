@@ -86,8 +86,8 @@ enum {
     MOR_FLAG_LEAN_FP8 = 2       /* Algorithm 2 keeps one representation per block: with this flag the FP8 payload of a
                                    block whose BF16 decision is already known when its codes would be stored is not
                                    written (those bytes of out->fp8 keep their previous content; mask[p] == 1 says so).
-                                   Today that is a per-tensor operand whose decision the amax pass has proven (see
-                                   MOR_STATS_FLAG_FUSED_FALLBACK): the quantize pass then moves 4 instead of 5 bytes
+                                   Today that is a per-tensor operand with dense rows whose decision the amax pass has proven
+                                   (see MOR_STATS_FLAG_FUSED_FALLBACK): the quantize pass then moves 4 instead of 5 bytes
                                    per element.  All other outputs are unchanged.  Ignored by mor_fake_quantize. */
 };
 

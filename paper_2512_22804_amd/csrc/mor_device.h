@@ -160,8 +160,9 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-// Two values at once, no NaN but the default one (0x7FC00000, either sign): v_cvt_pk_bf16_f32, which agrees with the function above
-// on every binary32 pattern that is not a NaN, subnormals included (checked over all of them), and truncates a NaN's payload.
+// Two values at once, no NaN but the default one (0x7FC00000, either sign): v_cvt_pk_bf16_f32, which rounds to nearest even like
+// the function above, subnormals included, and truncates a NaN's payload.  (The de-quantize tests compare it on products with all
+// 2^23 mantissas of the scale, ties and results below 2^-126 among them.)
 // One instruction instead of seven per pair: fake quantization of an 8192 x 4096 operand 28.9 -> 28.1 us at 128x128, 25.6 -> 24.9
 // at 1x128, 47.5 -> 43.7 per tensor.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -448,8 +449,8 @@ constexpr int kBufAux = 2;      // cache-policy field of the buffer loads: non-t
 // Cache policies of the buffer stores.  kBufStoreAux: non-temporal and written through at system scope (nt sc1); the de-quantize
 // kernel takes 60.5 us with it where nt alone takes 61.2, fake quantization at 128x1 with columns kept in BF16 (stored over the
 // de-quantized values) 76.5 against 81.9 us.  kBufStoreNt: nt alone, for the per-tensor quantize pass, which reads its operand
-// partly from the Infinity Cache (130.3 against 131.4 us per call of 8192 x 14336), and for 1x128 operands with padded rows (a
-// pair of 4099 x 5000 slices 51.7 against 53.9 us).
+// partly from the Infinity Cache (8192 x 14336 kept in E4M3 97.6 against 101.2 us per call, falling back to BF16 134.8 against
+// 135.8), and for 1x128 operands with padded rows (a pair of 4099 x 5000 slices 50.8 against 53.1 us).
 constexpr int kBufStoreAux = 18, kBufStoreNt = 2;
 typedef __amdgpu_buffer_rsrc_t BufRsrc;
 constexpr uint32_t kBufOutside = 0x80000000u;

@@ -115,9 +115,9 @@ constexpr int kTensorChunksPerThread = 8;                       // 16-byte chunk
 constexpr int kTensorChunksPerBlock = 256 * kTensorChunksPerThread;
 constexpr int kSmallChunksPerThread = 2;                        // ... of a small operand with padded rows that is alone (see kOneTensorMaxChunks)
 constexpr int kAmaxOneTile = 768;        // tiles of a pass-A launch up to which every one gets a workgroup (three per compute unit); also the size of
-                                         // the partials' arrays.  1251 tiles of padded rows: 51.6 us per call at 512 workgroups, 53.3 at 1251
+                                         // the partials' arrays.  1251 tiles of padded rows: 50.8 us per call at 512 workgroups, 51.9 at 1251
 constexpr int kMaxAmaxBlocks = 512;      // pass A of larger launches, all its workgroups resident.  The two parts of the six gradients of
-                                         // a layer (256 and 235 MB) take 45 + 39 us at 512, 49 + 39 us at 2048 with three resident per
+                                         // a layer (256 and 224 MiB) take 45 + 39 us at 512, 49 + 39 us at 2048 with three resident per
                                          // compute unit; the whole layer 409 us at 512, 411 at 384, 413 at 768, 428 at 2048
 constexpr int kProveMaxWg = 8192;      // workgroups of one launch (and partial records per operand) of the block-shaped GAM pre-pass
 
@@ -146,7 +146,7 @@ __device__ __forceinline__ uint32_t block_allmin_u16(uint32_t v, uint32_t* sh4) 
 // bounds-checked buffer accesses.  An operand whose tiles span 2 GB or more (a few columns of very long rows), or whose chunk
 // numbers leave those ranges, is `wide`: plain 64-bit arithmetic, one chunk at a time.
 // Bound by HBM like the dense form.  Measured with its 1 x 128 sibling (SubRows) on a pair of 4099 x 5000 column slices of
-// 10 000-element rows in one call with statistics: 51.6 us, against 103.5 us with kernels of one 16-byte chunk per lane that
+// 10 000-element rows in one call with statistics: 50.8 us, against 103.5 us with kernels of one 16-byte chunk per lane that
 // proved no fallback (a third read of the gradient) and took their statistics in launches of their own.
 struct RowMap {
     int64_t ld;                    // elements, of x
@@ -2280,9 +2280,9 @@ void BatchRun::per_tensor_operands(int crit) {
                 }
                 // Launch shape.  Several operands in the launch: one 32 KB tile per workgroup of pass B (up to 16384), at most
                 // three workgroups resident per compute unit.  One operand alone does better with persistent workgroups that are
-                // all resident from the start (224 MiB falling back: 129 us per call with 512 workgroups in pass A and 1280 in
-                // pass B, 130 with 768 and 1536, 135 with one tile per workgroup; the six gradients of a layer 409 us against 414 the
-                // other way round).
+                // all resident from the start (224 MiB kept in E4M3: 97.6 us per call with 512 workgroups in pass A and 1280 in pass B, 99.9
+                // with 768 and 1536, 102.9 with one tile per workgroup of pass B; falling back to BF16 134.8, 136.0 and 134.6; a
+                // layer with its six gradients 408 us, 414 at 768 and 1536).
                 const bool solo = last - first == 1 && total_tiles <= 2000ll * kSoloQuantBlocks;
                 // Up to kAmaxOneTile tiles, and what fits the chip at once in pass B, a workgroup takes one tile.
                 const int amax_cap = one || total_tiles <= kAmaxOneTile ? kAmaxOneTile : kMaxAmaxBlocks;

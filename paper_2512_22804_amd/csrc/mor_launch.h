@@ -135,17 +135,18 @@ constexpr int kResidency5 = 31000;
 constexpr int kBatchMax = 64;     // operands per batch call
 
 // Operands that are read twice (amax first, then quantize).  The first pass reads them without the non-temporal hint, so that
-// they stay in the Infinity Cache (256 MB) for the second one, and a batch takes them in groups of at most kKeepGroupBytes,
-// both passes of one group before the next group's.  Measured with bare passes (2 bytes read; 2 read and 3 written per
-// element): 64 MB 39 -> 32 us, 224 MB 135 -> 114, 480 MB 295 -> 260 in one group and 228 in two, 960 MB 597 -> 566 in one.
-// The first pass itself is up to 15 % slower that way (6.0 instead of 7.0 TB/s), which an operand far larger than the cache does
-// not get back: above kKeepMaxBytes the hint stays.
+// they stay in the Infinity Cache (256 MB) for the second one, and a batch takes per-tensor operands and most of those under GAM
+// scales in parts of at most kKeepGroupBytes, both passes of one part before the next part's.  Measured with bare passes (2 bytes
+// read; 2 read and 3 written per element): 64 MB 39 -> 32 us, 224 MB 135 -> 114, 480 MB 295 -> 260 in one part and 228 in two,
+// 960 MB 597 -> 566 in one.  The first pass itself is up to 15 % slower that way (6.0 instead of 7.0 TB/s), which an operand far
+// larger than the cache does not get back: above kKeepMaxBytes the hint stays (pre-passes of GAM scaling and column amax).
 constexpr int64_t kKeepGroupBytes = 256ll << 20;
 constexpr int64_t kKeepMaxBytes = 1ll << 30;
-// Per-tensor operands, whose quantize pass may also write a BF16 copy, keep at most the last kKeepTensorBytes of a group.  More
-// pays in calls that follow each other (224 MiB falling back to BF16, us per call: none 146.4, 64 MB 138, 96 MB 134.8, 128 MB 132.2, all
-// 128.9; the six gradients of a layer 429, 412, 407.9, 406.6, 408), but a call whose output buffers have just been filled by
-// others finds their unwritten lines in the cache and has them evicted: 179, 184.6, 185.8, 188.9, 203 us for its first pass.
+// Per-tensor operands, whose quantize pass may also write a BF16 copy, keep kKeepTensorBytes of a part at any size: the same share
+// of each of its operands, at the operand's end.  More pays in calls that follow each other (224 MiB falling back to BF16, us per
+// call: none 146.4, 64 MiB 138, 96 MiB 134.8, 128 MiB 132.2, all 128.9; the six gradients of a layer 429, 412, 407.9, 406.6, 408), but a
+// call whose output buffers have just been filled by others finds their unwritten lines in the cache and has them evicted: 179,
+// 184.6, 185.8, 188.9, 203 us for its first pass.
 constexpr int64_t kKeepTensorBytes = 96ll << 20;
 inline bool keep_for_second_pass(const KShape& sh) { return sh.rows * sh.cols * 2 <= kKeepMaxBytes; }
 

@@ -1,4 +1,4 @@
-"""Batches whose twice-read operands exceed the Infinity Cache are taken in parts of at most 256 MB: every operand must come out
+"""Batches whose twice-read operands exceed the Infinity Cache are mostly taken in parts of at most 256 MB: every operand must come out
 as from a call of its own, whichever part it falls into and whatever shares its launches."""
 import pytest
 import torch
@@ -18,7 +18,7 @@ def _operand(rows, cols, seed, dev):
 def test_parts_equal_single_calls(scaling, scope):
     from paper_2512_22804_amd import binding as B
     dev = torch.device("cuda:0")
-    # two parts of the GAM operands (and of the columns, and of the per-tensor ones): 117 + 100 MB fit one part, the third does not
+    # two parts of the GAM operands and of the per-tensor ones: 117 + 100 MB fit one part, the third does not; columns share one set of launches
     shapes = [("block128", 4096, 14336), ("channel_row", 12288, 4096), ("block64", 4096, 8192), ("sub1x128", 8192, 8192),
               ("channel_col", 4096, 14336), ("channel_col", 8192, 8192), ("channel_col", 1024, 8192),
               ("tensor", 4096, 14336), ("tensor", 12288, 4096), ("tensor", 8192, 4096), ("tensor", 128, 256)]
