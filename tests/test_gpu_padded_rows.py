@@ -211,3 +211,55 @@ def test_padded_rows_prove_their_decision(rows, cols, ld, frac, proven):
     at = (4 * 768 + 3 * 4 * 16384) // 4                    # 768 amax records, 16 384 of each of three sums
     words = out.workspace.view(torch.int32)[at:at + 2].tolist()
     assert words == [0x4100, proven] and int(out.mask[0]) == proven
+
+
+@pytest.mark.parametrize("rows, cols, ld", SHAPES)
+def test_grouped_padded_tensors(rows, cols, ld):
+    """Two or more per-tensor operands with padded rows in a call, however small, share the grouped kernels (tiles of 2048 chunks)."""
+    import parity
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    for kind in ("normal", "grad", "half", "large", "inf"):
+        xb = _operand(rows, cols, ld, kind)
+        for kw in ({}, {"crit": "e4m3_vs_e5m2", "scaling": "gam"}, {"crit": "e4m3_vs_e5m2", "formats": "e4m3|e5m2|bf16"}):
+            p = B.make_params(rows, cols, "tensor", ld=ld, threshold=0.045, **kw)
+            outs = [parity.guarded_outputs(p, dev, bf16_fill=parity.FILL) for _ in range(2)]
+            fakes = [parity.guarded_outputs(p, dev, want_bf16=False, want_fp8=False) for _ in range(2)]
+            ys = [torch.full((rows, cols), 0x5A5A, dtype=torch.int16, device=dev) for _ in range(2)]
+            x = parity.to_dev(xb)
+            items = B.make_batch([(p, x, o, None) for o, _ in outs] + [(p, x, o, None, y) for (o, _), y in zip(fakes, ys)])
+            ws = torch.full((B.mor_batch_workspace_bytes(items),), 0xFF, dtype=torch.uint8, device=dev)
+            B.mor_analyze_quantize_batch(items, 1e-2, ws)
+            torch.cuda.synchronize()
+            for _, guards in outs + fakes:
+                guards.check()
+            for o, _ in outs:
+                parity.compare(xb, "tensor", cols=cols, label=kind, gpu=(p, o), **kw)
+            o = outs[0][0]
+            want = torch.full_like(ys[0], 0x1111)
+            B.mor_dequantize(p, o.fp8, o.scale, o.mask, o.bf16, want)
+            for (f, _), y in zip(fakes, ys):
+                assert torch.equal(y, want) and torch.equal(f.mask, o.mask) and torch.equal(f.err_sum, o.err_sum)
+
+
+@pytest.mark.parametrize("cols, ld", [(8, 2097152), (136, 3000000)])
+def test_grouped_rows_too_long_for_tile_offsets(cols, ld):
+    import parity
+    from paper_2512_22804_amd import binding as B
+    rows = 520
+    dev = torch.device("cuda:0")
+    small = parity.to_dev(_operand(rows, cols, cols, "half"))
+    buf = torch.zeros(rows * ld, dtype=torch.int16, device=dev).view(rows, ld)
+    buf[:, :cols] = small
+    p, q = (B.make_params(rows, cols, "tensor", ld=n) for n in (ld, cols))
+    a = [B.alloc_outputs(p, dev, bf16_fill=parity.FILL) for _ in range(2)]
+    b = B.alloc_outputs(q, dev, bf16_fill=parity.FILL)
+    items = B.make_batch([(p, buf, o, None) for o in a])
+    ws = torch.full((B.mor_batch_workspace_bytes(items),), 0xFF, dtype=torch.uint8, device=dev)
+    B.mor_analyze_quantize_batch(items, 1e-2, ws)
+    B.mor_analyze_quantize(q, small, b)
+    torch.cuda.synchronize()
+    for o in a:
+        for f in ("fp8", "bf16", "scale", "amax", "nnz", "mask"):
+            assert torch.equal(getattr(o, f), getattr(b, f)), f
+        assert torch.allclose(o.err_sum, b.err_sum, rtol=1e-5, atol=0)      # the error sums' own bound
