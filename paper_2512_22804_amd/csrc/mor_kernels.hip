@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void k_sub1x128_strided(const uint16_t* __rest
 // ======================================================================================
 constexpr int kTensorChunksPerThread = 8;                       // 16-byte chunks per thread in pass B
 constexpr int kTensorChunksPerBlock = 256 * kTensorChunksPerThread;
-constexpr int kSmallChunksPerThread = 2;                        // ... of a small operand with padded rows that is alone (see kOneTensorMaxChunks)
+constexpr int kSmallChunksPerThread = 2, kMidChunksPerThread = 4;      // ... of a small operand that is alone (see one_max_chunks)
 constexpr int kAmaxOneTile = 768;        // tiles of a pass-A launch up to which every one gets a workgroup (three per compute unit); also the size of
                                          // the partials' arrays.  1251 tiles of padded rows: 50.8 us per call at 512 workgroups, 51.9 at 1251
 constexpr int kMaxAmaxBlocks = 512;      // pass A of larger launches, all its workgroups resident.  The two parts of the six gradients of
@@ -1083,6 +1083,8 @@ __global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStat
 }
 
 // Per-tensor operands of a group share three launches (amax, quantize, finish + fallback copy).
+enum : uint32_t { kTensorLean = 1u,       // a proven BF16 operand gets no FP8 payload
+                  kTensorReport = 2u };  // dense operands say in their statistics that the decision was proven
 struct TensorOp {
     const uint16_t* x;
     int64_t n_chunks, n_tiles;
@@ -1091,7 +1093,7 @@ struct TensorOp {
     float th;
     uint32_t mode;                       // scaling algorithm
     uint32_t three;                      // type list [E4M3, E5M2, BF16]
-    uint32_t lean;                       // a proven BF16 operand gets no FP8 payload
+    uint32_t flags;                      // kTensorLean, kTensorReport
     int n_amax, n_slots;                 // workgroups this operand gets in pass A / pass B
     uint32_t* amax_part;                 // [n_amax]
     float* err; float* err5; uint32_t* zero;   // [n_slots] each
@@ -1176,6 +1178,8 @@ __device__ __forceinline__ void tensor_amax_body(const G& g, int block) {
                 for (int u = 0; u < CH; ++u) mn2 = min_nonzero_m1(v[u], mn2);
             }
             if (prove) {
+                // (tiles of a few chunks per lane: the wave's amax, the lane's alone would be a weak bound)
+                if constexpr (CH != kTensorChunksPerThread) { const uint32_t a = wave_allmax_u32(fold_max16(a2)); a2 = a | (a << 16); }
                 // t = running amax with 20 taken off the exponent (0 if that underflows); 1 <= m < t  <=>  m-1 < t-1
                 const uint32_t t2 = pk_sub_sat_u16(a2, 0x0A000A00u);
                 const uint32_t tm1 = pk_sub_sat_u16(t2, 0x00010001u);
@@ -1215,7 +1219,6 @@ __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupS
     if ((int)blockIdx.x >= stats_first) { stats_partial_body(riders, (int)blockIdx.x - stats_first); return; }
     tensor_amax_body<STRIDED, kTensorChunksPerThread>(g, (int)blockIdx.x + block0);      // block0: the launch covers a part of the table's operands
 }
-__global__ __launch_bounds__(256) void k_tensor_amax_one(OneTensor g) { tensor_amax_body<true, kSmallChunksPerThread>(g, (int)blockIdx.x); }
 // What pass A found out about the operand: its amax, and whether the sum of the certain-flush lower bounds proves the BF16
 // decision.  Same values in every workgroup that calls it.  All partials are loaded together and one barrier exchanges the wave
 // results: every workgroup of pass B waits for this before it can scale anything.
@@ -1246,16 +1249,14 @@ __device__ __forceinline__ uint32_t tensor_pass_a_result(const TensorOp& t, bool
     return max(max(sha[0], sha[1]), max(sha[2], sha[3]));
 }
 // STRIDED: operands with padded leading dimensions (see RowMap).
-template <int CRIT, bool FAKE, bool STRIDED, int CH, class G>
-__device__ __forceinline__ void tensor_quant_body(const G& g, int block) {
+// Workgroup b of the operand's n_slots.  `raw` holds its last tile afterwards; acc receives its sums.  Returns whether the BF16
+// decision was proven (the fallback is then written).
+template <int CRIT, bool FAKE, bool STRIDED, int CH>
+__device__ __forceinline__ bool tensor_quant_body(const TensorOp& t, int b, u32x4 (&bufA)[CH], TensorAcc& acc, uint32_t& abits) {
     constexpr int kTile = 256 * CH;
-    const int op = group_find32(g.slot_end, g.n, block);
-    const TensorOp& t = g.op[op];
-    const int b = block - (op ? g.slot_end[op - 1] : 0);
     const uint16_t* __restrict__ x = t.x;
     uint8_t* __restrict__ fp8 = t.o.fp8;
     const int64_t n_chunks = t.n_chunks, n_tiles = t.n_tiles, n_slots = t.n_slots;
-    u32x4 bufA[CH];
     const bool wide = STRIDED && t.rm.cpr == 0u;             // chunk by chunk, in the careful path below; pass A proves nothing then
     auto load_tile = [&](u32x4* raw, int64_t tile) {
         const int64_t c0 = tile * kTile + threadIdx.x;
@@ -1282,7 +1283,7 @@ __device__ __forceinline__ void tensor_quant_body(const G& g, int block) {
     int64_t tl = b;
     load_tile(bufA, tl);
     bool proven;                                             // then the BF16 fallback is written in this sweep
-    const uint32_t abits = tensor_pass_a_result(t, proven);
+    abits = tensor_pass_a_result(t, proven);
     uint16_t* __restrict__ bf16 = t.o.bf16;
     if (b == 0 && threadIdx.x == 0) { t.abits[0] = abits; t.abits[1] = proven ? 1u : 0u; }
     // one block = the group: under GAM the block's own mantissa is the group mantissa and the scale is s_b
@@ -1291,10 +1292,10 @@ __device__ __forceinline__ void tensor_quant_body(const G& g, int block) {
     const float s5 = (CRIT == kCritEq3) ? block_scale(abits, kE5M2Max, mode, group_mantissa_bits(abits, kE5M2Max, mode)) : 0.0f;
     const bool fast = abits < fast_amax_limit(mode) && !wide;
     const bool dual = CRIT == kCritEq3 && s5 == 128.0f * s;
-    const bool emit = !(proven && t.lean != 0u);             // lean payload: the codes of a proven BF16 operand are not stored
+    const bool emit = !(proven && (t.flags & kTensorLean) != 0u);             // lean payload: the codes of a proven BF16 operand are not stored
     const float s_inv = FAKE ? 1.0f / s : 0.0f;
     uint16_t* __restrict__ fakep = t.o.fake;     // fake quantization: == bf16, so a proven fallback is already in place
-    TensorAcc acc{{0.0f, 0.0f, 0.0f, 0.0f}, 0u};
+    acc = TensorAcc{{0.0f, 0.0f, 0.0f, 0.0f}, 0u};
     // Stores go through bounds-checked buffer windows over the tile (a tail tile's window is shorter; a payload that
     // is not wanted gets a null window), so the quantization sweep has no branches and stays one basic block: with
     // per-lane or per-operand branches around the stores the compiler defers the error terms of all eight chunks
@@ -1384,19 +1385,67 @@ __device__ __forceinline__ void tensor_quant_body(const G& g, int block) {
         if (tl >= n_tiles) break;
         load_tile(bufA, tl);
     }
-    TensorPartials tp{t.err, t.err5, t.zero};
-    tensor_publish<CRIT>(acc, tp, b);
+    return proven;
 }
 template <int CRIT, bool FAKE, bool STRIDED>
 __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int block0) {
-    tensor_quant_body<CRIT, FAKE, STRIDED, kTensorChunksPerThread>(g, (int)blockIdx.x + block0);
+    const int block = (int)blockIdx.x + block0;
+    const int op = group_find32(g.slot_end, g.n, block);
+    const TensorOp& t = g.op[op];
+    const int b = block - (op ? g.slot_end[op - 1] : 0);
+    u32x4 raw[kTensorChunksPerThread];
+    TensorAcc acc;
+    uint32_t abits;
+    tensor_quant_body<CRIT, FAKE, STRIDED, kTensorChunksPerThread>(t, b, raw, acc, abits);
+    TensorPartials tp{t.err, t.err5, t.zero};
+    tensor_publish<CRIT>(acc, tp, b);
 }
-template <int CRIT, bool FAKE>
-__global__ __launch_bounds__(256) void k_tensor_quant_one(OneTensor g) {
-    tensor_quant_body<CRIT, FAKE, true, kSmallChunksPerThread>(g, (int)blockIdx.x);
+// Decision on a per-tensor operand from its sums (se and se5 over n non-zero elements): every thread of the workgroup calls it and gets
+// the mask; with `emit`, thread 0 writes the outputs and the statistics.
+template <int CRIT>
+__device__ __forceinline__ uint32_t tensor_decide(const TensorOp& t, float near_tol, double se, double se5, unsigned long long n, uint32_t abits,
+                                                  bool proven, bool emit) {
+    if (abits >= kInfBits) { se = (double)__builtin_inff(); se5 = se; }
+    uint32_t mask;
+    if constexpr (CRIT == kCritEq3) mask = (se < se5) ? 0u : 1u;
+    else mask = ((n ? se / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
+    uint32_t amin_bits = 0u;
+    if (t.three && mask == 1u) {           // Eq. (4): the operand is kept in E5M2 if its dynamic range fits
+        __shared__ uint32_t sh4[4];
+        amin_bits = global_amin_bits(t.amax_part, t.n_amax, sh4);
+        if (range_fits_e5m2(abits, amin_bits, n ? 1u : 0u)) mask = 2u;
+    }
+    if (emit && threadIdx.x == 0) {
+        const KOut& o = t.o;
+        const float err_f = (float)se;
+        const uint32_t nnz32 = n > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)n;
+        const uint32_t mg = group_mantissa_bits(abits, kE4M3Max, t.mode), mg5 = group_mantissa_bits(abits, kE5M2Max, t.mode);
+        const float s = mask == 2u ? block_scale(abits, kE5M2Max, t.mode, mg5) : block_scale(abits, kE4M3Max, t.mode, mg);
+        if (t.three && o.amin) o.amin[0] = __uint_as_float(amin_bits << 16);
+        o.scale[0] = s;
+        if (t.mode != kScaleFp32 && o.e8m0) o.e8m0[0] = (uint8_t)(__float_as_uint(s) >> 23);
+        if (t.mode != kScaleFp32 && o.gmant) { o.gmant[0] = mg; o.gmant[1] = mg5; }
+        o.amax[0] = __uint_as_float(abits << 16);
+        o.err_sum[0] = err_f;
+        o.nnz[0] = nnz32;
+        if constexpr (CRIT == kCritEq3) o.err5_sum[0] = (float)se5;
+        o.mask[0] = (uint8_t)mask;
+        if (t.stats) {     // statistics of a one-block operand, same arithmetic as k_stats_single
+            StatsDev* st = t.stats;
+            const float metric = nnz32 ? err_f / (float)nnz32 : 0.0f;
+#pragma unroll
+            for (int k = 0; k < 12; ++k) st->hist[k] = 0u;
+            st->hist[stats_bin(metric)] = 1u;
+            const bool near = fabs((double)metric - (double)t.th) <= (double)near_tol * (double)t.th;
+            const unsigned long long total = (unsigned long long)t.n_chunks * 8ull;
+            stats_finish(st, 1, total, (double)err_f, nnz32, mask == 1u ? 1ull : 0ull, near ? 1ull : 0ull, mask == 2u ? 1ull : 0ull,
+                         mask == 1u ? total : 0ull, mask == 2u ? total : 0ull, proven && (t.flags & kTensorReport) != 0u ? 1u : 0u);
+        }
+    }
+    return mask;
 }
-template <int CRIT, bool STRIDED, int CH, class G>
-__device__ __forceinline__ void tensor_finish_body(const G& g, int block) {
+template <int CRIT, bool STRIDED>
+__device__ __forceinline__ void tensor_finish_body(const GroupTensor& g, int block) {
     const int op = group_find32(g.copy_end, g.n, block);
     const TensorOp& t = g.op[op];
     const int b = block - (op ? g.copy_end[op - 1] : 0);
@@ -1412,60 +1461,16 @@ __device__ __forceinline__ void tensor_finish_body(const G& g, int block) {
     sz = block_sum_shfl<unsigned long long>(sz, shl);
     if constexpr (CRIT == kCritEq3) se5 = block_sum_shfl<double>(se5, shd);
     const uint32_t abits = t.abits[0];
-    const unsigned long long n_padded = (unsigned long long)t.n_tiles * (256 * CH) * 8;
-    const unsigned long long n = n_padded - sz;
-    if (abits >= kInfBits) { se = (double)__builtin_inff(); se5 = se; }
-    uint32_t mask;
-    if constexpr (CRIT == kCritEq3) mask = (se < se5) ? 0u : 1u;
-    else mask = ((n ? se / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
-    const float s5 = block_scale(abits, kE5M2Max, t.mode, group_mantissa_bits(abits, kE5M2Max, t.mode));
-    uint32_t amin_bits = 0u;
-    if (t.three && mask == 1u) {           // Eq. (4): the operand is kept in E5M2 if its dynamic range fits
-        __shared__ uint32_t sh4[4];
-        amin_bits = global_amin_bits(t.amax_part, t.n_amax, sh4);
-        if (range_fits_e5m2(abits, amin_bits, n ? 1u : 0u)) mask = 2u;
-    }
-    if (b == 0 && threadIdx.x == 0) {
-        const KOut& o = t.o;
-        const float err_f = (float)se;
-        const uint32_t nnz32 = n > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)n;
-        const uint32_t mg = group_mantissa_bits(abits, kE4M3Max, t.mode);
-        const float s = mask == 2u ? s5 : block_scale(abits, kE4M3Max, t.mode, mg);
-        if (t.three && o.amin) o.amin[0] = __uint_as_float(amin_bits << 16);
-        o.scale[0] = s;
-        if (t.mode != kScaleFp32 && o.e8m0) o.e8m0[0] = (uint8_t)(__float_as_uint(s) >> 23);
-        if (t.mode != kScaleFp32 && o.gmant) { o.gmant[0] = mg; o.gmant[1] = group_mantissa_bits(abits, kE5M2Max, t.mode); }
-        o.amax[0] = __uint_as_float(abits << 16);
-        o.err_sum[0] = err_f;
-        o.nnz[0] = nnz32;
-        if constexpr (CRIT == kCritEq3) o.err5_sum[0] = (float)se5;
-        o.mask[0] = (uint8_t)mask;
-        if (t.stats) {     // statistics of a one-block operand, same arithmetic as k_stats_single
-            StatsDev* st = t.stats;
-            const float metric = nnz32 ? err_f / (float)nnz32 : 0.0f;
-#pragma unroll
-            for (int k = 0; k < 12; ++k) st->hist[k] = 0u;
-            st->hist[stats_bin(metric)] = 1u;
-            const bool near = fabs((double)metric - (double)t.th) <= (double)g.near_tol * (double)t.th;
-            const unsigned long long total = (unsigned long long)t.n_chunks * 8ull;
-            stats_finish(st, 1, total, (double)err_f, nnz32, mask == 1u ? 1ull : 0ull, near ? 1ull : 0ull, mask == 2u ? 1ull : 0ull,
-                         mask == 1u ? total : 0ull, mask == 2u ? total : 0ull, proven && !STRIDED ? 1u : 0u);
-        }
-    }
-    // Small operands find their rows without a 64-bit division, whose latency counts there (0.2 us of 12.7); larger ones lose by the
-    // branch (2048 x 4096 copied under Eq. 3: 26.3 against 24.5 us per call).
-    auto chunk_off = [&](int64_t c, int64_t ld) -> int64_t {
-        if (CH != kSmallChunksPerThread || t.rm.cpr == 0u || c >= 0x7FFFFFFF) return tensor_chunk_off<STRIDED>(t, c, ld);
-        const uint32_t r = row_div(t.rm, (uint32_t)c);
-        return (int64_t)r * ld + (int64_t)((uint32_t)c - r * t.rm.cpr) * 8;
-    };
+    const unsigned long long n_padded = (unsigned long long)t.n_tiles * kTensorChunksPerBlock * 8;
+    const uint32_t mask = tensor_decide<CRIT>(t, g.near_tol, se, se5, n_padded - sz, abits, proven, b == 0);
     if (mask == 2u) {
         const bool fast = abits < fast_amax_limit(t.mode);
+        const float s5 = block_scale(abits, kE5M2Max, t.mode, group_mantissa_bits(abits, kE5M2Max, t.mode));
         uint16_t* __restrict__ fakep = t.o.fake;
         const float s_inv = fakep ? 1.0f / s5 : 0.0f;
         for (int64_t c = (int64_t)b * 256 + threadIdx.x; c < t.n_chunks; c += (int64_t)nb * 256)
-            requant_chunk_e5m2(t.x + chunk_off(c, t.rm.ld), fakep ? nullptr : t.o.fp8 + chunk_off(c, t.o.ld_fp8),
-                               fakep ? fakep + chunk_off(c, t.o.ld_fake) : nullptr, s5, s_inv, fast);
+            requant_chunk_e5m2(t.x + tensor_chunk_off<STRIDED>(t, c, t.rm.ld), fakep ? nullptr : t.o.fp8 + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fp8),
+                               fakep ? fakep + tensor_chunk_off<STRIDED>(t, c, t.o.ld_fake) : nullptr, s5, s_inv, fast);
         return;
     }
     if (proven || mask == 0u || t.o.bf16 == nullptr) return;
@@ -1475,27 +1480,158 @@ __device__ __forceinline__ void tensor_finish_body(const G& g, int block) {
         for (; c + 3 * stride < t.n_chunks; c += 4 * stride) {
             u32x4 v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = load16(t.x + chunk_off(c + u * stride, t.rm.ld));
+            for (int u = 0; u < 4; ++u) v[u] = load16(t.x + tensor_chunk_off<STRIDED>(t, c + u * stride, t.rm.ld));
 #pragma unroll
-            for (int u = 0; u < 4; ++u) store16(t.o.bf16 + chunk_off(c + u * stride, t.o.ld_bf16), v[u]);
+            for (int u = 0; u < 4; ++u) store16(t.o.bf16 + tensor_chunk_off<STRIDED>(t, c + u * stride, t.o.ld_bf16), v[u]);
         }
         for (; c < t.n_chunks; c += stride)
-            store16(t.o.bf16 + chunk_off(c, t.o.ld_bf16), load16(t.x + chunk_off(c, t.rm.ld)));
+            store16(t.o.bf16 + tensor_chunk_off<STRIDED>(t, c, t.o.ld_bf16), load16(t.x + tensor_chunk_off<STRIDED>(t, c, t.rm.ld)));
     } else {
         copy_chunk_tiles(t.x, t.o.bf16, t.n_chunks, b, nb);
+    }
+}
+// ---- a small operand alone in its call: two launches instead of three.  The workgroups of pass B keep their tile in registers, leave
+//      their sums and draw a ticket; the last one decides for the operand and tells the others, which copy their tile if it stays in
+//      BF16 after all (or rewrite it in E5M2).  Nobody waits without end: a workgroup that is not told in time (others may not have
+//      found a place on the chip) says so, looks once more and leaves; the one that decides tells first and then looks who has left,
+//      so that at least one of the two sees to the tile (if both do, they store the same bytes).
+constexpr int kTicketGroup = 16;             // workgroups to a first ticket; tickets of one address complete some 15 ns apart
+constexpr int kOneMaxSlots = 1024;
+constexpr int kOneLine = 32;                 // words: a line of its own for every ticket and every copy of the decision
+constexpr int kTicketRoot = kOneMaxSlots / kTicketGroup * kOneLine;
+constexpr int kToldCopies = 32;              // of the decision, so that few workgroups look at one line
+constexpr int kOneTold = kTicketRoot + kOneLine, kOneLeft = kOneTold + kToldCopies * kOneLine, kOneSyncWords = kOneLeft + kOneMaxSlots;
+constexpr int kOnePolls = 1024;              // about half a millisecond
+enum : uint32_t { kToldNothing = 0u, kToldMask = 1u };      // kToldMask + the mask
+static_assert(8192 + kOneSyncWords <= kMaxQuantBlocks && kOneMaxSlots <= 8192, "the words lie behind the zero counts in their array");
+__device__ __forceinline__ uint32_t* one_sync(const TensorOp& t) { return t.zero + 8192; }
+__device__ __forceinline__ uint32_t agent_load(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float agent_load(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <class T>
+__device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+template <int CH>
+__global__ __launch_bounds__(256) void k_tensor_amax_one(OneTensor g) {
+    uint32_t* sync = one_sync(g.op[0]);
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < (uint32_t)kOneSyncWords; i += gridDim.x * 256u) sync[i] = 0u;
+    tensor_amax_body<true, CH>(g, (int)blockIdx.x);
+}
+template <int CRIT, bool FAKE, int CH>
+__global__ __launch_bounds__(256, 4) void k_tensor_quant_one(OneTensor g) {
+    constexpr int kTile = 256 * CH;
+    __shared__ float shf[8];
+    __shared__ uint32_t shu[4], sh_last, sh_told, sh_left[kOneMaxSlots / 32];
+    __shared__ double shd[4];
+    __shared__ unsigned long long shl[4];
+    const TensorOp& t = g.op[0];
+    const int tid = threadIdx.x, w = tid >> 6, b = (int)blockIdx.x, n_slots = (int)gridDim.x;      // a tile each
+    uint32_t* sync = one_sync(t);
+    uint32_t* told_at = sync + kOneTold + (b % kToldCopies) * kOneLine;
+    u32x4 raw[CH];
+    TensorAcc acc;
+    uint32_t abits;
+    const bool proven = tensor_quant_body<CRIT, FAKE, true, CH>(t, b, raw, acc, abits);
+    // ---- sums of the tile, ticket
+    const float e_w = wave_allsum_f32(acc.s.e0 + acc.s.e1);
+    const uint32_t z_w = wave_allsum_u32(fold_add16(acc.zero2));
+    float e5_w = 0.0f;
+    if constexpr (CRIT == kCritEq3) e5_w = wave_allsum_f32(acc.s.f0 + acc.s.f1);
+    if ((tid & 63) == 0) { shf[w] = e_w; shf[4 + w] = e5_w; shu[w] = z_w; }
+    __syncthreads();
+    if (tid == 0) {
+        agent_store(t.err + b, (shf[0] + shf[1]) + (shf[2] + shf[3]));
+        agent_store(t.zero + b, (shu[0] + shu[1]) + (shu[2] + shu[3]));
+        if constexpr (CRIT == kCritEq3) agent_store(t.err5 + b, (shf[4] + shf[5]) + (shf[6] + shf[7]));
+        wait_memory();                                        // the sums have arrived before the ticket is drawn
+        const uint32_t grp = (uint32_t)b / kTicketGroup, n_grp = (uint32_t)(n_slots + kTicketGroup - 1) / kTicketGroup;
+        const uint32_t in_grp = (uint32_t)n_slots - grp * kTicketGroup < kTicketGroup ? (uint32_t)n_slots - grp * kTicketGroup : kTicketGroup;
+        bool last = __hip_atomic_fetch_add(sync + grp * kOneLine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == in_grp - 1u;
+        if (last) last = __hip_atomic_fetch_add(sync + kTicketRoot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_grp - 1u;
+        sh_last = last ? 1u : 0u;
+    }
+    __syncthreads();
+    const bool decides = sh_last != 0u, open = !proven && (t.o.bf16 != nullptr || t.three != 0u);      // open: the decision may ask for one more store
+    // What the decision asks for in one tile: the BF16 fallback (from the registers where they hold it), or the E5M2 payload.
+    auto chunk_off = [&](int64_t c, int64_t ld) -> int64_t {
+        if (t.rm.cpr == 0u) return tensor_chunk_off<true>(t, c, ld);
+        const uint32_t r = row_div(t.rm, (uint32_t)c);        // (an operand that comes here has fewer than 2^31 chunks)
+        return (int64_t)r * ld + (int64_t)((uint32_t)c - r * t.rm.cpr) * 8;
+    };
+    auto finish_tile = [&](uint32_t mask, int tile, bool held) {
+        const bool fast = abits < fast_amax_limit(t.mode);
+        const float s5 = block_scale(abits, kE5M2Max, t.mode, group_mantissa_bits(abits, kE5M2Max, t.mode)), s_inv = FAKE ? 1.0f / s5 : 0.0f;
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const int64_t c = (int64_t)tile * kTile + u * 256 + tid;
+            if (c >= t.n_chunks) continue;
+            const uint16_t* src = t.x + chunk_off(c, t.rm.ld);
+            if (mask == 2u) requant_chunk_e5m2(src, FAKE ? nullptr : t.o.fp8 + chunk_off(c, t.o.ld_fp8), FAKE ? t.o.fake + chunk_off(c, t.o.ld_fake) : nullptr, s5, s_inv, fast);
+            else if (t.o.bf16) store16(t.o.bf16 + chunk_off(c, t.o.ld_bf16), held && t.rm.cpr != 0u ? raw[u] : load16(src));
+        }
+    };
+    if (!decides) {
+        if (!open) return;
+        if (tid == 0) {
+            uint32_t told = kToldNothing;
+            for (int poll = 0; poll < kOnePolls && told == kToldNothing; ++poll) {
+                told = agent_load(told_at);
+                if (told == kToldNothing) __builtin_amdgcn_s_sleep(8);
+            }
+            sh_told = told;
+        }
+        __syncthreads();
+        uint32_t told = sh_told;
+        if (told == kToldNothing) {                            // (uniform) what this workgroup has stored comes before the word that it left
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __syncthreads();
+            if (tid == 0) {
+                agent_store(sync + kOneLeft + b, 1u);
+                wait_memory();
+                sh_told = agent_load(told_at);
+            }
+            __syncthreads();
+            told = sh_told;
+            if (told == kToldNothing) return;
+        }
+        if (told != kToldMask) finish_tile(told - kToldMask, b, true);
+        return;
+    }
+    double se = 0.0, se5 = 0.0;
+    unsigned long long sz = 0;
+#pragma unroll
+    for (int k = 0; k < kOneMaxSlots / 256; ++k) {
+        const int i = tid + k * 256, ic = i < n_slots ? i : n_slots - 1;      // always a valid slot: the loads need no branch
+        const float ev = agent_load(t.err + ic), e5v = CRIT == kCritEq3 ? agent_load(t.err5 + ic) : 0.0f;
+        const uint32_t zv = agent_load(t.zero + ic);
+        se += i < n_slots ? (double)ev : 0.0; se5 += i < n_slots ? (double)e5v : 0.0; sz += i < n_slots ? zv : 0u;
+    }
+    se = block_sum_shfl<double>(se, shd);
+    sz = block_sum_shfl<unsigned long long>(sz, shl);
+    if constexpr (CRIT == kCritEq3) se5 = block_sum_shfl<double>(se5, shd);
+    const unsigned long long n_padded = (unsigned long long)t.n_tiles * kTile * 8;
+    const uint32_t mask = tensor_decide<CRIT>(t, g.near_tol, se, se5, n_padded - sz, abits, proven, true);
+    if (!open) return;
+    if (tid < kToldCopies) agent_store(sync + kOneTold + tid * kOneLine, kToldMask + mask);
+    if (mask == 0u) return;
+    finish_tile(mask, b, true);
+    wait_memory();
+    if (tid < kOneMaxSlots / 32) sh_left[tid] = 0u;
+    __syncthreads();                                           // (the decision has been told: the wave that stored it has waited)
+    for (int i = tid; i < n_slots; i += 256)
+        if (agent_load(sync + kOneLeft + i) != 0u) atomicOr(&sh_left[i >> 5], 1u << (i & 31));
+    __syncthreads();
+    unsigned long long some = __ballot((tid & 63) < kOneMaxSlots / 32 && sh_left[tid & (kOneMaxSlots / 32 - 1)] != 0u);
+    for (; some; some &= some - 1ull) {                        // 32 tiles each (the same in every wave)
+        const int i0 = (__ffsll(some) - 1) * 32;
+        for (uint32_t left = sh_left[i0 >> 5]; left; left &= left - 1u) finish_tile(mask, i0 + __ffs((int)left) - 1, false);
     }
 }
 // Workgroups from `stats_first` on combine the riders' partial statistics records (one workgroup per operand).
 template <int CRIT, bool STRIDED>
 __global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, GroupStats riders, int stats_first) {
     if ((int)blockIdx.x >= stats_first) { stats_final_body(riders, (int)blockIdx.x - stats_first); return; }
-    tensor_finish_body<CRIT, STRIDED, kTensorChunksPerThread>(g, (int)blockIdx.x);
+    tensor_finish_body<CRIT, STRIDED>(g, (int)blockIdx.x);
 }
-template <int CRIT>
-__global__ __launch_bounds__(256) void k_tensor_finish_one(OneTensor g) {
-    tensor_finish_body<CRIT, true, kSmallChunksPerThread>(g, (int)blockIdx.x);
-}
-
 // Group loop of Algorithm 1 for sub-tensor operands: the operand's amax (partials of pass A) gives the
 // group mantissas for E4M3 and E5M2, which the block kernels read; also written to the caller's output.
 // (E8M0-only operands have a zero mantissa, which their block kernels know.)
@@ -2204,33 +2340,40 @@ void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_p
         else k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
     }
 }
-// A small operand with padded rows that is alone: the same three passes over tiles of two chunks per lane, from a table of one operand,
-// with a finish workgroup for every 1024 chunks that may have to be copied.  Such a call is a chain of launches, so what counts is
-// what the host spends on each (3.8 KB of kernel arguments for a table of eight operands and the statistics' riders, 0.4 KB here)
-// and the depth of a workgroup's work.  us per call, these kernels / the grouped ones: 256 x 4096 11.5 / 14.9 kept in E4M3, 11.7 / 14.0
-// kept in BF16; 1024 x 4096 13.6 / 16.1 and 13.9 / 14.5; four chunks per lane 12.0 at 256 x 4096, one 13.1.
-constexpr int64_t kOneTensorMaxChunks = 1 << 19;      // (1280 x 4096, beyond it: 18.2 and 16.6 us, 18.3 and 20.8 with the kernels of one chunk per lane
-                                                      // that the grouped ones replaced)
-void launch_one_tensor(const GroupTensor& g, int a_end, int s_end, int c_end, int crit, bool fake, hipStream_t st, KProf* prof) {
+// A small operand that is alone: two passes over tiles of two chunks per lane, or four from one_mid_chunks on, from a table of one
+// operand.  Such a call is a chain of launches, so what counts is their number, what the host spends on each (3.8 KB of kernel
+// arguments for a table of eight operands and the statistics' riders, 0.4 KB here) and the depth of a workgroup's work.  us per call, here /
+// with the three launches that larger operands take: dense 64 x 256 9.9 / 13.4, 1024 x 1024 10.8 / 14.4, 1024 x 4096 13.4 / 15.6,
+// 2048 x 4096 16.2 / 18.4 (kept in E4M3); kept in BF16 without a proof 11.6 / 16.0, 14.7 / 18.4, 20.0 / 22.4.  Two and four chunks
+// per lane: 10.8 and 11.5 at 1024 x 1024, 12.1 and 12.6 at 768 x 4096, 15.5 and 14.7 at 1024 x 4096 kept in BF16.
+// A tile per workgroup, and workgroups that wait to be told: 1024 at most under Eq. 2, of the 1792 that the kernel's registers let be
+// resident, and 512 under Eq. 3, of 1024.
+constexpr int64_t one_max_chunks(int crit) { return crit == kCritEq3 ? 1 << 19 : 1 << 20; }
+constexpr int64_t one_mid_chunks(int crit) { return crit == kCritEq3 ? (1 << 18) + 1 : 1 << 19; }
+static_assert(one_max_chunks(kCritEq2) <= (int64_t)kOneMaxSlots * 256 * kMidChunksPerThread && one_mid_chunks(kCritEq2) <= (int64_t)kOneMaxSlots * 256 * kSmallChunksPerThread,
+              "a slot per tile");
+template <int CRIT, bool FAKE>
+void launch_one_quant(const OneTensor& o, int slots, bool mid, hipStream_t st) {
+    if (mid) k_tensor_quant_one<CRIT, FAKE, kMidChunksPerThread><<<dim3(slots), dim3(256), 0, st>>>(o);
+    else k_tensor_quant_one<CRIT, FAKE, kSmallChunksPerThread><<<dim3(slots), dim3(256), 0, st>>>(o);
+}
+void launch_one_tensor(const GroupTensor& g, int a_end, int s_end, bool mid, int crit, bool fake, hipStream_t st, KProf* prof) {
     OneTensor o;
     o.n = 1; o.near_tol = g.near_tol; o.op[0] = g.op[0];
-    o.amax_end[0] = a_end; o.slot_end[0] = s_end; o.copy_end[0] = c_end;
-    const dim3 block(256);
-    { ProfScope ps(prof, kKernTensorAmax, st); k_tensor_amax_one<<<dim3(a_end), block, 0, st>>>(o); }
+    o.amax_end[0] = a_end; o.slot_end[0] = s_end; o.copy_end[0] = 0;
     {
-        ProfScope ps(prof, kKernTensorQuant, st);
-        const dim3 grid(s_end);
-        if (fake) {
-            if (crit == kCritEq3) k_tensor_quant_one<kCritEq3, true><<<grid, block, 0, st>>>(o);
-            else k_tensor_quant_one<kCritEq2, true><<<grid, block, 0, st>>>(o);
-        } else {
-            if (crit == kCritEq3) k_tensor_quant_one<kCritEq3, false><<<grid, block, 0, st>>>(o);
-            else k_tensor_quant_one<kCritEq2, false><<<grid, block, 0, st>>>(o);
-        }
+        ProfScope ps(prof, kKernTensorAmax, st);
+        if (mid) k_tensor_amax_one<kMidChunksPerThread><<<dim3(a_end), dim3(256), 0, st>>>(o);
+        else k_tensor_amax_one<kSmallChunksPerThread><<<dim3(a_end), dim3(256), 0, st>>>(o);
     }
-    ProfScope ps(prof, kKernFallbackCopy, st);
-    if (crit == kCritEq3) k_tensor_finish_one<kCritEq3><<<dim3(c_end), block, 0, st>>>(o);
-    else k_tensor_finish_one<kCritEq2><<<dim3(c_end), block, 0, st>>>(o);
+    ProfScope ps(prof, kKernTensorQuant, st);
+    if (fake) {
+        if (crit == kCritEq3) launch_one_quant<kCritEq3, true>(o, s_end, mid, st);
+        else launch_one_quant<kCritEq2, true>(o, s_end, mid, st);
+    } else {
+        if (crit == kCritEq3) launch_one_quant<kCritEq3, false>(o, s_end, mid, st);
+        else launch_one_quant<kCritEq2, false>(o, s_end, mid, st);
+    }
 }
 void BatchRun::per_tensor_operands(int crit) {
     // ---- per-tensor operands: amax pass, quantize pass, finish (+ fallback copy) pass; FP8 payload and fake
@@ -2244,13 +2387,15 @@ void BatchRun::per_tensor_operands(int crit) {
             GroupTensor g; g.n = cnt; g.near_tol = near_tol;
             const bool ride = !riders_used && n_stats_groups > 0;
             const KShape& sh0 = items[idx[0]].sh;
-            const bool one = strided && cnt == 1 && !ride && sh0.rows * (sh0.cols / 8) <= kOneTensorMaxChunks;
+            const int64_t chunks0 = sh0.rows * (sh0.cols / 8);
+            const bool one = cnt == 1 && !ride && chunks0 <= one_max_chunks(crit), mid = chunks0 >= one_mid_chunks(crit);
             int64_t all_tiles = 0;
             for (int k = 0; k < cnt; ++k) {
                 const BatchItem& it = items[idx[k]];
                 TensorOp& t = g.op[k];
-                t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u; t.lean = it.lean && !strided ? 1u : 0u;      // (padded rows always get their payload, and report no proof)
-                set_tensor_layout(t, it.sh, it.o, one ? 256 * kSmallChunksPerThread : kTensorChunksPerBlock);
+                t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u; 
+                t.flags = strided ? 0u : (it.lean ? kTensorLean : 0u) | kTensorReport;      // (padded rows always get their payload, and report no proof)
+                set_tensor_layout(t, it.sh, it.o, one ? 256 * (mid ? kMidChunksPerThread : kSmallChunksPerThread) : kTensorChunksPerBlock);
                 all_tiles += t.n_tiles;
                 const TensorPlan pl = plan_tensor(it.sh.rows, it.sh.cols);
                 char* w = carve(pl.bytes);
@@ -2296,7 +2441,7 @@ void BatchRun::per_tensor_operands(int crit) {
                     t.n_slots = share(t.n_tiles, total_tiles, quant_cap, t.n_tiles);
                     t.keep_from = bytes > kKeepTensorBytes ? t.n_tiles - t.n_tiles * (kKeepTensorBytes >> 15) / total_tiles : 0;
                     a_end += t.n_amax; s_end += t.n_slots;
-                    c_end += (t.o.bf16 || t.three) ? share(t.n_tiles, all_tiles, 2048, one ? (t.n_chunks + 1023) / 1024 : 2048) : 1;
+                    c_end += (t.o.bf16 || t.three) ? share(t.n_tiles, all_tiles, 2048, 2048) : 1;
                     g.amax_end[k] = a_end; g.slot_end[k] = s_end; g.copy_end[k] = c_end;
                 }
                 p.a1 = a_end; p.s1 = s_end;
@@ -2310,7 +2455,7 @@ void BatchRun::per_tensor_operands(int crit) {
                 ride_final = ride_partial > riders.n ? riders.n : 0;      // single-workgroup operands are final already
                 riders_used = true;
             }
-            if (one) launch_one_tensor(g, a_end, s_end, c_end, crit, fake, st, prof);
+            if (one) launch_one_tensor(g, a_end, s_end, mid, crit, fake, st, prof);
             else if (strided) launch_tensor_passes<true>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             else launch_tensor_passes<false>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             cnt = 0;
