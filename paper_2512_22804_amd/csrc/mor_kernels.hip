@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void k_sub1x128_strided(const uint16_t* __rest
 // ======================================================================================
 constexpr int kTensorChunksPerThread = 8;                       // 16-byte chunks per thread in pass B
 constexpr int kTensorChunksPerBlock = 256 * kTensorChunksPerThread;
-constexpr int kSmallChunksPerThread = 2, kMidChunksPerThread = 4;      // ... of a small operand that is alone (see one_max_chunks)
+constexpr int kSmallChunksPerThread = 2;                        // ... in pass A of a small operand that is alone (see one_max_chunks)
 constexpr int kAmaxOneTile = 768;        // tiles of a pass-A launch up to which every one gets a workgroup (three per compute unit); also the size of
                                          // the partials' arrays.  1251 tiles of padded rows: 50.8 us per call at 512 workgroups, 51.9 at 1251
 constexpr int kMaxAmaxBlocks = 512;      // pass A of larger launches, all its workgroups resident.  The two parts of the six gradients of
@@ -179,10 +179,16 @@ __device__ __forceinline__ uint32_t row_off(const RowPos& p, uint32_t row_bytes,
 }
 
 // Smallest non-zero magnitude pattern of the operand from the partial words (0 when it has no non-zero element).
-__device__ __forceinline__ uint32_t global_amin_bits(const uint32_t* __restrict__ part, int n_part_amax, uint32_t* sh4) {
+template <int T>             // lanes of the workgroup
+__device__ __forceinline__ uint32_t global_amin_bits(const uint32_t* __restrict__ part, int n_part_amax) {
+    __shared__ uint32_t sh[T / 64];
     uint32_t m = 0xFFFFu;
-    for (int i = threadIdx.x; i < n_part_amax; i += 256) m = min(m, part[i] >> 16);
-    m = block_allmin_u16(m, sh4);
+    for (int i = threadIdx.x; i < n_part_amax; i += T) m = min(m, part[i] >> 16);
+    m = 0xFFFFu - wave_allmax_u32(0xFFFFu - m);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < T / 64; ++k) m = min(m, sh[k]);
     return m == 0xFFFFu ? 0u : m + 1u;
 }
 // The E5M2 payload of a whole operand (three-way recipe, per-tensor granularity): one more sweep that overwrites the
@@ -1249,14 +1255,17 @@ __device__ __forceinline__ uint32_t tensor_pass_a_result(const TensorOp& t, bool
     return max(max(sha[0], sha[1]), max(sha[2], sha[3]));
 }
 // STRIDED: operands with padded leading dimensions (see RowMap).
-// Workgroup b of the operand's n_slots.  `raw` holds its last tile afterwards; acc receives its sums.  Returns whether the BF16
-// decision was proven (the fallback is then written).
-template <int CRIT, bool FAKE, bool STRIDED, int CH>
-__device__ __forceinline__ bool tensor_quant_body(const TensorOp& t, int b, u32x4 (&bufA)[CH], TensorAcc& acc, uint32_t& abits) {
-    constexpr int kTile = 256 * CH;
+template <int CRIT, bool FAKE, bool STRIDED>
+__global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int block0) {
+    constexpr int CH = kTensorChunksPerThread, kTile = 256 * CH;
+    const int block = (int)blockIdx.x + block0;
+    const int op = group_find32(g.slot_end, g.n, block);
+    const TensorOp& t = g.op[op];
+    const int b = block - (op ? g.slot_end[op - 1] : 0);
     const uint16_t* __restrict__ x = t.x;
     uint8_t* __restrict__ fp8 = t.o.fp8;
     const int64_t n_chunks = t.n_chunks, n_tiles = t.n_tiles, n_slots = t.n_slots;
+    u32x4 bufA[CH];
     const bool wide = STRIDED && t.rm.cpr == 0u;             // chunk by chunk, in the careful path below; pass A proves nothing then
     auto load_tile = [&](u32x4* raw, int64_t tile) {
         const int64_t c0 = tile * kTile + threadIdx.x;
@@ -1283,7 +1292,7 @@ __device__ __forceinline__ bool tensor_quant_body(const TensorOp& t, int b, u32x
     int64_t tl = b;
     load_tile(bufA, tl);
     bool proven;                                             // then the BF16 fallback is written in this sweep
-    abits = tensor_pass_a_result(t, proven);
+    const uint32_t abits = tensor_pass_a_result(t, proven);
     uint16_t* __restrict__ bf16 = t.o.bf16;
     if (b == 0 && threadIdx.x == 0) { t.abits[0] = abits; t.abits[1] = proven ? 1u : 0u; }
     // one block = the group: under GAM the block's own mantissa is the group mantissa and the scale is s_b
@@ -1295,7 +1304,7 @@ __device__ __forceinline__ bool tensor_quant_body(const TensorOp& t, int b, u32x
     const bool emit = !(proven && (t.flags & kTensorLean) != 0u);             // lean payload: the codes of a proven BF16 operand are not stored
     const float s_inv = FAKE ? 1.0f / s : 0.0f;
     uint16_t* __restrict__ fakep = t.o.fake;     // fake quantization: == bf16, so a proven fallback is already in place
-    acc = TensorAcc{{0.0f, 0.0f, 0.0f, 0.0f}, 0u};
+    TensorAcc acc{{0.0f, 0.0f, 0.0f, 0.0f}, 0u};
     // Stores go through bounds-checked buffer windows over the tile (a tail tile's window is shorter; a payload that
     // is not wanted gets a null window), so the quantization sweep has no branches and stays one basic block: with
     // per-lane or per-operand branches around the stores the compiler defers the error terms of all eight chunks
@@ -1385,24 +1394,12 @@ __device__ __forceinline__ bool tensor_quant_body(const TensorOp& t, int b, u32x
         if (tl >= n_tiles) break;
         load_tile(bufA, tl);
     }
-    return proven;
-}
-template <int CRIT, bool FAKE, bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int block0) {
-    const int block = (int)blockIdx.x + block0;
-    const int op = group_find32(g.slot_end, g.n, block);
-    const TensorOp& t = g.op[op];
-    const int b = block - (op ? g.slot_end[op - 1] : 0);
-    u32x4 raw[kTensorChunksPerThread];
-    TensorAcc acc;
-    uint32_t abits;
-    tensor_quant_body<CRIT, FAKE, STRIDED, kTensorChunksPerThread>(t, b, raw, acc, abits);
     TensorPartials tp{t.err, t.err5, t.zero};
     tensor_publish<CRIT>(acc, tp, b);
 }
 // Decision on a per-tensor operand from its sums (se and se5 over n non-zero elements): every thread of the workgroup calls it and gets
 // the mask; with `emit`, thread 0 writes the outputs and the statistics.
-template <int CRIT>
+template <int CRIT, int T>
 __device__ __forceinline__ uint32_t tensor_decide(const TensorOp& t, float near_tol, double se, double se5, unsigned long long n, uint32_t abits,
                                                   bool proven, bool emit) {
     if (abits >= kInfBits) { se = (double)__builtin_inff(); se5 = se; }
@@ -1411,8 +1408,7 @@ __device__ __forceinline__ uint32_t tensor_decide(const TensorOp& t, float near_
     else mask = ((n ? se / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
     uint32_t amin_bits = 0u;
     if (t.three && mask == 1u) {           // Eq. (4): the operand is kept in E5M2 if its dynamic range fits
-        __shared__ uint32_t sh4[4];
-        amin_bits = global_amin_bits(t.amax_part, t.n_amax, sh4);
+        amin_bits = global_amin_bits<T>(t.amax_part, t.n_amax);
         if (range_fits_e5m2(abits, amin_bits, n ? 1u : 0u)) mask = 2u;
     }
     if (emit && threadIdx.x == 0) {
@@ -1462,7 +1458,7 @@ __device__ __forceinline__ void tensor_finish_body(const GroupTensor& g, int blo
     if constexpr (CRIT == kCritEq3) se5 = block_sum_shfl<double>(se5, shd);
     const uint32_t abits = t.abits[0];
     const unsigned long long n_padded = (unsigned long long)t.n_tiles * kTensorChunksPerBlock * 8;
-    const uint32_t mask = tensor_decide<CRIT>(t, g.near_tol, se, se5, n_padded - sz, abits, proven, b == 0);
+    const uint32_t mask = tensor_decide<CRIT, 256>(t, g.near_tol, se, se5, n_padded - sz, abits, proven, b == 0);
     if (mask == 2u) {
         const bool fast = abits < fast_amax_limit(t.mode);
         const float s5 = block_scale(abits, kE5M2Max, t.mode, group_mantissa_bits(abits, kE5M2Max, t.mode));
@@ -1496,7 +1492,7 @@ __device__ __forceinline__ void tensor_finish_body(const GroupTensor& g, int blo
 //      found a place on the chip) says so, looks once more and leaves; the one that decides tells first and then looks who has left,
 //      so that at least one of the two sees to the tile (if both do, they store the same bytes).
 constexpr int kTicketGroup = 16;             // workgroups to a first ticket; tickets of one address complete some 15 ns apart
-constexpr int kOneMaxSlots = 1024;
+constexpr int kOneMaxSlots = 512;
 constexpr int kOneLine = 32;                 // words: a line of its own for every ticket and every copy of the decision
 constexpr int kTicketRoot = kOneMaxSlots / kTicketGroup * kOneLine;
 constexpr int kToldCopies = 32;              // of the decision, so that few workgroups look at one line
@@ -1510,37 +1506,185 @@ __device__ __forceinline__ float agent_load(const float* p) { return __hip_atomi
 template <class T>
 __device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-template <int CH>
 __global__ __launch_bounds__(256) void k_tensor_amax_one(OneTensor g) {
     uint32_t* sync = one_sync(g.op[0]);
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < (uint32_t)kOneSyncWords; i += gridDim.x * 256u) sync[i] = 0u;
-    tensor_amax_body<true, CH>(g, (int)blockIdx.x);
+    tensor_amax_body<true, kSmallChunksPerThread>(g, (int)blockIdx.x);
 }
-template <int CRIT, bool FAKE, int CH>
-__global__ __launch_bounds__(256, 4) void k_tensor_quant_one(OneTensor g) {
-    constexpr int kTile = 256 * CH;
+// Quantizes 8 values; the terms come out one by one, for a chain of additions that another lane has begun.
+template <bool E5M2, bool FAKE>
+__device__ __forceinline__ u32x2 quant8_terms(const u32x4& raw, float s, float s_inv, float (&e)[8], u32x4& deq) {
+    int w0 = 0, w1 = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float y0 = __uint_as_float(raw[j] << 16) * s, y1 = __uint_as_float(raw[j] & 0xFFFF0000u) * s;
+        int& w = j < 2 ? w0 : w1;
+        w = (j & 1) ? cvt_pk8<E5M2>(y0, y1, w, true) : cvt_pk8<E5M2>(y0, y1, w, false);
+        const f32x2 q = (j & 1) ? cvt_pk_f32<E5M2>(w, true) : cvt_pk_f32<E5M2>(w, false);
+        e[2 * j] = rel_term(y0, q.x);
+        e[2 * j + 1] = rel_term(y1, q.y);
+        if constexpr (FAKE) deq[j] = pk_bf16_rne(q.x * s_inv, q.y * s_inv);
+    }
+    return u32x2{(uint32_t)w0, (uint32_t)w1};
+}
+template <bool FAKE>
+__device__ __forceinline__ u32x2 quant8_dual_terms(const u32x4& raw, float s, float s_inv, float (&e)[8], float (&f)[8], u32x4& deq) {      // see quant8_dual
+    int w0 = 0, w1 = 0;
+    constexpr float kInv128 = 0.0078125f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float y0 = __uint_as_float(raw[j] << 16) * s, y1 = __uint_as_float(raw[j] & 0xFFFF0000u) * s;
+        int& w = j < 2 ? w0 : w1;
+        w = (j & 1) ? cvt_pk8<false>(y0, y1, w, true) : cvt_pk8<false>(y0, y1, w, false);
+        const f32x2 q = (j & 1) ? cvt_pk_f32<false>(w, true) : cvt_pk_f32<false>(w, false);
+        const float r0 = __builtin_amdgcn_rcpf(__builtin_fabsf(y0)), r1 = __builtin_amdgcn_rcpf(__builtin_fabsf(y1));
+        e[2 * j] = __builtin_amdgcn_fmed3f(__builtin_fabsf(y0 - q.x) * r0, 0.0f, 1.0f);
+        e[2 * j + 1] = __builtin_amdgcn_fmed3f(__builtin_fabsf(y1 - q.y) * r1, 0.0f, 1.0f);
+        const i16x2 none = {0, 0};
+        const i16x2 c5 = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(none, y0, y1, kInv128, false);
+        const f32x2 q5 = __builtin_amdgcn_cvt_scalef32_pk_f32_bf8((uint32_t)(uint16_t)c5.x, kInv128, false);
+        f[2 * j] = __builtin_amdgcn_fmed3f(__builtin_fabsf(y0 - q5.x) * r0, 0.0f, 1.0f);
+        f[2 * j + 1] = __builtin_amdgcn_fmed3f(__builtin_fabsf(y1 - q5.y) * r1, 0.0f, 1.0f);
+        if constexpr (FAKE) deq[j] = pk_bf16_rne(q.x * s_inv, q.y * s_inv);
+    }
+    return u32x2{(uint32_t)w0, (uint32_t)w1};
+}
+// T lanes with CH chunks each.  Dense operands: a tile is the 2048 chunks that 256 lanes take in the grouped kernels, and the sums are
+// those of the grouped kernels bit for bit: two lanes that hold a chain of additions in halves hand it on through shared memory.
+template <int CRIT, bool FAKE, int T, int CH>
+__global__ __launch_bounds__(T, 4) void k_tensor_quant_one(OneTensor g) {
+    constexpr int Q = T / 256, NW = T / 64, kTile = T * CH;
+    __shared__ float4 run[256];
     __shared__ float shf[8];
-    __shared__ uint32_t shu[4], sh_last, sh_told, sh_left[kOneMaxSlots / 32];
-    __shared__ double shd[4];
-    __shared__ unsigned long long shl[4];
+    __shared__ uint32_t sha[NW], shz[NW], sh_last, sh_told, sh_left[kOneMaxSlots / 32];
+    __shared__ unsigned long long shl[NW];
+    __shared__ double shd[8];
     const TensorOp& t = g.op[0];
-    const int tid = threadIdx.x, w = tid >> 6, b = (int)blockIdx.x, n_slots = (int)gridDim.x;      // a tile each
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, q = tid >> 8, l = tid & 255;
+    const int b = (int)blockIdx.x, n_slots = (int)gridDim.x;                        // a tile each
+    const int64_t c_first = (int64_t)b * kTile, n_chunks = t.n_chunks;
+    const uint32_t first = (uint32_t)(q * CH * 256 + l);                            // this lane's first chunk in the tile, then 256 further
+    const uint32_t valid = (uint32_t)(n_chunks - c_first < kTile ? n_chunks - c_first : kTile);
+    const bool wide = t.rm.cpr == 0u;
     uint32_t* sync = one_sync(t);
     uint32_t* told_at = sync + kOneTold + (b % kToldCopies) * kOneLine;
+    auto chunk_off = [&](int64_t c, int64_t ld) -> int64_t {
+        if (wide) return tensor_chunk_off<true>(t, c, ld);
+        const uint32_t r = row_div(t.rm, (uint32_t)c);        // (an operand that comes here has fewer than 2^31 chunks)
+        return (int64_t)r * ld + (int64_t)((uint32_t)c - r * t.rm.cpr) * 8;
+    };
+    // ---- the tile
     u32x4 raw[CH];
-    TensorAcc acc;
-    uint32_t abits;
-    const bool proven = tensor_quant_body<CRIT, FAKE, true, CH>(t, b, raw, acc, abits);
-    // ---- sums of the tile, ticket
-    const float e_w = wave_allsum_f32(acc.s.e0 + acc.s.e1);
-    const uint32_t z_w = wave_allsum_u32(fold_add16(acc.zero2));
-    float e5_w = 0.0f;
-    if constexpr (CRIT == kCritEq3) e5_w = wave_allsum_f32(acc.s.f0 + acc.s.f1);
-    if ((tid & 63) == 0) { shf[w] = e_w; shf[4 + w] = e5_w; shu[w] = z_w; }
+    RowPos pos0{0u, 0u};
+    const int64_t row0 = wide ? 0 : row_tile_first(t.rm, c_first, first, pos0);
+    if (!wide) {
+        const BufRsrc rx = make_buf(t.x + row0 * t.rm.ld);
+        RowPos pos = pos0;
+#pragma unroll
+        for (int u = 0; u < CH; ++u) { raw[u] = buf_load16(rx, row_off<16>(pos, (uint32_t)t.rm.ld * 2u, first + u * 256u < valid), 0u); row_step(t.rm, pos); }
+    } else {
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+            raw[u] = first + u * 256u < valid ? load16(t.x + chunk_off(c_first + first + u * 256u, t.rm.ld)) : u32x4{0u, 0u, 0u, 0u};
+    }
+    // ---- what pass A found out
+    uint32_t abits = 0u;
+    unsigned long long fl = 0ull;
+#pragma unroll
+    for (int k = 0; k < kAmaxOneTile / T + (kAmaxOneTile % T ? 1 : 0); ++k) {
+        const int i = tid + k * T, ic = i < t.n_amax ? i : t.n_amax - 1;              // always a valid slot: the loads need no branch
+        const uint32_t av = t.amax_part[ic], fv = t.flush_need ? t.flush_part[ic] : 0u;
+        abits = max(abits, av & 0xFFFFu);
+        fl += i < t.n_amax ? fv : 0u;
+    }
+    abits = wave_allmax_u32(abits);
+    fl = wave_allsum_u64(fl);
+    if (lane == 0) { sha[w] = abits; shl[w] = fl; }
     __syncthreads();
+    fl = 0ull;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) { abits = max(abits, sha[k]); fl += shl[k]; }
+    const bool proven = t.flush_need != 0ull && fl >= t.flush_need;                  // then the BF16 fallback is written here
+    if (b == 0 && tid == 0) { t.abits[0] = abits; t.abits[1] = proven ? 1u : 0u; }
+    const uint32_t mode = t.mode;
+    const float s = block_scale(abits, kE4M3Max, mode, group_mantissa_bits(abits, kE4M3Max, mode));
+    const float s5 = (CRIT == kCritEq3) ? block_scale(abits, kE5M2Max, mode, group_mantissa_bits(abits, kE5M2Max, mode)) : 0.0f;
+    const bool fast = abits < fast_amax_limit(mode) && !wide, dual = CRIT == kCritEq3 && s5 == 128.0f * s;
+    const bool emit = !(proven && (t.flags & kTensorLean) != 0u), dense = (t.flags & kTensorReport) != 0u;
+    const float s_inv = FAKE ? 1.0f / s : 0.0f;
+    const BufRsrc r8 = make_buf_window(t.o.fp8 + row0 * t.o.ld_fp8, (FAKE || !emit || wide) ? 0u : 0x7FFFFFFFu);
+    const BufRsrc rb = make_buf_window(t.o.bf16 + row0 * t.o.ld_bf16, proven ? 0x7FFFFFFFu : 0u);
+    const BufRsrc rf = make_buf_window(t.o.fake + row0 * t.o.ld_fake, (FAKE && !proven && !wide) ? 0x7FFFFFFFu : 0u);
+    // ---- quantize: codes or values stored, terms kept (one lane has its whole chain only if Q is 1)
+    uint32_t z2 = 0u;
+    float e[CH][8], f[CH][8];
+    RowPos pos = pos0;
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        const bool live = first + u * 256u < valid;
+        z2 = zero2_of(raw[u], z2);
+        u32x4 deq;
+        u32x2 codes{0u, 0u};
+        if (fast) {
+            if (CRIT == kCritEq3 && dual) {
+                codes = quant8_dual_terms<FAKE>(raw[u], s, s_inv, e[u], f[u], deq);
+            } else {
+                codes = quant8_terms<false, FAKE>(raw[u], s, s_inv, e[u], deq);
+                if constexpr (CRIT == kCritEq3) { u32x4 none; (void)quant8_terms<true, false>(raw[u], s5, 0.0f, f[u], none); }
+            }
+            buf_store16<kBufStoreNt>(rb, row_off<16>(pos, (uint32_t)t.o.ld_bf16 * 2u, live), raw[u]);       // proven fallback
+            if constexpr (FAKE) buf_store16<kBufStoreNt>(rf, row_off<16>(pos, (uint32_t)t.o.ld_fake * 2u, live), deq);
+            else buf_store8<kBufStoreNt>(r8, row_off<8>(pos, (uint32_t)t.o.ld_fp8, live), 0u, codes);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { e[u][j] = 0.0f; f[u][j] = 0.0f; }
+            if (live) {
+                const int64_t c = c_first + first + u * 256u;
+                const uint16_t* src = t.x + chunk_off(c, t.rm.ld);
+                e[u][0] = quant8_careful_mem<false>(src, s, (FAKE || !emit) ? nullptr : t.o.fp8 + chunk_off(c, t.o.ld_fp8),
+                                                    (FAKE && !proven) ? t.o.fake + chunk_off(c, t.o.ld_fake) : nullptr, s_inv);
+                if constexpr (CRIT == kCritEq3) f[u][0] = quant8_careful_mem<true>(src, s5, nullptr);
+                if (proven) store16(t.o.bf16 + chunk_off(c, t.o.ld_bf16), raw[u]);
+            }
+        }
+        row_step(t.rm, pos);
+    }
+    // ---- sums: dense operands in one chain per lane of 256, padded ones chunk by chunk (as the grouped kernels)
+    TileSums sum{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+        if (q == k) {
+            if (k > 0) { const float4 v = run[l]; sum = TileSums{v.x, v.y, v.z, v.w}; }
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                TileSums c = dense ? sum : TileSums{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    c.e0 += e[u][2 * j]; c.e1 += e[u][2 * j + 1];
+                    if constexpr (CRIT == kCritEq3) { c.f0 += f[u][2 * j]; c.f1 += f[u][2 * j + 1]; }
+                }
+                sum = dense ? c : sum + c;
+            }
+            if (k + 1 < Q) run[l] = float4{sum.e0, sum.e1, sum.f0, sum.f1};
+        }
+        if (k + 1 < Q) __syncthreads();
+    }
+    const uint32_t z_w = wave_allsum_u32(fold_add16(z2));
+    if (lane == 0) shz[w] = z_w;
+    if (q == Q - 1) {
+        const float e_w = wave_allsum_f32(sum.e0 + sum.e1);
+        float e5_w = 0.0f;
+        if constexpr (CRIT == kCritEq3) e5_w = wave_allsum_f32(sum.f0 + sum.f1);
+        if (lane == 0) { shf[w & 3] = e_w; shf[4 + (w & 3)] = e5_w; }
+    }
+    __syncthreads();
+    // ---- ticket
     if (tid == 0) {
+        uint32_t z = 0u;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) z += shz[k];
         agent_store(t.err + b, (shf[0] + shf[1]) + (shf[2] + shf[3]));
-        agent_store(t.zero + b, (shu[0] + shu[1]) + (shu[2] + shu[3]));
+        agent_store(t.zero + b, z);
         if constexpr (CRIT == kCritEq3) agent_store(t.err5 + b, (shf[4] + shf[5]) + (shf[6] + shf[7]));
         wait_memory();                                        // the sums have arrived before the ticket is drawn
         const uint32_t grp = (uint32_t)b / kTicketGroup, n_grp = (uint32_t)(n_slots + kTicketGroup - 1) / kTicketGroup;
@@ -1552,21 +1696,16 @@ __global__ __launch_bounds__(256, 4) void k_tensor_quant_one(OneTensor g) {
     __syncthreads();
     const bool decides = sh_last != 0u, open = !proven && (t.o.bf16 != nullptr || t.three != 0u);      // open: the decision may ask for one more store
     // What the decision asks for in one tile: the BF16 fallback (from the registers where they hold it), or the E5M2 payload.
-    auto chunk_off = [&](int64_t c, int64_t ld) -> int64_t {
-        if (t.rm.cpr == 0u) return tensor_chunk_off<true>(t, c, ld);
-        const uint32_t r = row_div(t.rm, (uint32_t)c);        // (an operand that comes here has fewer than 2^31 chunks)
-        return (int64_t)r * ld + (int64_t)((uint32_t)c - r * t.rm.cpr) * 8;
-    };
     auto finish_tile = [&](uint32_t mask, int tile, bool held) {
-        const bool fast = abits < fast_amax_limit(t.mode);
-        const float s5 = block_scale(abits, kE5M2Max, t.mode, group_mantissa_bits(abits, kE5M2Max, t.mode)), s_inv = FAKE ? 1.0f / s5 : 0.0f;
+        const bool fast5 = abits < fast_amax_limit(mode);
+        const float sc5 = block_scale(abits, kE5M2Max, mode, group_mantissa_bits(abits, kE5M2Max, mode)), inv5 = FAKE ? 1.0f / sc5 : 0.0f;
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            const int64_t c = (int64_t)tile * kTile + u * 256 + tid;
-            if (c >= t.n_chunks) continue;
+            const int64_t c = (int64_t)tile * kTile + first + u * 256;
+            if (c >= n_chunks) continue;
             const uint16_t* src = t.x + chunk_off(c, t.rm.ld);
-            if (mask == 2u) requant_chunk_e5m2(src, FAKE ? nullptr : t.o.fp8 + chunk_off(c, t.o.ld_fp8), FAKE ? t.o.fake + chunk_off(c, t.o.ld_fake) : nullptr, s5, s_inv, fast);
-            else if (t.o.bf16) store16(t.o.bf16 + chunk_off(c, t.o.ld_bf16), held && t.rm.cpr != 0u ? raw[u] : load16(src));
+            if (mask == 2u) requant_chunk_e5m2(src, FAKE ? nullptr : t.o.fp8 + chunk_off(c, t.o.ld_fp8), FAKE ? t.o.fake + chunk_off(c, t.o.ld_fake) : nullptr, sc5, inv5, fast5);
+            else if (t.o.bf16) store16(t.o.bf16 + chunk_off(c, t.o.ld_bf16), held ? raw[u] : load16(src));
         }
     };
     if (!decides) {
@@ -1596,20 +1735,31 @@ __global__ __launch_bounds__(256, 4) void k_tensor_quant_one(OneTensor g) {
         if (told != kToldMask) finish_tile(told - kToldMask, b, true);
         return;
     }
+    // (256 lanes, in the order of the finish pass of the grouped kernels)
     double se = 0.0, se5 = 0.0;
     unsigned long long sz = 0;
+    if (q == 0) {
 #pragma unroll
-    for (int k = 0; k < kOneMaxSlots / 256; ++k) {
-        const int i = tid + k * 256, ic = i < n_slots ? i : n_slots - 1;      // always a valid slot: the loads need no branch
-        const float ev = agent_load(t.err + ic), e5v = CRIT == kCritEq3 ? agent_load(t.err5 + ic) : 0.0f;
-        const uint32_t zv = agent_load(t.zero + ic);
-        se += i < n_slots ? (double)ev : 0.0; se5 += i < n_slots ? (double)e5v : 0.0; sz += i < n_slots ? zv : 0u;
+        for (int k = 0; k < kOneMaxSlots / 256; ++k) {
+            const int i = l + k * 256, ic = i < n_slots ? i : n_slots - 1;            // always a valid slot: the loads need no branch
+            const float ev = agent_load(t.err + ic), e5v = CRIT == kCritEq3 ? agent_load(t.err5 + ic) : 0.0f;
+            const uint32_t zv = agent_load(t.zero + ic);
+            se += i < n_slots ? (double)ev : 0.0; se5 += i < n_slots ? (double)e5v : 0.0; sz += i < n_slots ? zv : 0u;
+        }
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) {
+            se += __shfl_xor(se, m, 64);
+            if constexpr (CRIT == kCritEq3) se5 += __shfl_xor(se5, m, 64);
+            sz += __shfl_xor(sz, m, 64);
+        }
+        if (lane == 0) { shd[w] = se; shd[4 + w] = se5; shl[w] = sz; }
     }
-    se = block_sum_shfl<double>(se, shd);
-    sz = block_sum_shfl<unsigned long long>(sz, shl);
-    if constexpr (CRIT == kCritEq3) se5 = block_sum_shfl<double>(se5, shd);
-    const unsigned long long n_padded = (unsigned long long)t.n_tiles * kTile * 8;
-    const uint32_t mask = tensor_decide<CRIT>(t, g.near_tol, se, se5, n_padded - sz, abits, proven, true);
+    __syncthreads();
+    se = (shd[0] + shd[1]) + (shd[2] + shd[3]);
+    se5 = (shd[4] + shd[5]) + (shd[6] + shd[7]);
+    sz = (shl[0] + shl[1]) + (shl[2] + shl[3]);
+    const unsigned long long n_padded = (unsigned long long)n_slots * kTile * 8;
+    const uint32_t mask = tensor_decide<CRIT, T>(t, g.near_tol, se, se5, n_padded - sz, abits, proven, true);
     if (!open) return;
     if (tid < kToldCopies) agent_store(sync + kOneTold + tid * kOneLine, kToldMask + mask);
     if (mask == 0u) return;
@@ -1617,10 +1767,10 @@ __global__ __launch_bounds__(256, 4) void k_tensor_quant_one(OneTensor g) {
     wait_memory();
     if (tid < kOneMaxSlots / 32) sh_left[tid] = 0u;
     __syncthreads();                                           // (the decision has been told: the wave that stored it has waited)
-    for (int i = tid; i < n_slots; i += 256)
+    for (int i = tid; i < n_slots; i += T)
         if (agent_load(sync + kOneLeft + i) != 0u) atomicOr(&sh_left[i >> 5], 1u << (i & 31));
     __syncthreads();
-    unsigned long long some = __ballot((tid & 63) < kOneMaxSlots / 32 && sh_left[tid & (kOneMaxSlots / 32 - 1)] != 0u);
+    unsigned long long some = __ballot(lane < kOneMaxSlots / 32 && sh_left[lane & (kOneMaxSlots / 32 - 1)] != 0u);
     for (; some; some &= some - 1ull) {                        // 32 tiles each (the same in every wave)
         const int i0 = (__ffsll(some) - 1) * 32;
         for (uint32_t left = sh_left[i0 >> 5]; left; left &= left - 1u) finish_tile(mask, i0 + __ffs((int)left) - 1, false);
@@ -1790,10 +1940,10 @@ static hipError_t launch_sub1x128(const uint16_t* x, const KShape& sh, const KOu
 }
 
 // Fills the chunk layout of a per-tensor operand (or of the amax pass of one): rows of sh.ld elements, outputs as in o.
-static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o, int tile_chunks = kTensorChunksPerBlock) {
+static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o) {
     const int64_t cpr = sh.cols / 8;
     t.n_chunks = sh.rows * cpr;
-    t.n_tiles = (t.n_chunks + tile_chunks - 1) / tile_chunks;
+    t.n_tiles = (t.n_chunks + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
     t.chunks_per_row = cpr;
     t.keep_from = keep_for_second_pass(sh) ? 0 : t.n_tiles;
     t.rm = RowMap{};
@@ -2340,39 +2490,54 @@ void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_p
         else k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
     }
 }
-// A small operand that is alone: two passes over tiles of two chunks per lane, or four from one_mid_chunks on, from a table of one
-// operand.  Such a call is a chain of launches, so what counts is their number, what the host spends on each (3.8 KB of kernel
-// arguments for a table of eight operands and the statistics' riders, 0.4 KB here) and the depth of a workgroup's work.  us per call, here /
-// with the three launches that larger operands take: dense 64 x 256 9.9 / 13.4, 1024 x 1024 10.8 / 14.4, 1024 x 4096 13.4 / 15.6,
-// 2048 x 4096 16.2 / 18.4 (kept in E4M3); kept in BF16 without a proof 11.6 / 16.0, 14.7 / 18.4, 20.0 / 22.4.  Two and four chunks
-// per lane: 10.8 and 11.5 at 1024 x 1024, 12.1 and 12.6 at 768 x 4096, 15.5 and 14.7 at 1024 x 4096 kept in BF16.
-// A tile per workgroup, and workgroups that wait to be told: 1024 at most under Eq. 2, of the 1792 that the kernel's registers let be
-// resident, and 512 under Eq. 3, of 1024.
-constexpr int64_t one_max_chunks(int crit) { return crit == kCritEq3 ? 1 << 19 : 1 << 20; }
-constexpr int64_t one_mid_chunks(int crit) { return crit == kCritEq3 ? (1 << 18) + 1 : 1 << 19; }
-static_assert(one_max_chunks(kCritEq2) <= (int64_t)kOneMaxSlots * 256 * kMidChunksPerThread && one_mid_chunks(kCritEq2) <= (int64_t)kOneMaxSlots * 256 * kSmallChunksPerThread,
+// A small operand that is alone: two launches from a table of one operand.  Such a call is a chain of launches, so what counts is their
+// number, what the host spends on each (3.8 KB of kernel arguments for a table of eight operands and the statistics' riders, 0.4 KB
+// here) and the depth of a workgroup's work.  The workgroups wait to be told, so at most half of those that the registers let be
+// resident together are launched.
+// us per call, here / with the three launches that larger operands take: dense, kept in E4M3, 64 x 256 10.2 / 13.4, 1024 x 1024
+// 11.5 / 14.1, 1024 x 4096 13.9 / 15.5, 2048 x 4096 17.0 / 18.4; kept in BF16 without a proof (Eq. 3) 13.1 / 15.9 and 15.5 / 18.4; padded
+// rows 256 x 4096 10.2 / 11.7, 2048 x 4096 17.2 / 18.8.  Dense with four lanes to a grouped lane's chunks 11.8 instead of 11.1 at 1024 x 1024.
+// (4096 x 4096, beyond: three launches, 23.1.)
+constexpr int64_t one_max_chunks(int crit) { return crit == kCritEq3 ? 1 << 19 : 1 << 20; }      // (Eq. 3 with eight chunks per lane does not fit the registers)
+constexpr int64_t kOnePadded2 = 1 << 18, kOneShared = 1 << 19;
+static_assert(kOnePadded2 <= (int64_t)kOneMaxSlots * 512 && kOneShared <= (int64_t)kOneMaxSlots * 1024 && one_max_chunks(kCritEq2) <= (int64_t)kOneMaxSlots * 2048,
               "a slot per tile");
-template <int CRIT, bool FAKE>
-void launch_one_quant(const OneTensor& o, int slots, bool mid, hipStream_t st) {
-    if (mid) k_tensor_quant_one<CRIT, FAKE, kMidChunksPerThread><<<dim3(slots), dim3(256), 0, st>>>(o);
-    else k_tensor_quant_one<CRIT, FAKE, kSmallChunksPerThread><<<dim3(slots), dim3(256), 0, st>>>(o);
+struct OneShape {
+    int lanes, chunks;
+};
+OneShape one_shape(int64_t n_chunks, bool dense) {
+    if (n_chunks > kOneShared) return {256, 8};
+    if (dense) return {512, 4};
+    return {256, n_chunks <= kOnePadded2 ? 2 : 4};
 }
-void launch_one_tensor(const GroupTensor& g, int a_end, int s_end, bool mid, int crit, bool fake, hipStream_t st, KProf* prof) {
+template <int CRIT, bool FAKE>
+void launch_one_quant(const OneTensor& o, const OneShape& s, int slots, hipStream_t st) {
+    const dim3 grid(slots), block(s.lanes);
+    if (s.lanes == 512) k_tensor_quant_one<CRIT, FAKE, 512, 4><<<grid, block, 0, st>>>(o);
+    else if (s.chunks == 2) k_tensor_quant_one<CRIT, FAKE, 256, 2><<<grid, block, 0, st>>>(o);
+    else if (CRIT == kCritEq3 || s.chunks == 4) k_tensor_quant_one<CRIT, FAKE, 256, 4><<<grid, block, 0, st>>>(o);
+    else if constexpr (CRIT == kCritEq2) k_tensor_quant_one<CRIT, FAKE, 256, 8><<<grid, block, 0, st>>>(o);
+}
+void launch_one_tensor(const TensorOp& t, float near_tol, int crit, bool fake, hipStream_t st, KProf* prof) {
     OneTensor o;
-    o.n = 1; o.near_tol = g.near_tol; o.op[0] = g.op[0];
-    o.amax_end[0] = a_end; o.slot_end[0] = s_end; o.copy_end[0] = 0;
-    {
-        ProfScope ps(prof, kKernTensorAmax, st);
-        if (mid) k_tensor_amax_one<kMidChunksPerThread><<<dim3(a_end), dim3(256), 0, st>>>(o);
-        else k_tensor_amax_one<kSmallChunksPerThread><<<dim3(a_end), dim3(256), 0, st>>>(o);
-    }
+    o.n = 1; o.near_tol = near_tol; o.op[0] = t;
+    const OneShape s = one_shape(t.n_chunks, (t.flags & kTensorReport) != 0u);
+    const int slots = (int)((t.n_chunks + s.lanes * s.chunks - 1) / (s.lanes * s.chunks));
+    TensorOp& a = o.op[0];
+    a.n_tiles = (a.n_chunks + 256 * kSmallChunksPerThread - 1) / (256 * kSmallChunksPerThread);      // pass A's tiles
+    a.n_amax = (int)(a.n_tiles < kAmaxOneTile ? a.n_tiles : kAmaxOneTile);
+    a.keep_from = 0;
+    a.n_slots = slots;
+    o.amax_end[0] = a.n_amax; o.slot_end[0] = slots; o.copy_end[0] = 0;
+    { ProfScope ps(prof, kKernTensorAmax, st); k_tensor_amax_one<<<dim3(a.n_amax), dim3(256), 0, st>>>(o); }
+    a.n_tiles = slots;
     ProfScope ps(prof, kKernTensorQuant, st);
     if (fake) {
-        if (crit == kCritEq3) launch_one_quant<kCritEq3, true>(o, s_end, mid, st);
-        else launch_one_quant<kCritEq2, true>(o, s_end, mid, st);
+        if (crit == kCritEq3) launch_one_quant<kCritEq3, true>(o, s, slots, st);
+        else launch_one_quant<kCritEq2, true>(o, s, slots, st);
     } else {
-        if (crit == kCritEq3) launch_one_quant<kCritEq3, false>(o, s_end, mid, st);
-        else launch_one_quant<kCritEq2, false>(o, s_end, mid, st);
+        if (crit == kCritEq3) launch_one_quant<kCritEq3, false>(o, s, slots, st);
+        else launch_one_quant<kCritEq2, false>(o, s, slots, st);
     }
 }
 void BatchRun::per_tensor_operands(int crit) {
@@ -2386,16 +2551,14 @@ void BatchRun::per_tensor_operands(int crit) {
             if (cnt == 0 || err != hipSuccess) { cnt = 0; return; }
             GroupTensor g; g.n = cnt; g.near_tol = near_tol;
             const bool ride = !riders_used && n_stats_groups > 0;
-            const KShape& sh0 = items[idx[0]].sh;
-            const int64_t chunks0 = sh0.rows * (sh0.cols / 8);
-            const bool one = cnt == 1 && !ride && chunks0 <= one_max_chunks(crit), mid = chunks0 >= one_mid_chunks(crit);
+            const bool one = cnt == 1 && !ride && items[idx[0]].sh.rows * (items[idx[0]].sh.cols / 8) <= one_max_chunks(crit);
             int64_t all_tiles = 0;
             for (int k = 0; k < cnt; ++k) {
                 const BatchItem& it = items[idx[k]];
                 TensorOp& t = g.op[k];
                 t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u; 
                 t.flags = strided ? 0u : (it.lean ? kTensorLean : 0u) | kTensorReport;      // (padded rows always get their payload, and report no proof)
-                set_tensor_layout(t, it.sh, it.o, one ? 256 * (mid ? kMidChunksPerThread : kSmallChunksPerThread) : kTensorChunksPerBlock);
+                set_tensor_layout(t, it.sh, it.o);
                 all_tiles += t.n_tiles;
                 const TensorPlan pl = plan_tensor(it.sh.rows, it.sh.cols);
                 char* w = carve(pl.bytes);
@@ -2430,7 +2593,7 @@ void BatchRun::per_tensor_operands(int crit) {
                 // layer with its six gradients 408 us, 414 at 768 and 1536).
                 const bool solo = last - first == 1 && total_tiles <= 2000ll * kSoloQuantBlocks;
                 // Up to kAmaxOneTile tiles, and what fits the chip at once in pass B, a workgroup takes one tile.
-                const int amax_cap = one || total_tiles <= kAmaxOneTile ? kAmaxOneTile : kMaxAmaxBlocks;
+                const int amax_cap = total_tiles <= kAmaxOneTile ? kAmaxOneTile : kMaxAmaxBlocks;
                 const int quant_cap = !solo ? kMaxQuantBlocks : (total_tiles <= kQuantOneTile ? kQuantOneTile : kSoloQuantBlocks);
                 TensorPart& p = parts[n_parts++];
                 p.lds = solo ? 0 : kResidency3;
@@ -2455,7 +2618,7 @@ void BatchRun::per_tensor_operands(int crit) {
                 ride_final = ride_partial > riders.n ? riders.n : 0;      // single-workgroup operands are final already
                 riders_used = true;
             }
-            if (one) launch_one_tensor(g, a_end, s_end, mid, crit, fake, st, prof);
+            if (one) launch_one_tensor(g.op[0], near_tol, crit, fake, st, prof);
             else if (strided) launch_tensor_passes<true>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             else launch_tensor_passes<false>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             cnt = 0;

@@ -29,6 +29,27 @@ def test_lone_small_operand(rows, cols, kind, crit, th):
         parity.compare_fake(x, "tensor", crit=crit, threshold=th)
 
 
+@pytest.mark.parametrize("rows, cols", [(9, 456), (512, 128), (1024, 2056), (1025, 4096)])
+@pytest.mark.parametrize("kind, crit", [("normal", "mean_rel_err"), ("grad", "e4m3_vs_e5m2"), ("large", "e4m3_vs_e5m2")])
+def test_alone_as_in_a_batch(rows, cols, kind, crit):
+    """Dense operands give the same bits alone as beside another one, in whose call the kernels for several operands take them."""
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    x = W.gradient(rows, -(-cols // 128) * 128, 6)[:, :cols].copy() if kind == "grad" else W.outlier_normal(rows, cols, 6)
+    if kind == "large":
+        x[0, 3] = 0x4D00
+    xd = torch.from_numpy(x.view(np.int16)).to(dev)
+    p = B.make_params(rows, cols, "tensor", crit=crit)
+    alone, beside, other = (B.alloc_outputs(p, dev, bf16_fill=0) for _ in range(3))
+    B.mor_analyze_quantize(p, xd, alone)
+    items = B.make_batch([(p, xd, beside, None), (p, xd.clone(), other, None)])
+    ws = torch.empty(B.mor_batch_workspace_bytes(items), dtype=torch.uint8, device=dev)
+    B.mor_analyze_quantize_batch(items, 1e-5, ws)
+    torch.cuda.synchronize()
+    for k in ("fp8", "bf16", "scale", "amax", "err_sum", "nnz", "mask") + (("err5_sum",) if alone.err5_sum is not None else ()):
+        assert torch.equal(getattr(alone, k), getattr(beside, k)), k
+
+
 @pytest.mark.parametrize("rows, cols, ld", [(513, 128, 128), (1024, 2056, 2064)])
 def test_three_types(rows, cols, ld):
     import parity
