@@ -529,9 +529,8 @@ __global__ __launch_bounds__(256) void k_block_amax_prove(GroupProve g) {
 // backward GEMMs, Section 4) and per-channel columns (Section 4.1.1 "Per-Channel", second operand).
 // A workgroup sweeps a strip of 128-row x 128-column tiles; a lane holds 8 rows x 8 columns of a tile
 // and keeps per-column scalars.  Per-channel columns span all strips, so they take three passes:
-//   kColAmax      column amax of the strip                     -> workspace partials
-//   (combine)     column amax, scales                          -> outputs + workspace scales
-//   kColExternal  quantize with those scales, strip error sums -> workspace partials
+//   kColAmax      column amax of the strip                                              -> workspace partials
+//   kColExternal  column amax over the strips, scales; quantize, strip error sums -> workspace partials
 //   (combine)     column error sums, decision, fallback columns
 // 128 x 1 sub-columns are complete inside a tile (kColLocal): one pass.
 // Proven columns (Eq. 2, two types, fallback buffer present): the amax pass also counts, per column, elements that are
@@ -557,11 +556,11 @@ struct ColOp {
     // per-channel columns: workspace, [n_strips x cols_padded] each, cols_padded = tiles_x * 128
     uint16_t* part_amax;
     float* part_err; float* part_err5; uint16_t* part_zero;
-    float* col_scale; float* col_scale5;                 // [cols_padded]
+    float* col_scale5;                                   // [cols_padded]
     uint16_t* col_amin;                                  // [cols_padded] (smallest non-zero pattern - 1), three-way recipe; its
                                                          // per-strip partials use part_zero, which is free until the quantize pass
-    uint8_t* col_proven;                                 // [cols_padded] 1: the column's BF16 decision is proven before the quantize
-                                                         // pass; the per-strip flush counts (16 bits) use part_err until then
+    uint8_t* col_proven;                                 // [cols_padded] 1: the column's BF16 decision is proven before it is quantized;
+                                                         // the per-strip flush counts (16 bits) use part_err5, which Eq. 2 leaves free
     uint32_t flush_need;                                 // that many certain flushes in a column prove its BF16 decision
     int32_t n_strips;
     int32_t copy_groups;                                 // workgroups per 128-column strip in the fallback-column pass
@@ -591,6 +590,7 @@ struct ColShared {
     uint16_t abits[128];         // column amax patterns of the tile
     uint8_t mask[128];
     uint32_t wg[8];              // per-wave amax / flush totals of a strip (column-amax pass)
+    unsigned long long fl[4];
 };
 
 // Combines a lane's 8 per-column values with the lanes that hold the same columns in the other row groups
@@ -622,6 +622,86 @@ __device__ __forceinline__ float colgroup_addf(float v) {
     return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
+// Per-channel columns: amax over the strips, scales (Algorithm 1) and proofs of the workgroup's 128 columns, left in shared memory
+// (abits, scale, scale5, and in mask whether the column is proven); the first strip's workgroups write them out as well.  Every
+// workgroup of the quantize pass does this for itself while its first tile is in flight, from figures that lie in the L2 cache: a
+// launch in between took 5.6 us of the 88 us of a linear layer's two operands (8192 x 4096 per-channel rows, 4096 x 6144 columns).
+// Under GAM the group amax of Algorithm 1 is the largest column amax, and for a tensor-level decision the certain flushes of all
+// columns together may prove it: the same values in every workgroup, from the per-workgroup figures of the amax pass.
+template <int CRIT>
+__device__ __forceinline__ void col_scales(const ColOp& t, int64_t strip, int64_t c0, int64_t unit, ColShared& sh) {
+    const int tid = threadIdx.x, w = tid >> 6, cc = tid & 127, half = tid >> 7;
+    const int64_t cols_padded = t.tiles_x * 128;
+    const int n_wg = (int)(t.n_strips * t.tiles_x);        // workgroups of the amax pass
+    const bool whole = t.prove && t.tensor_need != 0ull;
+    const uint16_t* __restrict__ part_flush = reinterpret_cast<const uint16_t*>(t.part_err5);
+    // two threads per column, every other strip each
+    uint32_t a = 0u, fl = 0u;
+    for (int s0 = half; s0 < t.n_strips; s0 += 16) {
+        uint32_t av[8], fv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int sidx = s0 + 2 * u < t.n_strips ? s0 + 2 * u : s0;       // always a valid strip: the loads need no branch
+            av[u] = t.part_amax[sidx * cols_padded + c0 + cc];
+            fv[u] = t.prove && !whole ? (uint32_t)part_flush[sidx * cols_padded + c0 + cc] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { a = max(a, av[u]); fl += s0 + 2 * u < t.n_strips ? fv[u] : 0u; }
+    }
+    uint32_t ga = 0u;
+    unsigned long long f = 0ull;
+    if (t.derive_gam || whole) {                           // uniform over the workgroup
+        const uint2* __restrict__ figures = reinterpret_cast<const uint2*>(t.wg + 2);
+        for (int i0 = tid; i0 < n_wg; i0 += 4 * 256) {
+            uint2 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = figures[i0 + u * 256 < n_wg ? i0 + u * 256 : i0];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { ga = max(ga, v[u].x); f += i0 + u * 256 < n_wg ? v[u].y : 0u; }
+        }
+        ga = wave_allmax_u32(ga);
+        f = wave_allsum_u64(f);
+        if ((tid & 63) == 0) { sh.wg[w] = ga; sh.fl[w] = f; }
+    }
+    uint32_t* col_a = &sh.amax[0][0][0];
+    uint32_t* col_f = &sh.zero[0][0][0];
+    if (half) { col_a[cc] = a; col_f[cc] = fl; }
+    __syncthreads();
+    if (half) { __syncthreads(); return; }
+    uint32_t mg = 0u, mg5 = 0u;
+    if (t.derive_gam) {
+        ga = max(max(sh.wg[0], sh.wg[1]), max(sh.wg[2], sh.wg[3]));
+        mg = group_mantissa_bits(ga, kE4M3Max, t.mode);
+        mg5 = group_mantissa_bits(ga, kE5M2Max, t.mode);
+    }
+    const bool all_proven = whole && (sh.fl[0] + sh.fl[1]) + (sh.fl[2] + sh.fl[3]) >= t.tensor_need;
+    if (unit == 0 && tid == 0) {
+        if (t.derive_gam) {
+            uint32_t* gam_out = const_cast<uint32_t*>(t.gam);
+            gam_out[0] = mg; gam_out[1] = mg5;
+            if (t.gmant) { t.gmant[0] = mg; t.gmant[1] = mg5; }
+        }
+        if (whole) t.wg[0] = all_proven ? 1u : 0u;
+        if (t.mode == kScaleE8M0) zero_group_mantissa(t.gmant);
+    }
+    a = max(a, col_a[cc]);
+    fl += col_f[cc];
+    const int64_t c = c0 + cc;
+    const bool proven = t.prove && c < t.cols && (whole ? all_proven : fl >= t.flush_need);
+    const float s = block_scale(a, kE4M3Max, t.mode, mg), s5 = CRIT == kCritEq3 || t.three ? block_scale(a, kE5M2Max, t.mode, mg5) : 0.0f;
+    sh.scale[cc] = s; sh.scale5[cc] = s5; sh.abits[cc] = (uint16_t)a; sh.mask[cc] = proven ? 1 : 0;
+    if (strip == 0) {
+        t.col_scale5[c] = s5;
+        if (t.prove) t.col_proven[c] = proven ? 1 : 0;
+        if (c < t.cols) {
+            t.o.amax[c] = __uint_as_float(a << 16);
+            t.o.scale[c] = s;
+            if (t.mode != kScaleFp32 && t.o.e8m0) t.o.e8m0[c] = (uint8_t)(__float_as_uint(s) >> 23);
+        }
+    }
+    __syncthreads();
+}
+
 template <int CRIT, int MODE, bool FAKE, bool EDGE>
 __device__ __forceinline__ void col_strip(const ColOp& t, int64_t unit, ColShared& sh) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, cg = tid & 15;
@@ -645,38 +725,20 @@ __device__ __forceinline__ void col_strip(const ColOp& t, int64_t unit, ColShare
     bool strip_fast = true;
     uint32_t mn_strip[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};      // kColAmax with three types
     uint32_t bound2[4] = {0u, 0u, 0u, 0u}, flush2[4] = {0u, 0u, 0u, 0u};              // kColAmax with the flush-count proof
+    // ragged operands: bounds-checked buffer accesses relative to the tile origin (a lane outside loads zeros
+    // and stores nothing, without a branch)
     uint64_t pv8 = 0ull;                                                                // kColExternal: proven flags of my 8 columns
-    if constexpr (MODE == kColExternal) {
-        if (t.prove) pv8 = *reinterpret_cast<const uint64_t*>(t.col_proven + c0 + cg * 8);
-    }
-    if constexpr (MODE == kColExternal) {
-        bool f = true;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            s[k] = t.col_scale[c0 + cg * 8 + k];
-            s5[k] = CRIT == kCritEq3 ? t.col_scale5[c0 + cg * 8 + k] : 0.0f;
-            s_inv[k] = FAKE ? 1.0f / s[k] : 0.0f;
-            const uint32_t col_abits = col_ok ? __float_as_uint(o.amax[col + k]) >> 16 : 0u;
-            f = f && col_abits < fast_amax_limit(mode);
-        }
-        strip_fast = f;      // per lane: the careful path has no cross-lane step, so no barrier is needed before the loads
-    }
-    for (int tt = 0; tt < t.tiles_per_strip; ++tt) {
+    u32x4 raw[kChunks];
+    auto load_tile = [&](int tt) {
         const int64_t r0 = (strip * t.tiles_per_strip + tt) * 128;
-        if (r0 >= t.rows) break;                                       // uniform over the workgroup
         const int64_t row = r0 + (tid >> 4);
         const uint16_t* __restrict__ src = t.x + row * t.ld + col;
-        auto is_valid = [&](int i) -> bool {
-            if constexpr (EDGE) return col_ok && row + i * 16 < t.rows;
-            else return true;                                          // rows and cols are multiples of 128
-        };
-        // ragged operands: bounds-checked buffer accesses relative to the tile origin (a lane outside loads zeros
-        // and stores nothing, without a branch)
         const BufRsrc rx = make_buf(t.x + r0 * t.ld + c0);
         const uint32_t xoff = (uint32_t)(((tid >> 4) * t.ld + cg * 8) * 2), xstep = (uint32_t)(16 * t.ld * 2);
-        // (the next tile's loads are not started early: with 32 more registers fewer workgroups fit, and the quantize pass
-        // of the per-channel columns took 407 us instead of 396 us)
-        u32x4 raw[kChunks];
+        auto is_valid = [&](int i) -> bool {
+            if constexpr (EDGE) return col_ok && row + i * 16 < t.rows;
+            else return true;
+        };
         if (MODE == kColAmax && t.keep) {
 #pragma unroll
             for (int i = 0; i < kChunks; ++i) raw[i] = buf_load16_first<true>(rx, is_valid(i) ? xoff : kBufOutside, i * xstep);
@@ -687,6 +749,33 @@ __device__ __forceinline__ void col_strip(const ColOp& t, int64_t unit, ColShare
                 else raw[i] = load16(src + (int64_t)i * 16 * t.ld);
             }
         }
+    };
+    if constexpr (MODE == kColExternal) {
+        load_tile(0);                    // in flight while the scales are formed
+        col_scales<CRIT>(t, strip, c0, unit, sh);
+        bool f = true;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            s[k] = sh.scale[cg * 8 + k];
+            s5[k] = CRIT == kCritEq3 ? sh.scale5[cg * 8 + k] : 0.0f;
+            s_inv[k] = FAKE ? 1.0f / s[k] : 0.0f;
+            f = f && sh.abits[cg * 8 + k] < fast_amax_limit(mode);
+        }
+        strip_fast = f;      // per lane: the careful path has no cross-lane step
+        if (t.prove) pv8 = *reinterpret_cast<const uint64_t*>(&sh.mask[cg * 8]);
+    }
+    for (int tt = 0; tt < t.tiles_per_strip; ++tt) {
+        const int64_t r0 = (strip * t.tiles_per_strip + tt) * 128;
+        if (r0 >= t.rows) break;                                       // uniform over the workgroup
+        const int64_t row = r0 + (tid >> 4);
+        const uint16_t* __restrict__ src = t.x + row * t.ld + col;
+        auto is_valid = [&](int i) -> bool {
+            if constexpr (EDGE) return col_ok && row + i * 16 < t.rows;
+            else return true;                                          // rows and cols are multiples of 128
+        };
+        // (the next tile's loads are not started early: with 32 more registers fewer workgroups fit, and the quantize pass
+        // of the per-channel columns took 407 us instead of 396 us)
+        if (MODE != kColExternal || tt > 0) load_tile(tt);
         // one sweep over the chunks for everything that reads the magnitudes (column amax, zero counts, smallest
         // non-zero magnitude), so that no masked copy of the tile stays in registers
         uint32_t mn2[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
@@ -1001,7 +1090,7 @@ __device__ __forceinline__ void col_strip(const ColOp& t, int64_t unit, ColShare
             }
             t.part_amax[strip * cols_padded + c0 + tid] = (uint16_t)a;
             if (t.three) t.part_zero[strip * cols_padded + c0 + tid] = (uint16_t)mn;
-            if (t.prove) reinterpret_cast<uint16_t*>(t.part_err)[strip * cols_padded + c0 + tid] = (uint16_t)fl;
+            if (t.prove) reinterpret_cast<uint16_t*>(t.part_err5)[strip * cols_padded + c0 + tid] = (uint16_t)fl;
         }
         // the strip's largest column amax and its flush total, for the combine kernel's whole-operand figures
         // (group amax of Algorithm 1, tensor-level proof)
@@ -1044,87 +1133,34 @@ __device__ __forceinline__ void col_strip(const ColOp& t, int64_t unit, ColShare
 }
 
 template <int CRIT, int MODE, bool FAKE, bool EDGE>
-__global__ __launch_bounds__(256) void k_col_group(GroupCol g) {
+__device__ __forceinline__ void col_group_body(const GroupCol& g) {
     __shared__ ColShared sh;
     const int op = group_find(g.unit_end, g.n, blockIdx.x);
     const ColOp& t = g.op[op];
     const int64_t unit = (int64_t)blockIdx.x - (op ? g.unit_end[op - 1] : 0);
     col_strip<CRIT, MODE, FAKE, EDGE>(t, unit, sh);
 }
+template <int CRIT, int MODE, bool FAKE, bool EDGE>
+__global__ __launch_bounds__(256) void k_col_group(GroupCol g) { col_group_body<CRIT, MODE, FAKE, EDGE>(g); }
+// (the bound keeps Eq. 3's variants with ragged edges at the four workgroups per compute unit that the launch asks for)
+template <int CRIT, bool FAKE, bool EDGE>
+__global__ __launch_bounds__(256, 4) void k_col_quant_group(GroupCol g) { col_group_body<CRIT, kColExternal, FAKE, EDGE>(g); }
 
-// Per-channel columns, first combine: column amax over the strips -> amax, scale (Algorithm 1), E8M0 byte.
-// Under GAM every workgroup first takes the largest column amax of the operand (the group amax of Algorithm 1), and for a tensor-level decision the sum of all columns' certain flushes: the same values in every
-// workgroup, from the per-workgroup figures of the amax pass (a handful of loads per thread).
-__global__ __launch_bounds__(256) void k_col_scales(GroupCol g) {
-    __shared__ uint32_t sh4[4];
-    __shared__ unsigned long long shl[4];
+// Per-channel columns, three-way recipe: smallest non-zero magnitude of the columns over the strips.  (A launch of its own: the
+// quantize pass writes over the strips' figures.)
+__global__ __launch_bounds__(256) void k_col_amin(GroupCol g) {
     const int op = group_find32(g.comb_end, g.n, blockIdx.x);
     const ColOp& t = g.op[op];
-    const int b = blockIdx.x - (op ? g.comb_end[op - 1] : 0);
-    const int tid = threadIdx.x;
-    const int64_t c = (int64_t)b * 256 + tid;
+    if (!t.three) return;
+    const int64_t c = (int64_t)(blockIdx.x - (op ? g.comb_end[op - 1] : 0)) * 256 + threadIdx.x;
     const int64_t cols_padded = t.tiles_x * 128;
-    const int64_t n_wg = (int64_t)t.n_strips * t.tiles_x;  // workgroups of the amax pass
-    uint32_t mg = 0u, mg5 = 0u;
-    if (t.derive_gam) {                                    // GAM (uniform over the workgroup)
-        uint32_t ga = 0u;
-        for (int64_t i = tid; i < n_wg; i += 256) ga = max(ga, t.wg[2 + 2 * i]);
-        ga = wave_allmax_u32(ga);
-        if ((tid & 63) == 0) sh4[tid >> 6] = ga;
-        __syncthreads();
-        ga = max(max(sh4[0], sh4[1]), max(sh4[2], sh4[3]));
-        mg = group_mantissa_bits(ga, kE4M3Max, t.mode);
-        mg5 = group_mantissa_bits(ga, kE5M2Max, t.mode);
-        if (b == 0 && tid == 0) {
-            uint32_t* gam_out = const_cast<uint32_t*>(t.gam);
-            gam_out[0] = mg; gam_out[1] = mg5;
-            if (t.gmant) { t.gmant[0] = mg; t.gmant[1] = mg5; }
-        }
-    }
-    bool all_proven = false;
-    if (t.prove && t.tensor_need) {                        // uniform over the workgroup
-        unsigned long long f = 0ull;
-        for (int64_t i = tid; i < n_wg; i += 256) f += t.wg[3 + 2 * i];
-#pragma unroll
-        for (int m = 32; m > 0; m >>= 1) f += __shfl_xor(f, m, 64);
-        if ((tid & 63) == 0) shl[tid >> 6] = f;
-        __syncthreads();
-        f = (shl[0] + shl[1]) + (shl[2] + shl[3]);
-        all_proven = f >= t.tensor_need;
-        if (b == 0 && tid == 0) t.wg[0] = all_proven ? 1u : 0u;
-    }
     if (c >= cols_padded) return;
-    uint32_t a = 0u;
+    uint32_t mn = 0xFFFFu;
 #pragma unroll 8
-    for (int sidx = 0; sidx < t.n_strips; ++sidx) a = max(a, (uint32_t)t.part_amax[sidx * cols_padded + c]);
-    if (t.three) {
-        uint32_t mn = 0xFFFFu;
-#pragma unroll 8
-        for (int sidx = 0; sidx < t.n_strips; ++sidx) mn = min(mn, (uint32_t)t.part_zero[sidx * cols_padded + c]);
-        t.col_amin[c] = (uint16_t)mn;
-    }
-    if (t.prove) {
-        if (t.tensor_need) {
-            t.col_proven[c] = (c < t.cols && all_proven) ? 1 : 0;
-        } else {
-            const uint16_t* __restrict__ part_flush = reinterpret_cast<const uint16_t*>(t.part_err);
-            uint32_t fl = 0u;
-#pragma unroll 8
-            for (int sidx = 0; sidx < t.n_strips; ++sidx) fl += part_flush[sidx * cols_padded + c];
-            t.col_proven[c] = (c < t.cols && fl >= t.flush_need) ? 1 : 0;
-        }
-    }
-    const float s = block_scale(a, kE4M3Max, t.mode, mg);
-    t.col_scale[c] = s;
-    t.col_scale5[c] = block_scale(a, kE5M2Max, t.mode, mg5);
-    if (c < t.cols) {
-        t.o.amax[c] = __uint_as_float(a << 16);
-        t.o.scale[c] = s;
-        if (t.mode != kScaleFp32 && t.o.e8m0) t.o.e8m0[c] = (uint8_t)(__float_as_uint(s) >> 23);
-        if (t.mode == kScaleE8M0 && c == 0) zero_group_mantissa(t.gmant);
-    }
+    for (int sidx = 0; sidx < t.n_strips; ++sidx) mn = min(mn, (uint32_t)t.part_zero[sidx * cols_padded + c]);
+    t.col_amin[c] = (uint16_t)mn;
 }
-// Second combine: column error sums over the strips (binary64, fixed order), non-zero counts, decision.
+// Combine: column error sums over the strips (binary64, fixed order), non-zero counts, decision.
 template <int CRIT>
 __global__ __launch_bounds__(256) void k_col_finish(GroupCol g) {
     const int op = group_find32(g.comb_end, g.n, blockIdx.x);
@@ -1392,9 +1428,16 @@ void fill_col_op(ColOp& t, const BatchItem& it, const uint32_t* gam) {
 template <int MODE, bool FAKE, bool EDGE>
 void launch_col_crit(const GroupCol& g, int64_t total, int crit, hipStream_t st) {
     const dim3 grid((unsigned)total), block(256);
-    const int lds = MODE == kColExternal ? kResidency4 : 0;      // 0.609 ms per twelve-operand pass at 4 per unit, 0.620 uncapped
-    if (crit == kCritEq3) k_col_group<kCritEq3, MODE, FAKE, EDGE><<<grid, block, lds, st>>>(g);
-    else k_col_group<kCritEq2, MODE, FAKE, EDGE><<<grid, block, lds, st>>>(g);
+    if constexpr (MODE == kColExternal) {
+        const int lds = kResidency4;      // 0.609 ms per twelve-operand pass at 4 per unit, 0.620 uncapped
+        if (crit == kCritEq3) k_col_quant_group<kCritEq3, FAKE, EDGE><<<grid, block, lds, st>>>(g);
+        else k_col_quant_group<kCritEq2, FAKE, EDGE><<<grid, block, lds, st>>>(g);
+    } else if constexpr (MODE == kColAmax) {
+        k_col_group<kCritEq2, MODE, false, EDGE><<<grid, block, 0, st>>>(g);
+    } else {
+        if (crit == kCritEq3) k_col_group<kCritEq3, MODE, FAKE, EDGE><<<grid, block, 0, st>>>(g);
+        else k_col_group<kCritEq2, MODE, FAKE, EDGE><<<grid, block, 0, st>>>(g);
+    }
 }
 template <int MODE>
 void launch_col_kind(const GroupCol& g, int64_t total, int crit, bool fake, bool edge, hipStream_t st) {
@@ -1465,7 +1508,9 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
                 g.copy_end[k] = copy;
             }
             { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColAmax>(g, total, kCritEq2, false, edge, st); }
-            { ProfScope ps(prof, kKernColumnCombine, st); k_col_scales<<<dim3((unsigned)comb), dim3(256), 0, st>>>(g); }
+            bool three = false;
+            for (int k = 0; k < g.n; ++k) three |= g.op[k].three != 0;
+            if (three) { ProfScope ps(prof, kKernColumnCombine, st); k_col_amin<<<dim3((unsigned)comb), dim3(256), 0, st>>>(g); }
             { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColExternal>(g, total, crit, fake, edge, st); }
             {
                 ProfScope ps(prof, kKernColumnCombine, st);
@@ -1494,7 +1539,6 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
             t.part_err = reinterpret_cast<float*>(w + pl.off_err);
             t.part_err5 = reinterpret_cast<float*>(w + pl.off_err5);
             t.part_zero = reinterpret_cast<uint16_t*>(w + pl.off_zero);
-            t.col_scale = reinterpret_cast<float*>(w + pl.off_scale);
             t.col_scale5 = reinterpret_cast<float*>(w + pl.off_scale5);
             t.col_amin = reinterpret_cast<uint16_t*>(w + pl.off_amin);
             t.col_proven = reinterpret_cast<uint8_t*>(w + pl.off_proven);
