@@ -529,34 +529,88 @@ __device__ __forceinline__ unsigned long long block_elems(const StatsGeom& g, in
     const int64_t w = g.cols - bc * g.pc < g.pc ? g.cols - bc * g.pc : g.pc;
     return (unsigned long long)(h * w);
 }
-struct StatsAcc {
+// What a wave has counted: the counters are the same in all its lanes (ballots: no lane-by-lane counters to be summed afterwards), the
+// sums are each lane's own until stats_reduce.  These kernels are chains of latencies: with fifteen counters per lane summed over the
+// waves twice, a lone 1024 x 4096 operand of 128 x 128 blocks took 10.8 us per call with statistics, 9.3 now (64 x 64 13.7 / 11.6,
+// 128 x 1 24.6 / 20.9).
+struct StatsTally {
     double e;
     unsigned long long n, eb, e5;        // non-zeros; elements in BF16 blocks; elements in E5M2 blocks
-    uint32_t cnt[kStatCnt];
+    uint32_t c[kStatCnt];
 };
-__device__ __forceinline__ void stats_acc_clear(StatsAcc& a) {
+__device__ __forceinline__ void tally_clear(StatsTally& a) {
     a.e = 0.0; a.n = 0ull; a.eb = 0ull; a.e5 = 0ull;
 #pragma unroll
-    for (int k = 0; k < kStatCnt; ++k) a.cnt[k] = 0u;
+    for (int k = 0; k < kStatCnt; ++k) a.c[k] = 0u;
 }
-__device__ __forceinline__ void stats_accumulate(int64_t p, const float* __restrict__ err_sum, const uint32_t* __restrict__ nnz,
-                                                 const uint8_t* __restrict__ mask, float th, float near_tol, const StatsGeom& geom,
-                                                 StatsAcc& a) {
-    const float es = err_sum[p];
-    const uint32_t nz = nnz[p];
-    const uint32_t mk = mask[p];
+// One block per lane; all lanes of the wave call (`ok`: this lane has a block).  `elems()` gives the block's elements.
+template <class F>
+__device__ __forceinline__ void tally(bool ok, float es, uint32_t nz, uint32_t mk, F elems, float th, float near_tol, StatsTally& a) {
     const float metric = nz ? es / (float)nz : 0.0f;           // binary32, IEEE division
-    const int bin = stats_bin(metric);
+    const float m = metric < __builtin_inff() ? metric : __builtin_inff();                // (NaN counts in the last bin, as in stats_bin)
+    uint32_t at_least = (uint32_t)__popcll(__ballot(ok));
 #pragma unroll
-    for (int k = 0; k < 12; ++k) a.cnt[k] += (bin == k) ? 1u : 0u;
-    a.e += (double)es;
-    a.n += nz;
-    a.cnt[12] += mk == 1u ? 1u : 0u;
-    a.cnt[13] += (fabs((double)metric - (double)th) <= (double)near_tol * (double)th) ? 1u : 0u;
-    a.cnt[14] += mk == 2u ? 1u : 0u;
-    if (mk) {
-        const unsigned long long ne = block_elems(geom, p);
-        if (mk == 1u) a.eb += ne; else a.e5 += ne;
+    for (int k = 1; k <= 11; ++k) {
+        const uint32_t v = (uint32_t)__popcll(__ballot(ok && m >= (float)(0.005 * k)));
+        a.c[k - 1] += at_least - v;
+        at_least = v;
+    }
+    a.c[11] += at_least;
+    a.c[12] += (uint32_t)__popcll(__ballot(ok && mk == 1u));
+    a.c[13] += (uint32_t)__popcll(__ballot(ok && fabs((double)metric - (double)th) <= (double)near_tol * (double)th));
+    a.c[14] += (uint32_t)__popcll(__ballot(ok && mk == 2u));
+    if (ok) {
+        a.e += (double)es;
+        a.n += nz;
+        if (mk == 1u) a.eb += elems();
+        if (mk == 2u) a.e5 += elems();
+    }
+}
+// `n` blocks from p0 on, step `stride` (a multiple of 64) per round of the workgroup's lanes; four blocks' loads in flight per lane.
+__device__ __forceinline__ void tally_blocks(const float* __restrict__ err_sum, const uint32_t* __restrict__ nnz, const uint8_t* __restrict__ mask,
+                                             int64_t first, int64_t stride, int64_t n_part, const StatsGeom& geom, float th, float near_tol, StatsTally& a) {
+    const int lane = threadIdx.x & 63;
+    for (int64_t base = first + (threadIdx.x - lane); base < n_part; base += 4 * stride) {      // uniform over the wave
+        float es[4]; uint32_t nz[4], mk[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t p = base + lane + u * stride, pc = p < n_part ? p : n_part - 1;        // always a valid block: the loads need no branch
+            es[u] = err_sum[pc]; nz[u] = nnz[pc]; mk[u] = mask[pc];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (base + u * stride >= n_part) break;            // uniform over the wave
+            const int64_t p = base + lane + u * stride;
+            tally(p < n_part, es[u], nz[u], mk[u], [&] { return block_elems(geom, p); }, th, near_tol, a);
+        }
+    }
+}
+template <int WAVES>
+struct StatsLds {
+    uint32_t c[WAVES][16];
+    double e[WAVES];
+    unsigned long long n[WAVES], eb[WAVES], e5[WAVES];
+};
+// Sums over the workgroup (one barrier, fixed order): the totals arrive in wave 0's lanes, counter k in lane k's `mine`.
+template <int WAVES>
+__device__ __forceinline__ void stats_reduce(StatsTally& a, uint32_t& mine, StatsLds<WAVES>& sh) {
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    a.e = wave_allsum_f64(a.e); a.n = wave_allsum_u64(a.n);
+    const bool kept = (a.c[12] | a.c[14]) != 0u;               // uniform over the wave
+    if (kept) { a.eb = wave_allsum_u64(a.eb); a.e5 = wave_allsum_u64(a.e5); }
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < kStatCnt; ++k) sh.c[w][k] = a.c[k];
+        sh.e[w] = a.e; sh.n[w] = a.n; sh.eb[w] = a.eb; sh.e5[w] = a.e5;
+    }
+    __syncthreads();
+    mine = 0u;
+    a.e = 0.0; a.n = 0ull; a.eb = 0ull; a.e5 = 0ull;
+    if (w != 0) return;
+#pragma unroll
+    for (int k = 0; k < WAVES; ++k) {
+        mine += sh.c[k][lane < kStatCnt ? lane : 0];
+        a.e += sh.e[k]; a.n += sh.n[k]; a.eb += sh.eb[k]; a.e5 += sh.e5[k];
     }
 }
 __device__ __forceinline__ void stats_finish(StatsDev* st, int64_t n_part, unsigned long long total_elems, double e,
@@ -576,31 +630,14 @@ __device__ __forceinline__ void stats_finish(StatsDev* st, int64_t n_part, unsig
     st->reserved = flags;
     st->reserved2 = 0u;
 }
-// Block-wide sums of the small counters without same-address atomics: DPP wave sums, one LDS row per
-// wave, then kStatCnt lanes add the four rows.  Result in sh[0][*].
-__device__ __forceinline__ void block_counts(const uint32_t (&v)[kStatCnt], uint32_t (*sh)[kStatCnt]) {
-    const int w = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < kStatCnt; ++k) {
-        const uint32_t s = wave_allsum_u32(v[k]);
-        if ((threadIdx.x & 63) == 0) sh[w][k] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x < kStatCnt) sh[0][threadIdx.x] = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
-    __syncthreads();
-}
-struct StatsShared {
-    uint32_t cnt[4][kStatCnt];
-    double d[4];
-    unsigned long long l[4];
-};
-// Reduces an accumulator over the workgroup: counters end in sh.cnt[0][*], the sums are returned in `a` on every thread.
-__device__ __forceinline__ void stats_block_reduce(StatsAcc& a, StatsShared& sh) {
-    block_counts(a.cnt, sh.cnt);
-    a.e = block_sum_shfl<double>(a.e, sh.d);            // fixed order: deterministic
-    a.n = block_sum_shfl<unsigned long long>(a.n, sh.l);
-    a.eb = block_sum_shfl<unsigned long long>(a.eb, sh.l);
-    a.e5 = block_sum_shfl<unsigned long long>(a.e5, sh.l);
+// Counter `k` of the totals that stats_reduce has left in wave 0.
+__device__ __forceinline__ uint32_t stats_counter(uint32_t mine, int k) { return (uint32_t)__builtin_amdgcn_readlane((int)mine, k); }
+// Wave 0 writes the final statistics.
+__device__ __forceinline__ void stats_write(StatsDev* out, int64_t n_part, unsigned long long total_elems, const StatsTally& t, uint32_t mine) {
+    if (threadIdx.x >= 64) return;
+    if (threadIdx.x < 12) out->hist[threadIdx.x] = mine;
+    const uint32_t bf16 = stats_counter(mine, 12), near = stats_counter(mine, 13), e5m2 = stats_counter(mine, 14);
+    if (threadIdx.x == 0) stats_finish(out, n_part, total_elems, t.e, t.n, bf16, near, e5m2, t.eb, t.e5, 0u);
 }
 
 // Up to a few thousand blocks: one workgroup, no atomics on global memory, deterministic sums.
@@ -608,14 +645,13 @@ __global__ __launch_bounds__(256) void k_stats_single(int64_t n_part, StatsGeom 
                                                       const float* __restrict__ err_sum, const uint32_t* __restrict__ nnz,
                                                       const uint8_t* __restrict__ mask, float th, float near_tol,
                                                       StatsDev* __restrict__ st) {
-    __shared__ StatsShared sh;
-    StatsAcc a;
-    stats_acc_clear(a);
-    for (int64_t p = threadIdx.x; p < n_part; p += 256) stats_accumulate(p, err_sum, nnz, mask, th, near_tol, geom, a);
-    stats_block_reduce(a, sh);
-    if (threadIdx.x < 12) st->hist[threadIdx.x] = sh.cnt[0][threadIdx.x];
-    if (threadIdx.x == 0)
-        stats_finish(st, n_part, (unsigned long long)(geom.rows * geom.cols), a.e, a.n, sh.cnt[0][12], sh.cnt[0][13], sh.cnt[0][14], a.eb, a.e5, 0u);
+    __shared__ StatsLds<4> sh;
+    StatsTally a;
+    uint32_t mine;
+    tally_clear(a);
+    tally_blocks(err_sum, nnz, mask, 0, 256, n_part, geom, th, near_tol, a);
+    stats_reduce(a, mine, sh);
+    stats_write(st, n_part, (unsigned long long)(geom.rows * geom.cols), a, mine);
 }
 
 // Many blocks: the accumulators live in the output struct, cleared by a tiny kernel first and
@@ -627,20 +663,21 @@ __global__ __launch_bounds__(256) void k_stats_multi(int64_t n_part, StatsGeom g
                                                      const float* __restrict__ err_sum, const uint32_t* __restrict__ nnz,
                                                      const uint8_t* __restrict__ mask, float th, float near_tol,
                                                      StatsDev* __restrict__ st) {
-    __shared__ StatsShared sh;
-    StatsAcc a;
-    stats_acc_clear(a);
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < n_part; p += stride)
-        stats_accumulate(p, err_sum, nnz, mask, th, near_tol, geom, a);
-    stats_block_reduce(a, sh);
-    if (threadIdx.x < 12 && sh.cnt[0][threadIdx.x]) atomicAdd(&st->hist[threadIdx.x], sh.cnt[0][threadIdx.x]);
+    __shared__ StatsLds<4> sh;
+    StatsTally a;
+    uint32_t mine;
+    tally_clear(a);
+    tally_blocks(err_sum, nnz, mask, (int64_t)blockIdx.x * 256, (int64_t)gridDim.x * 256, n_part, geom, th, near_tol, a);
+    stats_reduce(a, mine, sh);
+    if (threadIdx.x >= 64) return;
+    if (threadIdx.x < 12 && mine) atomicAdd(&st->hist[threadIdx.x], mine);
+    const uint32_t bf16 = stats_counter(mine, 12), near = stats_counter(mine, 13), e5m2 = stats_counter(mine, 14);
     if (threadIdx.x == 0) {
         atomicAdd(&st->err_sum_total, a.e);
         atomicAdd(&st->nnz_total, a.n);
-        atomicAdd(&st->n_bf16_part, (unsigned long long)sh.cnt[0][12]);
-        atomicAdd(&st->n_near_threshold, (unsigned long long)sh.cnt[0][13]);
-        atomicAdd(&st->n_e5m2_part, (unsigned long long)sh.cnt[0][14]);
+        atomicAdd(&st->n_bf16_part, (unsigned long long)bf16);
+        atomicAdd(&st->n_near_threshold, (unsigned long long)near);
+        atomicAdd(&st->n_e5m2_part, (unsigned long long)e5m2);
         atomicAdd(&st->n_elem_bf16, a.eb);
         atomicAdd(&st->n_elem_e5m2, a.e5);
     }
@@ -700,181 +737,91 @@ struct GroupStats {
     float near_tol;
     StatsOp op[kMaxGroupStats];
 };
+// Wave 0 leaves the workgroup's record.
+__device__ __forceinline__ void stats_record(StatsRec* r, const StatsTally& t, uint32_t mine) {
+    if (threadIdx.x < kStatCnt) r->cnt[threadIdx.x] = mine;
+    if (threadIdx.x == 0) { r->e = t.e; r->n = t.n; r->eb = t.eb; r->e5 = t.e5; }
+}
+// Workgroup of T lanes: its share of an operand's blocks, into its record, or (the operand's only workgroup) the final statistics.
+template <int T>
 __device__ __forceinline__ void stats_partial_body(const GroupStats& g, int block) {
-    __shared__ StatsShared sh;
+    __shared__ StatsLds<T / 64> sh;
     const int op = group_find32(g.wg_end, g.n, block);
     const StatsOp& t = g.op[op];
     const int b = block - (op ? g.wg_end[op - 1] : 0);
     const int nb = g.wg_end[op] - (op ? g.wg_end[op - 1] : 0);
-    StatsAcc a;
-    stats_acc_clear(a);
-    for (int64_t p = (int64_t)b * 256 + threadIdx.x; p < t.n_part; p += (int64_t)nb * 256)
-        stats_accumulate(p, t.err_sum, t.nnz, t.mask, t.th, g.near_tol, t.geom, a);
-    stats_block_reduce(a, sh);
-    if (nb == 1) {      // the whole operand in one workgroup: write the result, no second pass needed
-        if (threadIdx.x < 12) t.out->hist[threadIdx.x] = sh.cnt[0][threadIdx.x];
-        if (threadIdx.x == 0)
-            stats_finish(t.out, t.n_part, (unsigned long long)(t.geom.rows * t.geom.cols), a.e, a.n, sh.cnt[0][12], sh.cnt[0][13],
-                         sh.cnt[0][14], a.eb, a.e5, 0u);
-        return;
-    }
-    StatsRec* r = t.rec + b;
-    if (threadIdx.x < kStatCnt) r->cnt[threadIdx.x] = sh.cnt[0][threadIdx.x];
-    if (threadIdx.x == 0) { r->e = a.e; r->n = a.n; r->eb = a.eb; r->e5 = a.e5; }
+    StatsTally a;
+    uint32_t mine;
+    tally_clear(a);
+    tally_blocks(t.err_sum, t.nnz, t.mask, (int64_t)b * T, (int64_t)nb * T, t.n_part, t.geom, t.th, g.near_tol, a);
+    stats_reduce(a, mine, sh);
+    if (nb == 1) stats_write(t.out, t.n_part, (unsigned long long)(t.geom.rows * t.geom.cols), a, mine);
+    else stats_record(t.rec + b, a, mine);
 }
-__device__ __forceinline__ void stats_final_body(const GroupStats& g, int op) {
-    __shared__ StatsShared sh;
-    const StatsOp& t = g.op[op];
-    const int nb = g.wg_end[op] - (op ? g.wg_end[op - 1] : 0);       // <= 256: one record per thread
-    if (nb == 1) return;                                             // already final
-    StatsAcc a;
-    stats_acc_clear(a);
-    if ((int)threadIdx.x < nb) {
-        const StatsRec& r = t.rec[threadIdx.x];
-        a.e = r.e; a.n = r.n; a.eb = r.eb; a.e5 = r.e5;
+// Sums of up to 256 records by a workgroup of 256 lanes.  Sixteen neighbouring lanes read a record together, eight bytes each (one line
+// per record; a record per lane would be a line per lane and load), and what is left of every quadword goes through shared memory.
+// Every thread may read the sums from `all` afterwards: the sum, three 64-bit counts, then pairs of counters.
+struct RecordSums {
+    unsigned long long part[16][16], all[16];
+};
+__device__ __forceinline__ unsigned long long row_allsum_u64(unsigned long long v) {
+    v += dpp_u64<kDppXor1>(v); v += dpp_u64<kDppXor2>(v); v += dpp_u64<kDppHalfMirror>(v); v += dpp_u64<kDppMirror>(v);
+    return v;
+}
+__device__ __forceinline__ double row_allsum_f64(double v) {
+    auto sh = [](double x, auto ctrl) { return __longlong_as_double((long long)dpp_u64<decltype(ctrl)::value>((unsigned long long)__double_as_longlong(x))); };
+    v += sh(v, std::integral_constant<int, kDppXor1>{}); v += sh(v, std::integral_constant<int, kDppXor2>{});
+    v += sh(v, std::integral_constant<int, kDppHalfMirror>{}); v += sh(v, std::integral_constant<int, kDppMirror>{});
+    return v;
+}
+__device__ __forceinline__ void sum_records(const StatsRec* __restrict__ rec, int n_rec, RecordSums& sh) {
+    const int tid = threadIdx.x, grp = tid >> 4, k = tid & 15;
+    const bool is_sum = k == 0;                                // (an error sum may be infinite: its bits are added as a double, never as integers)
+    unsigned long long n = 0ull;                               // a 64-bit count, or two counters side by side (no operand has 2^32 blocks)
+    double e = 0.0;
+    for (int i0 = grp; i0 < n_rec; i0 += 4 * 16) {
+        unsigned long long v[4];
 #pragma unroll
-        for (int k = 0; k < kStatCnt; ++k) a.cnt[k] = r.cnt[k];      // per-workgroup counts fit 32 bits
+        for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const unsigned long long*>(rec + (i0 + u * 16 < n_rec ? i0 + u * 16 : i0))[k];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool ok = i0 + u * 16 < n_rec;
+            n += ok ? v[u] : 0ull;
+            e += ok && is_sum ? __longlong_as_double((long long)v[u]) : 0.0;
+        }
     }
-    stats_block_reduce(a, sh);
-    if (threadIdx.x < 12) t.out->hist[threadIdx.x] = sh.cnt[0][threadIdx.x];
+    sh.part[grp][k] = is_sum ? (unsigned long long)__double_as_longlong(e) : n;
+    __syncthreads();
+    const unsigned long long v = sh.part[k][grp];              // sixteen lanes per quadword now
+    const unsigned long long c = row_allsum_u64(v);
+    const double f = row_allsum_f64(grp == 0 ? __longlong_as_double((long long)v) : 0.0);
+    if (k == 0) sh.all[grp] = grp == 0 ? (unsigned long long)__double_as_longlong(f) : c;
+    __syncthreads();
+}
+__device__ __forceinline__ uint32_t record_counter(const RecordSums& sh, int k) { return (uint32_t)(sh.all[4 + (k >> 1)] >> (32 * (k & 1))); }
+__device__ __forceinline__ void stats_final_body(const GroupStats& g, int op) {
+    __shared__ RecordSums sh;
+    const StatsOp& t = g.op[op];
+    const int nb = g.wg_end[op] - (op ? g.wg_end[op - 1] : 0);       // <= kStatsMaxWg = 256
+    if (nb == 1) return;                                             // already final
+    sum_records(t.rec, nb, sh);
+    if (threadIdx.x < 12) t.out->hist[threadIdx.x] = record_counter(sh, threadIdx.x);
     if (threadIdx.x == 0)
-        stats_finish(t.out, t.n_part, (unsigned long long)(t.geom.rows * t.geom.cols), a.e, a.n, sh.cnt[0][12], sh.cnt[0][13],
-                     sh.cnt[0][14], a.eb, a.e5, 0u);
+        stats_finish(t.out, t.n_part, (unsigned long long)(t.geom.rows * t.geom.cols), __longlong_as_double((long long)sh.all[0]), sh.all[1], record_counter(sh, 12),
+                     record_counter(sh, 13), record_counter(sh, 14), sh.all[2], sh.all[3], 0u);
 }
 
 // ---- statistics launches of their own (operands that found no per-tensor launch to ride on, e.g. a single sub-tensor
 //      operand): here the statistics are on the critical path of the call, so the kernels are built for latency --
-//      workgroups of 1024 lanes, every lane's loads in flight together, the fifteen small counters packed two per
-//      dword, wave sums through DPP, one barrier.  An operand of up to kStatsDirectParts blocks is finished by one
-//      workgroup in one launch; larger ones leave one record per workgroup for the combine launch.
+//      workgroups of 1024 lanes, every lane's loads in flight together, counters by ballots, one barrier.  An operand of up to
+//      kStatsDirectParts blocks is finished by one workgroup in one launch; larger ones leave one record per workgroup for
+//      the combine launch.
 constexpr int kStatsFastThreads = 1024;
 constexpr int kStatsFastPerLane = 4;                   // blocks per lane of a partial workgroup
-constexpr int64_t kStatsDirectParts = 16384;           // one workgroup, 16 blocks per lane at most: packed 16-bit counters cannot overflow
-struct StatsPacked {
-    double e;
-    unsigned long long n, eb, e5;
-    uint32_t pk[8];        // counter k of StatsAcc::cnt in half (k & 1) of pk[k >> 1]
-};
-// Totals of one workgroup: the packed per-lane counters (at most 65535 blocks per lane) are widened before they are summed.
-struct StatsTotals {
-    double e;
-    unsigned long long n, eb, e5;
-    uint32_t c[kStatCnt];
-};
-template <int WAVES>
-struct StatsFastShared {
-    double e[WAVES];
-    unsigned long long n[WAVES], eb[WAVES], e5[WAVES];
-    uint32_t c[WAVES][kStatCnt];
-};
-__device__ __forceinline__ void stats_accumulate_packed(float es, uint32_t nz, uint32_t mk, unsigned long long ne, float th, float near_tol,
-                                                        StatsPacked& a) {
-    const float metric = nz ? es / (float)nz : 0.0f;           // binary32, IEEE division
-    const int bin = stats_bin(metric);
-    const uint32_t inc = 1u << ((bin & 1) * 16);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) a.pk[k] += ((bin >> 1) == k) ? inc : 0u;
-    a.e += (double)es;
-    a.n += nz;
-    a.pk[6] += (mk == 1u ? 1u : 0u) + ((fabs((double)metric - (double)th) <= (double)near_tol * (double)th) ? 0x10000u : 0u);
-    a.pk[7] += mk == 2u ? 1u : 0u;
-    if (mk == 1u) a.eb += ne;
-    if (mk == 2u) a.e5 += ne;
-}
-__device__ __forceinline__ void stats_wave_sums(StatsTotals& t) {
-    t.e = wave_allsum_f64(t.e); t.n = wave_allsum_u64(t.n); t.eb = wave_allsum_u64(t.eb); t.e5 = wave_allsum_u64(t.e5);
-#pragma unroll
-    for (int k = 0; k < kStatCnt; ++k) t.c[k] = wave_allsum_u32(t.c[k]);
-}
-// Sums over the workgroup (WAVES <= 64 waves), fixed order; the totals arrive in every lane of wave 0 (the other waves
-// return with meaningless values).
-template <int WAVES>
-__device__ __forceinline__ void stats_fast_reduce(StatsTotals& t, StatsFastShared<WAVES>& sh) {
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    stats_wave_sums(t);
-    if (lane == 0) {
-        sh.e[w] = t.e; sh.n[w] = t.n; sh.eb[w] = t.eb; sh.e5[w] = t.e5;
-#pragma unroll
-        for (int k = 0; k < kStatCnt; ++k) sh.c[w][k] = t.c[k];
-    }
-    __syncthreads();
-    if (w != 0) return;
-    const bool live = lane < WAVES;
-    const int src = live ? lane : 0;
-    t.e = live ? sh.e[src] : 0.0; t.n = live ? sh.n[src] : 0ull; t.eb = live ? sh.eb[src] : 0ull; t.e5 = live ? sh.e5[src] : 0ull;
-#pragma unroll
-    for (int k = 0; k < kStatCnt; ++k) t.c[k] = live ? sh.c[src][k] : 0u;
-    stats_wave_sums(t);
-}
-// Value k (per lane, 0 .. kStatCnt - 1) of the totals, without indexing registers dynamically.
-__device__ __forceinline__ uint32_t stats_pick(const StatsTotals& t, int k) {
-    uint32_t v = 0u;
-#pragma unroll
-    for (int j = 0; j < kStatCnt; ++j) v = k == j ? t.c[j] : v;
-    return v;
-}
-// Wave 0 writes either the operand's final statistics (`final_out`) or this workgroup's record.
-__device__ __forceinline__ void stats_emit(const StatsTotals& t, StatsDev* out, int64_t n_part, unsigned long long total_elems, StatsRec* rec) {
-    if (threadIdx.x >= 64) return;
-    const uint32_t mine = stats_pick(t, (int)threadIdx.x < kStatCnt ? (int)threadIdx.x : 0);
-    if (rec == nullptr) {
-        if (threadIdx.x < 12) out->hist[threadIdx.x] = mine;
-        if (threadIdx.x == 0)
-            stats_finish(out, n_part, total_elems, t.e, t.n, t.c[12], t.c[13], t.c[14], t.eb, t.e5, 0u);
-        return;
-    }
-    if (threadIdx.x < kStatCnt) rec->cnt[threadIdx.x] = mine;
-    if (threadIdx.x == 0) { rec->e = t.e; rec->n = t.n; rec->eb = t.eb; rec->e5 = t.e5; }
-}
-__global__ __launch_bounds__(kStatsFastThreads) void k_stats_group_partial(GroupStats g) {
-    __shared__ StatsFastShared<kStatsFastThreads / 64> sh;
-    const int op = group_find32(g.wg_end, g.n, blockIdx.x);
-    const StatsOp& t = g.op[op];
-    const int b = blockIdx.x - (op ? g.wg_end[op - 1] : 0);
-    const int nb = g.wg_end[op] - (op ? g.wg_end[op - 1] : 0);
-    StatsPacked a;
-    a.e = 0.0; a.n = 0ull; a.eb = 0ull; a.e5 = 0ull;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) a.pk[k] = 0u;
-    const int64_t stride = (int64_t)nb * kStatsFastThreads;
-    for (int64_t p0 = (int64_t)b * kStatsFastThreads + threadIdx.x; p0 < t.n_part; p0 += 4 * stride) {
-        float es[4]; uint32_t nz[4], mk[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {                          // four blocks' loads in flight per lane
-            const int64_t p = p0 + u * stride;
-            const bool ok = p < t.n_part;
-            es[u] = ok ? t.err_sum[p] : 0.0f; nz[u] = ok ? t.nnz[p] : 0u; mk[u] = ok ? (uint32_t)t.mask[p] : 3u;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (mk[u] != 3u) stats_accumulate_packed(es[u], nz[u], mk[u], mk[u] ? block_elems(t.geom, p0 + u * stride) : 0ull, t.th, g.near_tol, a);
-    }
-    StatsTotals tot;
-    tot.e = a.e; tot.n = a.n; tot.eb = a.eb; tot.e5 = a.e5;
-#pragma unroll
-    for (int k = 0; k < kStatCnt; ++k) tot.c[k] = (k & 1) ? a.pk[k >> 1] >> 16 : a.pk[k >> 1] & 0xFFFFu;
-    stats_fast_reduce(tot, sh);
-    stats_emit(tot, t.out, t.n_part, (unsigned long long)(t.geom.rows * t.geom.cols), nb == 1 ? nullptr : t.rec + b);
-}
-// Combine launch: one workgroup of 256 lanes per operand, one record per lane.
-__global__ __launch_bounds__(256) void k_stats_group_final(GroupStats g) {
-    __shared__ StatsFastShared<4> sh;
-    const StatsOp& t = g.op[blockIdx.x];
-    const int nb = g.wg_end[blockIdx.x] - (blockIdx.x ? g.wg_end[blockIdx.x - 1] : 0);       // <= kStatsMaxWg = 256
-    if (nb == 1) return;                                                                       // already final
-    StatsTotals tot;
-    tot.e = 0.0; tot.n = 0ull; tot.eb = 0ull; tot.e5 = 0ull;
-#pragma unroll
-    for (int k = 0; k < kStatCnt; ++k) tot.c[k] = 0u;
-    if ((int)threadIdx.x < nb) {
-        const StatsRec& r = t.rec[threadIdx.x];
-        tot.e = r.e; tot.n = r.n; tot.eb = r.eb; tot.e5 = r.e5;
-#pragma unroll
-        for (int k = 0; k < kStatCnt; ++k) tot.c[k] = r.cnt[k];
-    }
-    stats_fast_reduce(tot, sh);
-    stats_emit(tot, t.out, t.n_part, (unsigned long long)(t.geom.rows * t.geom.cols), nullptr);
-}
+constexpr int64_t kStatsDirectParts = 16384;           // one workgroup, 16 blocks per lane at most
+__global__ __launch_bounds__(kStatsFastThreads) void k_stats_group_partial(GroupStats g) { stats_partial_body<kStatsFastThreads>(g, (int)blockIdx.x); }
+// Combine launch: one workgroup per operand.
+__global__ __launch_bounds__(256) void k_stats_group_final(GroupStats g) { stats_final_body(g, (int)blockIdx.x); }
 
 // ======================================================================================
 // Tensor-level decision over sub-tensor scaling (Section 3.1): the deferred block kernels wrote
@@ -908,51 +855,41 @@ struct GroupScope {
     ScopeOp op[kMaxGroupScope];
 };
 // Four blocks' loads in flight per lane.  With statistics the same sweep also fills the workgroup's record (histogram bins,
-// near-threshold blocks), so no statistics launch follows.  Per-channel operands of one linear layer, 67 + 50 MB: 88.3 us per call
-// against 103.4 us with statistics launches, three barriers per sum and an empty fallback-column launch.
+// near-threshold blocks), so no statistics launch follows.
 __global__ __launch_bounds__(256) void k_scope_reduce_group(GroupScope g) {
     __shared__ double shd[4];
-    __shared__ StatsFastShared<4> sh;
+    __shared__ StatsLds<4> sh;
     const int op = group_find32(g.red_end, g.n, blockIdx.x);
     const ScopeOp& t = g.op[op];
     const int b = blockIdx.x - (op ? g.red_end[op - 1] : 0);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const bool eq3 = t.crit == kCritEq3, want = t.stats != nullptr;
     double e5 = 0.0;
-    StatsPacked acc;
-    acc.e = 0.0; acc.n = 0ull; acc.eb = 0ull; acc.e5 = 0ull;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) acc.pk[k] = 0u;
+    StatsTally a;
+    tally_clear(a);
     const int64_t stride = (int64_t)t.n_red * 256;
-    for (int64_t p0 = (int64_t)b * 256 + threadIdx.x; p0 < t.n_part; p0 += 4 * stride) {
+    for (int64_t base = (int64_t)b * 256 + w * 64; base < t.n_part; base += 4 * stride) {       // uniform over the wave
         float es[4], es5[4];
         uint32_t nz[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const bool ok = p0 + u * stride < t.n_part;
-            const int64_t p = ok ? p0 + u * stride : p0;       // always a valid block: the loads need no branch
-            es[u] = t.err_sum[p]; nz[u] = t.nnz[p]; es5[u] = eq3 ? t.err5_sum[p] : 0.0f;
+            const int64_t p = base + lane + u * stride, pc = p < t.n_part ? p : t.n_part - 1;    // always a valid block: the loads need no branch
+            es[u] = t.err_sum[pc]; nz[u] = t.nnz[pc]; es5[u] = eq3 ? t.err5_sum[pc] : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if (p0 + u * stride >= t.n_part) continue;
-            e5 += (double)es5[u];
-            if (want) stats_accumulate_packed(es[u], nz[u], 0u, 0ull, t.th, t.near_tol, acc);
-            else { acc.e += (double)es[u]; acc.n += nz[u]; }
+            if (base + u * stride >= t.n_part) break;          // uniform over the wave
+            const bool ok = base + lane + u * stride < t.n_part;
+            e5 += ok ? (double)es5[u] : 0.0;
+            if (want) tally(ok, es[u], nz[u], 0u, [] { return 0ull; }, t.th, t.near_tol, a);
+            else if (ok) { a.e += (double)es[u]; a.n += nz[u]; }
         }
     }
-    e5 = block_sum_shfl<double>(e5, shd);
-    StatsTotals tot;
-    tot.e = acc.e; tot.n = acc.n; tot.eb = 0ull; tot.e5 = 0ull;
-    if (!want) {                                               // the sums alone (uniform over the workgroup)
-        tot.e = block_sum_shfl<double>(tot.e, shd);
-        tot.n = block_sum_shfl<unsigned long long>(tot.n, sh.n);
-    } else {
-#pragma unroll
-        for (int k = 0; k < kStatCnt; ++k) tot.c[k] = (k & 1) ? acc.pk[k >> 1] >> 16 : acc.pk[k >> 1] & 0xFFFFu;
-        stats_fast_reduce(tot, sh);                            // the totals arrive in wave 0
-    }
-    if (threadIdx.x == 0) { t.part_err[b] = tot.e; t.part_nnz[b] = tot.n; t.part_err5[b] = e5; }
-    if (want) stats_emit(tot, nullptr, 0, 0ull, t.rec + b);
+    if (eq3) { e5 = wave_allsum_f64(e5); if (lane == 0) shd[w] = e5; }
+    uint32_t mine;
+    stats_reduce(a, mine, sh);                                 // (its barrier also covers shd)
+    if (threadIdx.x == 0) { t.part_err[b] = a.e; t.part_nnz[b] = a.n; t.part_err5[b] = eq3 ? (shd[0] + shd[1]) + (shd[2] + shd[3]) : 0.0; }
+    if (want) stats_record(t.rec + b, a, mine);
 }
 // Same decision in every wave that calls it (fixed summation order over the operand's partial records), no barrier.
 __device__ __forceinline__ uint32_t scope_decision(const ScopeOp& t) {
@@ -975,7 +912,7 @@ __device__ __forceinline__ uint32_t scope_decision(const ScopeOp& t) {
 // Decision (every workgroup re-derives it from the partial records: the same value everywhere), mask broadcast over the
 // operand's workgroups, statistics by its first one, then the copy of a BF16 tensor that no earlier pass has proven and written.
 __global__ __launch_bounds__(256) void k_scope_copy_group(GroupScope g) {
-    __shared__ StatsFastShared<4> sh;
+    __shared__ RecordSums sh;
     const int op = group_find32(g.copy_end, g.n, blockIdx.x);
     const ScopeOp& t = g.op[op];
     const int b = blockIdx.x - (op ? g.copy_end[op - 1] : 0);
@@ -984,26 +921,12 @@ __global__ __launch_bounds__(256) void k_scope_copy_group(GroupScope g) {
     if (b == 0 && threadIdx.x == 0) t.decision[0] = m;
     for (int64_t p = (int64_t)b * 256 + threadIdx.x; p < t.n_part; p += (int64_t)nb * 256) t.mask[p] = (uint8_t)m;
     if (b == 0 && t.stats) {                                   // uniform over the workgroup
-        StatsTotals tot;
-        tot.e = 0.0; tot.n = 0ull; tot.eb = 0ull; tot.e5 = 0ull;
-#pragma unroll
-        for (int k = 0; k < kStatCnt; ++k) tot.c[k] = 0u;
-        if ((int)threadIdx.x < t.n_red) {
-            const StatsRec& r = t.rec[threadIdx.x];
-            tot.e = r.e; tot.n = r.n;
-#pragma unroll
-            for (int k = 0; k < kStatCnt; ++k) tot.c[k] = r.cnt[k];
-        }
-        stats_fast_reduce(tot, sh);
+        sum_records(t.rec, t.n_red, sh);
         const unsigned long long total = (unsigned long long)(t.rows * t.cols);
-        tot.c[12] = 0u;
-        if (m) tot.eb = total;
-        if (threadIdx.x < 64) {
-            const uint32_t mine = stats_pick(tot, (int)threadIdx.x < kStatCnt ? (int)threadIdx.x : 0);
-            if (threadIdx.x < 12) t.stats->hist[threadIdx.x] = mine;
-            if (threadIdx.x == 0)
-                stats_finish(t.stats, t.n_part, total, tot.e, tot.n, m ? (unsigned long long)t.n_part : 0ull, tot.c[13], 0ull, tot.eb, 0ull, 0u);
-        }
+        if (threadIdx.x < 12) t.stats->hist[threadIdx.x] = record_counter(sh, threadIdx.x);
+        if (threadIdx.x == 0)
+            stats_finish(t.stats, t.n_part, total, __longlong_as_double((long long)sh.all[0]), sh.all[1], m ? (unsigned long long)t.n_part : 0ull,
+                         record_counter(sh, 13), 0ull, m ? total : 0ull, 0ull, 0u);
     }
     if (t.bf16 == nullptr || m == 0u || (t.proven && t.proven[0] != 0u)) return;
     if (t.ld == t.cols && t.ld_bf16 == t.cols) {
@@ -1063,16 +986,6 @@ __global__ __launch_bounds__(256, CRIT == kCritEq3 || ROWS ? 4 : 6) void k_sub1x
 // operand with statistics 8.5 instead of 11.3 us per call, 8192 x 4096 26.4 instead of 29.1.
 constexpr int kSoloFinalThreads = 1024;
 constexpr int kSoloQ = kSoloRecWords / 2;              // quadwords: seven pairs of counters and one counter, the sum, the non-zeros
-__device__ __forceinline__ unsigned long long row_allsum_u64(unsigned long long v) {
-    v += dpp_u64<kDppXor1>(v); v += dpp_u64<kDppXor2>(v); v += dpp_u64<kDppHalfMirror>(v); v += dpp_u64<kDppMirror>(v);
-    return v;
-}
-__device__ __forceinline__ double row_allsum_f64(double v) {
-    auto sh = [](double x, auto ctrl) { return __longlong_as_double((long long)dpp_u64<decltype(ctrl)::value>((unsigned long long)__double_as_longlong(x))); };
-    v += sh(v, std::integral_constant<int, kDppXor1>{}); v += sh(v, std::integral_constant<int, kDppXor2>{});
-    v += sh(v, std::integral_constant<int, kDppHalfMirror>{}); v += sh(v, std::integral_constant<int, kDppMirror>{});
-    return v;
-}
 __global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStats s) {
     constexpr int kGroups = kSoloFinalThreads / 16;
     __shared__ unsigned long long part[kGroups][kSoloQ];
@@ -1251,7 +1164,7 @@ __device__ __forceinline__ void tensor_amax_body(const G& g, int block) {
 }
 template <bool STRIDED>
 __global__ __launch_bounds__(256) void k_tensor_amax_group(GroupTensor g, GroupStats riders, int stats_first, int block0) {
-    if ((int)blockIdx.x >= stats_first) { stats_partial_body(riders, (int)blockIdx.x - stats_first); return; }
+    if ((int)blockIdx.x >= stats_first) { stats_partial_body<256>(riders, (int)blockIdx.x - stats_first); return; }
     tensor_amax_body<STRIDED, kTensorChunksPerThread>(g, (int)blockIdx.x + block0);      // block0: the launch covers a part of the table's operands
 }
 // What pass A found out about the operand: its amax, and whether the sum of the certain-flush lower bounds proves the BF16
