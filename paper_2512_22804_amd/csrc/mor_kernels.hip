@@ -844,6 +844,8 @@ struct ScopeOp {
     // fallback copy
     const uint16_t* x; uint16_t* bf16;
     int64_t rows, cols, ld, ld_bf16;
+    // per-channel columns: the blocks' sums are still those of the strips, [n_strips x cols_padded]; the reduce pass adds them up
+    ColumnSums col;
     // selection statistics: all blocks get one decision, so the reduce pass can count everything that does not depend on it
     StatsDev* stats;                                                       // optional
     StatsRec* rec;                                                         // [n_red]
@@ -854,6 +856,34 @@ struct GroupScope {
     int32_t red_end[kMaxGroupScope], copy_end[kMaxGroupScope];
     ScopeOp op[kMaxGroupScope];
 };
+// Error sums and non-zero count of a column from those of its strips (binary64, fixed order), into the outputs: what the combine launch of
+// the per-channel columns does where the columns decide one by one.
+__device__ __forceinline__ void column_sums(const ScopeOp& t, int64_t c, bool live, bool eq3, float& es, uint32_t& nz, float& es5) {
+    double e = 0.0, e5 = 0.0;
+    unsigned long long z = 0ull;
+    for (int s0 = 0; s0 < t.col.n_strips; s0 += 8) {
+        float ev[8], e5v[8];
+        uint32_t zv[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int64_t at = (int64_t)(s0 + k < t.col.n_strips ? s0 + k : s0) * t.col.cols_padded + c;      // always a valid strip: the loads need no branch
+            ev[k] = t.col.err[at]; zv[k] = t.col.zero[at]; e5v[k] = eq3 ? t.col.err5[at] : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const bool ok = s0 + k < t.col.n_strips;
+            e += ok ? (double)ev[k] : 0.0; e5 += ok ? (double)e5v[k] : 0.0; z += ok ? zv[k] : 0u;
+        }
+    }
+    const unsigned long long n = (unsigned long long)((t.rows + 127) / 128) * 128ull - z;      // (rows beyond the tensor were counted as zeros)
+    if (__float_as_uint(t.col.amax[c]) >> 16 >= kInfBits) { e = (double)__builtin_inff(); e5 = e; }
+    es = (float)e; es5 = (float)e5;
+    nz = n > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)n;
+    if (!live) return;
+    const_cast<float*>(t.err_sum)[c] = es;
+    const_cast<uint32_t*>(t.nnz)[c] = nz;
+    if (eq3) const_cast<float*>(t.err5_sum)[c] = es5;
+}
 // Four blocks' loads in flight per lane.  With statistics the same sweep also fills the workgroup's record (histogram bins,
 // near-threshold blocks), so no statistics launch follows.
 __global__ __launch_bounds__(256) void k_scope_reduce_group(GroupScope g) {
@@ -874,7 +904,10 @@ __global__ __launch_bounds__(256) void k_scope_reduce_group(GroupScope g) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int64_t p = base + lane + u * stride, pc = p < t.n_part ? p : t.n_part - 1;    // always a valid block: the loads need no branch
-            es[u] = t.err_sum[pc]; nz[u] = t.nnz[pc]; es5[u] = eq3 ? t.err5_sum[pc] : 0.0f;
+            if (t.col.n_strips) {                              // uniform over the workgroup
+                if (base + u * stride >= t.n_part) break;
+                column_sums(t, pc, p < t.n_part, eq3, es[u], nz[u], es5[u]);
+            } else { es[u] = t.err_sum[pc]; nz[u] = t.nnz[pc]; es5[u] = eq3 ? t.err5_sum[pc] : 0.0f; }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -2356,7 +2389,9 @@ void BatchRun::tensor_level_decisions() {
         t.th = it.th; t.crit = it.crit;
         t.proven = scope_proof_applies(it) ? gam_of[i] + 2 : nullptr;
         if (column_tensor_proof_applies(it)) t.proven = column_tensor_proven_word(col_ws[i], it.sh.rows, it.sh.cols);
-        int64_t want = (t.n_part + 1023) / 1024;
+        t.col = ColumnSums{};
+        if (it.gran == kGranCol) t.col = column_sums_of(col_ws[i], it.sh.rows, it.sh.cols, it.o.amax);
+        int64_t want = it.gran == kGranCol ? (t.n_part + 255) / 256 : (t.n_part + 1023) / 1024;      // (a column is a sum over the strips)
         t.n_red = (int)(want < 1 ? 1 : (want > kScopeBlocks ? kScopeBlocks : want));
         t.stats = static_cast<StatsDev*>(it.stats);
         t.rec = it.stats ? reinterpret_cast<StatsRec*>(carve(sizeof(StatsRec) * kStatsMaxWg)) : nullptr;

@@ -240,6 +240,13 @@ inline int scope_copy_budget(int n_unproven, int64_t unproven_bytes) {
     if (v > cap) v = cap;
     return (int)(v < 1024 ? 1024 : v);
 }
+// Per-channel columns: what the quantize pass has left of each strip, [n_strips x cols_padded], and the columns' amax.
+struct ColumnSums {
+    const float* err; const float* err5; const uint16_t* zero; const float* amax;
+    int64_t cols_padded;
+    int32_t n_strips;        // 0: not per-channel columns
+};
+ColumnSums column_sums_of(const char* column_workspace, int64_t rows, int64_t cols, const float* amax);
 uint32_t* column_tensor_proven_word(char* column_workspace, int64_t rows, int64_t cols);
 hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int cnt, int crit, const uint32_t* const* gam_of,
                                     char* const* ws_of, hipStream_t st, KProf* prof);

@@ -551,12 +551,13 @@ struct ColOp {
     uint32_t group_rows;        // 128 x 1 blocks under GAM with bands of rows as groups (0: one group)
     uint8_t defer, mode, three, prove;   // prove: count certain flushes in the amax pass (see below)
     uint8_t derive_gam;
+    uint8_t scaled;             // the scales have been formed by a launch of their own
     uint8_t keep;               // column-amax pass: the operand stays in the Infinity Cache for the quantize pass
     const uint32_t* gam;
     // per-channel columns: workspace, [n_strips x cols_padded] each, cols_padded = tiles_x * 128
     uint16_t* part_amax;
     float* part_err; float* part_err5; uint16_t* part_zero;
-    float* col_scale5;                                   // [cols_padded]
+    float* col_scale; float* col_scale5;                 // [cols_padded]
     uint16_t* col_amin;                                  // [cols_padded] (smallest non-zero pattern - 1), three-way recipe; its
                                                          // per-strip partials use part_zero, which is free until the quantize pass
     uint8_t* col_proven;                                 // [cols_padded] 1: the column's BF16 decision is proven before it is quantized;
@@ -634,6 +635,16 @@ __device__ __forceinline__ void col_scales(const ColOp& t, int64_t strip, int64_
     const int64_t cols_padded = t.tiles_x * 128;
     const int n_wg = (int)(t.n_strips * t.tiles_x);        // workgroups of the amax pass
     const bool whole = t.prove && t.tensor_need != 0ull;
+    if (t.scaled) {                                        // uniform over the workgroup
+        if (tid < 128) {
+            const int64_t c = c0 + tid;
+            sh.scale[tid] = t.col_scale[c]; sh.scale5[tid] = t.col_scale5[c];
+            sh.abits[tid] = c < t.cols ? (uint16_t)(__float_as_uint(t.o.amax[c]) >> 16) : (uint16_t)0;
+            sh.mask[tid] = t.prove ? t.col_proven[c] : (uint8_t)0;
+        }
+        __syncthreads();
+        return;
+    }
     const uint16_t* __restrict__ part_flush = reinterpret_cast<const uint16_t*>(t.part_err5);
     // two threads per column, every other strip each
     uint32_t a = 0u, fl = 0u;
@@ -1146,6 +1157,79 @@ __global__ __launch_bounds__(256) void k_col_group(GroupCol g) { col_group_body<
 template <int CRIT, bool FAKE, bool EDGE>
 __global__ __launch_bounds__(256, 4) void k_col_quant_group(GroupCol g) { col_group_body<CRIT, kColExternal, FAKE, EDGE>(g); }
 
+// Per-channel columns of a launch with many workgroups (see kColScaleWgs): column amax over the strips -> amax, scale (Algorithm 1),
+// E8M0 byte, once and for all.
+// Under GAM every workgroup first takes the largest column amax of the operand (the group amax of Algorithm 1), and for a tensor-level decision the sum of all columns' certain flushes: the same values in every
+// workgroup, from the per-workgroup figures of the amax pass (a handful of loads per thread).
+__global__ __launch_bounds__(256) void k_col_scales(GroupCol g) {
+    __shared__ uint32_t sh4[4];
+    __shared__ unsigned long long shl[4];
+    const int op = group_find32(g.comb_end, g.n, blockIdx.x);
+    const ColOp& t = g.op[op];
+    const int b = blockIdx.x - (op ? g.comb_end[op - 1] : 0);
+    const int tid = threadIdx.x;
+    const int64_t c = (int64_t)b * 256 + tid;
+    const int64_t cols_padded = t.tiles_x * 128;
+    const int64_t n_wg = (int64_t)t.n_strips * t.tiles_x;  // workgroups of the amax pass
+    uint32_t mg = 0u, mg5 = 0u;
+    if (t.derive_gam) {                                    // GAM (uniform over the workgroup)
+        uint32_t ga = 0u;
+        for (int64_t i = tid; i < n_wg; i += 256) ga = max(ga, t.wg[2 + 2 * i]);
+        ga = wave_allmax_u32(ga);
+        if ((tid & 63) == 0) sh4[tid >> 6] = ga;
+        __syncthreads();
+        ga = max(max(sh4[0], sh4[1]), max(sh4[2], sh4[3]));
+        mg = group_mantissa_bits(ga, kE4M3Max, t.mode);
+        mg5 = group_mantissa_bits(ga, kE5M2Max, t.mode);
+        if (b == 0 && tid == 0) {
+            uint32_t* gam_out = const_cast<uint32_t*>(t.gam);
+            gam_out[0] = mg; gam_out[1] = mg5;
+            if (t.gmant) { t.gmant[0] = mg; t.gmant[1] = mg5; }
+        }
+    }
+    bool all_proven = false;
+    if (t.prove && t.tensor_need) {                        // uniform over the workgroup
+        unsigned long long f = 0ull;
+        for (int64_t i = tid; i < n_wg; i += 256) f += t.wg[3 + 2 * i];
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) f += __shfl_xor(f, m, 64);
+        if ((tid & 63) == 0) shl[tid >> 6] = f;
+        __syncthreads();
+        f = (shl[0] + shl[1]) + (shl[2] + shl[3]);
+        all_proven = f >= t.tensor_need;
+        if (b == 0 && tid == 0) t.wg[0] = all_proven ? 1u : 0u;
+    }
+    if (c >= cols_padded) return;
+    uint32_t a = 0u;
+#pragma unroll 8
+    for (int sidx = 0; sidx < t.n_strips; ++sidx) a = max(a, (uint32_t)t.part_amax[sidx * cols_padded + c]);
+    if (t.three) {
+        uint32_t mn = 0xFFFFu;
+#pragma unroll 8
+        for (int sidx = 0; sidx < t.n_strips; ++sidx) mn = min(mn, (uint32_t)t.part_zero[sidx * cols_padded + c]);
+        t.col_amin[c] = (uint16_t)mn;
+    }
+    if (t.prove) {
+        if (t.tensor_need) {
+            t.col_proven[c] = (c < t.cols && all_proven) ? 1 : 0;
+        } else {
+            const uint16_t* __restrict__ part_flush = reinterpret_cast<const uint16_t*>(t.part_err5);
+            uint32_t fl = 0u;
+#pragma unroll 8
+            for (int sidx = 0; sidx < t.n_strips; ++sidx) fl += part_flush[sidx * cols_padded + c];
+            t.col_proven[c] = (c < t.cols && fl >= t.flush_need) ? 1 : 0;
+        }
+    }
+    const float s = block_scale(a, kE4M3Max, t.mode, mg);
+    t.col_scale[c] = s;
+    t.col_scale5[c] = block_scale(a, kE5M2Max, t.mode, mg5);
+    if (c < t.cols) {
+        t.o.amax[c] = __uint_as_float(a << 16);
+        t.o.scale[c] = s;
+        if (t.mode != kScaleFp32 && t.o.e8m0) t.o.e8m0[c] = (uint8_t)(__float_as_uint(s) >> 23);
+        if (t.mode == kScaleE8M0 && c == 0) zero_group_mantissa(t.gmant);
+    }
+}
 // Per-channel columns, three-way recipe: smallest non-zero magnitude of the columns over the strips.  (A launch of its own: the
 // quantize pass writes over the strips' figures.)
 __global__ __launch_bounds__(256) void k_col_amin(GroupCol g) {
@@ -1167,7 +1251,7 @@ __global__ __launch_bounds__(256) void k_col_finish(GroupCol g) {
     const ColOp& t = g.op[op];
     const int64_t c = (int64_t)(blockIdx.x - (op ? g.comb_end[op - 1] : 0)) * 256 + threadIdx.x;
     const int64_t cols_padded = t.tiles_x * 128;
-    if (c >= t.cols) return;
+    if (c >= t.cols || t.defer) return;
     double e = 0.0, e5 = 0.0;
     unsigned long long z = 0;
 #pragma unroll 8
@@ -1184,29 +1268,31 @@ __global__ __launch_bounds__(256) void k_col_finish(GroupCol g) {
     t.o.err_sum[c] = (float)e;
     t.o.nnz[c] = n > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)n;
     if constexpr (CRIT == kCritEq3) t.o.err5_sum[c] = (float)e5;
-    if (!t.defer) {
-        uint32_t mk;
-        if constexpr (CRIT == kCritEq3) mk = (e < e5) ? 0u : 1u;
-        else mk = ((n ? e / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
-        if (t.three) {                     // a column that failed M_1 is kept in E5M2 if its dynamic range fits (Eq. 4)
-            uint32_t amin_bits = 0u;
-            if (mk == 1u) {
-                amin_bits = n ? (((uint32_t)t.col_amin[c] + 1u) & 0xFFFFu) : 0u;
-                if (range_fits_e5m2(abits, amin_bits, n ? 1u : 0u)) {
-                    mk = 2u;
-                    const float s5 = t.col_scale5[c];
-                    t.o.scale[c] = s5;
-                    if (t.mode != kScaleFp32 && t.o.e8m0) t.o.e8m0[c] = (uint8_t)(__float_as_uint(s5) >> 23);
-                }
+    uint32_t mk;
+    if constexpr (CRIT == kCritEq3) mk = (e < e5) ? 0u : 1u;
+    else mk = ((n ? e / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
+    if (t.three) {                     // a column that failed M_1 is kept in E5M2 if its dynamic range fits (Eq. 4)
+        uint32_t amin_bits = 0u;
+        if (mk == 1u) {
+            amin_bits = n ? (((uint32_t)t.col_amin[c] + 1u) & 0xFFFFu) : 0u;
+            if (range_fits_e5m2(abits, amin_bits, n ? 1u : 0u)) {
+                mk = 2u;
+                const float s5 = t.col_scale5[c];
+                t.o.scale[c] = s5;
+                if (t.mode != kScaleFp32 && t.o.e8m0) t.o.e8m0[c] = (uint8_t)(__float_as_uint(s5) >> 23);
             }
-            if (t.o.amin) t.o.amin[c] = __uint_as_float(amin_bits << 16);
         }
-        t.o.mask[c] = (uint8_t)mk;
+        if (t.o.amin) t.o.amin[c] = __uint_as_float(amin_bits << 16);
     }
+    t.o.mask[c] = (uint8_t)mk;
 }
 // Columns kept in BF16 are copied: 16 bytes at a time where all eight columns of a chunk are kept, else by element.
 // Columns kept in E5M2 (three-way recipe) get their payload here, element by element, over the E4M3 one.
 // A workgroup takes one 128-column strip and strides over the rows with the other workgroups of that strip.
+// Workgroups of a launch up to which each forms its columns' scales itself.  What they read for it grows with the product of the
+// operands' strips and workgroups, while the launch that it saves becomes a small part of the call: 768 workgroups 88.3 -> 80.4 us,
+// 1024 (14336 x 4096) 92.5 -> 83.2, the 11 000 of a layer's twelve operands 554 -> 542; beyond 2048 the launch stays.
+constexpr int64_t kColScaleWgs = 2048;
 constexpr int kColCopyRowGroups = 32;      // at most, per 128-column strip
 constexpr int kColCopyBudget = 4096;       // workgroups per launch, about
 __global__ __launch_bounds__(256) void k_col_fallback(GroupCol g) {
@@ -1450,6 +1536,11 @@ bool col_needs_edge(const BatchItem& it) { return it.sh.rows % 128 != 0 || it.sh
 uint32_t* column_tensor_proven_word(char* ws, int64_t rows, int64_t cols) {
     return reinterpret_cast<uint32_t*>(ws + plan_columns(rows, cols).off_wg);
 }
+ColumnSums column_sums_of(const char* ws, int64_t rows, int64_t cols, const float* amax) {
+    const ColPlan pl = plan_columns(rows, cols);
+    return ColumnSums{reinterpret_cast<const float*>(ws + pl.off_err), reinterpret_cast<const float*>(ws + pl.off_err5), reinterpret_cast<const uint16_t*>(ws + pl.off_zero),
+                      amax, pl.cols_padded, pl.n_strips};
+}
 size_t column_workspace_bytes(int64_t rows, int64_t cols) { return plan_columns(rows, cols).bytes; }
 
 // 128 x 1 sub-columns: grouped, one pass.
@@ -1508,11 +1599,15 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
                 g.copy_end[k] = copy;
             }
             { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColAmax>(g, total, kCritEq2, false, edge, st); }
+            const bool scaled = total > kColScaleWgs;
             bool three = false;
-            for (int k = 0; k < g.n; ++k) three |= g.op[k].three != 0;
-            if (three) { ProfScope ps(prof, kKernColumnCombine, st); k_col_amin<<<dim3((unsigned)comb), dim3(256), 0, st>>>(g); }
+            for (int k = 0; k < g.n; ++k) { three |= g.op[k].three != 0; g.op[k].scaled = scaled ? 1 : 0; }
+            if (scaled) { ProfScope ps(prof, kKernColumnCombine, st); k_col_scales<<<dim3((unsigned)comb), dim3(256), 0, st>>>(g); }
+            else if (three) { ProfScope ps(prof, kKernColumnCombine, st); k_col_amin<<<dim3((unsigned)comb), dim3(256), 0, st>>>(g); }
             { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColExternal>(g, total, crit, fake, edge, st); }
-            {
+            bool singly = false;      // some operand's columns are decided one by one; the others' sums are added up by the tensor-level reduce pass
+            for (int k = 0; k < g.n; ++k) singly |= !g.op[k].defer;
+            if (singly) {
                 ProfScope ps(prof, kKernColumnCombine, st);
                 if (crit == kCritEq3) k_col_finish<kCritEq3><<<dim3((unsigned)comb), dim3(256), 0, st>>>(g);
                 else k_col_finish<kCritEq2><<<dim3((unsigned)comb), dim3(256), 0, st>>>(g);
@@ -1539,6 +1634,7 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
             t.part_err = reinterpret_cast<float*>(w + pl.off_err);
             t.part_err5 = reinterpret_cast<float*>(w + pl.off_err5);
             t.part_zero = reinterpret_cast<uint16_t*>(w + pl.off_zero);
+            t.col_scale = reinterpret_cast<float*>(w + pl.off_scale);
             t.col_scale5 = reinterpret_cast<float*>(w + pl.off_scale5);
             t.col_amin = reinterpret_cast<uint16_t*>(w + pl.off_amin);
             t.col_proven = reinterpret_cast<uint8_t*>(w + pl.off_proven);
