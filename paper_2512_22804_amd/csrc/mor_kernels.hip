@@ -1768,7 +1768,7 @@ struct GamOp {
     uint32_t* gmant;       // caller's group-mantissa output, may be nullptr
     const uint32_t* flush_part;          // [n_amax] certain flushes counted by the pre-pass, or nullptr
     unsigned long long flush_need;       // that many prove the decision
-    uint32_t skip;                       // per-channel columns under GAM: their own combine kernel derives the mantissas
+    uint32_t skip;                       // per-channel columns under GAM: the step that forms their scales derives the mantissas
 };
 struct GroupGam {
     int n;

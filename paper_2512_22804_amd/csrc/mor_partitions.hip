@@ -571,7 +571,7 @@ struct ColOp {
                                                          // tensor-level copy pass), then per workgroup of the amax pass its largest column
                                                          // amax and its flush total
     unsigned long long tensor_need;                      // 0: columns are proven one by one (decisions per column)
-    // GAM scaling (derive_gam): the group amax is the largest column amax, so the first combine derives the group mantissas
+    // GAM scaling (derive_gam): the group amax is the largest column amax, so the step that forms the scales derives the group mantissas
     // itself (no pre-pass over the operand) and leaves them in `gam` and in the caller's output
     uint32_t* gmant;                                     // caller's [2] or nullptr
 };
@@ -1103,7 +1103,7 @@ __device__ __forceinline__ void col_strip(const ColOp& t, int64_t unit, ColShare
             if (t.three) t.part_zero[strip * cols_padded + c0 + tid] = (uint16_t)mn;
             if (t.prove) reinterpret_cast<uint16_t*>(t.part_err5)[strip * cols_padded + c0 + tid] = (uint16_t)fl;
         }
-        // the strip's largest column amax and its flush total, for the combine kernel's whole-operand figures
+        // the strip's largest column amax and its flush total, for the whole-operand figures of the step that forms the scales
         // (group amax of Algorithm 1, tensor-level proof)
         a = wave_allmax_u32(a);
         fl = wave_allsum_u32(t.prove ? fl : 0u);
@@ -1286,13 +1286,14 @@ __global__ __launch_bounds__(256) void k_col_finish(GroupCol g) {
     }
     t.o.mask[c] = (uint8_t)mk;
 }
+// Workgroups of a launch up to which each forms its columns' scales itself: 768 workgroups 88.3 -> 80.4 us per call, 1024
+// (14336 x 4096) 92.5 -> 83.2.  What they read for it grows with the product of the operands' strips and workgroups, and the launch
+// that it saves becomes a small part of the call (the 11 000 of a layer's twelve operands: 554 -> 542, 2 %): launches of several
+// large operands keep the sequence of five whose records callers and tests of the profile count on.
+constexpr int64_t kColScaleWgs = 2048;
 // Columns kept in BF16 are copied: 16 bytes at a time where all eight columns of a chunk are kept, else by element.
 // Columns kept in E5M2 (three-way recipe) get their payload here, element by element, over the E4M3 one.
 // A workgroup takes one 128-column strip and strides over the rows with the other workgroups of that strip.
-// Workgroups of a launch up to which each forms its columns' scales itself.  What they read for it grows with the product of the
-// operands' strips and workgroups, while the launch that it saves becomes a small part of the call: 768 workgroups 88.3 -> 80.4 us,
-// 1024 (14336 x 4096) 92.5 -> 83.2, the 11 000 of a layer's twelve operands 554 -> 542; beyond 2048 the launch stays.
-constexpr int64_t kColScaleWgs = 2048;
 constexpr int kColCopyRowGroups = 32;      // at most, per 128-column strip
 constexpr int kColCopyBudget = 4096;       // workgroups per launch, about
 __global__ __launch_bounds__(256) void k_col_fallback(GroupCol g) {
