@@ -1114,6 +1114,7 @@ __device__ __forceinline__ int64_t tensor_chunk_off(const TensorOp& t, int64_t c
 template <bool STRIDED, int CH, class G>
 __device__ __forceinline__ void tensor_amax_body(const G& g, int block) {
     constexpr int kTile = 256 * CH;
+    constexpr bool kSmall = CH != kTensorChunksPerThread;
     __shared__ uint32_t sh4[4];
     const int op = group_find32(g.amax_end, g.n, block);
     const TensorOp& t = g.op[op];
@@ -1124,7 +1125,8 @@ __device__ __forceinline__ void tensor_amax_body(const G& g, int block) {
     uint32_t mn2 = 0xFFFFFFFFu;                   // three-way recipe: smallest non-zero pattern, minus one, per half-word
     for (int64_t tile = b; tile < t.n_tiles; tile += t.n_amax) {
         const int64_t c0 = tile * kTile + threadIdx.x;
-        if (c0 + (CH - 1) * 256 < t.n_chunks && !(STRIDED && t.rm.cpr == 0u)) {
+        // Small tiles are taken whole, chunks beyond the operand as zeros: the reduction over the wave below needs all its lanes.
+        if ((kSmall || c0 + (CH - 1) * 256 < t.n_chunks) && !(STRIDED && t.rm.cpr == 0u)) {
             u32x4 v[CH];
             if constexpr (STRIDED) {
                 RowPos pos;
@@ -1133,7 +1135,7 @@ __device__ __forceinline__ void tensor_amax_body(const G& g, int block) {
                 const uint32_t row_bytes = (uint32_t)t.rm.ld * 2u;
                 uint32_t off[CH];
 #pragma unroll
-                for (int u = 0; u < CH; ++u) { off[u] = row_off<16>(pos, row_bytes, true); row_step(t.rm, pos); }
+                for (int u = 0; u < CH; ++u) { off[u] = row_off<16>(pos, row_bytes, !kSmall || c0 + u * 256 < t.n_chunks); row_step(t.rm, pos); }
                 if (tile >= t.keep_from) {
 #pragma unroll
                     for (int u = 0; u < CH; ++u) v[u] = buf_load16_first<true>(rx, off[u], 0u);
@@ -1159,10 +1161,11 @@ __device__ __forceinline__ void tensor_amax_body(const G& g, int block) {
                 for (int u = 0; u < CH; ++u) mn2 = min_nonzero_m1(v[u], mn2);
             }
             if (prove) {
-                // (tiles of a few chunks per lane: the wave's amax, the lane's alone would be a weak bound)
-                if constexpr (CH != kTensorChunksPerThread) { const uint32_t a = wave_allmax_u32(fold_max16(a2)); a2 = a | (a << 16); }
+                // (tiles of a few chunks per lane: the wave's amax, the lane's alone would be a weak bound; all lanes are here)
+                uint32_t bound2 = a2;
+                if constexpr (kSmall) { const uint32_t a = wave_allmax_u32(fold_max16(a2)); bound2 = a | (a << 16); }
                 // t = running amax with 20 taken off the exponent (0 if that underflows); 1 <= m < t  <=>  m-1 < t-1
-                const uint32_t t2 = pk_sub_sat_u16(a2, 0x0A000A00u);
+                const uint32_t t2 = pk_sub_sat_u16(bound2, 0x0A000A00u);
                 const uint32_t tm1 = pk_sub_sat_u16(t2, 0x00010001u);
                 uint32_t keep2 = 0u;                       // per half-word: elements of this tile NOT certain to flush
 #pragma unroll

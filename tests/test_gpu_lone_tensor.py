@@ -1,0 +1,77 @@
+"""A small per-tensor operand alone in its call: operands that end inside a wave of the amax pass.  Under Eq. 2 with a BF16 output that
+pass also counts elements that are certain to flush, against the amax of a whole wave: lanes beyond the operand's end take part in that
+reduction and bring nothing, and the amax itself comes from every lane that holds data."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_22804_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+LARGE = 0x4300                                            # 128.0, far above the rest
+
+
+def _normal(rows, cols, ld, seed):
+    x = W.outlier_normal(rows, ld, seed)
+    x[(x & 0x7FFF) >= 0x4200] = 0x3F80                    # nothing else of that size (32 and above)
+    return x
+
+
+def _run(B, p, x, fake=False):
+    out = B.alloc_outputs(p, x.device, bf16_fill=0)
+    if fake:
+        B.mor_fake_quantize(p, x, torch.empty_like(x), out)
+    else:
+        B.mor_analyze_quantize(p, x, out)
+    return out
+
+
+# an amax tile is 512 chunks of 8 elements, a wave takes 64 of the first 256 and the same of the second; above 768 tiles a workgroup
+# takes several, and what it found in the first must not stand for the last
+@pytest.mark.parametrize("tiles", [0, 20, 800])
+@pytest.mark.parametrize("r", [1, 5, 7, 9, 15, 17, 63, 65, 255])
+@pytest.mark.parametrize("padded", [False, True])
+def test_largest_value_in_the_last_tile(tiles, r, padded):
+    import parity
+    from paper_2512_22804_amd import binding as B
+    n = 512 * tiles + 256 + r
+    rows, cols, ld = (n, 8, 24) if padded else (1, 8 * n, 8 * n)
+    x = _normal(rows, cols, ld, r)
+    xd = parity.to_dev(x)
+    p = B.make_params(rows, cols, "tensor", ld=ld)
+    last = 512 * tiles
+    for at in sorted({last, last + min(4, r), last + r - 1, last + r, last + 255, last + 256, last + 256 + r // 2, n - 1}):
+        pos = (at, 7) if padded else (0, 8 * at + 7)
+        old = x[pos]
+        x[pos] = LARGE
+        xd[pos] = LARGE
+        out = _run(B, p, xd)
+        assert float(out.amax[0]) == 128.0 and float(out.scale[0]) == 3.5, (n, at)
+        if at == n - 1 or (tiles == 20 and at >= n - r):
+            parity.compare(x, "tensor", cols=cols, label=f"chunk {at} of {n}")
+        x[pos] = old
+        xd[pos] = int(old.view(np.int16))
+
+
+@pytest.mark.parametrize("rows, cols, pad", [(1500, 2880, 0), (2049, 2304, 0), (4000, 1000, 0), (1000, 5000, 0), (1500, 2880, 40), (1000, 5000, 8)])
+def test_largest_value_is_the_last(rows, cols, pad):
+    import parity
+    x = _normal(rows, cols, cols + pad, 2)
+    x[rows - 1, cols - 1] = LARGE | 0x8000
+    if pad:
+        x[:, cols:] = 0x7F80                              # what lies between the rows is not the operand's
+    parity.compare(x, "tensor", cols=cols)
+    parity.compare_fake(x, "tensor", cols=cols)
+
+
+@pytest.mark.parametrize("rows, cols, pad", [(700, 1000, 0), (700, 1000, 24), (1, 8, 0), (1500, 2880, 0)])
+def test_all_zero(rows, cols, pad):
+    import parity
+    from paper_2512_22804_amd import binding as B
+    x = np.zeros((rows, cols + pad), np.uint16)
+    x[:, 1::2] = 0x8000                                   # both signs
+    xd = parity.to_dev(x)
+    for fake in (False, True):
+        out = _run(B, B.make_params(rows, cols, "tensor", ld=cols + pad), xd, fake)
+        assert float(out.amax[0]) == 0.0 and float(out.scale[0]) == 1.0 and int(out.nnz[0]) == 0 and int(out.mask[0]) == 0
+    parity.compare(x, "tensor", cols=cols)
