@@ -1916,6 +1916,11 @@ static hipError_t launch_sub1x128(const uint16_t* x, const KShape& sh, const KOu
     return hipGetLastError();
 }
 
+// Whether a tile's rows can be addressed through a RowMap; if not, the kernels for padded rows take the operand chunk by chunk.
+static bool tensor_rows_fit(const KShape& sh, const KOut& o) {
+    const int64_t cpr = sh.cols / 8;
+    return cpr < (1 << 28) && row_map_fits(longest_row(sh, o), kTensorChunksPerBlock / cpr + 2);
+}
 // Fills the chunk layout of a per-tensor operand (or of the amax pass of one): rows of sh.ld elements, outputs as in o.
 static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o) {
     const int64_t cpr = sh.cols / 8;
@@ -1925,7 +1930,7 @@ static void set_tensor_layout(TensorOp& t, const KShape& sh, const KOut& o) {
     t.keep_from = keep_for_second_pass(sh) ? 0 : t.n_tiles;
     t.rm = RowMap{};
     t.rm.ld = sh.ld;
-    if (cpr >= (1 << 28) || !row_map_fits(longest_row(sh, o), kTensorChunksPerBlock / cpr + 2)) return;      // wide: cpr stays 0
+    if (!tensor_rows_fit(sh, o)) return;      // wide: cpr stays 0
     t.rm.cpr = (uint32_t)cpr;
     recip_of(cpr, &t.rm.mul, &t.rm.shift);
     t.rm.step_r = (uint32_t)(256 / cpr);
@@ -2530,7 +2535,10 @@ void BatchRun::per_tensor_operands(int crit) {
             if (cnt == 0 || err != hipSuccess) { cnt = 0; return; }
             GroupTensor g; g.n = cnt; g.near_tol = near_tol;
             const bool ride = !riders_used && n_stats_groups > 0;
-            const bool one = cnt == 1 && !ride && items[idx[0]].sh.rows * (items[idx[0]].sh.cols / 8) <= one_max_chunks(crit);
+            const BatchItem& it0 = items[idx[0]];
+            // (the kernels of the two launches address rows through a RowMap, so a dense operand whose rows are too long for it stays with the
+            // dense kernels, which number chunks without it: 1 x 8 388 608 kept in BF16 45.2 us as one of these, without a proof, 17.6 with the dense kernels)
+            const bool one = cnt == 1 && !ride && it0.sh.rows * (it0.sh.cols / 8) <= one_max_chunks(crit) && (strided || tensor_rows_fit(it0.sh, it0.o));
             int64_t all_tiles = 0;
             for (int k = 0; k < cnt; ++k) {
                 const BatchItem& it = items[idx[k]];

@@ -1,4 +1,4 @@
-"""A small per-tensor operand alone in its call: operands that end inside a wave of the amax pass.  Under Eq. 2 with a BF16 output that
+"""A small per-tensor operand alone in its call.  Most tests here: operands that end inside a wave of the amax pass.  Under Eq. 2 with a BF16 output that
 pass also counts elements that are certain to flush, against the amax of a whole wave: lanes beyond the operand's end take part in that
 reduction and bring nothing, and the amax itself comes from every lane that holds data."""
 import numpy as np
@@ -75,3 +75,32 @@ def test_all_zero(rows, cols, pad):
         out = _run(B, B.make_params(rows, cols, "tensor", ld=cols + pad), xd, fake)
         assert float(out.amax[0]) == 0.0 and float(out.scale[0]) == 1.0 and int(out.nnz[0]) == 0 and int(out.mask[0]) == 0
     parity.compare(x, "tensor", cols=cols)
+
+
+# 2^22 elements and more do not fit the rows of the kernels for lone operands; 2^23 are as many as those take
+@pytest.mark.parametrize("cols", [(1 << 22) - 8, 1 << 22, (1 << 22) + 8, 5000 * 1000, 1 << 23])
+@pytest.mark.parametrize("kind", ["normal", "grad"])
+def test_one_long_row(cols, kind):
+    """The same bits, and the same proof of a BF16 decision, as in rows of eight and as beside another operand."""
+    import parity
+    from paper_2512_22804_amd import binding as B
+    x = W.gradient(1, -(-cols // 128) * 128, 8)[:, :cols].copy() if kind == "grad" else W.outlier_normal(1, cols, 8)
+    xd = parity.to_dev(x)
+    p, short = B.make_params(1, cols, "tensor"), B.make_params(cols // 8, 8, "tensor")
+
+    def call(*operands):
+        entries = []
+        for q in operands:
+            st = torch.full((B.STATS_BYTES,), 0xEE, dtype=torch.uint8, device=xd.device)
+            entries.append((q, xd, B.alloc_outputs(q, xd.device, bf16_fill=0), st))
+        items = B.make_batch(entries)
+        B.mor_analyze_quantize_batch(items, 1e-5, torch.empty(B.mor_batch_workspace_bytes(items), dtype=torch.uint8, device=xd.device))
+        torch.cuda.synchronize()
+        return entries[0][2], B.read_stats(entries[0][3])
+    alone, stats = call(p)
+    for other, other_stats in (call(short), call(p, p)):
+        for k in ("fp8", "bf16", "scale", "amax", "err_sum", "nnz", "mask"):
+            assert torch.equal(getattr(alone, k).flatten(), getattr(other, k).flatten()), k
+        assert stats == other_stats
+    assert int(alone.mask[0]) == (kind == "grad") and stats["flags"] == (B.MOR_STATS_FLAG_FUSED_FALLBACK if kind == "grad" else 0)
+    parity.compare(x, "tensor")
