@@ -1111,6 +1111,22 @@ __device__ __forceinline__ int64_t tensor_chunk_off(const TensorOp& t, int64_t c
 // pass (2 more bytes read per element) is skipped.  The outputs are the same either way.
 // Workgroups from `stats_first` on do not belong to pass A: they compute the partial statistics records of the batch's
 // sub-tensor operands (whose kernels have already run), in the shadow of this bandwidth-bound pass.
+// Elements among CH chunks that are certain to flush, `bound2` (both half-words) being the amax or a lower bound of it.
+template <int CH>
+__device__ __forceinline__ uint32_t certain_flushes(const u32x4 (&v)[CH], uint32_t bound2) {
+    // t = bound with 20 taken off the exponent (0 if that underflows); 1 <= m < t  <=>  m-1 < t-1
+    const uint32_t t2 = pk_sub_sat_u16(bound2, 0x0A000A00u);
+    const uint32_t tm1 = pk_sub_sat_u16(t2, 0x00010001u);
+    uint32_t keep2 = 0u;                       // per half-word: elements NOT certain to flush
+#pragma unroll
+    for (int u = 0; u < CH; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t mm1 = pk_sub_u16(v[u][j] & 0x7FFF7FFFu, 0x00010001u);     // wraps to 0xFFFF for zeros
+            keep2 = pk_add_u16(keep2, pk_is_zero_u16(pk_sub_sat_u16(tm1, mm1)));
+        }
+    return 8u * CH - fold_add16(keep2);
+}
 template <bool STRIDED, int CH, class G>
 __device__ __forceinline__ void tensor_amax_body(const G& g, int block) {
     constexpr int kTile = 256 * CH;
@@ -1164,18 +1180,7 @@ __device__ __forceinline__ void tensor_amax_body(const G& g, int block) {
                 // (tiles of a few chunks per lane: the wave's amax, the lane's alone would be a weak bound; all lanes are here)
                 uint32_t bound2 = a2;
                 if constexpr (kSmall) { const uint32_t a = wave_allmax_u32(fold_max16(a2)); bound2 = a | (a << 16); }
-                // t = running amax with 20 taken off the exponent (0 if that underflows); 1 <= m < t  <=>  m-1 < t-1
-                const uint32_t t2 = pk_sub_sat_u16(bound2, 0x0A000A00u);
-                const uint32_t tm1 = pk_sub_sat_u16(t2, 0x00010001u);
-                uint32_t keep2 = 0u;                       // per half-word: elements of this tile NOT certain to flush
-#pragma unroll
-                for (int u = 0; u < CH; ++u)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const uint32_t mm1 = pk_sub_u16(v[u][j] & 0x7FFF7FFFu, 0x00010001u);     // wraps to 0xFFFF for zeros
-                        keep2 = pk_add_u16(keep2, pk_is_zero_u16(pk_sub_sat_u16(tm1, mm1)));
-                    }
-                flushed += 8u * CH - fold_add16(keep2);        // widened tile by tile: 16 bits would hold 2047 tiles of a workgroup
+                flushed += certain_flushes<CH>(v, bound2);     // widened tile by tile: 16 bits would hold 2047 tiles of a workgroup
             }
         } else {
             for (int u = 0; u < CH; ++u)
@@ -1484,10 +1489,56 @@ __device__ __forceinline__ float agent_load(const float* p) { return __hip_atomi
 template <class T>
 __device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__global__ __launch_bounds__(256) void k_tensor_amax_one(OneTensor g) {
-    uint32_t* sync = one_sync(g.op[0]);
-    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < (uint32_t)kOneSyncWords; i += gridDim.x * 256u) sync[i] = 0u;
+__device__ __forceinline__ void clear_one_sync(const TensorOp& t) {
+    uint32_t* sync = one_sync(t);
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < (uint32_t)kOneSyncWords; i += gridDim.x * blockDim.x) sync[i] = 0u;
+}
+__global__ __launch_bounds__(256) void k_tensor_amax_one(OneTensor g) {      // padded rows
+    clear_one_sync(g.op[0]);
     tensor_amax_body<true, kSmallChunksPerThread>(g, (int)blockIdx.x);
+}
+// Dense rows: a workgroup takes a tile of the grouped kernels and counts certain flushes as they do, so that the proof (which the statistics
+// report, and which leaves out a lean operand's payload) does not depend on the kernel: a chunk's bound is the amax of the eight chunks that
+// one lane of theirs takes, here spread over Q lanes that exchange it, and counted are lanes whose eight chunks all exist.
+template <int T, int CH>
+__global__ __launch_bounds__(T) void k_tensor_amax_one_dense(OneTensor g) {
+    constexpr int Q = T / 256, NW = T / 64;
+    static_assert(T * CH == kTensorChunksPerBlock, "a tile of the grouped kernels");
+    __shared__ uint32_t lane_max[Q][256], sha[NW], shm[NW], shf[NW];
+    const TensorOp& t = g.op[0];
+    clear_one_sync(t);
+    const int tid = threadIdx.x, w = tid >> 6, q = tid >> 8, l = tid & 255;
+    const int64_t c_first = (int64_t)blockIdx.x * kTensorChunksPerBlock;
+    const uint32_t valid = (uint32_t)(t.n_chunks - c_first < kTensorChunksPerBlock ? t.n_chunks - c_first : kTensorChunksPerBlock);
+    const BufRsrc rx = make_buf(t.x + c_first * 8);
+    const uint32_t first = (uint32_t)(q * CH * 256 + l);                            // this lane's first chunk in the tile, then 256 further
+    u32x4 v[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) v[u] = buf_load16_first<true>(rx, off_if(first + u * 256u < valid, (first + u * 256u) * 16u), 0u);
+    uint32_t a2 = 0u, mn2 = 0xFFFFFFFFu, flushed = 0u;
+#pragma unroll
+    for (int u = 0; u < CH; ++u) a2 = amax2_of(v[u], a2);
+    if (t.three) {
+#pragma unroll
+        for (int u = 0; u < CH; ++u) mn2 = min_nonzero_m1(v[u], mn2);
+    }
+    if (t.flush_need != 0ull) {
+        lane_max[q][l] = a2;
+        __syncthreads();
+        uint32_t bound2 = 0u;
+#pragma unroll
+        for (int k = 0; k < Q; ++k) bound2 = pk_max_u16(bound2, lane_max[k][l]);
+        flushed = (uint32_t)l + (kTensorChunksPerThread - 1) * 256u < valid ? certain_flushes<CH>(v, bound2) : 0u;
+    }
+    const uint32_t a_w = wave_allmax_u32(fold_max16(a2)), m_w = wave_allmax_u32(0xFFFFu - fold_min16(mn2)), f_w = wave_allsum_u32(flushed);
+    if ((tid & 63) == 0) { sha[w] = a_w; shm[w] = m_w; shf[w] = f_w; }
+    __syncthreads();
+    if (tid != 0) return;
+    uint32_t a = 0u, m = 0u, f = 0u;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) { a = max(a, sha[k]); m = max(m, shm[k]); f += shf[k]; }
+    t.amax_part[blockIdx.x] = a | (t.three ? (0xFFFFu - m) << 16 : 0u);
+    t.flush_part[blockIdx.x] = f;
 }
 // Quantizes 8 values; the terms come out one by one, for a chain of additions that another lane has begun.
 template <bool E5M2, bool FAKE>
@@ -2484,6 +2535,8 @@ void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_p
 // (4096 x 4096, beyond: three launches, 23.1.)
 constexpr int64_t one_max_chunks(int crit) { return crit == kCritEq3 ? 1 << 19 : 1 << 20; }      // (Eq. 3 with eight chunks per lane does not fit the registers)
 constexpr int64_t kOnePadded2 = 1 << 18, kOneShared = 1 << 19;
+constexpr int kDenseAmaxLanes = 512;      // us per call at 256 / 512 / 1024 lanes: 1024 x 1024 11.60 / 11.57 / 11.74, 2048 x 4096 15.3 / 15.2 / 15.5
+static_assert(one_max_chunks(kCritEq2) <= (int64_t)kAmaxOneTile * kTensorChunksPerBlock, "a workgroup per dense tile");
 static_assert(kOnePadded2 <= (int64_t)kOneMaxSlots * 512 && kOneShared <= (int64_t)kOneMaxSlots * 1024 && one_max_chunks(kCritEq2) <= (int64_t)kOneMaxSlots * 2048,
               "a slot per tile");
 struct OneShape {
@@ -2505,15 +2558,21 @@ void launch_one_quant(const OneTensor& o, const OneShape& s, int slots, hipStrea
 void launch_one_tensor(const TensorOp& t, float near_tol, int crit, bool fake, hipStream_t st, KProf* prof) {
     OneTensor o;
     o.n = 1; o.near_tol = near_tol; o.op[0] = t;
-    const OneShape s = one_shape(t.n_chunks, (t.flags & kTensorReport) != 0u);
+    const bool dense = (t.flags & kTensorReport) != 0u;
+    const OneShape s = one_shape(t.n_chunks, dense);
     const int slots = (int)((t.n_chunks + s.lanes * s.chunks - 1) / (s.lanes * s.chunks));
     TensorOp& a = o.op[0];
-    a.n_tiles = (a.n_chunks + 256 * kSmallChunksPerThread - 1) / (256 * kSmallChunksPerThread);      // pass A's tiles
+    const int amax_tile = dense ? kTensorChunksPerBlock : 256 * kSmallChunksPerThread;
+    a.n_tiles = (a.n_chunks + amax_tile - 1) / amax_tile;      // pass A's tiles
     a.n_amax = (int)(a.n_tiles < kAmaxOneTile ? a.n_tiles : kAmaxOneTile);
     a.keep_from = 0;
     a.n_slots = slots;
     o.amax_end[0] = a.n_amax; o.slot_end[0] = slots; o.copy_end[0] = 0;
-    { ProfScope ps(prof, kKernTensorAmax, st); k_tensor_amax_one<<<dim3(a.n_amax), dim3(256), 0, st>>>(o); }
+    {
+        ProfScope ps(prof, kKernTensorAmax, st);
+        if (dense) k_tensor_amax_one_dense<kDenseAmaxLanes, kTensorChunksPerBlock / kDenseAmaxLanes><<<dim3(a.n_amax), dim3(kDenseAmaxLanes), 0, st>>>(o);
+        else k_tensor_amax_one<<<dim3(a.n_amax), dim3(256), 0, st>>>(o);
+    }
     a.n_tiles = slots;
     ProfScope ps(prof, kKernTensorQuant, st);
     if (fake) {

@@ -104,3 +104,41 @@ def test_one_long_row(cols, kind):
         assert stats == other_stats
     assert int(alone.mask[0]) == (kind == "grad") and stats["flags"] == (B.MOR_STATS_FLAG_FUSED_FALLBACK if kind == "grad" else 0)
     parity.compare(x, "tensor")
+
+
+# small values in whole lanes (chunk modulo 256) of the amax pass have no large neighbour in their lane: no flush is certain, whatever their
+# wave holds; small values in single chunks have one
+@pytest.mark.parametrize("rows, cols", [(1, 2400), (128, 128), (255, 72), (600, 1000), (1024, 1024), (1500, 2880), (2048, 4096)])
+@pytest.mark.parametrize("kind", ["lanes", "chunks", "few"])
+def test_proof_alone_as_in_a_batch(rows, cols, kind):
+    """The proof of a BF16 decision, which the statistics report and which leaves out a lean operand's payload."""
+    import parity
+    from paper_2512_22804_amd import binding as B
+    n = rows * cols // 8
+    x = _normal(rows, cols, cols, 11)
+    chunks = x.reshape(n, 8)
+    at = np.arange(n)
+    small = at % 8 == 5 if kind == "lanes" else at // 256 % 8 == 3 if kind == "chunks" else at % 293 < 14
+    chunks[small] = (chunks[small] & 0x8000) | 0x0110
+    xd = parity.to_dev(x)
+    p = B.make_params(rows, cols, "tensor", lean_fp8=True)
+
+    def call(k):
+        entries = []
+        for _ in range(k):
+            out = B.alloc_outputs(p, xd.device, bf16_fill=0)
+            out.fp8.fill_(0xA7)
+            entries.append((p, xd, out, torch.full((B.STATS_BYTES,), 0xEE, dtype=torch.uint8, device=xd.device)))
+        items = B.make_batch(entries)
+        B.mor_analyze_quantize_batch(items, 1e-5, torch.empty(B.mor_batch_workspace_bytes(items), dtype=torch.uint8, device=xd.device))
+        torch.cuda.synchronize()
+        return entries[0][2], B.read_stats(entries[0][3])
+    (alone, stats), (beside, beside_stats) = call(1), call(2)
+    assert stats == beside_stats
+    for k in ("fp8", "bf16", "scale", "amax", "err_sum", "nnz", "mask"):
+        assert torch.equal(getattr(alone, k), getattr(beside, k)), k
+    proven = stats["flags"] == B.MOR_STATS_FLAG_FUSED_FALLBACK
+    assert bool((alone.fp8 == 0xA7).all()) == proven
+    assert int(alone.mask[0]) == bool(small.any())
+    if kind != "few":
+        assert proven == (kind == "chunks" and n >= 2048)
