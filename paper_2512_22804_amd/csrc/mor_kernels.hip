@@ -1489,12 +1489,13 @@ __device__ __forceinline__ float agent_load(const float* p) { return __hip_atomi
 template <class T>
 __device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+template <int T>             // lanes of the workgroup (as a constant: blockDim is read from memory, 0.25 us)
 __device__ __forceinline__ void clear_one_sync(const TensorOp& t) {
     uint32_t* sync = one_sync(t);
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < (uint32_t)kOneSyncWords; i += gridDim.x * blockDim.x) sync[i] = 0u;
+    for (uint32_t i = blockIdx.x * (uint32_t)T + threadIdx.x; i < (uint32_t)kOneSyncWords; i += gridDim.x * (uint32_t)T) sync[i] = 0u;
 }
 __global__ __launch_bounds__(256) void k_tensor_amax_one(OneTensor g) {      // padded rows
-    clear_one_sync(g.op[0]);
+    clear_one_sync<256>(g.op[0]);
     tensor_amax_body<true, kSmallChunksPerThread>(g, (int)blockIdx.x);
 }
 // Dense rows: a workgroup takes a tile of the grouped kernels and counts certain flushes as they do, so that the proof (which the statistics
@@ -1506,7 +1507,7 @@ __global__ __launch_bounds__(T) void k_tensor_amax_one_dense(OneTensor g) {
     static_assert(T * CH == kTensorChunksPerBlock, "a tile of the grouped kernels");
     __shared__ uint32_t lane_max[Q][256], sha[NW], shm[NW], shf[NW];
     const TensorOp& t = g.op[0];
-    clear_one_sync(t);
+    clear_one_sync<T>(t);
     const int tid = threadIdx.x, w = tid >> 6, q = tid >> 8, l = tid & 255;
     const int64_t c_first = (int64_t)blockIdx.x * kTensorChunksPerBlock;
     const uint32_t valid = (uint32_t)(t.n_chunks - c_first < kTensorChunksPerBlock ? t.n_chunks - c_first : kTensorChunksPerBlock);
@@ -2535,7 +2536,7 @@ void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_p
 // (4096 x 4096, beyond: three launches, 23.1.)
 constexpr int64_t one_max_chunks(int crit) { return crit == kCritEq3 ? 1 << 19 : 1 << 20; }      // (Eq. 3 with eight chunks per lane does not fit the registers)
 constexpr int64_t kOnePadded2 = 1 << 18, kOneShared = 1 << 19;
-constexpr int kDenseAmaxLanes = 512;      // us per call at 256 / 512 / 1024 lanes: 1024 x 1024 11.60 / 11.57 / 11.74, 2048 x 4096 15.3 / 15.2 / 15.5
+constexpr int kDenseAmaxLanes = 512;      // us per call at 256 / 512 / 1024 lanes, less 0.4 since: 1024 x 1024 11.60 / 11.57 / 11.74, 2048 x 4096 15.3 / 15.2 / 15.5
 static_assert(one_max_chunks(kCritEq2) <= (int64_t)kAmaxOneTile * kTensorChunksPerBlock, "a workgroup per dense tile");
 static_assert(kOnePadded2 <= (int64_t)kOneMaxSlots * 512 && kOneShared <= (int64_t)kOneMaxSlots * 1024 && one_max_chunks(kCritEq2) <= (int64_t)kOneMaxSlots * 2048,
               "a slot per tile");
