@@ -142,3 +142,15 @@ def test_proof_alone_as_in_a_batch(rows, cols, kind):
     assert int(alone.mask[0]) == bool(small.any())
     if kind != "few":
         assert proven == (kind == "chunks" and n >= 2048)
+
+
+# rows of 2^22 elements: chunk by chunk; 2^18 chunks, one more, 2^19 and one more
+@pytest.mark.parametrize("chunks", [(1 << 18), (1 << 18) + 1, 1 << 19, (1 << 19) + 1])
+@pytest.mark.parametrize("crit, formats, kind", [("mean_rel_err", "e4m3|bf16", "normal"), ("mean_rel_err", "e4m3|bf16", "grad"),
+                                                 ("e4m3_vs_e5m2", "e4m3|bf16", "grad"), ("e4m3_vs_e5m2", "e4m3|e5m2|bf16", "grad")])
+def test_rows_beyond_the_row_map(chunks, crit, formats, kind):
+    import parity
+    cols, ld = 8 * chunks, (1 << 22) + 128
+    x = W.gradient(1, ld, 9) if kind == "grad" else W.outlier_normal(1, ld, 9)
+    parity.compare(x, "tensor", crit=crit, formats=formats, cols=cols)
+    parity.compare_fake(x, "tensor", crit=crit, formats=formats, cols=cols)
