@@ -134,6 +134,7 @@ static mor_status make_item(const mor_params* p, const uint16_t* x, const mor_ou
     item->lean = ((p->flags & MOR_FLAG_LEAN_FP8) && !fake_y) ? 1 : 0;
     item->th = p->threshold;
     item->stats = stats;
+    item->polls = mor::kOnePolls;
     return MOR_OK;
 }
 
@@ -312,6 +313,24 @@ mor_status mor_histogram_update(uint32_t* hist12_dev, const mor_stats* stats_dev
     const int clear = (reset_interval > 0 && step % reset_interval == 0) ? 1 : 0;
     hipError_t e = mor::launch_histogram_update(hist12_dev, stats_dev, clear, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? MOR_OK : MOR_ERR_HIP;
+}
+
+// Not part of the interface (mor.h does not declare it): mor_analyze_quantize, or mor_fake_quantize where `y` is set, with the number of
+// times that a workgroup of a lone per-tensor operand looks for the decision before it leaves its tile to the one that decides.  With 0 the
+// tests see that path, which takes a full chip otherwise.  `left` receives where the workspace keeps a word per workgroup that left: byte
+// offset, number of words.
+mor_status mor_test_lone_tensor(const mor_params* p, const uint16_t* x, const mor_outputs* out, uint16_t* y, int64_t ld_y, void* workspace,
+                                size_t workspace_bytes, void* stream, int32_t polls, int64_t* left) {
+    if (!left || polls < 0 || polls > mor::kOnePolls) return MOR_ERR_UNSUPPORTED;
+    mor::BatchItem it{};
+    mor_status st = make_item(p, x, out, nullptr, y, ld_y, &it);
+    if (st != MOR_OK) return st;
+    if (it.gran != MOR_GRAN_TENSOR) return MOR_ERR_UNSUPPORTED;
+    it.polls = polls;
+    const mor::LeftWords w = mor::lone_tensor_left_words();
+    left[0] = (int64_t)w.offset;
+    left[1] = w.count;
+    return run_batch(&it, 1, 0.0f, workspace, workspace_bytes, stream, nullptr);
 }
 
 const char* mor_status_string(mor_status s) {

@@ -1480,7 +1480,6 @@ constexpr int kOneLine = 32;                 // words: a line of its own for eve
 constexpr int kTicketRoot = kOneMaxSlots / kTicketGroup * kOneLine;
 constexpr int kToldCopies = 32;              // of the decision, so that few workgroups look at one line
 constexpr int kOneTold = kTicketRoot + kOneLine, kOneLeft = kOneTold + kToldCopies * kOneLine, kOneSyncWords = kOneLeft + kOneMaxSlots;
-constexpr int kOnePolls = 1024;              // about half a millisecond
 enum : uint32_t { kToldNothing = 0u, kToldMask = 1u };      // kToldMask + the mask
 static_assert(8192 + kOneSyncWords <= kMaxQuantBlocks && kOneMaxSlots <= 8192, "the words lie behind the zero counts in their array");
 __device__ __forceinline__ uint32_t* one_sync(const TensorOp& t) { return t.zero + 8192; }
@@ -1582,7 +1581,7 @@ __device__ __forceinline__ u32x2 quant8_dual_terms(const u32x4& raw, float s, fl
 // T lanes with CH chunks each.  Dense operands: a tile is the 2048 chunks that 256 lanes take in the grouped kernels, and the sums are
 // those of the grouped kernels bit for bit: two lanes that hold a chain of additions in halves hand it on through shared memory.
 template <int CRIT, bool FAKE, int T, int CH>
-__global__ __launch_bounds__(T, 4) void k_tensor_quant_one(OneTensor g) {
+__global__ __launch_bounds__(T, 4) void k_tensor_quant_one(OneTensor g, int polls) {
     constexpr int Q = T / 256, NW = T / 64, kTile = T * CH;
     __shared__ float4 run[256];
     __shared__ float shf[8];
@@ -1742,7 +1741,7 @@ __global__ __launch_bounds__(T, 4) void k_tensor_quant_one(OneTensor g) {
         if (!open) return;
         if (tid == 0) {
             uint32_t told = kToldNothing;
-            for (int poll = 0; poll < kOnePolls && told == kToldNothing; ++poll) {
+            for (int poll = 0; poll < polls && told == kToldNothing; ++poll) {
                 told = agent_load(told_at);
                 if (told == kToldNothing) __builtin_amdgcn_s_sleep(8);
             }
@@ -1927,6 +1926,8 @@ TensorPlan plan_tensor(int64_t, int64_t) {
     pl.bytes = off;
     return pl;
 }
+
+LeftWords lone_tensor_left_words() { return {plan_tensor(0, 0).off_nnz_part + sizeof(uint32_t) * (8192 + kOneLeft), kOneMaxSlots}; }
 
 size_t scope_workspace_bytes(int64_t) { return align16(3 * sizeof(double) * kScopeBlocks + 16); }
 
@@ -2552,15 +2553,15 @@ OneShape one_shape(int64_t n_chunks, bool dense, bool wide) {
     return wide ? OneShape{512, 2} : OneShape{256, 4};
 }
 template <int CRIT, bool FAKE>
-void launch_one_quant(const OneTensor& o, const OneShape& s, int slots, hipStream_t st) {
+void launch_one_quant(const OneTensor& o, const OneShape& s, int slots, int polls, hipStream_t st) {
     const dim3 grid(slots), block(s.lanes);
-    if (s.lanes == 512 && s.chunks == 2) k_tensor_quant_one<CRIT, FAKE, 512, 2><<<grid, block, 0, st>>>(o);
-    else if (s.lanes == 512) k_tensor_quant_one<CRIT, FAKE, 512, 4><<<grid, block, 0, st>>>(o);
-    else if (s.chunks == 2) k_tensor_quant_one<CRIT, FAKE, 256, 2><<<grid, block, 0, st>>>(o);
-    else if (CRIT == kCritEq3 || s.chunks == 4) k_tensor_quant_one<CRIT, FAKE, 256, 4><<<grid, block, 0, st>>>(o);
-    else if constexpr (CRIT == kCritEq2) k_tensor_quant_one<CRIT, FAKE, 256, 8><<<grid, block, 0, st>>>(o);
+    if (s.lanes == 512 && s.chunks == 2) k_tensor_quant_one<CRIT, FAKE, 512, 2><<<grid, block, 0, st>>>(o, polls);
+    else if (s.lanes == 512) k_tensor_quant_one<CRIT, FAKE, 512, 4><<<grid, block, 0, st>>>(o, polls);
+    else if (s.chunks == 2) k_tensor_quant_one<CRIT, FAKE, 256, 2><<<grid, block, 0, st>>>(o, polls);
+    else if (CRIT == kCritEq3 || s.chunks == 4) k_tensor_quant_one<CRIT, FAKE, 256, 4><<<grid, block, 0, st>>>(o, polls);
+    else if constexpr (CRIT == kCritEq2) k_tensor_quant_one<CRIT, FAKE, 256, 8><<<grid, block, 0, st>>>(o, polls);
 }
-void launch_one_tensor(const TensorOp& t, float near_tol, int crit, bool fake, hipStream_t st, KProf* prof) {
+void launch_one_tensor(const TensorOp& t, float near_tol, int crit, bool fake, int polls, hipStream_t st, KProf* prof) {
     OneTensor o;
     o.n = 1; o.near_tol = near_tol; o.op[0] = t;
     const bool dense = (t.flags & kTensorReport) != 0u;
@@ -2581,11 +2582,11 @@ void launch_one_tensor(const TensorOp& t, float near_tol, int crit, bool fake, h
     a.n_tiles = slots;
     ProfScope ps(prof, kKernTensorQuant, st);
     if (fake) {
-        if (crit == kCritEq3) launch_one_quant<kCritEq3, true>(o, s, slots, st);
-        else launch_one_quant<kCritEq2, true>(o, s, slots, st);
+        if (crit == kCritEq3) launch_one_quant<kCritEq3, true>(o, s, slots, polls, st);
+        else launch_one_quant<kCritEq2, true>(o, s, slots, polls, st);
     } else {
-        if (crit == kCritEq3) launch_one_quant<kCritEq3, false>(o, s, slots, st);
-        else launch_one_quant<kCritEq2, false>(o, s, slots, st);
+        if (crit == kCritEq3) launch_one_quant<kCritEq3, false>(o, s, slots, polls, st);
+        else launch_one_quant<kCritEq2, false>(o, s, slots, polls, st);
     }
 }
 void BatchRun::per_tensor_operands(int crit) {
@@ -2669,7 +2670,7 @@ void BatchRun::per_tensor_operands(int crit) {
                 ride_final = ride_partial > riders.n ? riders.n : 0;      // single-workgroup operands are final already
                 riders_used = true;
             }
-            if (one) launch_one_tensor(g.op[0], near_tol, crit, fake, st, prof);
+            if (one) launch_one_tensor(g.op[0], near_tol, crit, fake, it0.polls, st, prof);
             else if (strided) launch_tensor_passes<true>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             else launch_tensor_passes<false>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             cnt = 0;

@@ -163,7 +163,15 @@ struct BatchItem {
     float th;
     void* stats;            // device mor_stats* or nullptr
     int64_t group_rows;     // GAM: 0 = one group (the whole operand); else the groups of Algorithm 1 are bands of this many rows
+    int polls;              // how often a workgroup of a lone per-tensor operand looks for the decision before it leaves its tile to another
 };
+constexpr int kOnePolls = 1024;      // about half a millisecond
+// Where such a call with the workspace of one operand keeps the words of the workgroups that left (for tests): bytes from its start, words.
+struct LeftWords {
+    size_t offset;
+    int count;
+};
+LeftWords lone_tensor_left_words();
 size_t batch_workspace_bytes(const BatchItem* items, int n);
 hipError_t launch_batch(const BatchItem* items, int n, float near_tol, void* ws, size_t ws_bytes, hipStream_t st, KProf* prof);
 
