@@ -2544,28 +2544,28 @@ static_assert(kOnePadded2 <= (int64_t)kOneMaxSlots * 512 && kOneShared <= (int64
 struct OneShape {
     int lanes, chunks;
 };
-// (Rows too long for a RowMap are taken chunk by chunk, a chain of latencies per lane: 1 x 4 194 296 in rows of 4 194 360 elements, kept in
-// E4M3, 19.9 us per call with two chunks per lane, 24.1 with four, 20.5 with three launches.)
-OneShape one_shape(int64_t n_chunks, bool dense, bool wide) {
+// Padded rows, two chunks per lane up to kOneShared: with 256 x 4 above kOnePadded2 the ordinary path takes the same time (768 x 4096 12.2 us
+// both), but one that goes chunk by chunk, a chain of latencies per lane, takes longer than with three launches: rows too long for a
+// RowMap (1 x 4 194 296) 19.9 us with two chunks, 24.1 with four, 20.5 with three launches; 768 x 4096 with an infinity, Eq. 3, 20.6, 24.3, 22.0.
+OneShape one_shape(int64_t n_chunks, bool dense) {
     if (n_chunks > kOneShared) return {256, 8};
     if (dense) return {512, 4};
     if (n_chunks <= kOnePadded2) return {256, 2};
-    return wide ? OneShape{512, 2} : OneShape{256, 4};
+    return {512, 2};
 }
 template <int CRIT, bool FAKE>
 void launch_one_quant(const OneTensor& o, const OneShape& s, int slots, int polls, hipStream_t st) {
     const dim3 grid(slots), block(s.lanes);
-    if (s.lanes == 512 && s.chunks == 2) k_tensor_quant_one<CRIT, FAKE, 512, 2><<<grid, block, 0, st>>>(o, polls);
-    else if (s.lanes == 512) k_tensor_quant_one<CRIT, FAKE, 512, 4><<<grid, block, 0, st>>>(o, polls);
+    if (s.lanes == 512 && s.chunks == 4) k_tensor_quant_one<CRIT, FAKE, 512, 4><<<grid, block, 0, st>>>(o, polls);
+    else if (s.lanes == 512) k_tensor_quant_one<CRIT, FAKE, 512, 2><<<grid, block, 0, st>>>(o, polls);
     else if (s.chunks == 2) k_tensor_quant_one<CRIT, FAKE, 256, 2><<<grid, block, 0, st>>>(o, polls);
-    else if (CRIT == kCritEq3 || s.chunks == 4) k_tensor_quant_one<CRIT, FAKE, 256, 4><<<grid, block, 0, st>>>(o, polls);
     else if constexpr (CRIT == kCritEq2) k_tensor_quant_one<CRIT, FAKE, 256, 8><<<grid, block, 0, st>>>(o, polls);
 }
 void launch_one_tensor(const TensorOp& t, float near_tol, int crit, bool fake, int polls, hipStream_t st, KProf* prof) {
     OneTensor o;
     o.n = 1; o.near_tol = near_tol; o.op[0] = t;
     const bool dense = (t.flags & kTensorReport) != 0u;
-    const OneShape s = one_shape(t.n_chunks, dense, t.rm.cpr == 0u);
+    const OneShape s = one_shape(t.n_chunks, dense);
     const int slots = (int)((t.n_chunks + s.lanes * s.chunks - 1) / (s.lanes * s.chunks));
     TensorOp& a = o.op[0];
     const int amax_tile = dense ? kTensorChunksPerBlock : 256 * kSmallChunksPerThread;

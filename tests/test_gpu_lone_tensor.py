@@ -154,3 +154,15 @@ def test_rows_beyond_the_row_map(chunks, crit, formats, kind):
     x = W.gradient(1, ld, 9) if kind == "grad" else W.outlier_normal(1, ld, 9)
     parity.compare(x, "tensor", crit=crit, formats=formats, cols=cols)
     parity.compare_fake(x, "tensor", crit=crit, formats=formats, cols=cols)
+
+
+@pytest.mark.parametrize("rows", [512, 513, 1023, 1024, 1025])      # 4096 of 4104 columns: two chunks per lane of 256, of 512, eight of 256
+@pytest.mark.parametrize("crit", ["mean_rel_err", "e4m3_vs_e5m2"])
+@pytest.mark.parametrize("special", [None, 0x7F80, 0xFFC1])
+def test_padded_rows_at_the_edges_of_the_shapes(rows, crit, special):
+    import parity
+    x = W.outlier_normal(rows, 4104, 12)
+    if special is not None:
+        x[rows // 2, 4095] = special
+    parity.compare(x, "tensor", crit=crit, cols=4096)
+    parity.compare_fake(x, "tensor", crit=crit, cols=4096)

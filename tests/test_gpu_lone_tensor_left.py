@@ -9,7 +9,7 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
-# threads x chunks of the kernels: 512 x 4 (dense), 256 x 8, 256 x 2, 256 x 4, 512 x 2 (rows beyond the row map)
+# threads x chunks of the kernels: 512 x 4 (dense), 256 x 8, 512 x 4 (one tile), 256 x 2, 512 x 2, 256 x 8, 512 x 2 (rows beyond the row map)
 OPERANDS = [(1000, 1048, 0), (2048, 4096, 0), (1, 8, 0), (1000, 1048, 8), (700, 4096, 4096), (1500, 4096, 64), (1, 2500000, 1700000)]
 
 
