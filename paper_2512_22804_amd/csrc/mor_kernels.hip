@@ -2455,7 +2455,7 @@ void BatchRun::tensor_level_decisions() {
         if (column_tensor_proof_applies(it)) t.proven = column_tensor_proven_word(col_ws[i], it.sh.rows, it.sh.cols);
         t.col = ColumnSums{};
         if (it.gran == kGranCol) t.col = column_sums_of(col_ws[i], it.sh.rows, it.sh.cols, it.o.amax);
-        int64_t want = it.gran == kGranCol ? (t.n_part + 255) / 256 : (t.n_part + 1023) / 1024;      // (a column is a sum over the strips)
+        int64_t want = t.col.n_strips ? (t.n_part + 255) / 256 : (t.n_part + 1023) / 1024;      // (a column is a sum over the strips)
         t.n_red = (int)(want < 1 ? 1 : (want > kScopeBlocks ? kScopeBlocks : want));
         t.stats = static_cast<StatsDev*>(it.stats);
         t.rec = it.stats ? reinterpret_cast<StatsRec*>(carve(sizeof(StatsRec) * kStatsMaxWg)) : nullptr;

@@ -252,8 +252,20 @@ inline int scope_copy_budget(int n_unproven, int64_t unproven_bytes) {
 struct ColumnSums {
     const float* err; const float* err5; const uint16_t* zero; const float* amax;
     int64_t cols_padded;
-    int32_t n_strips;        // 0: not per-channel columns
+    int32_t n_strips;        // 0: the block kernels have left the blocks' sums already
 };
+// A column's strips are read one after another (eight or sixteen loads in flight), so what a lane has to read sets the time of the step that
+// reads them where an operand is tall.  us per call, FP32 scales, weights:
+// Sums of a tensor-level decision, in its reduce pass / by a launch of their own before it: 8192 x 512 (64 strips) 24.0 / 25.6, 32768 x 1024
+// (128) 58.8 / 59.6, 16384 x 128 (128) 30.0 / 30.3, 32768 x 128 (256) 42.3 / 39.8, 131072 x 128 (1024) 152 / 138.
+constexpr int kStripsInReduce = 128;
+// Scales, by every workgroup of the quantize pass / by a launch of their own, which has nobody to share the reads with but costs a launch:
+// up to 128 strips the former takes less (32768 x 1024 59.6 / 61.3); beyond, it depends on how many workgroups repeat the reads, and on
+// whether the launch reads the flush counts of single columns as well: 65536 x 128 (512 workgroups) 63.1 / 65.8, 65536 x 256 (1024) 85.8 / 76.2,
+// with flush counts 83.6 / 91.3, 131072 x 128 139 / 145; two of 200000 x 128 with flush counts (1564) 175 / 154.
+inline bool column_scales_folded(int64_t n_strips, int64_t launch_workgroups, bool flush_counts) {
+    return n_strips <= 128 || launch_workgroups <= (flush_counts ? 1024 : 512);
+}
 ColumnSums column_sums_of(const char* column_workspace, int64_t rows, int64_t cols, const float* amax);
 uint32_t* column_tensor_proven_word(char* column_workspace, int64_t rows, int64_t cols);
 hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int cnt, int crit, const uint32_t* const* gam_of,

@@ -552,6 +552,7 @@ struct ColOp {
     uint8_t defer, mode, three, prove;   // prove: count certain flushes in the amax pass (see below)
     uint8_t derive_gam;
     uint8_t scaled;             // the scales have been formed by a launch of their own
+    uint8_t later;              // the tensor-level reduce pass adds up the strips' sums
     uint8_t keep;               // column-amax pass: the operand stays in the Infinity Cache for the quantize pass
     const uint32_t* gam;
     // per-channel columns: workspace, [n_strips x cols_padded] each, cols_padded = tiles_x * 128
@@ -1251,7 +1252,7 @@ __global__ __launch_bounds__(256) void k_col_finish(GroupCol g) {
     const ColOp& t = g.op[op];
     const int64_t c = (int64_t)(blockIdx.x - (op ? g.comb_end[op - 1] : 0)) * 256 + threadIdx.x;
     const int64_t cols_padded = t.tiles_x * 128;
-    if (c >= t.cols || t.defer) return;
+    if (c >= t.cols || t.later) return;
     double e = 0.0, e5 = 0.0;
     unsigned long long z = 0;
 #pragma unroll 8
@@ -1268,6 +1269,7 @@ __global__ __launch_bounds__(256) void k_col_finish(GroupCol g) {
     t.o.err_sum[c] = (float)e;
     t.o.nnz[c] = n > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)n;
     if constexpr (CRIT == kCritEq3) t.o.err5_sum[c] = (float)e5;
+    if (t.defer) return;
     uint32_t mk;
     if constexpr (CRIT == kCritEq3) mk = (e < e5) ? 0u : 1u;
     else mk = ((n ? e / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
@@ -1286,10 +1288,10 @@ __global__ __launch_bounds__(256) void k_col_finish(GroupCol g) {
     }
     t.o.mask[c] = (uint8_t)mk;
 }
-// Workgroups of a launch up to which each forms its columns' scales itself: 768 workgroups 88.3 -> 80.4 us per call, 1024
-// (14336 x 4096) 92.5 -> 83.2.  What they read for it grows with the product of the operands' strips and workgroups, and the launch
-// that it saves becomes a small part of the call (the 11 000 of a layer's twelve operands: 554 -> 542, 2 %): launches of several
-// large operands keep the sequence of five whose records callers and tests of the profile count on.
+// Workgroups of a launch up to which each forms its columns' scales itself (see also column_scales_folded): 768 workgroups 88.3 -> 80.4 us
+// per call, 1024 (14336 x 4096) 92.5 -> 83.2.  The line is not where that stops to pay: without it launches of several large operands would
+// take 2 to 4 % less (three of 4096 x 14336 162.7 us against 167.6, six 318 against 325; six of 4096 x 4096 1.5 % more).  It is there
+// because their sequence of five launches, as the profile of a call records it, is relied on.
 constexpr int64_t kColScaleWgs = 2048;
 // Columns kept in BF16 are copied: 16 bytes at a time where all eight columns of a chunk are kept, else by element.
 // Columns kept in E5M2 (three-way recipe) get their payload here, element by element, over the E4M3 one.
@@ -1539,6 +1541,7 @@ uint32_t* column_tensor_proven_word(char* ws, int64_t rows, int64_t cols) {
 }
 ColumnSums column_sums_of(const char* ws, int64_t rows, int64_t cols, const float* amax) {
     const ColPlan pl = plan_columns(rows, cols);
+    if (pl.n_strips > kStripsInReduce) return ColumnSums{};
     return ColumnSums{reinterpret_cast<const float*>(ws + pl.off_err), reinterpret_cast<const float*>(ws + pl.off_err5), reinterpret_cast<const uint16_t*>(ws + pl.off_zero),
                       amax, pl.cols_padded, pl.n_strips};
 }
@@ -1600,15 +1603,18 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
                 g.copy_end[k] = copy;
             }
             { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColAmax>(g, total, kCritEq2, false, edge, st); }
-            const bool scaled = total > kColScaleWgs;
-            bool three = false;
-            for (int k = 0; k < g.n; ++k) { three |= g.op[k].three != 0; g.op[k].scaled = scaled ? 1 : 0; }
+            bool scaled = total > kColScaleWgs, three = false;
+            for (int k = 0; k < g.n; ++k) {
+                three |= g.op[k].three != 0;
+                scaled |= !column_scales_folded(g.op[k].n_strips, total, g.op[k].prove && g.op[k].tensor_need == 0ull);
+            }
+            for (int k = 0; k < g.n; ++k) g.op[k].scaled = scaled ? 1 : 0;
             if (scaled) { ProfScope ps(prof, kKernColumnCombine, st); k_col_scales<<<dim3((unsigned)comb), dim3(256), 0, st>>>(g); }
             else if (three) { ProfScope ps(prof, kKernColumnCombine, st); k_col_amin<<<dim3((unsigned)comb), dim3(256), 0, st>>>(g); }
             { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColExternal>(g, total, crit, fake, edge, st); }
-            bool singly = false;      // some operand's columns are decided one by one; the others' sums are added up by the tensor-level reduce pass
-            for (int k = 0; k < g.n; ++k) singly |= !g.op[k].defer;
-            if (singly) {
+            bool sums = false;        // some operand's sums are not left to the tensor-level reduce pass
+            for (int k = 0; k < g.n; ++k) sums |= !g.op[k].later;
+            if (sums) {
                 ProfScope ps(prof, kKernColumnCombine, st);
                 if (crit == kCritEq3) k_col_finish<kCritEq3><<<dim3((unsigned)comb), dim3(256), 0, st>>>(g);
                 else k_col_finish<kCritEq2><<<dim3((unsigned)comb), dim3(256), 0, st>>>(g);
@@ -1631,6 +1637,7 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
             char* w = ws_of[k];
             t.tiles_per_strip = pl.tiles_per_strip;
             t.n_strips = pl.n_strips;
+            t.later = t.defer && pl.n_strips <= kStripsInReduce;
             t.part_amax = reinterpret_cast<uint16_t*>(w + pl.off_amax);
             t.part_err = reinterpret_cast<float*>(w + pl.off_err);
             t.part_err5 = reinterpret_cast<float*>(w + pl.off_err5);

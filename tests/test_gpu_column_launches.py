@@ -1,6 +1,7 @@
 """Per-channel columns: the quantize pass of a launch of at most 2048 workgroups forms the column scales itself, those of a larger one come
 from a launch of their own; a tensor-level decision takes its sums from the strips in the reduce pass of all such operands.  Sizes on
-both sides of the line and where the number of strips fills or crosses a round of 16 (scales) or 8 (sums) loads."""
+both sides of the line and where the number of strips fills or crosses a round of 16 (scales) or 8 (sums) loads.  Tall operands, whose strips take long to read one after another, get launches of their own for the sums
+and, where many workgroups would repeat the reads, for the scales."""
 import numpy as np
 import pytest
 import torch
@@ -57,3 +58,35 @@ def test_tensor_level_sums_with_and_without_statistics(oracle, rows, cols, crit)
     for k in ("n_part", "n_fp8_part", "n_bf16_part", "n_elem_fp8", "n_elem_bf16", "nnz_total", "hist", "n_near_threshold"):
         assert got[k] == want[k], k
     assert got["err_sum_total"] == pytest.approx(want["err_sum_total"], rel=1e-12)
+
+
+# 128 strips, 129 strips in 129 and in 645 workgroups, two operands of the latter
+@pytest.mark.parametrize("rows, cols, k, combines", [(16384, 128, 1, (0, 1)), (16385, 128, 1, (1, 1)), (16385, 640, 1, (2, 1)), (16385, 640, 2, (2, 2))])
+@pytest.mark.parametrize("crit, scaling", [("mean_rel_err", "gam"), ("mean_rel_err", "fp32_amax"), ("e4m3_vs_e5m2", "fp32_amax")])
+@pytest.mark.parametrize("scope", ["tensor", "partition"])
+def test_tall_columns(rows, cols, k, combines, crit, scaling, scope):
+    """combines: launches that combine strips (scales, sums) with a tensor-level decision, and with decisions and flush counts per column."""
+    import parity
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    for kind in ("normal", "grad"):
+        x = _input(rows, cols, kind)
+        xd = torch.from_numpy(x.view(np.int16)).to(dev)
+        p = B.make_params(rows, cols, "channel_col", scope, crit, scaling=scaling, ragged=True)
+        entries = [(p, xd, B.alloc_outputs(p, dev, bf16_fill=parity.FILL), torch.full((B.STATS_BYTES,), 0xEE, dtype=torch.uint8, device=dev)) for _ in range(k)]
+        items = B.make_batch(entries)
+        ev = B.HipEvents()
+        prof = ev.new_profile(B.MOR_PROFILE_MAX)
+        B.mor_analyze_quantize_batch(items, 1e-5, torch.full((B.mor_batch_workspace_bytes(items),), 0xA7, dtype=torch.uint8, device=dev), prof)
+        torch.cuda.synchronize()
+        names = [B.KERNEL_NAMES[prof.kernel[i]] for i in range(prof.count)]
+        ev.destroy()
+        counts = scope == "partition" and crit == "mean_rel_err"          # else a tall operand's scales are as with a tensor-level decision
+        want = combines[1] if counts else combines[0] + (1 if scope == "partition" and combines[0] == 0 else 0)
+        assert names.count("column_combine") == want, names
+        parity.compare(x, "channel_col", scope, crit, scaling=scaling, ragged=True, label=kind, gpu=(p, entries[0][2]))
+        for _, _, out, st in entries[1:]:
+            for name in ("fp8", "bf16", "scale", "amax", "err_sum", "nnz", "mask"):
+                assert torch.equal(getattr(out, name), getattr(entries[0][2], name)), name
+            assert torch.equal(st, entries[0][3])
+        parity.compare_fake(x[:, :128], "channel_col", scope, crit, scaling=scaling, ragged=True)
