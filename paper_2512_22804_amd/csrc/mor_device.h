@@ -132,27 +132,6 @@ __device__ __forceinline__ float rel_term(float y, float q) {
     return __builtin_amdgcn_fmed3f(__builtin_fabsf(d) * __builtin_amdgcn_rcpf(__builtin_fabsf(y)), 0.0f, 1.0f);
 }
 
-// Quantize 8 values with scale s; returns the 8 codes (little-endian element order) and adds
-// the 8 error terms to err0/err1.
-template <bool E5M2>
-__device__ __forceinline__ u32x2 quant8_fast(const u32x4& raw, float s, float& err0, float& err1) {
-    int w0 = 0, w1 = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        float y0 = __uint_as_float(raw[j] << 16) * s;
-        float y1 = __uint_as_float(raw[j] & 0xFFFF0000u) * s;
-        f32x2 q;
-        if (j == 0) { w0 = cvt_pk8<E5M2>(y0, y1, w0, false); q = cvt_pk_f32<E5M2>(w0, false); }
-        if (j == 1) { w0 = cvt_pk8<E5M2>(y0, y1, w0, true);  q = cvt_pk_f32<E5M2>(w0, true); }
-        if (j == 2) { w1 = cvt_pk8<E5M2>(y0, y1, w1, false); q = cvt_pk_f32<E5M2>(w1, false); }
-        if (j == 3) { w1 = cvt_pk8<E5M2>(y0, y1, w1, true);  q = cvt_pk_f32<E5M2>(w1, true); }
-        err0 += rel_term(y0, q.x);
-        err1 += rel_term(y1, q.y);
-    }
-    u32x2 r; r.x = (uint32_t)w0; r.y = (uint32_t)w1;
-    return r;
-}
-
 // binary32 -> BF16, round to nearest even; NaN -> quiet NaN with the sign kept.
 __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
     const uint32_t u = __float_as_uint(f);
@@ -171,10 +150,11 @@ __device__ __forceinline__ uint32_t pk_bf16_rne(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// The same as quant8_fast, optionally (FAKE) also producing the eight de-quantized values
-// bf16_rne(fl32(q * s_inv)) of the fake-quantization workflow (Section 4, Figure 4).
-template <bool E5M2, bool FAKE>
-__device__ __forceinline__ u32x2 quant8_fast_deq(const u32x4& raw, float s, float s_inv, float& err0, float& err1, u32x4& deq) {
+// Quantizes eight values with scale s; returns the codes (little-endian element order), optionally (FAKE) also the eight de-quantized
+// values bf16_rne(fl32(q * s_inv)) of the fake-quantization workflow (Section 4, Figure 4).  `term(i, t)` receives the error term of
+// value i, in order.
+template <bool E5M2, bool FAKE, class Term>
+__device__ __forceinline__ u32x2 quant8_each(const u32x4& raw, float s, float s_inv, u32x4& deq, Term term) {
     int w0 = 0, w1 = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -185,22 +165,37 @@ __device__ __forceinline__ u32x2 quant8_fast_deq(const u32x4& raw, float s, floa
         if (j == 1) { w0 = cvt_pk8<E5M2>(y0, y1, w0, true);  q = cvt_pk_f32<E5M2>(w0, true); }
         if (j == 2) { w1 = cvt_pk8<E5M2>(y0, y1, w1, false); q = cvt_pk_f32<E5M2>(w1, false); }
         if (j == 3) { w1 = cvt_pk8<E5M2>(y0, y1, w1, true);  q = cvt_pk_f32<E5M2>(w1, true); }
-        err0 += rel_term(y0, q.x);
-        err1 += rel_term(y1, q.y);
+        term(2 * j, rel_term(y0, q.x));
+        term(2 * j + 1, rel_term(y1, q.y));
         if constexpr (FAKE) deq[j] = pk_bf16_rne(q.x * s_inv, q.y * s_inv);
     }
     u32x2 r; r.x = (uint32_t)w0; r.y = (uint32_t)w1;
     return r;
 }
+// Terms added to two chains (even and odd values).
+template <bool E5M2>
+__device__ __forceinline__ u32x2 quant8_fast(const u32x4& raw, float s, float& err0, float& err1) {
+    u32x4 none;
+    return quant8_each<E5M2, false>(raw, s, 0.0f, none, [&](int i, float t) { if (i & 1) err1 += t; else err0 += t; });
+}
+template <bool E5M2, bool FAKE>
+__device__ __forceinline__ u32x2 quant8_fast_deq(const u32x4& raw, float s, float s_inv, float& err0, float& err1, u32x4& deq) {
+    return quant8_each<E5M2, FAKE>(raw, s, s_inv, deq, [&](int i, float t) { if (i & 1) err1 += t; else err0 += t; });
+}
+// Terms one by one, for a chain of additions that another lane has begun.
+template <bool E5M2, bool FAKE>
+__device__ __forceinline__ u32x2 quant8_terms(const u32x4& raw, float s, float s_inv, float (&e)[8], u32x4& deq) {
+    return quant8_each<E5M2, FAKE>(raw, s, s_inv, deq, [&](int i, float t) { e[i] = t; });
+}
 // Eq. (3) needs the error sums of both formats.  When the E5M2 scale is exactly 128 times the E4M3 scale (57344 = 128 * 448:
 // always so for binary32 amax scales unless one of them was clamped, and for GAM / E8M0 scales whose exponents differ
 // by 7), y5 = 128 * y exactly, so the E5M2 term |y5 - q5| / |y5| equals |y - q5 / 128| / |y|: one reciprocal serves both
 // terms, and gfx950's scaled conversions (v_cvt_scalef32_pk_bf8_f32 encodes src / 2^e, v_cvt_scalef32_pk_f32_bf8
-// decodes to code * 2^e, e taken from the scale operand 2^-7) deliver q5 / 128 without forming y5.  Adds the E4M3 terms
-// to e0 / e1 and the E5M2 terms to f0 / f1; returns the E4M3 codes.
+// decodes to code * 2^e, e taken from the scale operand 2^-7) deliver q5 / 128 without forming y5.  `term4(i, t)` and
+// `term5(i, t)` receive the E4M3 and the E5M2 term of value i, in order; returns the E4M3 codes.
 typedef short i16x2 __attribute__((ext_vector_type(2)));
-template <bool FAKE>
-__device__ __forceinline__ u32x2 quant8_dual(const u32x4& raw, float s, float s_inv, float& e0, float& e1, float& f0, float& f1, u32x4& deq) {
+template <bool FAKE, class Term4, class Term5>
+__device__ __forceinline__ u32x2 quant8_dual_each(const u32x4& raw, float s, float s_inv, u32x4& deq, Term4 term4, Term5 term5) {
     int w0 = 0, w1 = 0;
     constexpr float kInv128 = 0.0078125f;
 #pragma unroll
@@ -213,17 +208,26 @@ __device__ __forceinline__ u32x2 quant8_dual(const u32x4& raw, float s, float s_
         if (j == 2) { w1 = cvt_pk8<false>(y0, y1, w1, false); q = cvt_pk_f32<false>(w1, false); }
         if (j == 3) { w1 = cvt_pk8<false>(y0, y1, w1, true);  q = cvt_pk_f32<false>(w1, true); }
         const float r0 = __builtin_amdgcn_rcpf(__builtin_fabsf(y0)), r1 = __builtin_amdgcn_rcpf(__builtin_fabsf(y1));
-        e0 += __builtin_amdgcn_fmed3f(__builtin_fabsf(y0 - q.x) * r0, 0.0f, 1.0f);
-        e1 += __builtin_amdgcn_fmed3f(__builtin_fabsf(y1 - q.y) * r1, 0.0f, 1.0f);
+        term4(2 * j, __builtin_amdgcn_fmed3f(__builtin_fabsf(y0 - q.x) * r0, 0.0f, 1.0f));
+        term4(2 * j + 1, __builtin_amdgcn_fmed3f(__builtin_fabsf(y1 - q.y) * r1, 0.0f, 1.0f));
         const i16x2 none = {0, 0};
         const i16x2 c5 = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(none, y0, y1, kInv128, false);
         const f32x2 q5 = __builtin_amdgcn_cvt_scalef32_pk_f32_bf8((uint32_t)(uint16_t)c5.x, kInv128, false);
-        f0 += __builtin_amdgcn_fmed3f(__builtin_fabsf(y0 - q5.x) * r0, 0.0f, 1.0f);
-        f1 += __builtin_amdgcn_fmed3f(__builtin_fabsf(y1 - q5.y) * r1, 0.0f, 1.0f);
+        term5(2 * j, __builtin_amdgcn_fmed3f(__builtin_fabsf(y0 - q5.x) * r0, 0.0f, 1.0f));
+        term5(2 * j + 1, __builtin_amdgcn_fmed3f(__builtin_fabsf(y1 - q5.y) * r1, 0.0f, 1.0f));
         if constexpr (FAKE) deq[j] = pk_bf16_rne(q.x * s_inv, q.y * s_inv);
     }
     u32x2 r; r.x = (uint32_t)w0; r.y = (uint32_t)w1;
     return r;
+}
+// Terms added to chains, as above; terms one by one.
+template <bool FAKE>
+__device__ __forceinline__ u32x2 quant8_dual(const u32x4& raw, float s, float s_inv, float& e0, float& e1, float& f0, float& f1, u32x4& deq) {
+    return quant8_dual_each<FAKE>(raw, s, s_inv, deq, [&](int i, float t) { if (i & 1) e1 += t; else e0 += t; }, [&](int i, float t) { if (i & 1) f1 += t; else f0 += t; });
+}
+template <bool FAKE>
+__device__ __forceinline__ u32x2 quant8_dual_terms(const u32x4& raw, float s, float s_inv, float (&e)[8], float (&f)[8], u32x4& deq) {
+    return quant8_dual_each<FAKE>(raw, s, s_inv, deq, [&](int i, float t) { e[i] = t; }, [&](int i, float t) { f[i] = t; });
 }
 // Eight values of eight different blocks (one column each): scales s[k], error terms added to err[k].
 template <bool E5M2, bool FAKE>

@@ -1543,44 +1543,6 @@ __global__ __launch_bounds__(T) void k_tensor_amax_one_dense(OneTensor g) {
     t.amax_part[blockIdx.x] = a | (t.three ? (0xFFFFu - m) << 16 : 0u);
     t.flush_part[blockIdx.x] = f;
 }
-// Quantizes 8 values; the terms come out one by one, for a chain of additions that another lane has begun.
-template <bool E5M2, bool FAKE>
-__device__ __forceinline__ u32x2 quant8_terms(const u32x4& raw, float s, float s_inv, float (&e)[8], u32x4& deq) {
-    int w0 = 0, w1 = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float y0 = __uint_as_float(raw[j] << 16) * s, y1 = __uint_as_float(raw[j] & 0xFFFF0000u) * s;
-        int& w = j < 2 ? w0 : w1;
-        w = (j & 1) ? cvt_pk8<E5M2>(y0, y1, w, true) : cvt_pk8<E5M2>(y0, y1, w, false);
-        const f32x2 q = (j & 1) ? cvt_pk_f32<E5M2>(w, true) : cvt_pk_f32<E5M2>(w, false);
-        e[2 * j] = rel_term(y0, q.x);
-        e[2 * j + 1] = rel_term(y1, q.y);
-        if constexpr (FAKE) deq[j] = pk_bf16_rne(q.x * s_inv, q.y * s_inv);
-    }
-    return u32x2{(uint32_t)w0, (uint32_t)w1};
-}
-template <bool FAKE>
-__device__ __forceinline__ u32x2 quant8_dual_terms(const u32x4& raw, float s, float s_inv, float (&e)[8], float (&f)[8], u32x4& deq) {      // see quant8_dual
-    int w0 = 0, w1 = 0;
-    constexpr float kInv128 = 0.0078125f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float y0 = __uint_as_float(raw[j] << 16) * s, y1 = __uint_as_float(raw[j] & 0xFFFF0000u) * s;
-        int& w = j < 2 ? w0 : w1;
-        w = (j & 1) ? cvt_pk8<false>(y0, y1, w, true) : cvt_pk8<false>(y0, y1, w, false);
-        const f32x2 q = (j & 1) ? cvt_pk_f32<false>(w, true) : cvt_pk_f32<false>(w, false);
-        const float r0 = __builtin_amdgcn_rcpf(__builtin_fabsf(y0)), r1 = __builtin_amdgcn_rcpf(__builtin_fabsf(y1));
-        e[2 * j] = __builtin_amdgcn_fmed3f(__builtin_fabsf(y0 - q.x) * r0, 0.0f, 1.0f);
-        e[2 * j + 1] = __builtin_amdgcn_fmed3f(__builtin_fabsf(y1 - q.y) * r1, 0.0f, 1.0f);
-        const i16x2 none = {0, 0};
-        const i16x2 c5 = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(none, y0, y1, kInv128, false);
-        const f32x2 q5 = __builtin_amdgcn_cvt_scalef32_pk_f32_bf8((uint32_t)(uint16_t)c5.x, kInv128, false);
-        f[2 * j] = __builtin_amdgcn_fmed3f(__builtin_fabsf(y0 - q5.x) * r0, 0.0f, 1.0f);
-        f[2 * j + 1] = __builtin_amdgcn_fmed3f(__builtin_fabsf(y1 - q5.y) * r1, 0.0f, 1.0f);
-        if constexpr (FAKE) deq[j] = pk_bf16_rne(q.x * s_inv, q.y * s_inv);
-    }
-    return u32x2{(uint32_t)w0, (uint32_t)w1};
-}
 // T lanes with CH chunks each.  Dense operands: a tile is the 2048 chunks that 256 lanes take in the grouped kernels, and the sums are
 // those of the grouped kernels bit for bit: two lanes that hold a chain of additions in halves hand it on through shared memory.
 template <int CRIT, bool FAKE, int T, int CH>
