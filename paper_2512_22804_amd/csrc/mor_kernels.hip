@@ -1068,7 +1068,8 @@ __global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStat
 
 // Per-tensor operands of a group share three launches (amax, quantize, finish + fallback copy).
 enum : uint32_t { kTensorLean = 1u,       // a proven BF16 operand gets no FP8 payload
-                  kTensorReport = 2u };  // dense operands say in their statistics that the decision was proven
+                  kTensorReport = 2u,    // the statistics say that the decision was proven
+                  kTensorDense = 4u };   // rows without padding (kernels that take both kinds)
 struct TensorOp {
     const uint16_t* x;
     int64_t n_chunks, n_tiles;
@@ -1077,7 +1078,7 @@ struct TensorOp {
     float th;
     uint32_t mode;                       // scaling algorithm
     uint32_t three;                      // type list [E4M3, E5M2, BF16]
-    uint32_t flags;                      // kTensorLean, kTensorReport
+    uint32_t flags;                      // kTensorLean, kTensorReport, kTensorDense
     int n_amax, n_slots;                 // workgroups this operand gets in pass A / pass B
     uint32_t* amax_part;                 // [n_amax]
     float* err; float* err5; uint32_t* zero;   // [n_slots] each
@@ -1604,7 +1605,7 @@ __global__ __launch_bounds__(T, 4) void k_tensor_quant_one(OneTensor g, int poll
     const float s = block_scale(abits, kE4M3Max, mode, group_mantissa_bits(abits, kE4M3Max, mode));
     const float s5 = (CRIT == kCritEq3) ? block_scale(abits, kE5M2Max, mode, group_mantissa_bits(abits, kE5M2Max, mode)) : 0.0f;
     const bool fast = abits < fast_amax_limit(mode) && !wide, dual = CRIT == kCritEq3 && s5 == 128.0f * s;
-    const bool emit = !(proven && (t.flags & kTensorLean) != 0u), dense = (t.flags & kTensorReport) != 0u;
+    const bool emit = !(proven && (t.flags & kTensorLean) != 0u), dense = (t.flags & kTensorDense) != 0u;
     const float s_inv = FAKE ? 1.0f / s : 0.0f;
     const BufRsrc r8 = make_buf_window(t.o.fp8 + row0 * t.o.ld_fp8, (FAKE || !emit || wide) ? 0u : 0x7FFFFFFFu);
     const BufRsrc rb = make_buf_window(t.o.bf16 + row0 * t.o.ld_bf16, proven ? 0x7FFFFFFFu : 0u);
@@ -2529,7 +2530,7 @@ void launch_one_quant(const OneTensor& o, const OneShape& s, int slots, int poll
 void launch_one_tensor(const TensorOp& t, float near_tol, int crit, bool fake, int polls, hipStream_t st, KProf* prof) {
     OneTensor o;
     o.n = 1; o.near_tol = near_tol; o.op[0] = t;
-    const bool dense = (t.flags & kTensorReport) != 0u;
+    const bool dense = (t.flags & kTensorDense) != 0u;
     const OneShape s = one_shape(t.n_chunks, dense);
     const int slots = (int)((t.n_chunks + s.lanes * s.chunks - 1) / (s.lanes * s.chunks));
     TensorOp& a = o.op[0];
@@ -2573,8 +2574,8 @@ void BatchRun::per_tensor_operands(int crit) {
             for (int k = 0; k < cnt; ++k) {
                 const BatchItem& it = items[idx[k]];
                 TensorOp& t = g.op[k];
-                t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u; 
-                t.flags = strided ? 0u : (it.lean ? kTensorLean : 0u) | kTensorReport;      // (padded rows always get their payload, and report no proof)
+                t.x = it.x; t.o = it.o; t.th = it.th; t.mode = (uint32_t)it.scaling; t.three = it.three ? 1u : 0u;
+                t.flags = strided ? 0u : kTensorDense | kTensorReport | (it.lean ? kTensorLean : 0u);      // (padded rows always get their payload, and report no proof)
                 set_tensor_layout(t, it.sh, it.o);
                 all_tiles += t.n_tiles;
                 const TensorPlan pl = plan_tensor(it.sh.rows, it.sh.cols);
