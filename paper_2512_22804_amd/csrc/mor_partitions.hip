@@ -624,7 +624,42 @@ __device__ __forceinline__ float colgroup_addf(float v) {
     return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
-// Per-channel columns: amax over the strips, scales (Algorithm 1) and proofs of the workgroup's 128 columns, left in shared memory
+// Per-channel columns, the steps of forming their scales.  Group mantissas of Algorithm 1 from the group amax, the largest column amax:
+struct ColMantissas {
+    uint32_t e4m3, e5m2;
+};
+__device__ __forceinline__ ColMantissas col_mantissas(const ColOp& t, uint32_t group_amax) {
+    if (!t.derive_gam) return {0u, 0u};
+    return {group_mantissa_bits(group_amax, kE4M3Max, t.mode), group_mantissa_bits(group_amax, kE5M2Max, t.mode)};
+}
+// What one thread of the launch writes for the operand: the mantissas, and whether the certain flushes of all columns prove its decision.
+__device__ __forceinline__ void col_group_outputs(const ColOp& t, const ColMantissas& m, bool whole, bool all_proven) {
+    if (t.derive_gam) {
+        uint32_t* gam_out = const_cast<uint32_t*>(t.gam);
+        gam_out[0] = m.e4m3; gam_out[1] = m.e5m2;
+        if (t.gmant) { t.gmant[0] = m.e4m3; t.gmant[1] = m.e5m2; }
+    }
+    if (whole) t.wg[0] = all_proven ? 1u : 0u;
+    if (t.mode == kScaleE8M0) zero_group_mantissa(t.gmant);
+}
+// Column c (of cols_padded) with amax pattern `a`: what the passes after this one read, and the caller's outputs.
+__device__ __forceinline__ void col_outputs(const ColOp& t, int64_t c, uint32_t a, float s, float s5, bool proven) {
+    t.col_scale5[c] = s5;
+    if (t.prove) t.col_proven[c] = proven ? 1 : 0;
+    if (c >= t.cols) return;
+    t.o.amax[c] = __uint_as_float(a << 16);
+    t.o.scale[c] = s;
+    if (t.mode != kScaleFp32 && t.o.e8m0) t.o.e8m0[c] = (uint8_t)(__float_as_uint(s) >> 23);
+}
+// Three-way recipe: smallest non-zero magnitude of the column over the strips.
+__device__ __forceinline__ void col_amin_of(const ColOp& t, int64_t c) {
+    uint32_t mn = 0xFFFFu;
+#pragma unroll 8
+    for (int sidx = 0; sidx < t.n_strips; ++sidx) mn = min(mn, (uint32_t)t.part_zero[sidx * (t.tiles_x * 128) + c]);
+    t.col_amin[c] = (uint16_t)mn;
+}
+
+// Amax over the strips, scales (Algorithm 1) and proofs of the workgroup's 128 columns, left in shared memory
 // (abits, scale, scale5, and in mask whether the column is proven); the first strip's workgroups write them out as well.  Every
 // workgroup of the quantize pass does this for itself while its first tile is in flight, from figures that lie in the L2 cache: a
 // launch in between took 5.6 us of the 88 us of a linear layer's two operands (8192 x 4096 per-channel rows, 4096 x 6144 columns).
@@ -680,37 +715,16 @@ __device__ __forceinline__ void col_scales(const ColOp& t, int64_t strip, int64_
     if (half) { col_a[cc] = a; col_f[cc] = fl; }
     __syncthreads();
     if (half) { __syncthreads(); return; }
-    uint32_t mg = 0u, mg5 = 0u;
-    if (t.derive_gam) {
-        ga = max(max(sh.wg[0], sh.wg[1]), max(sh.wg[2], sh.wg[3]));
-        mg = group_mantissa_bits(ga, kE4M3Max, t.mode);
-        mg5 = group_mantissa_bits(ga, kE5M2Max, t.mode);
-    }
+    const ColMantissas m = col_mantissas(t, max(max(sh.wg[0], sh.wg[1]), max(sh.wg[2], sh.wg[3])));
     const bool all_proven = whole && (sh.fl[0] + sh.fl[1]) + (sh.fl[2] + sh.fl[3]) >= t.tensor_need;
-    if (unit == 0 && tid == 0) {
-        if (t.derive_gam) {
-            uint32_t* gam_out = const_cast<uint32_t*>(t.gam);
-            gam_out[0] = mg; gam_out[1] = mg5;
-            if (t.gmant) { t.gmant[0] = mg; t.gmant[1] = mg5; }
-        }
-        if (whole) t.wg[0] = all_proven ? 1u : 0u;
-        if (t.mode == kScaleE8M0) zero_group_mantissa(t.gmant);
-    }
+    if (unit == 0 && tid == 0) col_group_outputs(t, m, whole, all_proven);
     a = max(a, col_a[cc]);
     fl += col_f[cc];
     const int64_t c = c0 + cc;
     const bool proven = t.prove && c < t.cols && (whole ? all_proven : fl >= t.flush_need);
-    const float s = block_scale(a, kE4M3Max, t.mode, mg), s5 = CRIT == kCritEq3 || t.three ? block_scale(a, kE5M2Max, t.mode, mg5) : 0.0f;
+    const float s = block_scale(a, kE4M3Max, t.mode, m.e4m3), s5 = CRIT == kCritEq3 || t.three ? block_scale(a, kE5M2Max, t.mode, m.e5m2) : 0.0f;
     sh.scale[cc] = s; sh.scale5[cc] = s5; sh.abits[cc] = (uint16_t)a; sh.mask[cc] = proven ? 1 : 0;
-    if (strip == 0) {
-        t.col_scale5[c] = s5;
-        if (t.prove) t.col_proven[c] = proven ? 1 : 0;
-        if (c < t.cols) {
-            t.o.amax[c] = __uint_as_float(a << 16);
-            t.o.scale[c] = s;
-            if (t.mode != kScaleFp32 && t.o.e8m0) t.o.e8m0[c] = (uint8_t)(__float_as_uint(s) >> 23);
-        }
-    }
+    if (strip == 0) col_outputs(t, c, a, s, s5, proven);
     __syncthreads();
 }
 
@@ -1160,8 +1174,7 @@ __global__ __launch_bounds__(256, 4) void k_col_quant_group(GroupCol g) { col_gr
 
 // Per-channel columns of a launch with many workgroups (see kColScaleWgs): column amax over the strips -> amax, scale (Algorithm 1),
 // E8M0 byte, once and for all.
-// Under GAM every workgroup first takes the largest column amax of the operand (the group amax of Algorithm 1), and for a tensor-level decision the sum of all columns' certain flushes: the same values in every
-// workgroup, from the per-workgroup figures of the amax pass (a handful of loads per thread).
+// Every workgroup takes the operand's figures (see col_scales), a handful of loads per thread, and then a column per thread.
 __global__ __launch_bounds__(256) void k_col_scales(GroupCol g) {
     __shared__ uint32_t sh4[4];
     __shared__ unsigned long long shl[4];
@@ -1172,64 +1185,35 @@ __global__ __launch_bounds__(256) void k_col_scales(GroupCol g) {
     const int64_t c = (int64_t)b * 256 + tid;
     const int64_t cols_padded = t.tiles_x * 128;
     const int64_t n_wg = (int64_t)t.n_strips * t.tiles_x;  // workgroups of the amax pass
-    uint32_t mg = 0u, mg5 = 0u;
-    if (t.derive_gam) {                                    // GAM (uniform over the workgroup)
-        uint32_t ga = 0u;
+    const bool whole = t.prove && t.tensor_need != 0ull;
+    uint32_t ga = 0u;
+    unsigned long long f = 0ull;
+    if (t.derive_gam) {                                    // uniform over the workgroup
         for (int64_t i = tid; i < n_wg; i += 256) ga = max(ga, t.wg[2 + 2 * i]);
         ga = wave_allmax_u32(ga);
-        if ((tid & 63) == 0) sh4[tid >> 6] = ga;
-        __syncthreads();
-        ga = max(max(sh4[0], sh4[1]), max(sh4[2], sh4[3]));
-        mg = group_mantissa_bits(ga, kE4M3Max, t.mode);
-        mg5 = group_mantissa_bits(ga, kE5M2Max, t.mode);
-        if (b == 0 && tid == 0) {
-            uint32_t* gam_out = const_cast<uint32_t*>(t.gam);
-            gam_out[0] = mg; gam_out[1] = mg5;
-            if (t.gmant) { t.gmant[0] = mg; t.gmant[1] = mg5; }
-        }
     }
-    bool all_proven = false;
-    if (t.prove && t.tensor_need) {                        // uniform over the workgroup
-        unsigned long long f = 0ull;
+    if (whole) {                                           // uniform over the workgroup
         for (int64_t i = tid; i < n_wg; i += 256) f += t.wg[3 + 2 * i];
-#pragma unroll
-        for (int m = 32; m > 0; m >>= 1) f += __shfl_xor(f, m, 64);
-        if ((tid & 63) == 0) shl[tid >> 6] = f;
-        __syncthreads();
-        f = (shl[0] + shl[1]) + (shl[2] + shl[3]);
-        all_proven = f >= t.tensor_need;
-        if (b == 0 && tid == 0) t.wg[0] = all_proven ? 1u : 0u;
+        f = wave_allsum_u64(f);
     }
+    if ((tid & 63) == 0) { sh4[tid >> 6] = ga; shl[tid >> 6] = f; }
+    __syncthreads();
+    const ColMantissas m = col_mantissas(t, max(max(sh4[0], sh4[1]), max(sh4[2], sh4[3])));
+    const bool all_proven = whole && (shl[0] + shl[1]) + (shl[2] + shl[3]) >= t.tensor_need;
+    if (b == 0 && tid == 0) col_group_outputs(t, m, whole, all_proven);
     if (c >= cols_padded) return;
-    uint32_t a = 0u;
+    uint32_t a = 0u, fl = 0u;
 #pragma unroll 8
     for (int sidx = 0; sidx < t.n_strips; ++sidx) a = max(a, (uint32_t)t.part_amax[sidx * cols_padded + c]);
-    if (t.three) {
-        uint32_t mn = 0xFFFFu;
+    if (t.three) col_amin_of(t, c);
+    if (t.prove && !whole) {
+        const uint16_t* __restrict__ part_flush = reinterpret_cast<const uint16_t*>(t.part_err5);
 #pragma unroll 8
-        for (int sidx = 0; sidx < t.n_strips; ++sidx) mn = min(mn, (uint32_t)t.part_zero[sidx * cols_padded + c]);
-        t.col_amin[c] = (uint16_t)mn;
+        for (int sidx = 0; sidx < t.n_strips; ++sidx) fl += part_flush[sidx * cols_padded + c];
     }
-    if (t.prove) {
-        if (t.tensor_need) {
-            t.col_proven[c] = (c < t.cols && all_proven) ? 1 : 0;
-        } else {
-            const uint16_t* __restrict__ part_flush = reinterpret_cast<const uint16_t*>(t.part_err5);
-            uint32_t fl = 0u;
-#pragma unroll 8
-            for (int sidx = 0; sidx < t.n_strips; ++sidx) fl += part_flush[sidx * cols_padded + c];
-            t.col_proven[c] = (c < t.cols && fl >= t.flush_need) ? 1 : 0;
-        }
-    }
-    const float s = block_scale(a, kE4M3Max, t.mode, mg);
+    const float s = block_scale(a, kE4M3Max, t.mode, m.e4m3);
     t.col_scale[c] = s;
-    t.col_scale5[c] = block_scale(a, kE5M2Max, t.mode, mg5);
-    if (c < t.cols) {
-        t.o.amax[c] = __uint_as_float(a << 16);
-        t.o.scale[c] = s;
-        if (t.mode != kScaleFp32 && t.o.e8m0) t.o.e8m0[c] = (uint8_t)(__float_as_uint(s) >> 23);
-        if (t.mode == kScaleE8M0 && c == 0) zero_group_mantissa(t.gmant);
-    }
+    col_outputs(t, c, a, s, block_scale(a, kE5M2Max, t.mode, m.e5m2), t.prove && c < t.cols && (whole ? all_proven : fl >= t.flush_need));
 }
 // Per-channel columns, three-way recipe: smallest non-zero magnitude of the columns over the strips.  (A launch of its own: the
 // quantize pass writes over the strips' figures.)
@@ -1240,10 +1224,7 @@ __global__ __launch_bounds__(256) void k_col_amin(GroupCol g) {
     const int64_t c = (int64_t)(blockIdx.x - (op ? g.comb_end[op - 1] : 0)) * 256 + threadIdx.x;
     const int64_t cols_padded = t.tiles_x * 128;
     if (c >= cols_padded) return;
-    uint32_t mn = 0xFFFFu;
-#pragma unroll 8
-    for (int sidx = 0; sidx < t.n_strips; ++sidx) mn = min(mn, (uint32_t)t.part_zero[sidx * cols_padded + c]);
-    t.col_amin[c] = (uint16_t)mn;
+    col_amin_of(t, c);
 }
 // Combine: column error sums over the strips (binary64, fixed order), non-zero counts, decision.
 template <int CRIT>
