@@ -1018,8 +1018,9 @@ __global__ __launch_bounds__(256, CRIT == kCritEq3 || ROWS ? 4 : 6) void k_sub1x
 }
 // Combine launch of the above: one workgroup, the records in a fixed order.  It is pure latency on the critical path of the call, so a
 // record is read by ten neighbouring lanes, eight bytes each (one line per record instead of one line per lane and load), and only
-// ten values per group of lanes are left to be summed through shared memory: the launch takes 2.2 us instead of 5.2, a 1000 x 4096
-// operand with statistics 8.5 instead of 11.3 us per call, 8192 x 4096 26.4 instead of 29.1.
+// ten values per group of lanes are left to be summed through shared memory: the launch takes 2.0 us at least and 3.4 on average instead of
+// 5.0 and 6.3 with a record per lane (calls of 1000 x 4096 and 8192 x 4096 under the profiler), 1000 x 4096 with statistics 8.3 instead of
+// 11.3 us per call, 8192 x 4096 26.5 instead of 29.3.
 constexpr int kSoloFinalThreads = 1024;
 constexpr int kSoloQ = kSoloRecWords / 2;              // quadwords: seven pairs of counters and one counter, the sum, the non-zeros
 __global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStats s) {
@@ -1477,7 +1478,10 @@ __device__ __forceinline__ void tensor_finish_body(const GroupTensor& g, int blo
 //      their sums and draw a ticket; the last one decides for the operand and tells the others, which copy their tile if it stays in
 //      BF16 after all (or rewrite it in E5M2).  Nobody waits without end: a workgroup that is not told in time (others may not have
 //      found a place on the chip) says so, looks once more and leaves; the one that decides tells first and then looks who has left,
-//      so that at least one of the two sees to the tile (if both do, they store the same bytes).
+//      so that at least one of the two sees to the tile (if both do, they store the same bytes).  Beside another stream's matrix
+//      products that fill the chip (8192 x 8192 x 8192 in BF16), where every launch waits for places, 9 calls of 1024 x 1024 end in the
+//      10.4 ms of twelve products, 3 with three launches, and the longest takes 1.5 ms (2.7); the products take 0 to 3 % longer.
+//      Beside copies of 1 GiB, and beside three streams of such calls, all calls take less than with three launches.
 constexpr int kTicketGroup = 16;             // workgroups to a first ticket; tickets of one address complete some 15 ns apart
 constexpr int kOneMaxSlots = 512;
 constexpr int kOneLine = 32;                 // words: a line of its own for every ticket and every copy of the decision
@@ -2497,13 +2501,12 @@ void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_p
 // number, what the host spends on each (3.8 KB of kernel arguments for a table of eight operands and the statistics' riders, 0.4 KB
 // here) and the depth of a workgroup's work.  The workgroups wait to be told, so at most half of those that the registers let be
 // resident together are launched.
-// us per call, here / with the three launches that larger operands take: dense, kept in E4M3, 64 x 256 10.2 / 13.4, 1024 x 1024
-// 11.5 / 14.1, 1024 x 4096 13.9 / 15.5, 2048 x 4096 17.0 / 18.4; kept in BF16 without a proof (Eq. 3) 13.1 / 15.9 and 15.5 / 18.4; padded
-// rows 256 x 4096 10.2 / 11.7, 2048 x 4096 17.2 / 18.8.  Dense with four lanes to a grouped lane's chunks 11.8 instead of 11.1 at 1024 x 1024.
-// (4096 x 4096, beyond: three launches, 23.1.)
+// us per call, here / with the three launches that larger operands take: dense, kept in E4M3, 64 x 256 9.4 / 13.8, 1024 x 1024
+// 11.1 / 14.1, 1024 x 4096 11.9 / 15.5, 2048 x 4096 14.6 / 18.4; kept in BF16 without a proof (Eq. 3) 1024 x 1024 12.7 / 15.9, 1024 x 4096
+// 13.4 / 18.4; padded rows 256 x 4096 9.9 / 11.5, 2048 x 4096 17.1 / 18.8.  (4096 x 4096, beyond: three launches, 23.1.)
 constexpr int64_t one_max_chunks(int crit) { return crit == kCritEq3 ? 1 << 19 : 1 << 20; }      // (Eq. 3 with eight chunks per lane does not fit the registers)
 constexpr int64_t kOnePadded2 = 1 << 18, kOneShared = 1 << 19;
-constexpr int kDenseAmaxLanes = 512;      // us per call at 256 / 512 / 1024 lanes, less 0.4 since: 1024 x 1024 11.60 / 11.57 / 11.74, 2048 x 4096 15.3 / 15.2 / 15.5
+constexpr int kDenseAmaxLanes = 512;      // us per call at 256 / 512 / 1024 lanes: 64 x 256 9.5 / 9.2 / 9.4, 1024 x 1024 11.2 / 11.2 / 11.4, 2048 x 4096 14.8 / 14.6 / 14.9
 static_assert(one_max_chunks(kCritEq2) <= (int64_t)kAmaxOneTile * kTensorChunksPerBlock, "a workgroup per dense tile");
 static_assert(kOnePadded2 <= (int64_t)kOneMaxSlots * 512 && kOneShared <= (int64_t)kOneMaxSlots * 1024 && one_max_chunks(kCritEq2) <= (int64_t)kOneMaxSlots * 2048,
               "a slot per tile");

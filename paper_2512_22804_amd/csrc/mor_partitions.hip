@@ -530,8 +530,9 @@ __global__ __launch_bounds__(256) void k_block_amax_prove(GroupProve g) {
 // A workgroup sweeps a strip of 128-row x 128-column tiles; a lane holds 8 rows x 8 columns of a tile
 // and keeps per-column scalars.  Per-channel columns span all strips, so they take three passes:
 //   kColAmax      column amax of the strip                                              -> workspace partials
-//   kColExternal  column amax over the strips, scales; quantize, strip error sums -> workspace partials
-//   (combine)     column error sums, decision, fallback columns
+//   (combine)     column amax over the strips, scales: a launch of its own, or by the next pass (kColScaleWgs, column_scales_folded)
+//   kColExternal  quantize with those scales, strip error sums                          -> workspace partials
+//   (combine)     column error sums, decision, fallback columns; or, for a tensor-level decision, its reduce pass (kStripsInReduce)
 // 128 x 1 sub-columns are complete inside a tile (kColLocal): one pass.
 // Proven columns (Eq. 2, two types, fallback buffer present): the amax pass also counts, per column, elements that are
 // certain to flush -- non-zero and below 2^-20 of a LOWER bound of the column amax (the column's amax inside the
@@ -1557,8 +1558,8 @@ hipError_t launch_subcol_items(const BatchItem* items, const int* idx, int cnt, 
     return hipGetLastError();
 }
 
-// Per-channel columns: all operands of one criterion share five launches per kernel variant (amax, scales, quantize,
-// finish, fallback columns), however large they are together: in parts of 256 MB, as other operands that are read twice, the
+// Per-channel columns: all operands of one criterion share two to five launches per kernel variant (amax, scales if not folded, quantize,
+// finish if sums are not left to the tensor-level reduce pass, fallback columns if decided one by one), however large they are together: in parts of 256 MB, as other operands that are read twice, the
 // five launches of each part cost more than its second read gains (the twelve operands of a layer 561 us per call in one go,
 // 637 in four parts, 591 in one go without the first pass leaving its operands in the Infinity Cache).  ws_of[k] is the
 // workspace of operand idx[k] (column_workspace_bytes).
