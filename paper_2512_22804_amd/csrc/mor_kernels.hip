@@ -857,19 +857,21 @@ struct GroupScope {
     ScopeOp op[kMaxGroupScope];
 };
 // Error sums and non-zero count of a column from those of its strips (binary64, fixed order), into the outputs: what the combine launch of
-// the per-channel columns does where the columns decide one by one.  (EQ3 is a constant: a branch around the third load of every strip
-// leaves one load in flight.  Under Eq. 3 8192 x 128 took 37.8 us per call with it, 23.7 without, 8192 x 4096 59.2 and 50.2.)
-template <bool EQ3>
-__device__ __forceinline__ void column_sums(const ScopeOp& t, int64_t c, bool live, float& es, uint32_t& nz, float& es5) {
+// the per-channel columns does where the columns decide one by one.  (The third load of a strip is always made, from the E4M3 sums where
+// there are no others: a branch around it leaves one load in flight, and a loop for each criterion makes the kernel so long that small
+// operands of other granularities pay for it.  us per call, Eq. 3 8192 x 4096 59.2 with the branch, 50.1 with two loops, 49.9 like this;
+// 128 x 128 blocks 1024 x 4096 11.3, 11.5, 11.3.)
+__device__ __forceinline__ void column_sums(const ScopeOp& t, int64_t c, bool live, bool eq3, float& es, uint32_t& nz, float& es5) {
     double e = 0.0, e5 = 0.0;
     unsigned long long z = 0ull;
+    const float* __restrict__ err5 = eq3 ? t.col.err5 : t.col.err;
     for (int s0 = 0; s0 < t.col.n_strips; s0 += 8) {
         float ev[8], e5v[8];
         uint32_t zv[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int64_t at = (int64_t)(s0 + k < t.col.n_strips ? s0 + k : s0) * t.col.cols_padded + c;      // always a valid strip: the loads need no branch
-            ev[k] = t.col.err[at]; zv[k] = t.col.zero[at]; e5v[k] = EQ3 ? t.col.err5[at] : 0.0f;
+            ev[k] = t.col.err[at]; zv[k] = t.col.zero[at]; e5v[k] = err5[at];
         }
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -884,7 +886,7 @@ __device__ __forceinline__ void column_sums(const ScopeOp& t, int64_t c, bool li
     if (!live) return;
     const_cast<float*>(t.err_sum)[c] = es;
     const_cast<uint32_t*>(t.nnz)[c] = nz;
-    if constexpr (EQ3) const_cast<float*>(t.err5_sum)[c] = es5;
+    if (eq3) const_cast<float*>(t.err5_sum)[c] = es5;
 }
 // Four blocks' loads in flight per lane.  With statistics the same sweep also fills the workgroup's record (histogram bins,
 // near-threshold blocks), so no statistics launch follows.
@@ -908,8 +910,7 @@ __global__ __launch_bounds__(256) void k_scope_reduce_group(GroupScope g) {
             const int64_t p = base + lane + u * stride, pc = p < t.n_part ? p : t.n_part - 1;    // always a valid block: the loads need no branch
             if (t.col.n_strips) {                              // uniform over the workgroup
                 if (base + u * stride >= t.n_part) break;
-                if (eq3) column_sums<true>(t, pc, p < t.n_part, es[u], nz[u], es5[u]);
-                else column_sums<false>(t, pc, p < t.n_part, es[u], nz[u], es5[u]);
+                column_sums(t, pc, p < t.n_part, eq3, es[u], nz[u], es5[u]);
             } else { es[u] = t.err_sum[pc]; nz[u] = t.nnz[pc]; es5[u] = eq3 ? t.err5_sum[pc] : 0.0f; }
         }
 #pragma unroll

@@ -256,9 +256,9 @@ struct ColumnSums {
 };
 // A column's strips are read one after another (eight or sixteen loads in flight), so what a lane has to read sets the time of the step that
 // reads them where an operand is tall.  us per call, FP32 scales, weights:
-// Sums of a tensor-level decision, in its reduce pass / by a launch of their own before it: 8192 x 512 (64 strips) 24.0 / 25.6, 32768 x 1024
-// (128) 58.8 / 59.6, 16384 x 128 (128) 30.0 / 30.3, 32768 x 128 (256) 42.3 / 39.8, 131072 x 128 (1024) 152 / 138.
-constexpr int kStripsInReduce = 128;
+// Sums of a tensor-level decision, in its reduce pass / by a launch of their own before it: 8192 x 512 (64 strips) 24.4 / 25.6, 12288 x 256
+// (96) 27.6 / 28.1, 14336 x 256 (112) 29.7 / 29.5, 16384 x 128 (128) 30.9 / 29.9, 32768 x 128 (256) 44.1 / 39.6.
+constexpr int kStripsInReduce = 96;
 // Scales, by every workgroup of the quantize pass / by a launch of their own, which has nobody to share the reads with but costs a launch:
 // up to 128 strips the former takes less (32768 x 1024 59.6 / 61.3); beyond, it depends on how many workgroups repeat the reads, and on
 // whether the launch reads the flush counts of single columns as well: 65536 x 128 (512 workgroups) 63.1 / 65.8, 65536 x 256 (1024) 85.8 / 76.2,

@@ -60,8 +60,9 @@ def test_tensor_level_sums_with_and_without_statistics(oracle, rows, cols, crit)
     assert got["err_sum_total"] == pytest.approx(want["err_sum_total"], rel=1e-12)
 
 
-# 128 strips, 129 strips in 129 and in 645 workgroups, two operands of the latter
-@pytest.mark.parametrize("rows, cols, k, combines", [(16384, 128, 1, (0, 1)), (16385, 128, 1, (1, 1)), (16385, 640, 1, (2, 1)), (16385, 640, 2, (2, 2))])
+# 96 and 97 strips, 128 strips in 640 workgroups, 129 strips in 129 and in 645, two operands of the latter
+@pytest.mark.parametrize("rows, cols, k, combines", [(12288, 128, 1, (0, 1)), (12289, 128, 1, (1, 1)), (16384, 640, 1, (1, 1)), (16385, 128, 1, (1, 1)),
+                                                     (16385, 640, 1, (2, 1)), (16385, 640, 2, (2, 2))])
 @pytest.mark.parametrize("crit, scaling", [("mean_rel_err", "gam"), ("mean_rel_err", "fp32_amax"), ("e4m3_vs_e5m2", "fp32_amax")])
 @pytest.mark.parametrize("scope", ["tensor", "partition"])
 def test_tall_columns(rows, cols, k, combines, crit, scaling, scope):
