@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void k_sub1x128_strided(const uint16_t* __rest
 // ======================================================================================
 constexpr int kTensorChunksPerThread = 8;                       // 16-byte chunks per thread in pass B
 constexpr int kTensorChunksPerBlock = 256 * kTensorChunksPerThread;
-constexpr int kSmallChunksPerThread = 2;                        // ... in pass A of a small operand that is alone (see one_max_chunks)
+constexpr int kSmallChunksPerThread = 2;                        // ... in pass A of a small operand with padded rows that is alone (see one_max_chunks)
 constexpr int kAmaxOneTile = 768;        // tiles of a pass-A launch up to which every one gets a workgroup (three per compute unit); also the size of
                                          // the partials' arrays.  1251 tiles of padded rows: 50.8 us per call at 512 workgroups, 51.9 at 1251
 constexpr int kMaxAmaxBlocks = 512;      // pass A of larger launches, all its workgroups resident.  The two parts of the six gradients of

@@ -660,12 +660,12 @@ __device__ __forceinline__ void col_amin_of(const ColOp& t, int64_t c) {
     t.col_amin[c] = (uint16_t)mn;
 }
 
-// Amax over the strips, scales (Algorithm 1) and proofs of the workgroup's 128 columns, left in shared memory
-// (abits, scale, scale5, and in mask whether the column is proven); the first strip's workgroups write them out as well.  Every
-// workgroup of the quantize pass does this for itself while its first tile is in flight, from figures that lie in the L2 cache: a
-// launch in between took 5.6 us of the 88 us of a linear layer's two operands (8192 x 4096 per-channel rows, 4096 x 6144 columns).
-// Under GAM the group amax of Algorithm 1 is the largest column amax, and for a tensor-level decision the certain flushes of all
-// columns together may prove it: the same values in every workgroup, from the per-workgroup figures of the amax pass.
+// Amax over the strips, scales (Algorithm 1) and proofs of the workgroup's 128 columns, left in shared memory (abits, scale, scale5, and in
+// mask whether the column is proven); the first strip's workgroups write them out as well.  Unless a launch of its own has formed them
+// (then they are read), every workgroup of the quantize pass does this for itself while its first tile is in flight, from figures that
+// lie in the L2 cache: a launch in between took 5.6 us of the 88 us of a linear layer's two operands (8192 x 4096 per-channel rows, 4096 x
+// 6144 columns).  Under GAM the group amax of Algorithm 1 is the largest column amax, and for a tensor-level decision the certain flushes
+// of all columns together may prove it: the same values in every workgroup, from the per-workgroup figures of the amax pass.
 template <int CRIT>
 __device__ __forceinline__ void col_scales(const ColOp& t, int64_t strip, int64_t c0, int64_t unit, ColShared& sh) {
     const int tid = threadIdx.x, w = tid >> 6, cc = tid & 127, half = tid >> 7;
