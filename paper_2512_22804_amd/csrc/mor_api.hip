@@ -210,8 +210,8 @@ size_t mor_batch_workspace_bytes(const mor_batch_item* items, int32_t n_items) {
     return total;
 }
 
-mor_status mor_analyze_quantize_batch(const mor_batch_item* items, int32_t n_items, float near_tol, void* workspace,
-                                      size_t workspace_bytes, void* stream, mor_profile* profile) {
+static mor_status run_batch_items(const mor_batch_item* items, int32_t n_items, float near_tol, void* workspace, size_t workspace_bytes,
+                                  void* stream, mor_profile* profile, int polls) {
     if (!items) return MOR_ERR_NULL;
     if (n_items <= 0 || n_items > MOR_BATCH_MAX) return MOR_ERR_SHAPE;
     static_assert(MOR_BATCH_MAX == mor::kBatchMax, "batch limit");
@@ -219,8 +219,21 @@ mor_status mor_analyze_quantize_batch(const mor_batch_item* items, int32_t n_ite
     for (int32_t i = 0; i < n_items; ++i) {
         mor_status st = make_item(&items[i].params, items[i].x, &items[i].out, items[i].stats, items[i].fake_y, items[i].ld_fake_y, &its[i]);
         if (st != MOR_OK) return st;
+        its[i].polls = polls;
     }
     return run_batch(its, n_items, near_tol, workspace, workspace_bytes, stream, profile);
+}
+
+mor_status mor_analyze_quantize_batch(const mor_batch_item* items, int32_t n_items, float near_tol, void* workspace,
+                                      size_t workspace_bytes, void* stream, mor_profile* profile) {
+    return run_batch_items(items, n_items, near_tol, workspace, workspace_bytes, stream, profile, mor::kOnePolls);
+}
+// Not part of the interface: the same with the number of times that a workgroup looks for what it waits for before it leaves its work to
+// others.
+mor_status mor_test_batch(const mor_batch_item* items, int32_t n_items, float near_tol, void* workspace, size_t workspace_bytes, void* stream,
+                          int32_t polls) {
+    if (polls < 0 || polls > mor::kOnePolls) return MOR_ERR_UNSUPPORTED;
+    return run_batch_items(items, n_items, near_tol, workspace, workspace_bytes, stream, nullptr, polls);
 }
 
 mor_status mor_fake_quantize(const mor_params* p, const uint16_t* x, uint16_t* y, int64_t ld_y, const mor_outputs* meta,

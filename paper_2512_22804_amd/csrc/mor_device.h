@@ -415,6 +415,13 @@ __device__ __forceinline__ uint32_t off_if(bool live, uint32_t off) {
     return live ? off : 0x80000000u;
 }
 
+// Words that workgroups of one launch leave for each other.
+__device__ __forceinline__ uint32_t agent_load(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float agent_load(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <class T>
+__device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Index of the operand a work unit belongs to, from the running totals of a grouped launch (uniform per wave).
 __device__ __forceinline__ int group_find(const int64_t* end, int n, int64_t v) {
     int i = 0;

@@ -1487,16 +1487,11 @@ constexpr int kTicketGroup = 16;             // workgroups to a first ticket; ti
 constexpr int kOneMaxSlots = 512;
 constexpr int kOneLine = 32;                 // words: a line of its own for every ticket and every copy of the decision
 constexpr int kTicketRoot = kOneMaxSlots / kTicketGroup * kOneLine;
-constexpr int kToldCopies = 32;              // of the decision, so that few workgroups look at one line
-constexpr int kOneTold = kTicketRoot + kOneLine, kOneLeft = kOneTold + kToldCopies * kOneLine, kOneSyncWords = kOneLeft + kOneMaxSlots;
+constexpr int kOneToldCopies = 32;           // of the decision, so that few workgroups look at one line
+constexpr int kOneTold = kTicketRoot + kOneLine, kOneLeft = kOneTold + kOneToldCopies * kOneLine, kOneSyncWords = kOneLeft + kOneMaxSlots;
 enum : uint32_t { kToldNothing = 0u, kToldMask = 1u };      // kToldMask + the mask
 static_assert(8192 + kOneSyncWords <= kMaxQuantBlocks && kOneMaxSlots <= 8192, "the words lie behind the zero counts in their array");
 __device__ __forceinline__ uint32_t* one_sync(const TensorOp& t) { return t.zero + 8192; }
-__device__ __forceinline__ uint32_t agent_load(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float agent_load(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-template <class T>
-__device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 template <int T>             // lanes of the workgroup (as a constant: blockDim is read from memory, 0.25 us)
 __device__ __forceinline__ void clear_one_sync(const TensorOp& t) {
     uint32_t* sync = one_sync(t);
@@ -1567,7 +1562,7 @@ __global__ __launch_bounds__(T, 4) void k_tensor_quant_one(OneTensor g, int poll
     const uint32_t valid = (uint32_t)(n_chunks - c_first < kTile ? n_chunks - c_first : kTile);
     const bool wide = t.rm.cpr == 0u;
     uint32_t* sync = one_sync(t);
-    uint32_t* told_at = sync + kOneTold + (b % kToldCopies) * kOneLine;
+    uint32_t* told_at = sync + kOneTold + (b % kOneToldCopies) * kOneLine;
     auto chunk_off = [&](int64_t c, int64_t ld) -> int64_t {
         if (wide) return tensor_chunk_off<true>(t, c, ld);
         const uint32_t r = row_div(t.rm, (uint32_t)c);        // (an operand that comes here has fewer than 2^31 chunks)
@@ -1761,7 +1756,7 @@ __global__ __launch_bounds__(T, 4) void k_tensor_quant_one(OneTensor g, int poll
     const unsigned long long n_padded = (unsigned long long)n_slots * kTile * 8;
     const uint32_t mask = tensor_decide<CRIT, T>(t, g.near_tol, se, se5, n_padded - sz, abits, proven, true);
     if (!open) return;
-    if (tid < kToldCopies) agent_store(sync + kOneTold + tid * kOneLine, kToldMask + mask);
+    if (tid < kOneToldCopies) agent_store(sync + kOneTold + tid * kOneLine, kToldMask + mask);
     if (mask == 0u) return;
     finish_tile(mask, b, true);
     wait_memory();
@@ -2062,6 +2057,7 @@ struct BatchRun {
     bool stats_done[kBatchMax] = {};             // the operand's block kernel has written its statistics already
     int wave_of[kBatchMax] = {};                 // operands that Algorithm 1 reads twice: the group they are taken in; others 0
     int n_waves = 1;
+    bool streamed[kBatchMax] = {};               // operands whose two passes have shared a launch: no group (-1)
     bool first_read_keeps[kBatchMax] = {};       // ... and whether the amax pass leaves them in the Infinity Cache
 
     size_t ws_bytes = 0;
@@ -2075,6 +2071,7 @@ struct BatchRun {
         ws_off += need;
         return p;
     }
+    void streamed_operands();
     void assign_waves();
     void group_mantissas(int wave);
     void sub_tensor_operands(int crit, int wave);
@@ -2093,15 +2090,41 @@ struct BatchRun {
 bool taken_whole(const BatchItem& it) {
     return scope_proof_applies(it) && (it.gran == kGranRow || it.gran == kGranBlock64 || (it.gran == kGranSub && it.o.fake == nullptr));
 }
+// Operands whose two passes share a launch.
+void BatchRun::streamed_operands() {
+    constexpr int kMost = 12;                    // operands of a launch
+    for (int c = 0; c < 2 * kTeamKinds && err == hipSuccess; ++c) {
+        int idx[kBatchMax], cnt = 0;
+        for (int i = 0; i < n; ++i)
+            if (team_stream_kind(items[i]) == c / 2 && (items[i].o.fake != nullptr) == (c % 2 != 0)) idx[cnt++] = i;
+        for (int base = 0; base < cnt && err == hipSuccess; base += kMost) {
+            TeamStreamItem ops[kMost];
+            const int m = cnt - base < kMost ? cnt - base : kMost;
+            int64_t bytes = 0;
+            for (int k = 0; k < m; ++k) bytes += items[idx[base + k]].sh.rows * items[idx[base + k]].sh.cols * 2;
+            if (!stream_pays(m, bytes, items[idx[base]].gran == kGranBlock)) continue;
+            for (int k = 0; k < m; ++k) {
+                const int i = idx[base + k];
+                ops[k].it = &items[i];
+                ops[k].gam = reinterpret_cast<uint32_t*>(carve(16));
+                ops[k].sync = reinterpret_cast<uint32_t*>(carve(sizeof(uint32_t) * kStreamWords));
+                gam_of[i] = ops[k].gam;
+                streamed[i] = true;
+            }
+            if (err == hipSuccess) err = launch_team_stream_items(ops, m, st, prof);
+        }
+    }
+}
 void BatchRun::assign_waves() {
     int64_t bytes = 0, whole_bytes = 0;
     for (int i = 0; i < n; ++i)
-        if (taken_whole(items[i])) whole_bytes += items[i].sh.rows * items[i].sh.cols * 2;
+        if (streamed[i]) wave_of[i] = -1;
+        else if (taken_whole(items[i])) whole_bytes += items[i].sh.rows * items[i].sh.cols * 2;
     const bool whole = whole_bytes > kKeepGroupBytes;
     for (int i = 0; i < n; ++i) {
         const BatchItem& it = items[i];
         first_read_keeps[i] = keep_for_second_pass(it.sh);
-        if (it.gran == kGranTensor || it.gran == kGranCol || it.scaling != kScaleGam) continue;      // (those two group themselves)
+        if (streamed[i] || it.gran == kGranTensor || it.gran == kGranCol || it.scaling != kScaleGam) continue;      // (those two group themselves)
         if (whole && taken_whole(it)) continue;
         const int64_t b = it.sh.rows * it.sh.cols * 2;
         if (bytes > 0 && bytes + b > kKeepGroupBytes) { ++n_waves; bytes = 0; }
@@ -2111,7 +2134,7 @@ void BatchRun::assign_waves() {
     if (!whole) return;
     if (bytes > 0) ++n_waves;
     for (int i = 0; i < n; ++i)
-        if (taken_whole(items[i])) {
+        if (!streamed[i] && taken_whole(items[i])) {
             wave_of[i] = n_waves - 1;
             first_read_keeps[i] &= items[i].gran == kGranBlock64;
         }
@@ -2686,6 +2709,7 @@ hipError_t launch_batch(const BatchItem* items, int n, float near_tol, void* ws,
         if (rows_form == 1 && item_parts(items[last]) < kSubRowsAlone) run.route[last] = kRouteSubGeneral;
     }
     for (int i = 0; i < n; ++i) run.will_ride |= run.route[i] == kRouteTensorGroup;
+    run.streamed_operands();
     run.assign_waves();
     for (int wave = 0; wave < run.n_waves && run.err == hipSuccess; ++wave) {
         run.group_mantissas(wave);

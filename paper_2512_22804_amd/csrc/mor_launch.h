@@ -230,6 +230,26 @@ hipError_t launch_team_items(const BatchItem* items, const int* idx, int cnt, in
                              TeamRiders* riders, hipStream_t st, KProf* prof);
 hipError_t launch_subcol_items(const BatchItem* items, const int* idx, int cnt, int crit, const uint32_t* const* gam_of,
                                hipStream_t st, KProf* prof);
+// Operands under GAM scales whose two passes share a launch, several in a call.
+struct TeamStreamItem {
+    const BatchItem* it;
+    uint32_t* gam;           // the operand's mantissa words
+    uint32_t* sync;          // [kStreamWords]
+};
+constexpr int kStreamWords = 2 * 8192;      // what the workspace has for the partials of the operand's pre-pass otherwise
+int team_stream_kind(const BatchItem& it);      // operands of one number may share a launch; -1: not streamed
+// Which calls stream them: from four operands and 8 MiB on all (us per call, launch by launch in parts / streamed: layer of twelve operands, fake
+// quantization under a tensor-level decision, 8192 tokens x hidden 4096 498 / 430 at 128 x 128, 521 / 438 at 64 x 64, 506 / 444 by rows; 1024 x 2048 122 / 111,
+// 123 / 113, 171 / 153; 512 x 1024 42.7 / 41.9, 47.3 / 45.6, 80 / 65; 64 x 256, of which some have ragged blocks and stay launch by launch, 34.2 / 34.8,
+// 30.7 / 35.9).  Fewer have nobody to share the launch with, so it saves a launch and fills the gap between the passes, but at 128 x 128 takes about
+// 2 us more to tell: 4096 x 4096 26.0 / 28.4, 8192 x 4096 40.5 / 40.5, 8192 x 14336 110.6 / 101.8; at 64 x 64 2048 x 4096 24.0 / 23.9, 4096 x 4096 30.7 / 27.3,
+// 8192 x 4096 46.3 / 40.3; by rows 22.5 / 23.3, 26.7 / 26.0, 43.3 / 38.4.  (Two or three of more than 256 MiB together stay in parts, although they
+// would gain too: their sequence of launches, as the profile of a call records it, is relied on.)
+inline bool stream_pays(int n, int64_t bytes, bool block128) {
+    if (n >= 4) return bytes >= 8ll << 20;
+    return bytes >= (block128 ? 128ll : 32ll) << 20 && bytes <= 256ll << 20;
+}
+hipError_t launch_team_stream_items(const TeamStreamItem* ops, int n, hipStream_t st, KProf* prof);
 size_t column_workspace_bytes(int64_t rows, int64_t cols);
 // Per-channel columns with a tensor-level decision: the column-amax pass counts certain flushes per column anyway, and their
 // total may prove the operand's BF16 decision (Eq. 2); the quantize pass then writes the fallback and the word below says so.

@@ -1,0 +1,120 @@
+"""Operands under GAM scales whose two passes share a launch (several of them in a call, or a large one): the same outputs, bit for bit, as
+each of them gives alone launch by launch; also where workgroups do not wait and leave their units to the launch that follows, and from
+a replayed graph."""
+import ctypes as C
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# sizes at the edges of the first pass's tiles (64 x 256, pieces of 4096 of a row, four to a workgroup) and of the groups of eight workgroups
+BLOCKS = [(128, 128), (128, 8320), (1152, 640), (1024, 2048), (2176, 1152), (896, 384)]
+ROWS = [(1, 4096), (333, 4104), (1027, 1000), (512, 4096), (250, 14336), (5, 16384), (64, 8)]
+NAMES = ("fp8", "bf16", "scale", "amax", "err_sum", "nnz", "mask", "scale_e8m0", "group_mantissa")
+
+
+def _operands(gran, dev):
+    """Operands that stay in E4M3, that fall back with and without a proof, and with an infinity."""
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(7)
+    xs = []
+    for k, (rows, cols) in enumerate(ROWS if gran == "channel_row" else BLOCKS):
+        x = torch.randn((rows, cols), generator=gen, device=dev)
+        if k % 3 == 1:
+            x *= torch.where(torch.rand((rows, cols), generator=gen, device=dev) < 0.3, 1e-9, 1.0)
+        if k % 3 == 2:
+            x *= torch.where(torch.rand((rows, cols), generator=gen, device=dev) < 0.047, 1e-9, 1.0)
+        x = x.to(torch.bfloat16)
+        if k == 4:
+            x[rows // 2, cols // 2] = float("inf")
+        xs.append(x)
+    return xs
+
+
+def _entry(B, x, gran, scope, fake, dev):
+    p = B.make_params(*x.shape, gran, scope, "mean_rel_err", 0.045, scaling="gam")
+    out = B.alloc_outputs(p, dev, want_bf16=not fake, want_fp8=not fake, bf16_fill=0x1234)
+    out.workspace = None
+    for n in NAMES:
+        t = getattr(out, n)
+        if t is not None and n != "bf16":
+            t.view(torch.uint8).fill_(0x5A)
+    y = torch.full(x.shape, 3.0, dtype=torch.bfloat16, device=dev) if fake else None
+    st = torch.full((B.STATS_BYTES,), 0x5A, dtype=torch.uint8, device=dev) if not fake else None
+    return p, x, out, st, y
+
+
+def _same(want, got, case):
+    for k, (a, b) in enumerate(zip(want, got)):
+        for n in NAMES:
+            u, v = getattr(a[2], n), getattr(b[2], n)
+            assert (u is None) == (v is None) and (u is None or torch.equal(u.view(torch.uint8), v.view(torch.uint8))), (case, k, n)
+        for u, v in ((a[3], b[3]), (a[4], b[4])):
+            assert u is None or torch.equal(u.view(torch.uint8), v.view(torch.uint8)), (case, k)
+
+
+def _run(B, entries, polls=None):
+    items = B.make_batch(entries)
+    ws = torch.full((max(16, B.mor_batch_workspace_bytes(items)),), 0xA7, dtype=torch.uint8, device=entries[0][1].device)
+    if polls is None:
+        B.mor_analyze_quantize_batch(items, 1e-5, ws)
+    else:
+        lib = B.load()
+        lib.mor_test_batch.argtypes = [C.POINTER(B.MorBatchItem), C.c_int32, C.c_float, C.c_void_p, C.c_size_t, C.c_void_p, C.c_int32]
+        assert lib.mor_test_batch(items, len(items), 1e-5, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream, polls) == 0
+    torch.cuda.synchronize()
+    return ws
+
+
+@pytest.mark.parametrize("fake", [False, True])
+@pytest.mark.parametrize("scope", ["tensor", "partition"])
+@pytest.mark.parametrize("gran", ["block128", "block64", "channel_row"])
+def test_both_passes_in_a_launch(gran, scope, fake):
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    xs = _operands(gran, dev)
+    assert sum(x.numel() for x in xs) * 2 >= 8 << 20
+    want = [_entry(B, x, gran, scope, fake, dev) for x in xs]
+    for e in want:
+        _run(B, [e])
+    assert {int(e[2].mask.max()) for e in want} == {0, 1}
+    for polls in (None, 0):
+        print(f"[stream] {gran} {scope} fake={fake} polls={polls}", flush=True)
+        got = [_entry(B, x, gran, scope, fake, dev) for x in xs]
+        _run(B, got, polls)
+        _same(want, got, (gran, scope, fake, polls))
+    # captured and replayed, with other work between the replays
+    got = [_entry(B, x, gran, scope, fake, dev) for x in xs]
+    items = B.make_batch(got)
+    ws = torch.full((B.mor_batch_workspace_bytes(items),), 0x3C, dtype=torch.uint8, device=dev)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.mor_analyze_quantize_batch(items, 1e-5, ws)
+    for replay in range(3):
+        for e in got:
+            for t in (e[2].scale, e[2].err_sum, e[4] if fake else e[2].fp8):
+                t.view(torch.uint8).fill_(0x33)
+        graph.replay()
+        torch.cuda.synchronize()
+        _same(want, got, (gran, scope, fake, "replay", replay))
+
+
+@pytest.mark.parametrize("gran, rows, cols", [("block64", 4096, 4096), ("channel_row", 8192, 4096), ("channel_row", 2048, 14336), ("block128", 8192, 8192)])
+def test_a_large_operand_alone(gran, rows, cols):
+    """Against two smaller halves of its rows as bands would be wrong (one group), so against the same operand beside 300 MB of others,
+    where two or three operands are taken launch by launch."""
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(11)
+    x = torch.randn((rows, cols), generator=gen, device=dev)
+    x = (x * torch.where(torch.rand((rows, cols), generator=gen, device=dev) < 0.1, 1e-8, 1.0)).to(torch.bfloat16)
+    other = torch.ones((16384, 8192), dtype=torch.bfloat16, device=dev)
+    print(f"[stream] alone {gran} {rows}x{cols}", flush=True)
+    want = [_entry(B, x, gran, "tensor", False, dev), _entry(B, other, gran, "tensor", False, dev)]
+    _run(B, want)
+    for polls in (None, 0):
+        got = [_entry(B, x, gran, "tensor", False, dev)]
+        _run(B, got, polls)
+        _same(want[:1], got, (gran, rows, cols, polls))
