@@ -64,6 +64,8 @@ def algorithmic_bytes(kernel: str, n_elem: int, n_part: int, fallback_frac: floa
         return 2.0 * n_elem
     if kernel == "tensor_quant":
         return 2.0 * n_elem + n_elem + (2.0 * n_elem if fused else 0.0)
+    if kernel == "tensor_stream":      # both passes
+        return algorithmic_bytes("tensor_amax", n_elem, n_part, fallback_frac, fused) + algorithmic_bytes("tensor_quant", n_elem, n_part, fallback_frac, fused)
     if kernel == "fallback_copy":
         return 0.0 if fused else 4.0 * n_elem * fallback_frac
     if kernel in ("stats_partial",):
@@ -341,7 +343,7 @@ def run_configs(B, W, torch, dev, log, target_ms=40.0):
 
 
 KERNEL_GRAN = {"sub1x128": "sub1x128", "team_block": "block128", "tensor_amax": "tensor", "tensor_quant": "tensor",
-               "fallback_copy": "tensor"}
+               "tensor_stream": "tensor", "fallback_copy": "tensor"}
 
 
 def main() -> int:
@@ -531,8 +533,8 @@ def main() -> int:
                 "traffic_matches_tree": bool(traffic is not None and traffic_sha == tree_sha),
                 "avg_launch_us": round(dom["ms"] / dom["launches"] * 1e3, 2),
                 "algorithmic_bytes_per_launch": round(dom["bytes"] / dom["launches"], 1),
-                # the gradients' second read finds up to 96 MiB of each part in the Infinity Cache: `achieved` and `traffic` count
-                # those bytes like the ones that HBM delivers
+                # the gradients' second read finds its operands in the Infinity Cache: `achieved` and `traffic` count those bytes like
+                # the ones that HBM delivers
                 "bytes_counted": "between L2 and the memory side, Infinity Cache hits included",
                 "per_kernel": {k: {"avg_us": round(r["ms"] / r["launches"] * 1e3, 2),
                                    "gbs": round(r["bytes"] / (r["ms"] * 1e-3) / 1e9, 1) if r["ms"] > 0 else 0.0,

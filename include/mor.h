@@ -247,7 +247,10 @@ typedef enum {
     MOR_KERNEL_GROUP_MANTISSA = 13,
     MOR_KERNEL_TEAM_BLOCK = 14,      /* 128x128 blocks, 64x64 blocks, per-channel rows (id 2 is no longer used) */
     MOR_KERNEL_COLUMN_TILE = 15,     /* 128x1 sub-columns; per-channel columns: amax and quantize passes */
-    MOR_KERNEL_COLUMN_COMBINE = 16   /* per-channel columns: scales from the amax partials, final decision */
+    MOR_KERNEL_COLUMN_COMBINE = 16,  /* per-channel columns: scales from the amax partials, final decision */
+    MOR_KERNEL_TENSOR_STREAM = 17,   /* per-tensor operands: amax and quantize passes in one launch */
+    MOR_KERNEL_TEAM_STREAM = 18,     /* 128x128 blocks, 64x64 blocks, per-channel rows under GAM scales: group amax and blocks in one launch */
+    MOR_KERNEL_STREAM_CLEAR = 19     /* clears the words that the workgroups of such a launch leave for each other */
 } mor_kernel_id;
 #define MOR_PROFILE_MAX 16
 typedef struct mor_profile {

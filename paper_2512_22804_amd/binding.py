@@ -43,7 +43,7 @@ MOR_STATS_FLAG_FUSED_FALLBACK = 1
 KERNEL_NAMES = {1: "sub1x128", 2: "block128", 3: "tensor_amax", 4: "tensor_quant", 5: "tensor_finalize",
                 6: "fallback_copy", 7: "scope_reduce", 8: "scope_decide", 9: "scope_fill_mask",
                 10: "stats_partial", 11: "stats_final", 12: "group_amax", 13: "group_mantissa", 14: "team_block",
-                15: "column_tile", 16: "column_combine"}
+                15: "column_tile", 16: "column_combine", 17: "tensor_stream", 18: "team_stream", 19: "stream_clear"}
 
 
 class MorParams(C.Structure):

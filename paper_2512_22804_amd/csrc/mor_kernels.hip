@@ -9,6 +9,7 @@
 
 #include "mor_device.h"
 #include "mor_launch.h"
+#include "mor_stream.h"
 #include "mor_sub1x128.h"
 
 namespace mor {
@@ -1243,14 +1244,45 @@ __device__ __forceinline__ uint32_t tensor_pass_a_result(const TensorOp& t, bool
     proven = prove && (shf[0] + shf[1]) + (shf[2] + shf[3]) >= t.flush_need;
     return max(max(sha[0], sha[1]), max(sha[2], sha[3]));
 }
-// STRIDED: operands with padded leading dimensions (see RowMap).
-template <int CRIT, bool FAKE, bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int block0) {
+// Where pass A shares the launch (see mor_stream.h): a lane's share of one of its tiles.  An element counts as certain to flush against
+// the amax of the tile that its wave holds.
+template <bool STRIDED>
+__device__ __forceinline__ void tensor_stream_count(const TensorOp& t, int tile, int tid, uint32_t& amax, uint32_t& flushes) {
     constexpr int CH = kTensorChunksPerThread, kTile = 256 * CH;
-    const int block = (int)blockIdx.x + block0;
-    const int op = group_find32(g.slot_end, g.n, block);
-    const TensorOp& t = g.op[op];
-    const int b = block - (op ? g.slot_end[op - 1] : 0);
+    const int64_t c_first = (int64_t)tile * kTile;
+    const uint32_t valid = (uint32_t)(t.n_chunks - c_first < kTile ? t.n_chunks - c_first : kTile);
+    RowPos pos{0u, 0u};
+    int64_t row0 = 0;
+    if constexpr (STRIDED) row0 = row_tile_first(t.rm, c_first, (uint32_t)tid, pos);
+    const BufRsrc rx = STRIDED ? make_buf(t.x + row0 * t.rm.ld) : make_buf_window(t.x + c_first * 8, valid * 16u);
+    u32x4 v[CH];
+    auto load = [&](auto keep) {
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            uint32_t off = (uint32_t)tid * 16u + u * 4096u;
+            if constexpr (STRIDED) { off = row_off<16>(pos, (uint32_t)t.rm.ld * 2u, (uint32_t)tid + u * 256u < valid); row_step(t.rm, pos); }
+            v[u] = buf_load16_first<decltype(keep)::value>(rx, off, 0u);
+        }
+    };
+    if (tile >= t.keep_from) load(std::true_type{});
+    else load(std::false_type{});
+    uint32_t a2 = 0u;
+#pragma unroll
+    for (int u = 0; u < CH; ++u) a2 = amax2_of(v[u], a2);
+    const uint32_t a = wave_allmax_u32(fold_max16(a2));
+    amax = max(amax, a);
+    if (t.flush_need != 0ull) flushes += certain_flushes<CH>(v, a | (a << 16));
+}
+struct TensorTold {
+    const uint32_t* copy;
+    int polls;
+};
+// STRIDED: operands with padded leading dimensions (see RowMap).  STREAM: pass A shares the launch, a tile per workgroup.
+template <int CRIT, bool FAKE, bool STRIDED, bool STREAM>
+__device__ __forceinline__ void tensor_quant_body(const TensorOp& t, int b, const TensorTold& told_by) {
+    constexpr int CH = kTensorChunksPerThread, kTile = 256 * CH;
+    uint32_t told = 0u;
+    if constexpr (STREAM) told = agent_load(told_by.copy);      // (before the tile's loads, so that it is there before them)
     const uint16_t* __restrict__ x = t.x;
     uint8_t* __restrict__ fp8 = t.o.fp8;
     const int64_t n_chunks = t.n_chunks, n_tiles = t.n_tiles, n_slots = t.n_slots;
@@ -1258,6 +1290,13 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
     const bool wide = STRIDED && t.rm.cpr == 0u;             // chunk by chunk, in the careful path below; pass A proves nothing then
     auto load_tile = [&](u32x4* raw, int64_t tile) {
         const int64_t c0 = tile * kTile + threadIdx.x;
+        if constexpr (STREAM && !STRIDED) {
+            const int64_t left = n_chunks - tile * kTile;
+            const BufRsrc rx = make_buf_window(x + tile * (kTile * 8), (uint32_t)(left < kTile ? left : kTile) * 16u);
+#pragma unroll
+            for (int u = 0; u < CH; ++u) raw[u] = buf_load16(rx, threadIdx.x * 16u + u * 4096u, 0u);
+            return;
+        }
         if constexpr (STRIDED) {
             // (wide: a null window, so all chunks read as zeros here; the careful path reads them itself)
             RowPos pos{0u, 0u};
@@ -1281,7 +1320,17 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
     int64_t tl = b;
     load_tile(bufA, tl);
     bool proven;                                             // then the BF16 fallback is written in this sweep
-    const uint32_t abits = tensor_pass_a_result(t, proven);
+    uint32_t abits;
+    if constexpr (STREAM) {
+        told = stream_told(told_by.copy, told, told_by.polls);
+        if (!told) {
+            told = stream_scan((int)n_tiles, (uint32_t)t.flush_need, [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { tensor_stream_count<STRIDED>(t, k, tid, amax, flushes); });
+            asm volatile("" : "+s"(tl));                     // the tile is loaded again, so that its registers need not be kept meanwhile
+            load_tile(bufA, tl);
+        }
+        abits = told & kAmaxBits;
+        proven = (told & kToldProven) != 0u;
+    } else abits = tensor_pass_a_result(t, proven);
     uint16_t* __restrict__ bf16 = t.o.bf16;
     if (b == 0 && threadIdx.x == 0) { t.abits[0] = abits; t.abits[1] = proven ? 1u : 0u; }
     // one block = the group: under GAM the block's own mantissa is the group mantissa and the scale is s_b
@@ -1379,12 +1428,53 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
     };
     for (;;) {
         process(bufA, tl);
+        if constexpr (STREAM) break;
         tl += n_slots;
         if (tl >= n_tiles) break;
         load_tile(bufA, tl);
     }
     TensorPartials tp{t.err, t.err5, t.zero};
     tensor_publish<CRIT>(acc, tp, b);
+}
+template <int CRIT, bool FAKE, bool STRIDED>
+__global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int block0) {
+    const int block = (int)blockIdx.x + block0;
+    const int op = group_find32(g.slot_end, g.n, block);
+    tensor_quant_body<CRIT, FAKE, STRIDED, false>(g.op[op], block - (op ? g.slot_end[op - 1] : 0), TensorTold{});
+}
+// Passes A and B of per-tensor operands under Eq. 2 in one launch (see mor_stream.h).  The first `rider_wgs` workgroups compute the partial
+// statistics records of the batch's sub-tensor operands.  The operand's words lie in the array of the E5M2 sums, which Eq. 2 leaves free.
+// g.amax_end: groups of the first pass; g.slot_end: workgroups of the second, a tile each, padded to groups of eight.
+__device__ __forceinline__ uint32_t* stream_words(const TensorOp& t) { return reinterpret_cast<uint32_t*>(t.err5); }
+__global__ __launch_bounds__(256) void k_tensor_stream_clear(GroupTensor g) {      // blockIdx.y = operand
+    const TensorOp& t = g.op[blockIdx.y];
+    stream_clear(stream_words(t), (int)t.n_tiles, (int)blockIdx.x);
+}
+template <bool FAKE, bool STRIDED>
+__global__ __launch_bounds__(256) void k_tensor_stream(GroupTensor g, GroupStats riders, StreamOrder order, int rider_wgs, int polls) {
+    const int block = (int)blockIdx.x - (rider_wgs + 7) / 8 * 8;
+    if (block < 0) {
+        if ((int)blockIdx.x < rider_wgs) stats_partial_body<256>(riders, (int)blockIdx.x);
+        return;
+    }
+    const StreamPlace place = stream_place(order, (uint32_t)block >> 3);
+    const int in8 = block & 7;
+    if (place.first) {
+        __shared__ uint32_t sh8[8];
+        const int op = group_find32(g.amax_end, g.n, (int)place.group);
+        const TensorOp& t = g.op[op];
+        const int in_op = (int)place.group - (op ? g.amax_end[op - 1] : 0), tiles = (int)t.n_tiles, tile = in_op * 8 + in8;
+        auto count = [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { tensor_stream_count<STRIDED>(t, k, tid, amax, flushes); };
+        if (tile < tiles) stream_first(stream_words(t), tile, sh8, count);
+        else if (in8 == 0 && in_op * 8 >= tiles) (void)stream_collect(stream_words(t), tiles, (uint32_t)t.flush_need, polls, sh8, count);
+        return;
+    }
+    const int wg = (int)place.group * 8 + in8;
+    const int op = group_find32(g.slot_end, g.n, wg);
+    const TensorOp& t = g.op[op];
+    const int b = wg - (op ? g.slot_end[op - 1] : 0);
+    if (b >= (int)t.n_tiles) return;
+    tensor_quant_body<kCritEq2, FAKE, STRIDED, true>(t, b, TensorTold{stream_copy(stream_words(t), b), polls});
 }
 // Decision on a per-tensor operand from its sums (se and se5 over n non-zero elements): every thread of the workgroup calls it and gets
 // the mask; with `emit`, thread 0 writes the outputs and the statistics.
@@ -2093,6 +2183,9 @@ bool taken_whole(const BatchItem& it) {
 // Operands whose two passes share a launch.
 void BatchRun::streamed_operands() {
     constexpr int kMost = 12;                    // operands of a launch
+    bool beside = false;
+    for (int i = 0; i < n; ++i)
+        beside |= items[i].scaling == kScaleGam && items[i].gran != kGranTensor && items[i].gran != kGranCol && team_stream_kind(items[i]) < 0;
     for (int c = 0; c < 2 * kTeamKinds && err == hipSuccess; ++c) {
         int idx[kBatchMax], cnt = 0;
         for (int i = 0; i < n; ++i)
@@ -2102,7 +2195,7 @@ void BatchRun::streamed_operands() {
             const int m = cnt - base < kMost ? cnt - base : kMost;
             int64_t bytes = 0;
             for (int k = 0; k < m; ++k) bytes += items[idx[base + k]].sh.rows * items[idx[base + k]].sh.cols * 2;
-            if (!stream_pays(m, bytes, items[idx[base]].gran == kGranBlock)) continue;
+            if (!stream_pays(m, bytes, items[idx[base]].gran == kGranBlock, beside)) continue;
             for (int k = 0; k < m; ++k) {
                 const int i = idx[base + k];
                 ops[k].it = &items[i];
@@ -2495,6 +2588,51 @@ struct TensorPart {
     int a0, a1, s0, s1;      // workgroups of pass A and pass B
     int lds;                 // residency cap
 };
+// Both passes in one launch, under Eq. 2 with two types.  us per call, with a launch for each pass / streamed: the six gradients of a layer (and its
+// other operands, statistics) 8192 tokens x hidden 4096 409 / 382.5, 4096 x 3072 236 / 212, 1024 x 2048 107 / 97, 512 x 1024 47 / 37; six of 4096 x 4096
+// kept in E4M3 102 / 81, two 38 / 35; three of 1024 x 4096 (768 tiles, a workgroup each in either pass) 21.6 / 23.5, four 24.3 / 24.8, six 36.4 / 32.0.  Alone
+// there is nothing to overlap: dense 4096 x 4096 23.0 / 24.2, 4099 x 5000 48.7 / 46.4 (with a 1 x 128 operand), 8192 x 4096 36.8 / 35.8, 14336 x 4096 53.5 /
+// 55.1, 8192 x 14336 97.7 / 100.5 (falling back to BF16 135 / 132.6); padded rows 4096 x 4096 24.3 / 25.5, 4099 x 5000 31.1 / 28.4, 8192 x 4096
+// 40.4 / 39.2, 8192 x 14336 105.6 / 106.2 (140.9 / 133.2).
+bool tensor_stream_pays(int n, int64_t tiles, bool strided, bool ride) {
+    if (n == 1) return tiles > 1024 && (strided || tiles <= 2560);
+    return tiles > (ride ? kAmaxOneTile : 1280);
+}
+template <bool STRIDED>
+hipError_t launch_tensor_stream(GroupTensor& g, const GroupStats& riders, int ride_partial, int c_end, int ride_final, bool fake, int polls, hipStream_t st, KProf* prof) {
+    uint32_t groups = 0u, largest = 0u;
+    int slots = 0, most = 0;
+    for (int k = 0; k < g.n; ++k) {
+        TensorOp& t = g.op[k];
+        const int tiles = (int)t.n_tiles;
+        const uint32_t mine = stream_groups(tiles);
+        groups += mine;
+        slots += (tiles + 7) / 8 * 8;
+        g.amax_end[k] = (int32_t)groups;
+        g.slot_end[k] = slots;
+        t.n_slots = tiles;
+        if (g.n > 1) t.keep_from = 0;                     // the second pass follows at the distance of one operand
+        if (mine > largest) largest = mine;
+        if (tiles > most) most = tiles;
+    }
+    StreamOrder order;
+    if (!stream_order(order, groups, largest, (uint32_t)slots / 8u)) return hipErrorInvalidValue;
+    {
+        ProfScope ps(prof, kKernStreamClear, st);
+        k_tensor_stream_clear<<<dim3(stream_clear_wgs(most), (unsigned)g.n), dim3(256), 0, st>>>(g);
+    }
+    {
+        ProfScope ps(prof, kKernTensorStream, st);
+        const dim3 grid(((unsigned)ride_partial + 7u) / 8u * 8u + 8u * groups + (unsigned)slots);
+        // (gradients of a layer 383.0 us per call uncapped, 382.5 at 5, 382.1 at 4, 382.4 at 3 workgroups per compute unit, kept lean 347.5, 347.7, 346.2,
+        // 354.9; a slice of 4099 x 5000 28.6, 28.6, 30.1, 28.5)
+        if (fake) k_tensor_stream<true, STRIDED><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls);
+        else k_tensor_stream<false, STRIDED><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls);
+    }
+    ProfScope ps(prof, kKernFallbackCopy, st);
+    k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
+    return hipGetLastError();
+}
 template <bool STRIDED>
 void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_parts, const GroupStats& riders, int ride_partial, int c_end,
                           int ride_final, int crit, bool fake, hipStream_t st, KProf* prof) {
@@ -2663,7 +2801,11 @@ void BatchRun::per_tensor_operands(int crit) {
                 ride_final = ride_partial > riders.n ? riders.n : 0;      // single-workgroup operands are final already
                 riders_used = true;
             }
-            if (one) launch_one_tensor(g.op[0], near_tol, crit, fake, it0.polls, st, prof);
+            bool stream = crit == kCritEq2 && tensor_stream_pays(cnt, all_tiles, strided, ride);
+            for (int k = 0; k < cnt; ++k) stream &= !g.op[k].three && g.op[k].n_tiles <= kStreamMaxTiles && !(strided && g.op[k].rm.cpr == 0u);
+            if (!one && stream) err = strided ? launch_tensor_stream<true>(g, riders, ride_partial, c_end, ride_final, fake, it0.polls, st, prof)
+                                              : launch_tensor_stream<false>(g, riders, ride_partial, c_end, ride_final, fake, it0.polls, st, prof);
+            else if (one) launch_one_tensor(g.op[0], near_tol, crit, fake, it0.polls, st, prof);
             else if (strided) launch_tensor_passes<true>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             else launch_tensor_passes<false>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             cnt = 0;

@@ -106,7 +106,7 @@ enum KernelId {
     kKernSub1x128 = 1, kKernBlock128 = 2, kKernTensorAmax = 3, kKernTensorQuant = 4, kKernTensorFinalize = 5,
     kKernFallbackCopy = 6, kKernScopeReduce = 7, kKernScopeDecide = 8, kKernScopeFillMask = 9,
     kKernStatsPartial = 10, kKernStatsFinal = 11, kKernGroupAmax = 12, kKernGroupMantissa = 13,
-    kKernTeamBlock = 14, kKernColumnTile = 15, kKernColumnCombine = 16
+    kKernTeamBlock = 14, kKernColumnTile = 15, kKernColumnCombine = 16, kKernTensorStream = 17, kKernTeamStream = 18, kKernStreamClear = 19
 };
 
 // Records the caller's events around one kernel launch when profiling is requested.
@@ -245,8 +245,11 @@ int team_stream_kind(const BatchItem& it);      // operands of one number may sh
 // 2 us more to tell: 4096 x 4096 26.0 / 28.4, 8192 x 4096 40.5 / 40.5, 8192 x 14336 110.6 / 101.8; at 64 x 64 2048 x 4096 24.0 / 23.9, 4096 x 4096 30.7 / 27.3,
 // 8192 x 4096 46.3 / 40.3; by rows 22.5 / 23.3, 26.7 / 26.0, 43.3 / 38.4.  (Two or three of more than 256 MiB together stay in parts, although they
 // would gain too: their sequence of launches, as the profile of a call records it, is relied on.)
-inline bool stream_pays(int n, int64_t bytes, bool block128) {
-    if (n >= 4) return bytes >= 8ll << 20;
+// Where other operands of the call have a pre-pass of their own (`beside`), streaming adds launches to theirs: layer with weights at 128 x 128,
+// activations at 1 x 128 and gradients per tensor under GAM scales, 512 x 1024 55 / 66, 2048 x 1024 52 / 62, 1024 x 2048 (110 MB of weights) 131 / 133, 4096 x 2048
+// 147 / 146, 4096 x 3072 (248 MB) 298 / 278.
+inline bool stream_pays(int n, int64_t bytes, bool block128, bool beside) {
+    if (n >= 4) return bytes >= (beside ? 128ll : 8ll) << 20;
     return bytes >= (block128 ? 128ll : 32ll) << 20 && bytes <= 256ll << 20;
 }
 hipError_t launch_team_stream_items(const TeamStreamItem* ops, int n, hipStream_t st, KProf* prof);

@@ -10,6 +10,7 @@
 
 #include "mor_device.h"
 #include "mor_launch.h"
+#include "mor_stream.h"
 #include "mor_sub1x128.h"
 
 namespace mor {
@@ -130,28 +131,18 @@ __device__ __forceinline__ void team_allsum3(float& a, float& b, uint32_t& z, Te
     }
 }
 
-// Operands whose two passes share a launch (see k_team_stream).  The operand's words in the workspace:
-constexpr int kToldLine = 32, kToldCopies = 32;       // copies of what the first pass has found, a line each
-constexpr int kStreamLeft = kToldCopies * kToldLine;  // how many units were left, then a bit for each unit (wave teams: for each wave of a unit)
-constexpr int kStreamBits = kStreamLeft + kToldLine, kStreamMaxBits = 16384;
-constexpr int kStreamTiles = kStreamBits + kStreamMaxBits / 32, kStreamMaxTiles = kStreamWords - kStreamTiles;      // then a word for each tile of the first pass
-// A tile's word: bit 31 (it is there), its certain flushes, its amax pattern.  What is told: bit 31, bit 30 (the BF16 decision is proven), the operand's amax pattern.
-constexpr uint32_t kThere = 0x80000000u, kToldProven = 0x40000000u, kAmaxBits = 0x7FFFu;
-constexpr int kFlushShift = 15;
+// An operand whose pre-pass shares the launch (see mor_stream.h).
 struct StreamUnit {
     const uint32_t* told;      // the copy to look at
-    uint32_t* sync;            // the operand's words
     int polls;
-    uint32_t figures;          // kTeamLeft: what was told
 };
 enum { kTeamAlone = 0,         // the operand's figures come from earlier launches
-       kTeamStream = 1,        // from the first pass in this launch
-       kTeamLeft = 2 };        // a unit that its workgroup has left
+       kTeamStream = 1 };      // from the first pass in this launch; `scan` finds them out from the operand itself
 
 // EDGE = false: the operand has no partial blocks (block teams), or its rows are a whole number of the
 // team's sweeps (row teams), so chunk validity is uniform over the team and costs no per-lane predicates.
-template <int TEAM, int CRIT, bool FAKE, bool EDGE, int FROM>
-__device__ __forceinline__ void team_block(const TeamOp& t, int64_t unit, TeamShared& sh, const StreamUnit& su) {
+template <int TEAM, int CRIT, bool FAKE, bool EDGE, int FROM, class Scan>
+__device__ __forceinline__ void team_block(const TeamOp& t, int64_t unit, TeamShared& sh, const StreamUnit& su, Scan scan) {
     constexpr bool PIPE = FROM != kTeamAlone;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const KOut& o = t.o;
@@ -213,50 +204,39 @@ __device__ __forceinline__ void team_block(const TeamOp& t, int64_t unit, TeamSh
     uint32_t told = 0u;
     if constexpr (FROM == kTeamStream) told = agent_load(su.told);      // (before the block's loads, so that it is there before them)
     u32x4 raw[NCH];
+    auto load_block = [&](uint32_t off) {
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-        if constexpr (BUF) raw[i] = buf_load16(rx, is_valid(i) ? xoff : kBufOutside, i * xstep);
-        else raw[i] = load16(src + i * src_step);
+        for (int i = 0; i < NCH; ++i) {
+            if constexpr (BUF || PIPE) raw[i] = buf_load16(rx, is_valid(i) ? off : kBufOutside, i * xstep);
+            else raw[i] = load16(src + i * src_step);
+        }
+    };
+    load_block(xoff);
+    if constexpr (PIPE) {
+        // The first pass ends well before the launch comes to the operand's blocks, so this is a look and no wait.
+        told = stream_told(su.told, told, su.polls);
+        if (!told) {
+            told = scan();
+            uint32_t off = xoff;
+            asm volatile("" : "+v"(off));                  // the block is loaded again, so that its registers need not be kept meanwhile
+            load_block(off);
+        }
     }
-    // tensor-level decision already proven by the pre-pass (uniform): the BF16 payload is stored below; a fake-quantized
-    // output of such an operand is its input, so the de-quantized values are not stored at all
-    bool proven = false;
-    if (!PIPE && t.prove) proven = t.gam[2] != 0u;
     // ---- amax and zero count (chunks outside the tensor count as zeros and change nothing)
     Scan8 sc{0u, 0u};
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) scan8(raw[i], sc);
+    for (int i = 0; i < NCH; ++i) {
+        scan8(raw[i], sc);
+        if constexpr (PIPE) asm volatile("" : "+v"(sc.amax2), "+v"(sc.zero2));      // (else the zero count follows the amax, with all masked words kept for it: 133 registers at 64 x 64 instead of 101)
+    }
     // pin both results here: otherwise the compiler sinks the zero count below the quantization sweep and keeps the
     // 32 masked words of the block alive across it
     asm volatile("" : "+v"(sc.amax2), "+v"(sc.zero2));
-    uint32_t amax = fold_max16(sc.amax2);
-    if constexpr (FROM == kTeamStream) {
-        // The first pass ends well before the launch comes to the operand's blocks, so this is a look and no wait, but for a chip
-        // that is full of other work: then the unit is left to the launch that follows.
-        told = (uint32_t)__builtin_amdgcn_readfirstlane((int)told);
-        for (int poll = 0; poll < su.polls && !(told & kThere); ++poll) {
-            __builtin_amdgcn_s_sleep(8);
-            told = (uint32_t)__builtin_amdgcn_readfirstlane((int)agent_load(su.told));
-        }
-        amax |= ~told & kThere;                            // a wave that was not told leaves the unit for its team
-    }
-    const uint32_t abits = team_allmax<TEAM>(amax, sh);
+    const uint32_t abits = team_allmax<TEAM>(fold_max16(sc.amax2), sh);
     const uint32_t mode = PIPE ? (uint32_t)kScaleGam : (uint32_t)t.mode;
     uint32_t mg = 0u, mg5 = 0u;
-    if constexpr (PIPE) {
-        if (FROM == kTeamStream && abits >= kThere) {
-            if (team_is_wg<TEAM>() ? tid == 0 : lane == 0) {
-                const uint32_t bit = team_is_wg<TEAM>() ? (uint32_t)unit : (uint32_t)unit * 4u + w;
-                __hip_atomic_fetch_or(su.sync + kStreamBits + (bit >> 5), 1u << (bit & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_fetch_add(su.sync + kStreamLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            return;
-        }
-        const uint32_t figures = FROM == kTeamLeft ? su.figures : told;
-        mg = group_mantissa_bits(figures & kAmaxBits, kE4M3Max, kScaleGam);
-        proven = (figures & kToldProven) != 0u;
-    }
-    if (!PIPE && mode == kScaleGam) { const uint32_t* gw = gam_words(t.gam, t.group_rows, r0); mg = gw[0]; mg5 = gw[1]; }
+    if constexpr (PIPE) mg = group_mantissa_bits(told & kAmaxBits, kE4M3Max, kScaleGam);
+    else if (mode == kScaleGam) { const uint32_t* gw = gam_words(t.gam, t.group_rows, r0); mg = gw[0]; mg5 = gw[1]; }
     float s = block_scale(abits, kE4M3Max, mode, mg);
     float s5 = 0.0f;                                       // only Eq. 3 and the three-way recipe look at E5M2
     if (!PIPE && (CRIT == kCritEq3 || t.three)) s5 = block_scale(abits, kE5M2Max, mode, mg5);
@@ -301,6 +281,11 @@ __device__ __forceinline__ void team_block(const TeamOp& t, int64_t unit, TeamSh
         }
         return e0 + e1;
     };
+    // tensor-level decision already proven by the pre-pass (uniform): the BF16 payload is stored below; a fake-quantized
+    // output of such an operand is its input, so the de-quantized values are not stored at all
+    bool proven = false;
+    if constexpr (PIPE) proven = (told & kToldProven) != 0u;
+    else if (t.prove) proven = t.gam[2] != 0u;
     float err, err5 = 0.0f;
     if (CRIT == kCritEq3 && fast && s5 == 128.0f * s) {
         // both formats in one sweep, one reciprocal per element (see quant8_dual)
@@ -390,7 +375,7 @@ __global__ __launch_bounds__(TEAM == kTeamBigRow ? 1024 : 256) void k_team_group
     const int op = group_find(g.unit_end, g.n, blockIdx.x);
     const TeamOp& t = g.op[op];
     const int64_t unit = (int64_t)blockIdx.x - (op ? g.unit_end[op - 1] : 0);
-    team_block<TEAM, CRIT, FAKE, EDGE, kTeamAlone>(t, unit, sh, StreamUnit{});
+    team_block<TEAM, CRIT, FAKE, EDGE, kTeamAlone>(t, unit, sh, StreamUnit{}, [] { return 0u; });
 }
 
 // Pre-pass of Algorithm 1 (group amax) for operands with 128 x 128 / 64 x 64 blocks or per-channel rows whose decision is taken
@@ -424,8 +409,8 @@ static_assert(kProvePiece == 4096, "scope_proof_units() counts pieces of 4096 el
 // KIND kProveBlock64: the same 128 x 128 tiles as for kProveBlock128, four blocks each; a lane's first four chunks lie
 // in an upper block, the others in a lower one, lanes with bit 3 set in a right-hand one.
 template <int KIND>
-__device__ __forceinline__ void prove_load(const ProveOp& t, int64_t unit, u32x4 (&raw)[kChunks]) {
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+__device__ __forceinline__ void prove_load(const ProveOp& t, int64_t unit, u32x4 (&raw)[kChunks], int tid) {
+    const int lane = tid & 63, w = tid >> 6;
     if constexpr (KIND == kProveRows) {
         // wave w of the workgroup's unit takes piece 4 * unit + w; chunks beyond the row (or beyond the operand) load zeros
         const int64_t piece = unit * 4 + w, row = piece / t.units_x, c0 = (piece - row * t.units_x) * kProvePiece;
@@ -539,10 +524,10 @@ __device__ __forceinline__ void prove_tiles(const ProveOp& t, int b, int nb, uin
     const int64_t n_wg_units = prove_units<KIND>(t);
     u32x4 cur[kChunks], nxt[kChunks];
     int64_t unit = b;
-    if (unit < n_wg_units) prove_load<KIND>(t, unit, cur);
+    if (unit < n_wg_units) prove_load<KIND>(t, unit, cur, (int)threadIdx.x);
     while (unit < n_wg_units) {
         const int64_t next = unit + nb;
-        if (next < n_wg_units) prove_load<KIND>(t, next, nxt);        // uniform over the workgroup
+        if (next < n_wg_units) prove_load<KIND>(t, next, nxt, (int)threadIdx.x);        // uniform over the workgroup
         prove_count<KIND>(cur, amax_run, flush_run);
 #pragma unroll
         for (int i = 0; i < kChunks; ++i) cur[i] = nxt[i];
@@ -572,16 +557,12 @@ __global__ __launch_bounds__(256) void k_block_amax_prove(GroupProve g) {
     }
 }
 
-// ---- Operands under GAM scales, several in a call: both passes over all of them in ONE launch.  The launch walks over the operands' tiles
-//      twice at once: the first pass (amax, certain flushes) leads, the block kernel follows at a distance of the largest operand and
-//      some more, so what it reads again lies in the Infinity Cache, and reads and writes are mixed evenly all the way.  A workgroup of
-//      the first pass leaves its figures in a word of its own; one workgroup behind an operand's last tile collects them and tells
-//      the blocks' workgroups.  Workgroups are dispatched in order, so those that a wait is for have always started before; still no
-//      wait is without end: who is not told in time leaves its unit, and a small launch behind sees to what was left.
-//      Bound by what fabric and memory deliver for 2 bytes read, then 2 read (from the Infinity Cache) and 2 or more written per element.
+// ---- Operands under GAM scales, both passes in one launch (see mor_stream.h).  Bound by what fabric and memory deliver for 2 bytes read, then
+//      2 read (from the Infinity Cache) and 2 or more written per element: 2.0 GB of a layer of twelve operands, fake quantization at 128 x 128, in
+//      430 us, 496 in parts of 256 MB with a launch for each pass and the mantissas.
 struct StreamFirst {
     int n;
-    int32_t group_end[kMaxTeamGroup];     // groups of eight workgroups: the operand's tiles, then the one that collects
+    int32_t group_end[kMaxTeamGroup];     // groups of eight workgroups
     ProveOp op[kMaxTeamGroup];            // amax_part: the operand's words; flush_part: its mantissa words
 };
 struct StreamTeam {
@@ -589,160 +570,84 @@ struct StreamTeam {
     StreamFirst first;
     int32_t units[kMaxTeamGroup];
     uint32_t flush_need[kMaxTeamGroup];   // 0: nothing is proven
-    uint32_t lead;                        // groups of the first pass before the first blocks, then ...
-    uint32_t mixed, mixed_first;          // ... groups of both, of the first pass among them ...
-    uint32_t mul, shift;                  // ... (reciprocal of `mixed`), then the remaining blocks
+    StreamOrder order;
     int32_t polls;
 };
-// Tiles of the first pass: 64 rows x 256 columns of operands in blocks, so that a load of the workgroup covers segments of 512 bytes (layer of
-// twelve operands 464 us, with tiles of 128 x 128 477, 32 x 512 466, 16 x 1024 469).  A block's bound is its amax in the 16 rows that a wave holds.
-template <int KIND>
-__device__ __forceinline__ void stream_tile(const ProveOp& t, int tile, uint32_t& amax, uint32_t& flushes) {
-    u32x4 raw[kChunks];
-    if constexpr (KIND == kProveRows) {
-        prove_load<kProveRows>(t, tile, raw);
-        prove_count<kProveRows>(raw, amax, flushes);
-    } else {
-        const int tid = threadIdx.x, tr = tile / (int)t.units_x, tc = tile - tr * (int)t.units_x, col = tc * 256 + (tid & 31) * 8;
-        const BufRsrc rx = make_buf(t.x + (int64_t)tr * 64 * t.ld + tc * 256);
-        const uint32_t off = off_if(col < t.cols, (uint32_t)(((tid >> 5) * t.ld + (tid & 31) * 8) * 2)), step = (uint32_t)(8 * t.ld * 2);
-#pragma unroll
-        for (int i = 0; i < kChunks; ++i) raw[i] = buf_load16_first<true>(rx, off, i * step);
-        uint32_t a2 = 0u;
-#pragma unroll
-        for (int i = 0; i < kChunks; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a2 = pk_max_u16(a2, raw[i][j] & 0x7FFF7FFFu);
-        uint32_t a = fold_max16(a2);
-        a = max(a, dpp_u32<kDppXor1>(a));
-        a = max(a, dpp_u32<kDppXor2>(a));
-        a = max(a, dpp_u32<kDppHalfMirror>(a));
-        if constexpr (KIND == kProveBlock128) a = max(a, dpp_u32<kDppMirror>(a));
-        const auto q = __builtin_amdgcn_permlane32_swap(a, a, false, false);
-        a = max(q[0], q[1]);
-        amax = a;
-        const uint32_t t1 = a > 0x0A00u ? a - 0x0A01u : 0u, bound2 = t1 | (t1 << 16);
-        uint32_t f2 = 0u;
-#pragma unroll
-        for (int i = 0; i < kChunks; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) f2 = pk_add_u16(f2, pk_certain_flush(raw[i][j], bound2));
-        flushes = fold_add16(f2);
-    }
-}
-__device__ __forceinline__ void stream_first(const ProveOp& t, int tile, uint32_t* sh8) {
-    uint32_t amax = 0u, flushes = 0u;
-    if (t.kind == kProveRows) stream_tile<kProveRows>(t, tile, amax, flushes);
-    else if (t.kind == kProveBlock64) stream_tile<kProveBlock64>(t, tile, amax, flushes);
-    else stream_tile<kProveBlock128>(t, tile, amax, flushes);
-    amax = wave_allmax_u32(amax);
-    flushes = wave_allsum_u32(flushes);                    // at most 4096
-    if ((threadIdx.x & 63) == 0) { sh8[threadIdx.x >> 6] = amax; sh8[4 + (threadIdx.x >> 6)] = flushes; }
-    __syncthreads();
-    if (threadIdx.x == 0)
-        agent_store(t.amax_part + kStreamTiles + tile, kThere | (((sh8[4] + sh8[5]) + (sh8[6] + sh8[7])) << kFlushShift) | max(max(sh8[0], sh8[1]), max(sh8[2], sh8[3])));
-}
 __device__ __forceinline__ int stream_tiles(const ProveOp& t) { return t.kind == kProveRows ? (int)((t.n_units + 3) / 4) : (int)t.n_units; }
-// What is to be told of the operand, from its tiles' words (uniform over the workgroup); 0 if some are not there after `polls` looks.
-__device__ __forceinline__ uint32_t stream_collect(const ProveOp& t, uint32_t flush_need, int polls, uint32_t* sh8) {
-    const uint32_t* words = t.amax_part + kStreamTiles;
-    const int n = stream_tiles(t), tid = threadIdx.x;
-    uint32_t amax = 0u, flushes = 0u;                      // (an operand has less than 2^32 elements)
-    bool all = true;
-    for (int i0 = tid; i0 < n; i0 += 8 * 256) {
-        uint32_t v[8];
-        for (;;) {
-            uint32_t there = kThere;
+// Tiles of the first pass: 64 rows x 256 columns of operands in blocks, so that a load of the workgroup covers segments of 512 bytes (layer of
+// twelve operands in parts 464 us, with tiles of 128 x 128 477, 32 x 512 466, 16 x 1024 469).  A block's bound is its amax in the 16 rows that a wave holds.
+template <int KIND>
+__device__ __forceinline__ void stream_block_tile(const ProveOp& t, int tile, int tid, uint32_t& amax, uint32_t& flushes) {
+    const int tr = tile / (int)t.units_x, tc = tile - tr * (int)t.units_x, col = tc * 256 + (tid & 31) * 8;
+    const BufRsrc rx = make_buf(t.x + (int64_t)tr * 64 * t.ld + tc * 256);
+    const uint32_t off = off_if(col < t.cols, (uint32_t)(((tid >> 5) * t.ld + (tid & 31) * 8) * 2)), step = (uint32_t)(8 * t.ld * 2);
+    u32x4 raw[kChunks];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) { v[u] = agent_load(words + (i0 + u * 256 < n ? i0 + u * 256 : i0)); there &= v[u]; }
-            all = there != 0u;
-            if (all || polls-- <= 0) break;
-            __builtin_amdgcn_s_sleep(8);
-        }
-        if (!all) break;
+    for (int i = 0; i < kChunks; ++i) raw[i] = buf_load16_first<true>(rx, off, i * step);
+    uint32_t a2 = 0u;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) { amax = max(amax, v[u] & kAmaxBits); flushes += i0 + u * 256 < n ? (v[u] & ~kThere) >> kFlushShift : 0u; }
-    }
-    amax = wave_allmax_u32(amax);
-    flushes = wave_allsum_u32(flushes);
-    if ((tid & 63) == 0) { sh8[tid >> 6] = amax; sh8[4 + (tid >> 6)] = flushes; }
-    const bool every = __syncthreads_and(all ? 1 : 0) != 0;
-    amax = max(max(sh8[0], sh8[1]), max(sh8[2], sh8[3]));
-    flushes = (sh8[4] + sh8[5]) + (sh8[6] + sh8[7]);
-    __syncthreads();
-    return every ? kThere | (flush_need != 0u && flushes >= flush_need ? kToldProven : 0u) | amax : 0u;
+    for (int i = 0; i < kChunks; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a2 = pk_max_u16(a2, raw[i][j] & 0x7FFF7FFFu);
+    uint32_t a = fold_max16(a2);
+    a = max(a, dpp_u32<kDppXor1>(a));
+    a = max(a, dpp_u32<kDppXor2>(a));
+    a = max(a, dpp_u32<kDppHalfMirror>(a));
+    if constexpr (KIND == kProveBlock128) a = max(a, dpp_u32<kDppMirror>(a));
+    const auto q = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    a = max(q[0], q[1]);
+    amax = max(amax, a);
+    const uint32_t t1 = a > 0x0A00u ? a - 0x0A01u : 0u, bound2 = t1 | (t1 << 16);
+    uint32_t f2 = 0u;
+#pragma unroll
+    for (int i = 0; i < kChunks; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f2 = pk_add_u16(f2, pk_certain_flush(raw[i][j], bound2));
+    flushes += fold_add16(f2);
 }
-// The operand's mantissa words, for the passes of a tensor-level decision, and the caller's output (one thread).
-__device__ __forceinline__ void stream_outputs(const ProveOp& t, const KOut& o, uint32_t figures) {
-    const uint32_t mg = group_mantissa_bits(figures & kAmaxBits, kE4M3Max, kScaleGam), mg5 = group_mantissa_bits(figures & kAmaxBits, kE5M2Max, kScaleGam);
-    t.flush_part[0] = mg; t.flush_part[1] = mg5; t.flush_part[2] = figures & kToldProven ? 1u : 0u;
-    if (o.gmant) { o.gmant[0] = mg; o.gmant[1] = mg5; }
+__device__ __forceinline__ void stream_count(const ProveOp& t, int tile, int tid, uint32_t& amax, uint32_t& flushes) {
+    if (t.kind == kProveRows) {
+        u32x4 raw[kChunks];
+        prove_load<kProveRows>(t, tile, raw, tid);
+        prove_count<kProveRows>(raw, amax, flushes);
+    } else if (t.kind == kProveBlock64) stream_block_tile<kProveBlock64>(t, tile, tid, amax, flushes);
+    else stream_block_tile<kProveBlock128>(t, tile, tid, amax, flushes);
 }
-__global__ __launch_bounds__(256) void k_stream_clear(StreamTeam g) {      // 4 KB of the words per workgroup, blockIdx.y = operand
+__global__ __launch_bounds__(256) void k_stream_clear(StreamTeam g) {      // blockIdx.y = operand
     const ProveOp& t = g.first.op[blockIdx.y];
-    const int i = (int)(blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i < kStreamTiles + stream_tiles(t)) *reinterpret_cast<u32x4*>(t.amax_part + i) = u32x4{0u, 0u, 0u, 0u};
+    stream_clear(t.amax_part, stream_tiles(t), (int)blockIdx.x);
 }
 // (TEAM kTeamWaveRow: rows of either length that a workgroup of 256 lanes holds)
 template <int TEAM, bool FAKE>
 __global__ __launch_bounds__(256) void k_team_stream(StreamTeam g) {
     __shared__ TeamShared sh;
-    const uint32_t group = blockIdx.x >> 3, in8 = blockIdx.x & 7u;
-    uint32_t first = group, blocks = 0u;                   // groups of either kind before this one
-    bool is_first = group < g.lead;
-    if (!is_first) {
-        const uint32_t m = group - g.lead;
-        const bool mixed = m < g.mixed;
-        const uint32_t before = mixed ? recip_div(m * g.mixed_first, g.mul, g.shift) : g.mixed_first;
-        is_first = mixed && recip_div((m + 1u) * g.mixed_first, g.mul, g.shift) != before;
-        first = g.lead + before;
-        blocks = m - before;
-    }
-    if (is_first) {
-        const int op = group_find32(g.first.group_end, g.first.n, (int)first);
+    const StreamPlace place = stream_place(g.order, blockIdx.x >> 3);
+    const int in8 = (int)(blockIdx.x & 7u);
+    if (place.first) {
+        const int op = group_find32(g.first.group_end, g.first.n, (int)place.group);
         const ProveOp& t = g.first.op[op];
-        const int in_op = (int)first - (op ? g.first.group_end[op - 1] : 0), n = stream_tiles(t), tile = in_op * 8 + (int)in8;
-        if (tile < n) { stream_first(t, tile, sh.u); return; }
-        if (in8 != 0u || in_op * 8 < n) return;            // the last of the operand's groups collects
-        const uint32_t figures = stream_collect(t, g.flush_need[op], g.polls, sh.u);
-        if (!figures) return;
-        if (threadIdx.x < kToldCopies) agent_store(t.amax_part + threadIdx.x * kToldLine, figures);
-        if (threadIdx.x == 0) stream_outputs(t, g.team.op[op].o, figures);
+        const int in_op = (int)place.group - (op ? g.first.group_end[op - 1] : 0), tiles = stream_tiles(t), tile = in_op * 8 + in8;
+        auto count = [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { stream_count(t, k, tid, amax, flushes); };
+        if (tile < tiles) { stream_first(t.amax_part, tile, sh.u, count); return; }
+        if (in8 != 0 || in_op * 8 < tiles) return;         // the last of the operand's groups collects
+        const uint32_t figures = stream_collect(t.amax_part, tiles, g.flush_need[op], g.polls, sh.u, count);
+        if (threadIdx.x != 0) return;
+        // the operand's mantissa words, for the passes of a tensor-level decision, and the caller's output
+        const uint32_t mg = group_mantissa_bits(figures & kAmaxBits, kE4M3Max, kScaleGam), mg5 = group_mantissa_bits(figures & kAmaxBits, kE5M2Max, kScaleGam);
+        t.flush_part[0] = mg; t.flush_part[1] = mg5; t.flush_part[2] = figures & kToldProven ? 1u : 0u;
+        uint32_t* gmant = g.team.op[op].o.gmant;
+        if (gmant) { gmant[0] = mg; gmant[1] = mg5; }
         return;
     }
-    const int64_t wg = (int64_t)blocks * 8 + in8;
+    const int64_t wg = (int64_t)place.group * 8 + in8;
     const int op = group_find(g.team.unit_end, g.team.n, wg);
     const int64_t unit = wg - (op ? g.team.unit_end[op - 1] : 0);
     if (unit >= g.units[op]) return;
-    uint32_t* sync = g.first.op[op].amax_part;
-    const StreamUnit su{sync + (unit & (kToldCopies - 1)) * kToldLine, sync, g.polls, 0u};
-    if (TEAM == kTeamWaveRow && g.team.op[op].cols > kWaveRowCols) team_block<kTeamWgRow, kCritEq2, FAKE, false, kTeamStream>(g.team.op[op], unit, sh, su);
-    else team_block<TEAM, kCritEq2, FAKE, false, kTeamStream>(g.team.op[op], unit, sh, su);
-}
-// Units that were left: nothing to do but on a chip that is full of other work.
-template <int TEAM, bool FAKE>
-__global__ __launch_bounds__(256) void k_team_stream_left(StreamTeam g) {
-    __shared__ TeamShared sh;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint64_t ops = __ballot(lane < g.first.n && g.first.op[lane < g.first.n ? lane : 0].amax_part[kStreamLeft] != 0u);
-    for (; ops; ops &= ops - 1) {                          // uniform over the workgroup
-        const int op = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)ops) - 1);
-        const ProveOp& t = g.first.op[op];
-        uint32_t figures = t.amax_part[0];
-        if (!(figures & kThere)) {
-            figures = stream_collect(t, g.flush_need[op], 0, sh.u);
-            if (blockIdx.x == 0 && threadIdx.x == 0) stream_outputs(t, g.team.op[op].o, figures);
-        }
-        const StreamUnit su{nullptr, nullptr, 0, figures};
-        const bool wg_rows = TEAM == kTeamWaveRow && g.team.op[op].cols > kWaveRowCols;
-        const int per_unit = team_is_wg<TEAM>() || wg_rows ? 1 : 4;      // bits
-        for (int unit = (int)blockIdx.x; unit < g.units[op]; unit += (int)gridDim.x) {
-            const int bit = unit * per_unit;
-            const uint32_t bits = t.amax_part[kStreamBits + (bit >> 5)] >> (bit & 31);
-            if (wg_rows) { if (bits & 1u) team_block<kTeamWgRow, kCritEq2, FAKE, false, kTeamLeft>(g.team.op[op], unit, sh, su); }
-            else if ((bits >> (per_unit == 1 ? 0 : w)) & 1u) team_block<TEAM, kCritEq2, FAKE, false, kTeamLeft>(g.team.op[op], unit, sh, su);
-        }
-    }
+    const ProveOp& f = g.first.op[op];
+    const StreamUnit su{stream_copy(f.amax_part, unit), g.polls};
+    auto scan = [&] { return stream_scan(stream_tiles(f), g.flush_need[op], [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { stream_count(f, k, tid, amax, flushes); }); };
+    if (TEAM == kTeamWaveRow && g.team.op[op].cols > kWaveRowCols) team_block<kTeamWgRow, kCritEq2, FAKE, false, kTeamStream>(g.team.op[op], unit, sh, su, scan);
+    else team_block<TEAM, kCritEq2, FAKE, false, kTeamStream>(g.team.op[op], unit, sh, su, scan);
 }
 
 // ======================================================================================
@@ -1684,21 +1589,13 @@ namespace {
 int stream_first_tiles(const BatchItem& it) {
     return (int)(it.gran == kGranRow ? scope_proof_units(it) : (it.sh.rows / 64) * ((it.sh.cols + 255) / 256));
 }
-// Workgroups of the first pass between an operand's last tile and its first block, at least, some 10 us: layer of twelve operands at 128 x 128, fake
-// quantization, 512 431.1, 1024 430.5, 1536 433.6, 2048 434.8 us per call.
-constexpr int kStreamMargin = 1024;
 template <int TEAM>
 void launch_team_stream(const StreamTeam& g, unsigned wgs, bool fake, hipStream_t st) {
     // layer of twelve operands, us per call uncapped / at 6 / 5 / 4 workgroups per compute unit: 128 x 128 425 / 427 / 428 / 435, 64 x 64 425 throughout,
     // per-channel rows 443 / 440 / 439 / 438
     const int lds = TEAM == kTeamWaveRow ? kResidency5 : 0;
-    if (fake) {
-        k_team_stream<TEAM, true><<<dim3(wgs), dim3(256), lds, st>>>(g);
-        k_team_stream_left<TEAM, true><<<dim3(256), dim3(256), 0, st>>>(g);
-    } else {
-        k_team_stream<TEAM, false><<<dim3(wgs), dim3(256), lds, st>>>(g);
-        k_team_stream_left<TEAM, false><<<dim3(256), dim3(256), 0, st>>>(g);
-    }
+    if (fake) k_team_stream<TEAM, true><<<dim3(wgs), dim3(256), lds, st>>>(g);
+    else k_team_stream<TEAM, false><<<dim3(wgs), dim3(256), lds, st>>>(g);
 }
 }  // namespace
 int team_stream_kind(const BatchItem& it) {
@@ -1706,10 +1603,7 @@ int team_stream_kind(const BatchItem& it) {
     const int kind = team_kind_of(it);
     if (kind < 0 || kind == kTeamBigRow || team_needs_edge(it, kind) || it.sh.rows * it.sh.cols > 0x7FFFFFFFll) return -1;
     if (it.gran != kGranRow && (it.sh.rows % 128 != 0 || it.sh.cols % 128 != 0 || 128 * it.sh.ld * 2 >= 0x7FFFFFFFll)) return -1;
-    int64_t units_x;
-    const int64_t units = team_units(it, kind, units_x);
-    const bool wave_teams = kind == kTeamHalf64 || kind == kTeamWaveRow;
-    if (units > kStreamMaxBits || units * (wave_teams ? 4 : 1) > kStreamMaxBits || stream_first_tiles(it) > kStreamMaxTiles) return -1;
+    if (stream_first_tiles(it) > kStreamMaxTiles) return -1;
     return kind == kTeamWgRow ? kTeamWaveRow : kind;
 }
 hipError_t launch_team_stream_items(const TeamStreamItem* ops, int n, hipStream_t st, KProf* prof) {
@@ -1740,25 +1634,19 @@ hipError_t launch_team_stream_items(const TeamStreamItem* ops, int n, hipStream_
         else { t.units_x = (it.sh.cols + 255) / 256; t.n_units = stream_first_tiles(it); }
         t.amax_part = ops[k].sync; t.flush_part = ops[k].gam;
         const int tiles = stream_first_tiles(it);
-        const uint32_t mine = (uint32_t)(tiles + 7) / 8u + 1u;
+        const uint32_t mine = stream_groups(tiles);
         groups += mine;
         g.first.group_end[k] = (int32_t)groups;
         if (mine > largest) largest = mine;
         if (tiles > most_tiles) most_tiles = tiles;
     }
     const uint32_t block_groups = (uint32_t)(total / 8);
-    g.lead = largest + kStreamMargin / 8;
-    if (g.lead > groups) g.lead = groups;
-    g.mixed_first = groups - g.lead;
-    g.mixed = g.mixed_first + (uint32_t)((uint64_t)block_groups * g.mixed_first / groups);
-    g.mul = g.shift = 0u;
-    if ((uint64_t)(g.mixed + 1) * g.mixed_first >= 0x7FFFFFFFull) return hipErrorInvalidValue;
-    if (g.mixed) recip_of(g.mixed, &g.mul, &g.shift);
+    if (!stream_order(g.order, groups, largest, block_groups)) return hipErrorInvalidValue;
     {
-        ProfScope ps(prof, kKernGroupMantissa, st);
-        k_stream_clear<<<dim3((unsigned)((kStreamTiles + most_tiles + 1023) / 1024), (unsigned)n), dim3(256), 0, st>>>(g);
+        ProfScope ps(prof, kKernStreamClear, st);
+        k_stream_clear<<<dim3(stream_clear_wgs(most_tiles), (unsigned)n), dim3(256), 0, st>>>(g);
     }
-    ProfScope ps(prof, kKernTeamBlock, st);
+    ProfScope ps(prof, kKernTeamStream, st);
     const unsigned wgs = 8u * (groups + block_groups);
     switch (team_stream_kind(*ops[0].it)) {
     case kTeamWg128: launch_team_stream<kTeamWg128>(g, wgs, fake, st); break;

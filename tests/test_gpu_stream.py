@@ -24,7 +24,7 @@ def _operands(gran, dev):
         if k % 3 == 1:
             x *= torch.where(torch.rand((rows, cols), generator=gen, device=dev) < 0.3, 1e-9, 1.0)
         if k % 3 == 2:
-            x *= torch.where(torch.rand((rows, cols), generator=gen, device=dev) < 0.047, 1e-9, 1.0)
+            x *= torch.where(torch.rand((rows, cols), generator=gen, device=dev) < 0.035, 1e-9, 1.0)
         x = x.to(torch.bfloat16)
         if k == 4:
             x[rows // 2, cols // 2] = float("inf")
@@ -118,3 +118,64 @@ def test_a_large_operand_alone(gran, rows, cols):
         got = [_entry(B, x, gran, "tensor", False, dev)]
         _run(B, got, polls)
         _same(want[:1], got, (gran, rows, cols, polls))
+
+
+# tile edges of per-tensor operands (2048 chunks of 8 elements): one chunk, a whole tile, a chunk more, ragged ones, and one that fills the launch
+TENSORS = [(8192, 2568), (1, 8), (1, 16384), (1, 16392), (333, 1000), (700, 4096)]
+
+
+@pytest.mark.parametrize("pad", [0, 8])
+@pytest.mark.parametrize("fake, lean", [(False, False), (True, False), (False, True)])
+def test_per_tensor_operands(fake, lean, pad):
+    """Against the oracle, and bit for bit against workgroups that do not wait."""
+    import numpy as np
+    import parity
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(17)
+    bufs = []
+    for k, (rows, cols) in enumerate(TENSORS):
+        x = torch.randn((rows, cols + pad), generator=gen, device=dev)
+        share = (0.3, 0.0, 0.035, 0.3, 0.0, 0.3)[k]       # proven to fall back, E4M3, falling back without a proof
+        x = (x * torch.where(torch.rand(x.shape, generator=gen, device=dev) < share, 1e-9, 1.0)).to(torch.bfloat16)
+        if k == 4:
+            x[rows // 2, cols // 2] = float("nan")
+        bufs.append(x)
+    results = []
+    for polls in (None, 0):
+        print(f"[stream] per tensor fake={fake} lean={lean} pad={pad} polls={polls}", flush=True)
+        entries, guards = [], []
+        for x, (rows, cols) in zip(bufs, TENSORS):
+            p = B.make_params(rows, cols, "tensor", ld=cols + pad, lean_fp8=lean)
+            out, g = parity.guarded_outputs(p, dev, want_bf16=not fake, bf16_fill=parity.FILL, want_fp8=not fake)
+            out.workspace = None
+            if not fake:
+                out.fp8.fill_(0xA7)
+            y = g.carve("y", (rows, cols), torch.int16, 0x1111) if fake else None
+            st = g.carve("stats", (B.STATS_BYTES,), torch.uint8, 0x5A)
+            entries.append((p, x[:, :cols], out, st, y.view(torch.bfloat16) if fake else None))
+            guards.append(g)
+        _run(B, entries, polls)
+        for g in guards:
+            g.check()
+        results.append(entries)
+    _same(*results, ("per tensor", fake, lean, pad))
+    flags = [B.read_stats(e[3])["flags"] for e in results[0]]
+    proven = [k for k in range(len(TENSORS)) if k in (0, 3, 5)]
+    assert flags == [0 if pad or k not in proven else B.MOR_STATS_FLAG_FUSED_FALLBACK for k in range(len(TENSORS))]
+    for k, (p, x, out, st, y) in enumerate(results[0]):
+        rows, cols = TENSORS[k]
+        bits = bufs[k].view(torch.int16).cpu().numpy().view(np.uint16)
+        want = parity.O.analyze_quantize(bits, "tensor", "partition", "mean_rel_err", 0.045, bf16_fill=parity.FILL, ld=cols + pad, cols=cols)
+        if lean and not pad and k in proven:
+            assert bool((out.fp8 == 0xA7).all())
+            out.fp8.copy_(torch.from_numpy(want.fp8.reshape(rows, cols)))
+        if not fake:
+            parity.compare(bits, "tensor", cols=cols, gpu=(p, out), label=f"stream {k}")
+        else:
+            alone, _ = parity.guarded_outputs(p, dev, want_bf16=False, want_fp8=False)
+            y1 = torch.zeros((rows, cols), dtype=torch.bfloat16, device=dev)
+            B.mor_fake_quantize(p, bufs[k], y1, alone)
+            assert torch.equal(y1.view(torch.int16), y.view(torch.int16))
+        assert int(out.mask[0]) == int(want.mask[0])
