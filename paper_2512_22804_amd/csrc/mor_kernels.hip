@@ -11,6 +11,7 @@
 #include "mor_launch.h"
 #include "mor_stream.h"
 #include "mor_sub1x128.h"
+#include "mor_team.h"
 
 namespace mor {
 
@@ -995,15 +996,14 @@ struct SoloStats {
 };
 // (Six workgroups per compute unit as for the kernel without statistics: the second launch bound makes the compiler fit
 // Eq. 2's variants into 80 registers, which it does without spilling; Eq. 3's variants need more either way.)
-template <int CRIT, bool FAKE, bool ROWS>
-__global__ __launch_bounds__(256, CRIT == kCritEq3 || ROWS ? 4 : 6) void k_sub1x128_solo_stats(SubRiders g, SoloStats s) {
-    __shared__ SubStatsShared ssh;
+template <int CRIT, bool FAKE, bool ROWS, class G>
+__device__ __forceinline__ void sub_solo_body(const G& g, StatsRec* rec, float near_tol, int block, int n_blocks, SubStatsShared& ssh) {
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (threadIdx.x < 17) reinterpret_cast<uint32_t*>(&ssh)[threadIdx.x] = 0u;      // c[16], n
     ssh.e_lane[threadIdx.x] = 0.0;
     ssh.n_lane[threadIdx.x] = 0u;
     __syncthreads();
-    sub_group_body<CRIT, FAKE, true, ROWS>(g, (int64_t)blockIdx.x, (int64_t)gridDim.x, &ssh, s.near_tol);
+    sub_group_body<CRIT, FAKE, true, ROWS>(g, (int64_t)block, (int64_t)n_blocks, &ssh, near_tol);
     const double e_w = wave_allsum_f64(ssh.e_lane[threadIdx.x]);
     const uint32_t n_w = wave_allsum_u32(ssh.n_lane[threadIdx.x]);
     if (lane == 0) { ssh.e[w] = e_w; atomicAdd(&ssh.n, n_w); }
@@ -1016,7 +1016,12 @@ __global__ __launch_bounds__(256, CRIT == kCritEq3 || ROWS ? 4 : 6) void k_sub1x
     if (lane == 16) word = (uint32_t)e_bits;
     if (lane == 17) word = (uint32_t)(e_bits >> 32);
     if (lane == 18) word = ssh.n;
-    if (lane < kSoloRecWords) reinterpret_cast<uint32_t*>(s.rec + blockIdx.x)[lane] = word;
+    if (lane < kSoloRecWords) reinterpret_cast<uint32_t*>(rec + block)[lane] = word;
+}
+template <int CRIT, bool FAKE, bool ROWS>
+__global__ __launch_bounds__(256, CRIT == kCritEq3 || ROWS ? 4 : 6) void k_sub1x128_solo_stats(SubRiders g, SoloStats s) {
+    __shared__ SubStatsShared ssh;
+    sub_solo_body<CRIT, FAKE, ROWS>(g, s.rec, s.near_tol, (int)blockIdx.x, (int)gridDim.x, ssh);
 }
 // Combine launch of the above: one workgroup, the records in a fixed order.  It is pure latency on the critical path of the call, so a
 // record is read by ten neighbouring lanes, eight bytes each (one line per record instead of one line per lane and load), and only
@@ -1025,8 +1030,9 @@ __global__ __launch_bounds__(256, CRIT == kCritEq3 || ROWS ? 4 : 6) void k_sub1x
 // 11.3 us per call, 8192 x 4096 26.5 instead of 29.3.
 constexpr int kSoloFinalThreads = 1024;
 constexpr int kSoloQ = kSoloRecWords / 2;              // quadwords: seven pairs of counters and one counter, the sum, the non-zeros
-__global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStats s) {
-    constexpr int kGroups = kSoloFinalThreads / 16;
+template <int T>
+__device__ __forceinline__ void solo_final_body(const SoloStats& s) {
+    constexpr int kGroups = T / 16;
     __shared__ unsigned long long part[kGroups][kSoloQ];
     __shared__ unsigned long long all[kSoloQ];
     const int tid = threadIdx.x, grp = tid >> 4, k = tid & 15;
@@ -1034,15 +1040,16 @@ __global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStat
     if (k < kSoloQ) {
         unsigned long long n = 0ull;                           // two counters side by side (no operand has 2^32 blocks), or the non-zeros
         double e = 0.0;
-        for (int i0 = grp; i0 < s.n_rec; i0 += 4 * kGroups) {
-            unsigned long long v[4];
+        constexpr int kFlight = T < 1024 ? 16 : 4;             // records' loads in flight per lane
+        for (int i0 = grp; i0 < s.n_rec; i0 += kFlight * kGroups) {
+            unsigned long long v[kFlight];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < kFlight; ++u) {
                 const int i = i0 + u * kGroups < s.n_rec ? i0 + u * kGroups : i0;      // always a valid record: the loads need no branch
                 v[u] = reinterpret_cast<const unsigned long long*>(s.rec + i)[k];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < kFlight; ++u) {
                 const bool ok = i0 + u * kGroups < s.n_rec;
                 n += ok ? v[u] : 0ull;
                 e += ok && is_sum ? __longlong_as_double((long long)v[u]) : 0.0;
@@ -1055,7 +1062,7 @@ __global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStat
         const int q = tid >> 4, j = tid & 15;
         unsigned long long v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = part[j + 16 * u][q];
+        for (int u = 0; u < 4; ++u) v[u] = u < kGroups / 16 ? part[j + 16 * (u < kGroups / 16 ? u : 0)][q] : 0ull;
         const unsigned long long n = row_allsum_u64((v[0] + v[1]) + (v[2] + v[3]));
         auto f = [&](int u) { return __longlong_as_double((long long)v[u]); };
         const double e = row_allsum_f64((f(0) + f(1)) + (f(2) + f(3)));
@@ -1068,6 +1075,8 @@ __global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStat
         stats_finish(s.out, s.n_part, s.total_elems, __longlong_as_double((long long)all[8]), all[9],
                      count(12), count(13), 0ull, 128ull * count(12) - (unsigned long long)s.edge_missing * count(14), 0ull, 0u);
 }
+
+__global__ __launch_bounds__(kSoloFinalThreads) void k_solo_stats_final(SoloStats s) { solo_final_body<kSoloFinalThreads>(s); }
 
 // Per-tensor operands of a group share three launches (amax, quantize, finish + fallback copy).
 enum : uint32_t { kTensorLean = 1u,       // a proven BF16 operand gets no FP8 payload
@@ -1446,19 +1455,82 @@ __global__ __launch_bounds__(256) void k_tensor_quant_group(GroupTensor g, int b
 // statistics records of the batch's sub-tensor operands.  The operand's words lie in the array of the E5M2 sums, which Eq. 2 leaves free.
 // g.amax_end: groups of the first pass; g.slot_end: workgroups of the second, a tile each, padded to groups of eight.
 __device__ __forceinline__ uint32_t* stream_words(const TensorOp& t) { return reinterpret_cast<uint32_t*>(t.err5); }
-__global__ __launch_bounds__(256) void k_tensor_stream_clear(GroupTensor g) {      // blockIdx.y = operand
-    const TensorOp& t = g.op[blockIdx.y];
-    stream_clear(stream_words(t), (int)t.n_tiles, (int)blockIdx.x);
+// Operands that are read once and have no part in the passes -- 128 x 128 blocks, a 1 x 128 operand, the other operands of a layer or of a slice
+// -- go through in workgroups spread evenly over the launch: the first pass, which only reads, and the others then overlap.  Their
+// table does not fit the kernel arguments with the others; the launch that clears the words puts it into the workspace.
+struct TensorFill {
+    GroupTeam team;
+    GroupSubT<1> sub;
+    StatsRec* sub_rec;       // the 1 x 128 operand's records, one per workgroup (nullptr: no statistics)
+    float near_tol;
+    int32_t sub_blocks;      // its workgroups
+};
+struct Spread {
+    uint32_t n, mul, shift;       // that many among a number of groups; reciprocal of that number
+};
+__device__ __forceinline__ uint32_t spread_before(const Spread& s, uint32_t group) { return recip_div(group * s.n, s.mul, s.shift); }
+struct FillOrder {
+    Spread sub, team;        // groups of eight workgroups: of the 1 x 128 operand, among the next `early` ones; of the blocks, among the rest
+    uint32_t alone;          // groups of the launch before all these
+    uint32_t early;
+};
+enum { kFillNone = 0, kFillFlat = 1, kFillRows = 2 };      // form of the 1 x 128 operand
+constexpr int kFillWords = 1024;
+static_assert(sizeof(TensorFill) <= 4 * kFillWords, "behind the words of an operand's tiles");
+constexpr int kTensorStreamMaxTiles = kStreamMaxTiles - kFillWords;
+__device__ __forceinline__ uint32_t* fill_table(uint32_t* words) { return words + kStreamWords - kFillWords; }
+struct StreamClear {
+    int32_t n, tiles[kMaxGroup];
+    uint32_t* words[kMaxGroup];
+};
+__global__ __launch_bounds__(256) void k_tensor_stream_clear(StreamClear c, TensorFill fill) {      // blockIdx.y = operand, then the table
+    if ((int)blockIdx.y < c.n) { stream_clear(c.words[blockIdx.y], c.tiles[blockIdx.y], (int)blockIdx.x); return; }
+    const uint32_t* from = reinterpret_cast<const uint32_t*>(&fill);
+    if (blockIdx.x == 0)
+        for (int i = (int)threadIdx.x; i < (int)(sizeof(TensorFill) / 4); i += 256) fill_table(c.words[0])[i] = from[i];
 }
-template <bool FAKE, bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_stream(GroupTensor g, GroupStats riders, StreamOrder order, int rider_wgs, int polls) {
+template <int FILL>
+__device__ __forceinline__ void fill_body(const TensorFill* __restrict__ fill, bool is_sub, int group, int in8) {
+    __shared__ TeamShared sh;
+    __shared__ SubStatsShared ssh;
+    if (is_sub) {
+        const int block = group * 8 + in8, blocks = fill->sub_blocks;
+        if (block >= blocks) return;
+        StatsRec* rec = fill->sub_rec;
+        if (rec) sub_solo_body<kCritEq2, false, FILL == kFillRows>(fill->sub, rec, fill->near_tol, block, blocks, ssh);
+        else sub_group_body<kCritEq2, false, false, FILL == kFillRows>(fill->sub, (int64_t)block, (int64_t)blocks, nullptr, 0.0f);
+        return;
+    }
+    const int64_t wg = (int64_t)group * 8 + in8;
+    const int n = fill->team.n;
+    if (wg >= fill->team.unit_end[n - 1]) return;
+    const int op = group_find(fill->team.unit_end, n, wg);
+    const TeamOp t = fill->team.op[op];
+    team_block<kTeamWg128, kCritEq2, false, false, kTeamAlone>(t, wg - (op ? fill->team.unit_end[op - 1] : 0), sh, StreamUnit{}, [] { return 0u; });
+}
+template <bool FAKE, bool STRIDED, int FILL>
+__global__ __launch_bounds__(256) void k_tensor_stream(GroupTensor g, GroupStats riders, StreamOrder order, int rider_wgs, int polls, FillOrder fo) {
     const int block = (int)blockIdx.x - (rider_wgs + 7) / 8 * 8;
     if (block < 0) {
         if ((int)blockIdx.x < rider_wgs) stats_partial_body<256>(riders, (int)blockIdx.x);
         return;
     }
-    const StreamPlace place = stream_place(order, (uint32_t)block >> 3);
+    uint32_t group = (uint32_t)block >> 3;
     const int in8 = block & 7;
+    if constexpr (FILL != kFillNone) {
+        if (group >= fo.alone) {
+            group -= fo.alone;
+            const bool early = group < fo.early;
+            const Spread& s = early ? fo.sub : fo.team;
+            const uint32_t in_part = early ? group : group - fo.early, before = spread_before(s, in_part);
+            if (spread_before(s, in_part + 1u) != before) {
+                fill_body<FILL>(reinterpret_cast<const TensorFill*>(fill_table(stream_words(g.op[0]))), early, (int)before, in8);
+                return;
+            }
+            group = fo.alone + group - (early ? before : fo.sub.n + before);
+        }
+    }
+    const StreamPlace place = stream_place(order, group);
     if (place.first) {
         __shared__ uint32_t sh8[8];
         const int op = group_find32(g.amax_end, g.n, (int)place.group);
@@ -1862,9 +1934,16 @@ __global__ __launch_bounds__(T, 4) void k_tensor_quant_one(OneTensor g, int poll
     }
 }
 // Workgroups from `stats_first` on combine the riders' partial statistics records (one workgroup per operand).
+// (`direct`: operands of the table, one bit each, whose statistics are still to be taken, by one workgroup; then the 1 x 128 operand of `solo`.)
 template <int CRIT, bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, GroupStats riders, int stats_first) {
-    if ((int)blockIdx.x >= stats_first) { stats_final_body(riders, (int)blockIdx.x - stats_first); return; }
+__global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, GroupStats riders, int stats_first, uint32_t direct, SoloStats solo) {
+    if ((int)blockIdx.x >= stats_first) {
+        const int op = (int)blockIdx.x - stats_first;
+        if (op >= riders.n) solo_final_body<256>(solo);
+        else if ((direct >> op) & 1u) stats_partial_body<256>(riders, op ? riders.wg_end[op - 1] : 0);
+        else stats_final_body(riders, op);
+        return;
+    }
     tensor_finish_body<CRIT, STRIDED>(g, (int)blockIdx.x);
 }
 // Group loop of Algorithm 1 for sub-tensor operands: the operand's amax (partials of pass A) gives the
@@ -2083,8 +2162,9 @@ int64_t item_parts(const BatchItem& it) { return geom_parts(make_geom(it.gran, i
 bool solo_stats_candidate(const BatchItem& it) {
     return it.stats && it.scope == 0 && (route_of(it) == kRouteSubFlat || route_of(it) == kRouteSubRows);
 }
+constexpr int64_t kStatsOneWg = 4096;        // blocks whose statistics one workgroup of 256 lanes takes
 int stats_wgs(int64_t n_part) {                        // riding in a launch of 256-lane workgroups
-    if (n_part <= 4096) return 1;                       // one workgroup writes the result directly
+    if (n_part <= kStatsOneWg) return 1;                // one workgroup writes the result directly
     int64_t w = (n_part + 1023) / 1024;
     return (int)(w > kStatsMaxWg ? kStatsMaxWg : w);
 }
@@ -2125,6 +2205,14 @@ size_t batch_workspace_bytes(const BatchItem* items, int n) {
 }
 
 namespace {
+// What goes along with the passes (see TensorFill), and the statistics that it leaves to the finish pass.
+struct StreamFill {
+    int form = kFillNone;
+    TensorFill table{};
+    FillOrder order{};
+    SoloStats solo{};
+    uint32_t direct = 0u;
+};
 // One batch call: the launches of every phase, in stream order.  The phases share the workspace cursor, the routes, the
 // group-mantissa words of Algorithm 1 and the statistics groups, which is all this object holds.
 constexpr int kMaxStatsGroups = (kBatchMax + kMaxGroupStats - 1) / kMaxGroupStats;
@@ -2161,6 +2249,10 @@ struct BatchRun {
         ws_off += need;
         return p;
     }
+    int fill_strided = -1;                       // the per-tensor launch that takes others along: 0 dense operands, 1 padded rows, -1 none
+    int fill_sub = -1, fill_team[kMaxTeamGroup], n_fill_team = 0;
+    void plan_fill();
+    void make_fill(StreamFill& f, GroupStats& riders, int& ride_final);
     void streamed_operands();
     void assign_waves();
     void group_mantissas(int wave);
@@ -2599,7 +2691,10 @@ bool tensor_stream_pays(int n, int64_t tiles, bool strided, bool ride) {
     return tiles > (ride ? kAmaxOneTile : 1280);
 }
 template <bool STRIDED>
-hipError_t launch_tensor_stream(GroupTensor& g, const GroupStats& riders, int ride_partial, int c_end, int ride_final, bool fake, int polls, hipStream_t st, KProf* prof) {
+hipError_t launch_tensor_stream(GroupTensor& g, const GroupStats& riders, int ride_partial, int c_end, int ride_final, bool fake, int polls, StreamFill& fill,
+                                hipStream_t st, KProf* prof) {
+    StreamClear clear;
+    clear.n = g.n;
     uint32_t groups = 0u, largest = 0u;
     int slots = 0, most = 0;
     for (int k = 0; k < g.n; ++k) {
@@ -2611,26 +2706,44 @@ hipError_t launch_tensor_stream(GroupTensor& g, const GroupStats& riders, int ri
         g.amax_end[k] = (int32_t)groups;
         g.slot_end[k] = slots;
         t.n_slots = tiles;
+        clear.tiles[k] = tiles;
+        clear.words[k] = reinterpret_cast<uint32_t*>(t.err5);
         if (g.n > 1) t.keep_from = 0;                     // the second pass follows at the distance of one operand
         if (mine > largest) largest = mine;
         if (tiles > most) most = tiles;
     }
     StreamOrder order;
     if (!stream_order(order, groups, largest, (uint32_t)slots / 8u)) return hipErrorInvalidValue;
+    if (fill.form != kFillNone) {
+        FillOrder& f = fill.order;
+        // The 1 x 128 operand, whose workgroups take longer than the others', goes in early: behind the first pass of a lone per-tensor operand, while
+        // that is collected, beside the first passes of several.  us per call, behind / beside: 1000 x 4096 and a slice like it 16.8 / 18.3, 4099 x 5000
+        // 47.8 / 50.0, 8192 x 14336 206 / 224; a layer of 8192 x hidden 4096 376.5 / 373.6, 1 x 128 and three gradients of 4096 x 4096 62.7 / 61.6.
+        const uint32_t span = g.n == 1 ? 0u : order.lead, rest = groups + (uint32_t)slots / 8u - order.lead + f.team.n;
+        f.alone = order.lead - span;
+        f.early = span + f.sub.n;
+        if ((uint64_t)(f.early + 1) * f.sub.n >= 0x7FFFFFFFull || (uint64_t)(rest + 1) * f.team.n >= 0x7FFFFFFFull) return hipErrorInvalidValue;
+        recip_of(f.early ? f.early : 1u, &f.sub.mul, &f.sub.shift);
+        recip_of(rest ? rest : 1u, &f.team.mul, &f.team.shift);
+    }
     {
         ProfScope ps(prof, kKernStreamClear, st);
-        k_tensor_stream_clear<<<dim3(stream_clear_wgs(most), (unsigned)g.n), dim3(256), 0, st>>>(g);
+        k_tensor_stream_clear<<<dim3(stream_clear_wgs(most), (unsigned)g.n + (fill.form != kFillNone ? 1u : 0u)), dim3(256), 0, st>>>(clear, fill.table);
     }
     {
         ProfScope ps(prof, kKernTensorStream, st);
-        const dim3 grid(((unsigned)ride_partial + 7u) / 8u * 8u + 8u * groups + (unsigned)slots);
+        const FillOrder& fo = fill.order;
+        const dim3 grid(((unsigned)ride_partial + 7u) / 8u * 8u + 8u * groups + (unsigned)slots + (fill.form != kFillNone ? 8u * (fo.sub.n + fo.team.n) : 0u));
         // (gradients of a layer 383.0 us per call uncapped, 382.5 at 5, 382.1 at 4, 382.4 at 3 workgroups per compute unit, kept lean 347.5, 347.7, 346.2,
         // 354.9; a slice of 4099 x 5000 28.6, 28.6, 30.1, 28.5)
-        if (fake) k_tensor_stream<true, STRIDED><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls);
-        else k_tensor_stream<false, STRIDED><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls);
+        if (fake) k_tensor_stream<true, STRIDED, kFillNone><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
+        else if (fill.form == kFillRows) k_tensor_stream<false, STRIDED, kFillRows><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
+        else if (fill.form == kFillFlat) {
+            if constexpr (!STRIDED) k_tensor_stream<false, STRIDED, kFillFlat><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
+        } else k_tensor_stream<false, STRIDED, kFillNone><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
     }
     ProfScope ps(prof, kKernFallbackCopy, st);
-    k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
+    k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end, fill.direct, fill.solo);
     return hipGetLastError();
 }
 template <bool STRIDED>
@@ -2655,8 +2768,8 @@ void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_p
     }
     {
         ProfScope ps(prof, kKernFallbackCopy, st);
-        if (crit == kCritEq3) k_tensor_finish_group<kCritEq3, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
-        else k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
+        if (crit == kCritEq3) k_tensor_finish_group<kCritEq3, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end, 0u, SoloStats{});
+        else k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end, 0u, SoloStats{});
     }
 }
 // A small operand that is alone: two launches from a table of one operand.  Such a call is a chain of launches, so what counts is their
@@ -2720,6 +2833,97 @@ void launch_one_tensor(const TensorOp& t, float near_tol, int crit, bool fake, i
         else launch_one_quant<kCritEq2, false>(o, s, slots, polls, st);
     }
 }
+// Can the operand's two passes share a launch?
+bool tensor_streams(const BatchItem& it) {
+    if (it.gran != kGranTensor || it.crit != kCritEq2 || it.three) return false;
+    if ((it.sh.rows * (it.sh.cols / 8) + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock > kTensorStreamMaxTiles) return false;
+    return item_is_flat(it) || tensor_rows_fit(it.sh, it.o);
+}
+// A small per-tensor operand alone and without statistics has kernels of its own, which a 1 x 128 operand beside it does not outweigh: us per call
+// apart / together, slices of 64 x 1024 12.7 / 14.2, 512 x 2048 12.8 / 15.2, 1000 x 4096 18.0 / 17.2, 2500 x 5000 37.2 / 33.0; with statistics 18.5 / 14.5, 19.1 / 15.3,
+// 22.8 / 16.8, 37.9 / 32.7, 4099 x 5000 48.2 / 47.8, 8192 x 4096 66.2 / 62.3.  Layers with statistics: 8192 tokens x hidden 4096 382.9 / 373.6 (lean, without 347.2 /
+// 328.9), 4096 x 2048 107.5 / 102.1, 512 x 1024 37.1 / 33.6, 64 x 256 21.3 / 16.1.
+constexpr int64_t kFillAloneTiles = 128;
+// Which operands go along with the passes of per-tensor ones (see TensorFill): those decided block by block under Eq. 2 with two types, FP8
+// payload and no pre-pass, of which one may have 1 x 128 blocks; with statistics, up to what one workgroup counts of 128 x 128 blocks.
+void BatchRun::plan_fill() {
+    for (int strided = 0; strided < 2 && fill_strided < 0; ++strided) {
+        int cnt = 0;
+        int64_t tiles = 0;
+        bool all = true;
+        for (int i = 0; i < n; ++i) {
+            const BatchItem& it = items[i];
+            if (it.gran != kGranTensor || it.crit != kCritEq2 || it.o.fake || item_is_flat(it) != (strided == 0)) continue;
+            all &= tensor_streams(it);
+            ++cnt;
+            tiles += (it.sh.rows * (it.sh.cols / 8) + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
+        }
+        bool counts = false;                               // the call counts statistics
+        for (int i = 0; i < n; ++i) counts |= items[i].stats != nullptr;
+        if (cnt == 0 || cnt > kMaxGroupTensor || !all || (cnt == 1 && !counts && tiles < kFillAloneTiles)) continue;
+        int others = 0, counted = 0, subs = 0;             // statistics of operands that do not go along, that do
+        for (int i = 0; i < n; ++i) {
+            const BatchItem& it = items[i];
+            if (it.gran == kGranTensor) continue;
+            const Route own = route_of(it);
+            const bool plain = it.crit == kCritEq2 && it.scope == 0 && !it.three && !it.o.fake && it.scaling != kScaleGam;
+            if (plain && (own == kRouteSubFlat || own == kRouteSubRows)) { ++subs; if (!strided || own == kRouteSubRows) fill_sub = i; }
+            else if (plain && own == kRouteTeam && team_kind_of(it) == kTeamWg128 && !team_needs_edge(it, kTeamWg128) && n_fill_team < kMaxTeamGroup &&
+                     (!it.stats || item_parts(it) <= kStatsOneWg)) { fill_team[n_fill_team++] = i; counted += it.stats != nullptr; }
+            else others += it.stats != nullptr;
+        }
+        if (subs > 1) { fill_sub = -1; others += subs; }
+        if ((fill_sub < 0 && n_fill_team == 0) || others + counted > kMaxGroupStats) { fill_sub = -1; n_fill_team = 0; continue; }
+        fill_strided = strided;
+    }
+    if (fill_strided < 0) return;
+    if (fill_sub >= 0) { wave_of[fill_sub] = -1; stats_done[fill_sub] = true; }
+    for (int k = 0; k < n_fill_team; ++k) { wave_of[fill_team[k]] = -1; stats_done[fill_team[k]] = true; }
+}
+void BatchRun::make_fill(StreamFill& f, GroupStats& riders, int& ride_final) {
+    TensorFill& t = f.table;
+    f.form = kFillFlat;
+    int64_t units = 0;
+    t.team.n = n_fill_team;
+    for (int k = 0; k < n_fill_team; ++k) {
+        const BatchItem& it = items[fill_team[k]];
+        int64_t units_x;
+        units += team_units(it, kTeamWg128, units_x);
+        set_team_op(t.team.op[k], it, units_x, nullptr);
+        t.team.unit_end[k] = units;
+        if (!it.stats) continue;
+        StatsOp& s = riders.op[riders.n];
+        s.err_sum = it.o.err_sum; s.nnz = it.o.nnz; s.mask = it.o.mask;
+        s.geom = make_geom(it.gran, it.sh.rows, it.sh.cols);
+        s.n_part = geom_parts(s.geom);
+        s.th = it.th; s.rec = nullptr; s.out = static_cast<StatsDev*>(it.stats);
+        riders.wg_end[riders.n] = (riders.n ? riders.wg_end[riders.n - 1] : 0) + 1;
+        f.direct |= 1u << riders.n++;
+    }
+    ride_final = riders.n;
+    if (fill_sub >= 0) {
+        const BatchItem& it = items[fill_sub];
+        if (route_of(it) == kRouteSubRows) f.form = kFillRows;
+        t.sub.n = 0;
+        sub_table_add(t.sub, it, nullptr);
+        t.sub.unit_end[0] = (item_parts(it) + 31) / 32;
+        int64_t per = (t.sub.unit_end[0] + 4 * kSubFlatMaxBlocks - 1) / (4 * kSubFlatMaxBlocks);
+        t.sub_blocks = (int32_t)((t.sub.unit_end[0] + 4 * per - 1) / (4 * per));
+        t.near_tol = near_tol;
+        if (it.stats) {
+            t.sub_rec = reinterpret_cast<StatsRec*>(carve(sizeof(StatsRec) * (size_t)t.sub_blocks));
+            f.solo.rec = t.sub_rec; f.solo.out = static_cast<StatsDev*>(it.stats);
+            f.solo.n_part = item_parts(it);
+            f.solo.total_elems = (unsigned long long)(it.sh.rows * it.sh.cols);
+            f.solo.edge_missing = (uint32_t)((128 - it.sh.cols % 128) % 128);
+            f.solo.near_tol = near_tol;
+            f.solo.n_rec = t.sub_blocks;
+            ++ride_final;
+        }
+    }
+    f.order.sub.n = (uint32_t)(t.sub_blocks + 7) / 8u;
+    f.order.team.n = (uint32_t)((units + 7) / 8);
+}
 void BatchRun::per_tensor_operands(int crit) {
     // ---- per-tensor operands: amax pass, quantize pass, finish (+ fallback copy) pass; FP8 payload and fake
     //      quantization are different kernels, and so are dense operands and padded leading dimensions
@@ -2734,7 +2938,8 @@ void BatchRun::per_tensor_operands(int crit) {
             const BatchItem& it0 = items[idx[0]];
             // (the kernels of the two launches address rows through a RowMap, so a dense operand whose rows are too long for it stays with the
             // dense kernels, which number chunks without it: 1 x 8 388 608 kept in BF16 45.2 us as one of these, without a proof, 17.6 with the dense kernels)
-            const bool one = cnt == 1 && !ride && it0.sh.rows * (it0.sh.cols / 8) <= one_max_chunks(crit) && (strided || tensor_rows_fit(it0.sh, it0.o));
+            const bool filled = fill_strided == (strided ? 1 : 0) && crit == kCritEq2 && !fake;
+            const bool one = cnt == 1 && !ride && !filled && it0.sh.rows * (it0.sh.cols / 8) <= one_max_chunks(crit) && (strided || tensor_rows_fit(it0.sh, it0.o));
             int64_t all_tiles = 0;
             for (int k = 0; k < cnt; ++k) {
                 const BatchItem& it = items[idx[k]];
@@ -2801,10 +3006,17 @@ void BatchRun::per_tensor_operands(int crit) {
                 ride_final = ride_partial > riders.n ? riders.n : 0;      // single-workgroup operands are final already
                 riders_used = true;
             }
-            bool stream = crit == kCritEq2 && tensor_stream_pays(cnt, all_tiles, strided, ride);
-            for (int k = 0; k < cnt; ++k) stream &= !g.op[k].three && g.op[k].n_tiles <= kStreamMaxTiles && !(strided && g.op[k].rm.cpr == 0u);
-            if (!one && stream) err = strided ? launch_tensor_stream<true>(g, riders, ride_partial, c_end, ride_final, fake, it0.polls, st, prof)
-                                              : launch_tensor_stream<false>(g, riders, ride_partial, c_end, ride_final, fake, it0.polls, st, prof);
+            bool stream = filled || (crit == kCritEq2 && tensor_stream_pays(cnt, all_tiles, strided, ride));
+            for (int k = 0; k < cnt; ++k) stream &= tensor_streams(items[idx[k]]);
+            if (!one && stream) {
+                StreamFill fill;
+                if (filled) {
+                    make_fill(fill, riders, ride_final);
+                    if (err != hipSuccess) { cnt = 0; return; }
+                }
+                err = strided ? launch_tensor_stream<true>(g, riders, ride_partial, c_end, ride_final, fake, it0.polls, fill, st, prof)
+                              : launch_tensor_stream<false>(g, riders, ride_partial, c_end, ride_final, fake, it0.polls, fill, st, prof);
+            }
             else if (one) launch_one_tensor(g.op[0], near_tol, crit, fake, it0.polls, st, prof);
             else if (strided) launch_tensor_passes<true>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
             else launch_tensor_passes<false>(g, parts, n_parts, riders, ride_partial, c_end, ride_final, crit, fake, st, prof);
@@ -2853,6 +3065,7 @@ hipError_t launch_batch(const BatchItem* items, int n, float near_tol, void* ws,
     for (int i = 0; i < n; ++i) run.will_ride |= run.route[i] == kRouteTensorGroup;
     run.streamed_operands();
     run.assign_waves();
+    run.plan_fill();
     for (int wave = 0; wave < run.n_waves && run.err == hipSuccess; ++wave) {
         run.group_mantissas(wave);
         for (int crit = 0; crit < 2 && run.err == hipSuccess; ++crit) run.sub_tensor_operands(crit, wave);

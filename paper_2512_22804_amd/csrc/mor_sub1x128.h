@@ -302,6 +302,7 @@ __device__ __forceinline__ void sub_unit_process(const u32x4 (&raw)[8], const ui
 // Descriptor table of a flat 1 x 128 launch (N operands); it travels in the kernel-argument segment.
 template <int N>
 struct GroupSubT {
+    static constexpr int kOps = N;
     int n;
     int64_t unit_end[N];       // running total of 32-block units
     const uint16_t* x[N];
@@ -332,7 +333,7 @@ template <int CRIT, bool FAKE, bool STATS, bool ROWS, class G>
 __device__ __forceinline__ void sub_group_body(const G& g, int64_t block, int64_t n_blocks, SubStatsShared* ssh,
                                                float near_tol) {
     const int lane = threadIdx.x & 63, row = lane >> 4, l = lane & 15;
-    const int64_t W = n_blocks * 4, total = g.unit_end[g.n - 1];
+    const int64_t W = n_blocks * 4, total = g.unit_end[G::kOps == 1 ? 0 : g.n - 1];
     int64_t u = block * 4 + (threadIdx.x >> 6);
     if (u >= total) return;
     const int lane_off = (row * 8) * 128 + l * 8;
@@ -341,7 +342,7 @@ __device__ __forceinline__ void sub_group_body(const G& g, int64_t block, int64_
         return ROWS ? SubRows{g.ld[op], g.cols[op], g.n_part[op], g.bpr[op], g.mul[op], g.shift[op]} : SubRows{0, 0, 0, 1u, 0u, 0u};
     };
     auto load_unit = [&](u32x4 (&raw)[8], int64_t unit, int& op, int64_t& local) {
-        op = group_find(g.unit_end, g.n, unit);
+        op = G::kOps == 1 ? 0 : group_find(g.unit_end, g.n, unit);
         local = unit - (op ? g.unit_end[op - 1] : 0);
         if constexpr (ROWS) {
             const SubRows sr = rows_of(op);

@@ -179,3 +179,73 @@ def test_per_tensor_operands(fake, lean, pad):
             B.mor_fake_quantize(p, bufs[k], y1, alone)
             assert torch.equal(y1.view(torch.int16), y.view(torch.int16))
         assert int(out.mask[0]) == int(want.mask[0])
+
+
+# (granularity, rows, cols, row padding, scaling): per-tensor operands first, then what goes along; edges of the 1 x 128 operand's units of 32 blocks and
+# of the number that its waves take (one up to 6144 units, then two), of its two forms, and of groups of eight 128 x 128 blocks
+ALONG = [
+    [("tensor", 300, 1000, 0, "fp32_amax"), ("sub1x128", 33, 128, 0, "fp32_amax")],
+    [("tensor", 1, 8, 0, "fp32_amax"), ("tensor", 2000, 4096, 0, "fp32_amax"), ("sub1x128", 6160, 4096, 0, "e8m0"), ("block128", 1152, 128, 0, "fp32_amax"),
+     ("block128", 128, 1024, 0, "e8m0")],
+    [("tensor", 300, 1000, 1000, "fp32_amax"), ("sub1x128", 301, 1000, 1000, "fp32_amax"), ("block128", 256, 256, 0, "fp32_amax")],
+    [("tensor", 700, 4096, 8, "gam"), ("tensor", 64, 8, 8, "fp32_amax"), ("sub1x128", 65, 4104, 0, "e8m0"), ("block128", 8320, 8064, 128, "fp32_amax"),
+     ("block128", 200, 256, 0, "fp32_amax"), ("block64", 128, 128, 0, "fp32_amax")],
+    [("tensor", 4096, 4096, 0, "fp32_amax"), ("block128", 8192, 8192, 0, "fp32_amax")],
+    [("tensor", 512, 2048, 0, "fp32_amax"), ("sub1x128", 64, 2048, 0, "fp32_amax"), ("sub1x128", 65, 2048, 0, "fp32_amax"), ("channel_col", 256, 384, 0, "fp32_amax")],
+]
+
+
+@pytest.mark.parametrize("counted", [True, False])
+@pytest.mark.parametrize("case", range(len(ALONG)))
+def test_operands_that_go_along(case, counted):
+    """1 x 128 and 128 x 128 operands in the launch of per-tensor ones: the outputs of each alone, and its statistics."""
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(100 + case)
+
+    def entries():
+        got = []
+        for x, (gran, rows, cols, pad, scaling) in zip(xs, ALONG[case]):
+            ragged = gran in ("sub1x128", "block128") and bool(cols % 128 or (gran == "block128" and rows % 128))
+            p = B.make_params(rows, cols, gran, ld=cols + pad, scaling=scaling, ragged=ragged)
+            out = B.alloc_outputs(p, dev, bf16_fill=0x1234)
+            out.workspace = None
+            for n in NAMES:
+                t = getattr(out, n)
+                if t is not None and n != "bf16":
+                    t.view(torch.uint8).fill_(0x5A)
+            got.append((p, x, out, torch.full((B.STATS_BYTES,), 0x5A, dtype=torch.uint8, device=dev) if counted else None, None))
+        return got
+
+    xs = []
+    for k, (gran, rows, cols, pad, scaling) in enumerate(ALONG[case]):
+        x = torch.randn((rows, cols + pad), generator=gen, device=dev)
+        tiny = torch.rand((rows, (cols + pad + 127) // 128), generator=gen, device=dev).repeat_interleave(128, 1)[:, :cols + pad] < 0.2
+        x = torch.where(tiny & (torch.rand(x.shape, generator=gen, device=dev) < 0.5), x * 1e-8, x).to(torch.bfloat16)
+        if gran == "sub1x128":
+            x[rows // 2, cols // 2] = float("inf")
+        xs.append(x[:, :cols])
+    want = entries()
+    for e in want:
+        _run(B, [e])
+    for polls in (None, 0):
+        print(f"[stream] along {case} counted={counted} polls={polls}", flush=True)
+        got = entries()
+        _run(B, got, polls)
+        for k, (a, b) in enumerate(zip(want, got)):
+            for n in NAMES:
+                u, v = getattr(a[2], n), getattr(b[2], n)
+                if u is None:
+                    continue
+                if n == "err_sum":      # other kernels alone, so another order: binary32 chains of up to 32 terms and steps in each
+                    assert torch.allclose(u, v, rtol=32 * 2.0 ** -24, atol=0.0), (case, k)
+                else:
+                    assert torch.equal(u.view(torch.uint8), v.view(torch.uint8)), (case, k, n)
+            if counted:
+                s, t = B.read_stats(a[3]), B.read_stats(b[3])
+                for key in s:
+                    if key in ("err_sum_total", "mean_err"):
+                        assert s[key] == t[key] or abs(s[key] - t[key]) <= 32 * 2.0 ** -24 * abs(s[key]), (case, k, key)
+                    elif key != "flags":                                                    # (which says how, not what)
+                        assert s[key] == t[key], (case, k, key)
