@@ -1465,10 +1465,6 @@ struct TensorFill {
     float near_tol;
     int32_t sub_blocks;      // its workgroups
 };
-struct Spread {
-    uint32_t n, mul, shift;       // that many among a number of groups; reciprocal of that number
-};
-__device__ __forceinline__ uint32_t spread_before(const Spread& s, uint32_t group) { return recip_div(group * s.n, s.mul, s.shift); }
 struct FillOrder {
     Spread sub, team;        // groups of eight workgroups: of the 1 x 128 operand, among the next `early` ones; of the blocks, among the rest
     uint32_t alone;          // groups of the launch before all these
@@ -2253,6 +2249,7 @@ struct BatchRun {
     int fill_sub = -1, fill_team[kMaxTeamGroup], n_fill_team = 0;
     void plan_fill();
     void make_fill(StreamFill& f, GroupStats& riders, int& ride_final);
+    void paired_operands();
     void streamed_operands();
     void assign_waves();
     void group_mantissas(int wave);
@@ -2272,16 +2269,53 @@ struct BatchRun {
 bool taken_whole(const BatchItem& it) {
     return scope_proof_applies(it) && (it.gran == kGranRow || it.gran == kGranBlock64 || (it.gran == kGranSub && it.o.fake == nullptr));
 }
+// The operands of linear layers under the per-channel strategy: rows and columns in common launches (see launch_channel_col_items).
+void BatchRun::paired_operands() {
+    for (int fake = 0; fake < 2 && err == hipSuccess; ++fake) {
+        PairRows rows;
+        rows.n = 0;
+        int row_idx[kPairMax], cols[kPairMax], n_cols = 0;
+        bool fits = true;
+        for (int i = 0; i < n; ++i) {
+            const BatchItem& it = items[i];
+            if (it.crit != kCritEq2 || it.three || (it.o.fake != nullptr) != (fake != 0)) continue;
+            const bool row = it.gran == kGranRow;
+            if (!row && it.gran != kGranCol) continue;
+            fits &= row ? rows.n < kPairMax && pair_takes_row(it) : n_cols < kPairMax;
+            if (!fits) break;
+            if (row) { row_idx[rows.n] = i; rows.ops[rows.n++].it = &it; fits &= it.scaling == rows.ops[0].it->scaling; }
+            else cols[n_cols++] = i;
+        }
+        if (!fits || rows.n == 0 || n_cols == 0 || !columns_pair(items, cols, n_cols)) continue;
+        for (int k = 0; k < rows.n; ++k) {
+            const int i = row_idx[k];
+            rows.ops[k].gam = nullptr; rows.ops[k].sync = nullptr;
+            if (items[i].scaling == kScaleGam) {
+                gam_of[i] = rows.ops[k].gam = reinterpret_cast<uint32_t*>(carve(16));
+                rows.ops[k].sync = reinterpret_cast<uint32_t*>(carve(sizeof(uint32_t) * kStreamWords));
+            }
+            streamed[i] = true;
+        }
+        char* ws_of[kPairMax];
+        for (int k = 0; k < n_cols; ++k) {
+            const int i = cols[k];
+            if (items[i].scaling == kScaleGam) gam_of[i] = reinterpret_cast<uint32_t*>(carve(16));
+            ws_of[k] = col_ws[i] = carve(column_workspace_bytes(items[i].sh.rows, items[i].sh.cols));
+            streamed[i] = true;
+        }
+        if (err == hipSuccess) err = launch_channel_col_items(items, cols, n_cols, kCritEq2, gam_of, ws_of, &rows, st, prof);
+    }
+}
 // Operands whose two passes share a launch.
 void BatchRun::streamed_operands() {
     constexpr int kMost = 12;                    // operands of a launch
     bool beside = false;
     for (int i = 0; i < n; ++i)
-        beside |= items[i].scaling == kScaleGam && items[i].gran != kGranTensor && items[i].gran != kGranCol && team_stream_kind(items[i]) < 0;
+        beside |= !streamed[i] && items[i].scaling == kScaleGam && items[i].gran != kGranTensor && items[i].gran != kGranCol && team_stream_kind(items[i]) < 0;
     for (int c = 0; c < 2 * kTeamKinds && err == hipSuccess; ++c) {
         int idx[kBatchMax], cnt = 0;
         for (int i = 0; i < n; ++i)
-            if (team_stream_kind(items[i]) == c / 2 && (items[i].o.fake != nullptr) == (c % 2 != 0)) idx[cnt++] = i;
+            if (!streamed[i] && team_stream_kind(items[i]) == c / 2 && (items[i].o.fake != nullptr) == (c % 2 != 0)) idx[cnt++] = i;
         for (int base = 0; base < cnt && err == hipSuccess; base += kMost) {
             TeamStreamItem ops[kMost];
             const int m = cnt - base < kMost ? cnt - base : kMost;
@@ -2591,7 +2625,7 @@ void BatchRun::sub_tensor_operands(int crit, int wave) {
                 col_ws[i] = ws_of[cnt];
                 idx[cnt++] = i;
             }
-        if (cnt && err == hipSuccess) err = launch_channel_col_items(items, idx, cnt, crit, gam_of, ws_of, st, prof);
+        if (cnt && err == hipSuccess) err = launch_channel_col_items(items, idx, cnt, crit, gam_of, ws_of, nullptr, st, prof);
     }
 }
 
@@ -2722,9 +2756,7 @@ hipError_t launch_tensor_stream(GroupTensor& g, const GroupStats& riders, int ri
         const uint32_t span = g.n == 1 ? 0u : order.lead, rest = groups + (uint32_t)slots / 8u - order.lead + f.team.n;
         f.alone = order.lead - span;
         f.early = span + f.sub.n;
-        if ((uint64_t)(f.early + 1) * f.sub.n >= 0x7FFFFFFFull || (uint64_t)(rest + 1) * f.team.n >= 0x7FFFFFFFull) return hipErrorInvalidValue;
-        recip_of(f.early ? f.early : 1u, &f.sub.mul, &f.sub.shift);
-        recip_of(rest ? rest : 1u, &f.team.mul, &f.team.shift);
+        if (!make_spread(f.sub, f.sub.n, f.early) || !make_spread(f.team, f.team.n, rest)) return hipErrorInvalidValue;
     }
     {
         ProfScope ps(prof, kKernStreamClear, st);
@@ -3063,6 +3095,7 @@ hipError_t launch_batch(const BatchItem* items, int n, float near_tol, void* ws,
         if (rows_form == 1 && item_parts(items[last]) < kSubRowsAlone) run.route[last] = kRouteSubGeneral;
     }
     for (int i = 0; i < n; ++i) run.will_ride |= run.route[i] == kRouteTensorGroup;
+    run.paired_operands();
     run.streamed_operands();
     run.assign_waves();
     run.plan_fill();

@@ -291,8 +291,16 @@ inline bool column_scales_folded(int64_t n_strips, int64_t launch_workgroups, bo
 }
 ColumnSums column_sums_of(const char* column_workspace, int64_t rows, int64_t cols, const float* amax);
 uint32_t* column_tensor_proven_word(char* column_workspace, int64_t rows, int64_t cols);
+// Per-channel rows that go along with per-channel columns, the operands of linear layers.
+constexpr int kPairMax = 4;
+struct PairRows {
+    TeamStreamItem ops[kPairMax];      // (without GAM scales: no words)
+    int n;
+};
+bool pair_takes_row(const BatchItem& it);
+bool columns_pair(const BatchItem* items, const int* idx, int cnt);
 hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int cnt, int crit, const uint32_t* const* gam_of,
-                                    char* const* ws_of, hipStream_t st, KProf* prof);
+                                    char* const* ws_of, const PairRows* rows, hipStream_t st, KProf* prof);
 
 // One operand of a de-quantize batch (validated by the caller).
 struct DeqItem {

@@ -226,6 +226,7 @@ struct StreamTeam {
     StreamFirst first;
     int32_t units[kMaxTeamGroup];
     uint32_t flush_need[kMaxTeamGroup];   // 0: nothing is proven
+    uint32_t* gmant[kMaxTeamGroup];       // the caller's outputs
     StreamOrder order;
     int32_t polls;
 };
@@ -273,6 +274,21 @@ __global__ __launch_bounds__(256) void k_stream_clear(StreamTeam g) {      // bl
     const ProveOp& t = g.first.op[blockIdx.y];
     stream_clear(t.amax_part, stream_tiles(t), (int)blockIdx.x);
 }
+// A workgroup of group `group` of the first pass: a tile, or the operand's collection, after which its mantissa words and the caller's output are written.
+__device__ __forceinline__ void stream_first_group(const StreamFirst& g, const uint32_t* flush_need, uint32_t* const* gmant_of, int polls, int group, int in8, uint32_t* sh8) {
+    const int op = group_find32(g.group_end, g.n, group);
+    const ProveOp& t = g.op[op];
+    const int in_op = group - (op ? g.group_end[op - 1] : 0), tiles = stream_tiles(t), tile = in_op * 8 + in8;
+    auto count = [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { stream_count(t, k, tid, amax, flushes); };
+    if (tile < tiles) { stream_first(t.amax_part, tile, sh8, count); return; }
+    if (in8 != 0 || in_op * 8 < tiles) return;             // the last of the operand's groups collects
+    const uint32_t figures = stream_collect(t.amax_part, tiles, flush_need[op], polls, sh8, count);
+    if (threadIdx.x != 0) return;
+    const uint32_t mg = group_mantissa_bits(figures & kAmaxBits, kE4M3Max, kScaleGam), mg5 = group_mantissa_bits(figures & kAmaxBits, kE5M2Max, kScaleGam);
+    t.flush_part[0] = mg; t.flush_part[1] = mg5; t.flush_part[2] = figures & kToldProven ? 1u : 0u;
+    uint32_t* gmant = gmant_of[op];
+    if (gmant) { gmant[0] = mg; gmant[1] = mg5; }
+}
 // (TEAM kTeamWaveRow: rows of either length that a workgroup of 256 lanes holds)
 template <int TEAM, bool FAKE>
 __global__ __launch_bounds__(256) void k_team_stream(StreamTeam g) {
@@ -280,19 +296,7 @@ __global__ __launch_bounds__(256) void k_team_stream(StreamTeam g) {
     const StreamPlace place = stream_place(g.order, blockIdx.x >> 3);
     const int in8 = (int)(blockIdx.x & 7u);
     if (place.first) {
-        const int op = group_find32(g.first.group_end, g.first.n, (int)place.group);
-        const ProveOp& t = g.first.op[op];
-        const int in_op = (int)place.group - (op ? g.first.group_end[op - 1] : 0), tiles = stream_tiles(t), tile = in_op * 8 + in8;
-        auto count = [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { stream_count(t, k, tid, amax, flushes); };
-        if (tile < tiles) { stream_first(t.amax_part, tile, sh.u, count); return; }
-        if (in8 != 0 || in_op * 8 < tiles) return;         // the last of the operand's groups collects
-        const uint32_t figures = stream_collect(t.amax_part, tiles, g.flush_need[op], g.polls, sh.u, count);
-        if (threadIdx.x != 0) return;
-        // the operand's mantissa words, for the passes of a tensor-level decision, and the caller's output
-        const uint32_t mg = group_mantissa_bits(figures & kAmaxBits, kE4M3Max, kScaleGam), mg5 = group_mantissa_bits(figures & kAmaxBits, kE5M2Max, kScaleGam);
-        t.flush_part[0] = mg; t.flush_part[1] = mg5; t.flush_part[2] = figures & kToldProven ? 1u : 0u;
-        uint32_t* gmant = g.team.op[op].o.gmant;
-        if (gmant) { gmant[0] = mg; gmant[1] = mg5; }
+        stream_first_group(g.first, g.flush_need, g.gmant, g.polls, (int)place.group, in8, sh.u);
         return;
     }
     const int64_t wg = (int64_t)place.group * 8 + in8;
@@ -359,13 +363,15 @@ struct ColOp {
     // itself (no pre-pass over the operand) and leaves them in `gam` and in the caller's output
     uint32_t* gmant;                                     // caller's [2] or nullptr
 };
-struct GroupCol {
+template <int N>
+struct GroupColT {
     int n;
-    int64_t unit_end[kMaxTeamGroup];
-    int32_t comb_end[kMaxTeamGroup];      // running workgroup totals of the combine kernels (256 columns each)
-    int32_t copy_end[kMaxTeamGroup];      // running workgroup totals of the fallback-column copy
-    ColOp op[kMaxTeamGroup];
+    int64_t unit_end[N];
+    int32_t comb_end[N];      // running workgroup totals of the combine kernels (256 columns each)
+    int32_t copy_end[N];      // running workgroup totals of the fallback-column copy
+    ColOp op[N];
 };
+using GroupCol = GroupColT<kMaxTeamGroup>;
 struct ColShared {
     uint32_t amax[4][16][4];     // packed per-column maxima: wave, lane column group, 4 words (8 columns)
     float scale[128], scale5[128];
@@ -955,6 +961,69 @@ __global__ __launch_bounds__(256) void k_col_group(GroupCol g) { col_group_body<
 template <int CRIT, bool FAKE, bool EDGE>
 __global__ __launch_bounds__(256, 4) void k_col_quant_group(GroupCol g) { col_group_body<CRIT, kColExternal, FAKE, EDGE>(g); }
 
+// ---- Per-channel rows and columns of linear layers (Section 4.1.1: one operand of a GEMM by rows, the other by columns) in common launches: the
+//      rows' pre-pass under GAM scales before the columns' amax pass, then the columns' quantize pass, whose workgroups take longest, before
+//      the rows.  Two launches (and one that clears the words of the rows' tiles) instead of four or five; us per call, launch by launch / so, FP8 payload, statistics:
+//      8192 x 4096 rows and 4096 x 6144 columns, GAM scales, tensor-level decision 74.1 / 64.0 (at four workgroups per compute unit 65.0), FP32 scales
+//      58.1 / 54.1; 2048 x 2048 and 2048 x 4096 36.8 / 28.1 (columns spread among the rows, at four, 32.0, so 29.6), 28.9 / 24.8; 512 x 1024 and 1024 x 2048 32.6 /
+//      24.0, 25.2 / 21.3.
+struct PairFirst {
+    StreamFirst first;
+    uint32_t flush_need[kPairMax];
+    uint32_t* gmant[kPairMax];
+    int32_t polls, first_groups;
+};
+struct PairCols {
+    int n;
+    int64_t unit_end[kPairMax];
+    ColOp op[kPairMax];
+};
+struct PairTeam {
+    int n;
+    int64_t unit_end[kPairMax];           // padded to groups of eight workgroups
+    TeamOp op[kPairMax];
+    const uint32_t* words[kPairMax];
+    int32_t units[kPairMax];
+};
+template <int MODE, bool FAKE, bool EDGE>
+__device__ __forceinline__ void pair_columns(const PairCols& c, int64_t wg, ColShared& sh) {
+    if (wg >= c.unit_end[c.n - 1]) return;
+    const int op = group_find(c.unit_end, c.n, wg);
+    col_strip<kCritEq2, MODE, FAKE, EDGE>(c.op[op], wg - (op ? c.unit_end[op - 1] : 0), sh);
+}
+template <bool EDGE>
+__global__ __launch_bounds__(256) void k_pair_first(PairFirst g, PairCols c) {
+    __shared__ ColShared sh;
+    const int group = (int)(blockIdx.x >> 3), in8 = (int)(blockIdx.x & 7u);
+    if (group < g.first_groups) {
+        stream_first_group(g.first, g.flush_need, g.gmant, g.polls, group, in8, sh.wg);
+        return;
+    }
+    pair_columns<kColAmax, false, EDGE>(c, (int64_t)(group - g.first_groups) * 8 + in8, sh);
+}
+// GAM: the first launch has told the rows' figures.
+template <bool FAKE, bool EDGE, bool GAM>
+__global__ __launch_bounds__(256, 4) void k_pair_second(PairTeam t, PairFirst g, PairCols c, int col_wgs) {
+    __shared__ ColShared csh;
+    __shared__ TeamShared sh;
+    const int64_t wg = (int64_t)blockIdx.x - col_wgs;
+    if (wg < 0) { pair_columns<kColExternal, FAKE, EDGE>(c, (int64_t)blockIdx.x, csh); return; }
+    if (wg >= t.unit_end[t.n - 1]) return;
+    const int op = group_find(t.unit_end, t.n, wg);
+    const int64_t unit = wg - (op ? t.unit_end[op - 1] : 0);
+    if (unit >= t.units[op]) return;
+    constexpr int kFrom = GAM ? kTeamStream : kTeamAlone;
+    const ProveOp& f = g.first.op[op];
+    const StreamUnit su{GAM ? stream_copy(t.words[op], unit) : nullptr, g.polls};
+    auto scan = [&] { return stream_scan(stream_tiles(f), g.flush_need[op], [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { stream_count(f, k, tid, amax, flushes); }); };
+    if (t.op[op].cols > kWaveRowCols) team_block<kTeamWgRow, kCritEq2, FAKE, false, kFrom>(t.op[op], unit, sh, su, scan);
+    else team_block<kTeamWaveRow, kCritEq2, FAKE, false, kFrom>(t.op[op], unit, sh, su, scan);
+}
+__global__ __launch_bounds__(256) void k_pair_clear(PairFirst g) {      // blockIdx.y = operand
+    const ProveOp& t = g.first.op[blockIdx.y];
+    stream_clear(t.amax_part, stream_tiles(t), (int)blockIdx.x);
+}
+
 // Per-channel columns of a launch with many workgroups (see kColScaleWgs): column amax over the strips -> amax, scale (Algorithm 1),
 // E8M0 byte, once and for all.
 // Every workgroup takes the operand's figures (see col_scales), a handful of loads per thread, and then a column per thread.
@@ -1224,6 +1293,13 @@ namespace {
 int stream_first_tiles(const BatchItem& it) {
     return (int)(it.gran == kGranRow ? scope_proof_units(it) : (it.sh.rows / 64) * ((it.sh.cols + 255) / 256));
 }
+void set_first_op(ProveOp& t, const TeamStreamItem& op) {
+    const BatchItem& it = *op.it;
+    t.x = it.x; t.ld = it.sh.ld; t.cols = it.sh.cols; t.kind = scope_proof_kind(it); t.keep = 1;
+    if (t.kind == kProveRows) { t.units_x = (it.sh.cols + kProvePiece - 1) / kProvePiece; t.n_units = it.sh.rows * t.units_x; }
+    else { t.units_x = (it.sh.cols + 255) / 256; t.n_units = stream_first_tiles(it); }
+    t.amax_part = op.sync; t.flush_part = op.gam;
+}
 template <int TEAM>
 void launch_team_stream(const StreamTeam& g, unsigned wgs, bool fake, hipStream_t st) {
     // layer of twelve operands, us per call uncapped / at 6 / 5 / 4 workgroups per compute unit: 128 x 128 425 / 427 / 428 / 435, 64 x 64 425 throughout,
@@ -1258,13 +1334,10 @@ hipError_t launch_team_stream_items(const TeamStreamItem* ops, int n, hipStream_
         set_team_op(u, it, units_x, ops[k].gam);
         g.units[k] = (int32_t)units;
         g.flush_need[k] = u.prove ? (uint32_t)flush_need_of(it.th, it.sh.rows * it.sh.cols) : 0u;
+        g.gmant[k] = it.o.gmant;
         total += (units + 7) / 8 * 8;
         g.team.unit_end[k] = total;
-        ProveOp& t = g.first.op[k];
-        t.x = it.x; t.ld = it.sh.ld; t.cols = it.sh.cols; t.kind = scope_proof_kind(it); t.keep = 1;
-        if (t.kind == kProveRows) { t.units_x = (it.sh.cols + kProvePiece - 1) / kProvePiece; t.n_units = it.sh.rows * t.units_x; }
-        else { t.units_x = (it.sh.cols + 255) / 256; t.n_units = stream_first_tiles(it); }
-        t.amax_part = ops[k].sync; t.flush_part = ops[k].gam;
+        set_first_op(g.first.op[k], ops[k]);
         const int tiles = stream_first_tiles(it);
         const uint32_t mine = stream_groups(tiles);
         groups += mine;
@@ -1396,8 +1469,77 @@ hipError_t launch_subcol_items(const BatchItem* items, const int* idx, int cnt, 
 // five launches of each part cost more than its second read gains (the twelve operands of a layer 561 us per call in one go,
 // 637 in four parts, 591 in one go without the first pass leaving its operands in the Infinity Cache).  ws_of[k] is the
 // workspace of operand idx[k] (column_workspace_bytes).
+namespace {
+// The rows' tables of the common launches.
+struct PairLaunch {
+    PairFirst first;
+    PairTeam team;
+    int64_t wgs;             // of the second launch
+    int most_tiles;
+    bool gam;
+};
+void set_pair(PairLaunch& p, const PairRows& rows) {
+    p.gam = rows.ops[0].it->scaling == kScaleGam;
+    p.first.first.n = p.team.n = rows.n;
+    p.first.polls = rows.ops[0].it->polls;
+    p.wgs = 0; p.most_tiles = 0;
+    uint32_t groups = 0u;
+    for (int k = 0; k < rows.n; ++k) {
+        const BatchItem& it = *rows.ops[k].it;
+        int64_t units_x;
+        const int64_t units = team_units(it, team_kind_of(it), units_x);
+        set_team_op(p.team.op[k], it, units_x, rows.ops[k].gam);
+        p.team.units[k] = (int32_t)units;
+        p.team.words[k] = rows.ops[k].sync;
+        p.wgs += (units + 7) / 8 * 8;
+        p.team.unit_end[k] = p.wgs;
+        set_first_op(p.first.first.op[k], rows.ops[k]);
+        p.first.flush_need[k] = p.team.op[k].prove ? (uint32_t)flush_need_of(it.th, it.sh.rows * it.sh.cols) : 0u;
+        p.first.gmant[k] = it.o.gmant;
+        const int tiles = stream_first_tiles(it);
+        groups += stream_groups(tiles);
+        p.first.first.group_end[k] = (int32_t)groups;
+        if (tiles > p.most_tiles) p.most_tiles = tiles;
+    }
+    p.first.first_groups = (int32_t)groups;
+}
+PairCols pair_cols(const GroupCol& g) {
+    PairCols c;
+    c.n = g.n;
+    for (int k = 0; k < g.n; ++k) { c.unit_end[k] = g.unit_end[k]; c.op[k] = g.op[k]; }
+    return c;
+}
+template <bool FAKE, bool EDGE>
+void launch_pair_second(const PairLaunch& p, const PairCols& c, hipStream_t st) {
+    const int col_wgs = (int)((c.unit_end[c.n - 1] + 7) / 8 * 8);
+    const dim3 grid((unsigned)(col_wgs + p.wgs));
+    if (p.gam) k_pair_second<FAKE, EDGE, true><<<grid, dim3(256), 0, st>>>(p.team, p.first, c, col_wgs);
+    else k_pair_second<FAKE, EDGE, false><<<grid, dim3(256), 0, st>>>(p.team, p.first, c, col_wgs);
+}
+}  // namespace
+bool pair_takes_row(const BatchItem& it) {
+    const int kind = team_kind_of(it);
+    if (it.scaling == kScaleGam) return team_stream_kind(it) == kTeamWaveRow;
+    return (kind == kTeamWaveRow || kind == kTeamWgRow) && it.sh.rows * it.sh.cols <= 0x7FFFFFFFll;
+}
+// Columns whose launches need no scales of their own (see k_col_scales) and are of one kind.
+bool columns_pair(const BatchItem* items, const int* idx, int cnt) {
+    int64_t total = 0;
+    for (int k = 0; k < cnt; ++k) {
+        const BatchItem& it = items[idx[k]];
+        const ColPlan pl = plan_columns(it.sh.rows, it.sh.cols);
+        total += (int64_t)pl.n_strips * ((it.sh.cols + 127) / 128);
+        if (col_needs_edge(it) != col_needs_edge(items[idx[0]])) return false;
+    }
+    if (total > kColScaleWgs) return false;
+    for (int k = 0; k < cnt; ++k)
+        if (!column_scales_folded(plan_columns(items[idx[k]].sh.rows, items[idx[k]].sh.cols).n_strips, total, items[idx[k]].scope != 1)) return false;
+    return true;
+}
 hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int cnt, int crit, const uint32_t* const* gam_of,
-                                    char* const* ws_of, hipStream_t st, KProf* prof) {
+                                    char* const* ws_of, const PairRows* rows, hipStream_t st, KProf* prof) {
+    PairLaunch pair;
+    if (rows) set_pair(pair, *rows);
     for (int variant = 0; variant < 4; ++variant) {
         const bool fake = (variant & 1) != 0, edge = (variant & 2) != 0;
         GroupCol g; g.n = 0;
@@ -1417,7 +1559,17 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
                 copy += (int)(t.tiles_x * groups);
                 g.copy_end[k] = copy;
             }
-            { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColAmax>(g, total, kCritEq2, false, edge, st); }
+            const PairCols pc = rows ? pair_cols(g) : PairCols{};
+            if (rows && pair.gam) {
+                {
+                    ProfScope ps(prof, kKernStreamClear, st);
+                    k_pair_clear<<<dim3(stream_clear_wgs(pair.most_tiles), (unsigned)rows->n), dim3(256), 0, st>>>(pair.first);
+                }
+                ProfScope ps(prof, kKernColumnTile, st);
+                const dim3 grid((unsigned)(8 * (pair.first.first_groups + (total + 7) / 8)));
+                if (edge) k_pair_first<true><<<grid, dim3(256), 0, st>>>(pair.first, pc);
+                else k_pair_first<false><<<grid, dim3(256), 0, st>>>(pair.first, pc);
+            } else { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColAmax>(g, total, kCritEq2, false, edge, st); }
             bool scaled = total > kColScaleWgs, three = false;
             for (int k = 0; k < g.n; ++k) {
                 three |= g.op[k].three != 0;
@@ -1426,7 +1578,11 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
             for (int k = 0; k < g.n; ++k) g.op[k].scaled = scaled ? 1 : 0;
             if (scaled) { ProfScope ps(prof, kKernColumnCombine, st); k_col_scales<<<dim3((unsigned)comb), dim3(256), 0, st>>>(g); }
             else if (three) { ProfScope ps(prof, kKernColumnCombine, st); k_col_amin<<<dim3((unsigned)comb), dim3(256), 0, st>>>(g); }
-            { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColExternal>(g, total, crit, fake, edge, st); }
+            if (rows) {
+                ProfScope ps(prof, kKernColumnTile, st);
+                if (fake) { if (edge) launch_pair_second<true, true>(pair, pc, st); else launch_pair_second<true, false>(pair, pc, st); }
+                else      { if (edge) launch_pair_second<false, true>(pair, pc, st); else launch_pair_second<false, false>(pair, pc, st); }
+            } else { ProfScope ps(prof, kKernColumnTile, st); launch_col_kind<kColExternal>(g, total, crit, fake, edge, st); }
             bool sums = false;        // some operand's sums are not left to the tensor-level reduce pass
             for (int k = 0; k < g.n; ++k) sums |= !g.op[k].later;
             if (sums) {

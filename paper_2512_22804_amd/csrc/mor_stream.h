@@ -56,6 +56,17 @@ inline bool stream_order(StreamOrder& o, uint32_t first_groups, uint32_t largest
 }
 inline uint32_t stream_groups(int tiles) { return (uint32_t)(tiles + 7) / 8u + 1u; }      // of an operand's first pass: its tiles, and the one that collects
 
+// Groups of eight workgroups spread evenly among others.
+struct Spread {
+    uint32_t n, mul, shift;       // that many among a number of groups; reciprocal of that number
+};
+__device__ __forceinline__ uint32_t spread_before(const Spread& s, uint32_t group) { return recip_div(group * s.n, s.mul, s.shift); }
+inline bool make_spread(Spread& s, uint32_t n, uint32_t all) {
+    s.n = n;
+    recip_of(all ? all : 1u, &s.mul, &s.shift);
+    return (uint64_t)(all + 1) * n < 0x7FFFFFFFull;
+}
+
 // `Tile`: count(tile, lane of the workgroup, amax, flushes) adds a lane's share of a tile to its figures, `amax` a pattern.
 template <class Tile>
 __device__ __forceinline__ void stream_first(uint32_t* words, int tile, uint32_t* sh8, Tile count) {

@@ -249,3 +249,58 @@ def test_operands_that_go_along(case, counted):
                         assert s[key] == t[key] or abs(s[key] - t[key]) <= 32 * 2.0 ** -24 * abs(s[key]), (case, k, key)
                     elif key != "flags":                                                    # (which says how, not what)
                         assert s[key] == t[key], (case, k, key)
+
+
+# rows and columns of linear layers: waves, workgroups, one row; whole tiles, ragged ones, a single column chunk
+PAIRS = [[(64, 256), (256, 256)], [(333, 4104), (1, 8), (512, 1000)], [(5, 16384), (1027, 1000), (128, 128), (1280, 640)], [(2048, 4096), (4096, 2048)]]
+
+
+@pytest.mark.parametrize("fake", [False, True])
+@pytest.mark.parametrize("scope", ["tensor", "partition"])
+@pytest.mark.parametrize("scaling", ["gam", "fp32_amax", "e8m0"])
+@pytest.mark.parametrize("case", range(len(PAIRS)))
+def test_rows_and_columns_together(case, scaling, scope, fake):
+    """Every operand by rows and by columns in one call: the outputs of each alone."""
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(31 + case)
+    ops = []
+    for k, (rows, cols) in enumerate(PAIRS[case]):
+        x = torch.randn((rows, cols), generator=gen, device=dev)
+        x = (x * torch.where(torch.rand(x.shape, generator=gen, device=dev) < (0.0, 0.3, 0.035)[k % 3], 1e-9, 1.0)).to(torch.bfloat16)
+        if k == 1:
+            x[0, cols // 2] = float("inf")
+        ops += [(x, "channel_row"), (x, "channel_col")]
+
+    def entries():
+        got = []
+        for x, gran in ops:
+            p = B.make_params(*x.shape, gran, scope, "mean_rel_err", 0.045, scaling=scaling)
+            out = B.alloc_outputs(p, dev, want_bf16=not fake, want_fp8=not fake, bf16_fill=0x1234)
+            out.workspace = None
+            for n in NAMES:
+                t = getattr(out, n)
+                if t is not None and n != "bf16":
+                    t.view(torch.uint8).fill_(0x5A)
+            got.append((p, x, out, None if fake else torch.full((B.STATS_BYTES,), 0x5A, dtype=torch.uint8, device=dev),
+                        torch.full(x.shape, 3.0, dtype=torch.bfloat16, device=dev) if fake else None))
+        return got
+
+    want = entries()
+    for e in want:
+        _run(B, [e])
+    for polls in (None, 0):
+        print(f"[stream] rows and columns {case} {scaling} {scope} fake={fake} polls={polls}", flush=True)
+        got = entries()
+        _run(B, got, polls)
+        for k, (a, b) in enumerate(zip(want, got)):
+            for n in NAMES:
+                u, v = getattr(a[2], n), getattr(b[2], n)
+                assert (u is None) == (v is None) and (u is None or torch.equal(u.view(torch.uint8), v.view(torch.uint8))), (case, k, n)
+            if fake:
+                assert torch.equal(a[4].view(torch.int16), b[4].view(torch.int16)), (case, k)
+            else:
+                s, t = B.read_stats(a[3]), B.read_stats(b[3])
+                for key in s:
+                    assert s[key] == t[key] or (isinstance(s[key], float) and abs(s[key] - t[key]) <= 1e-12 * abs(s[key])), (case, k, key)
