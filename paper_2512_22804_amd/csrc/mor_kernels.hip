@@ -948,6 +948,15 @@ __device__ __forceinline__ uint32_t scope_decision(const ScopeOp& t) {
     n = wave_allsum_u64(n);
     return ((n ? e / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
 }
+__device__ __forceinline__ void scope_copy(const ScopeOp& t, int b, int nb) {
+    if (t.ld == t.cols && t.ld_bf16 == t.cols) {
+        copy_chunk_tiles(t.x, t.bf16, t.rows * t.cols / 8, b, nb);
+    } else {
+        const int64_t cpr = t.cols / 8;
+        for (int64_t r = b; r < t.rows; r += nb)
+            for (int64_t c = threadIdx.x; c < cpr; c += 256) store16(t.bf16 + r * t.ld_bf16 + c * 8, load16(t.x + r * t.ld + c * 8));
+    }
+}
 // Decision (every workgroup re-derives it from the partial records: the same value everywhere), mask broadcast over the
 // operand's workgroups, statistics by its first one, then the copy of a BF16 tensor that no earlier pass has proven and written.
 __global__ __launch_bounds__(256) void k_scope_copy_group(GroupScope g) {
@@ -968,13 +977,81 @@ __global__ __launch_bounds__(256) void k_scope_copy_group(GroupScope g) {
                          record_counter(sh, 13), 0ull, m ? total : 0ull, 0ull, 0u);
     }
     if (t.bf16 == nullptr || m == 0u || (t.proven && t.proven[0] != 0u)) return;
-    if (t.ld == t.cols && t.ld_bf16 == t.cols) {
-        copy_chunk_tiles(t.x, t.bf16, t.rows * t.cols / 8, b, nb);
-    } else {
-        const int64_t cpr = t.cols / 8;
-        for (int64_t r = b; r < t.rows; r += nb)
-            for (int64_t c = threadIdx.x; c < cpr; c += 256) store16(t.bf16 + r * t.ld_bf16 + c * 8, load16(t.x + r * t.ld + c * 8));
+    scope_copy(t, b, nb);
+}
+// Operands of few blocks: the decision from the blocks' sums in every workgroup, without the reduce launch before it.  What is read for it lies
+// in the L2 cache; a proven operand's workgroups that have no part of the mask to write leave at once.
+// A launch is what bounds a small operand here.  us per call, weights with FP32 scales, two launches / this one: 128 x 128 blocks of 256 x 1024 13.6 / 9.2,
+// 1 x 128 of 256 x 1024 (2048 blocks) 13.7 / 9.4, 64 x 64 of 4096 x 4096 (4096) 20.7 / 18.8, 1 x 128 of 1024 x 1024 (8192) 13.8 / 12.3 but channels of
+// 8192 x 4096 (8192) 27.6 / 27.8; with GAM scales 21.0 / 17.1, 21.3 / 17.4, 27.2 / 25.6, 21.7 / 18.4, 38.1 / 38.3.  With statistics, which one workgroup
+// counts: 13.6 / 9.4, 13.5 / 12.4, 22.7 / 25.1, 14.3 / 24.1, 29.7 / 39.8.
+constexpr int64_t kScopeDirect = 4096, kScopeDirectStats = 2048;      // blocks of an operand, without and with statistics
+__global__ __launch_bounds__(256) void k_scope_direct_group(GroupScope g) {
+    __shared__ double she[4], she5[4];
+    __shared__ unsigned long long shn[4];
+    __shared__ StatsLds<4> sh;
+    const int op = group_find32(g.copy_end, g.n, blockIdx.x);
+    const ScopeOp& t = g.op[op];
+    const int b = blockIdx.x - (op ? g.copy_end[op - 1] : 0);
+    const int nb = g.copy_end[op] - (op ? g.copy_end[op - 1] : 0);
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, n_part = (int)t.n_part;
+    const bool eq3 = t.crit == kCritEq3, copied = t.bf16 == nullptr || (t.proven && t.proven[0] != 0u);
+    if (copied && (int64_t)b * 256 >= t.n_part) return;        // (uniform over the workgroup)
+    double e = 0.0, e5 = 0.0;
+    unsigned long long n = 0ull;
+    for (int i0 = tid; i0 < n_part; i0 += 8 * 256) {
+        float ev[8], e5v[8];
+        uint32_t nv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = i0 + u * 256 < n_part ? i0 + u * 256 : i0;      // always a valid block: the loads need no branch
+            ev[u] = t.err_sum[i]; nv[u] = t.nnz[i]; e5v[u] = eq3 ? t.err5_sum[i] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const bool ok = i0 + u * 256 < n_part;
+            e += ok ? (double)ev[u] : 0.0; e5 += ok ? (double)e5v[u] : 0.0; n += ok ? nv[u] : 0u;
+        }
     }
+    e = wave_allsum_f64(e);
+    n = wave_allsum_u64(n);
+    if (eq3) e5 = wave_allsum_f64(e5);
+    if (lane == 0) { she[w] = e; she5[w] = e5; shn[w] = n; }
+    __syncthreads();
+    e = (she[0] + she[1]) + (she[2] + she[3]);
+    n = (shn[0] + shn[1]) + (shn[2] + shn[3]);
+    uint32_t m;
+    if (eq3) m = e < (she5[0] + she5[1]) + (she5[2] + she5[3]) ? 0u : 1u;
+    else m = ((n ? e / (double)n : 0.0) < (double)t.th) ? 0u : 1u;
+    if (b == 0 && tid == 0) t.decision[0] = m;
+    for (int p = b * 256 + tid; p < n_part; p += nb * 256) t.mask[p] = (uint8_t)m;
+    if (b == 0 && t.stats) {                                   // uniform over the workgroup
+        StatsTally a;
+        tally_clear(a);
+        for (int base = w * 64; base < n_part; base += 4 * 256) {       // uniform over the wave
+            float es[4];
+            uint32_t nz[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = base + lane + u * 256 < n_part ? base + lane + u * 256 : n_part - 1;
+                es[u] = t.err_sum[i]; nz[u] = t.nnz[i];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (base + u * 256 >= n_part) break;           // uniform over the wave
+                tally(base + lane + u * 256 < n_part, es[u], nz[u], 0u, [] { return 0ull; }, t.th, t.near_tol, a);
+            }
+        }
+        uint32_t mine;
+        stats_reduce(a, mine, sh);
+        const unsigned long long total = (unsigned long long)(t.rows * t.cols);
+        if (tid < 12) t.stats->hist[tid] = mine;
+        if (tid < 64) {
+            const uint32_t near = stats_counter(mine, 13);
+            if (tid == 0) stats_finish(t.stats, t.n_part, total, a.e, a.n, m ? (unsigned long long)n_part : 0ull, near, 0ull, m ? total : 0ull, 0ull, 0u);
+        }
+    }
+    if (!copied && m != 0u) scope_copy(t, b, nb);
 }
 
 // ---- a lone dense 1 x 128 operand: the block kernel gathers the statistics of its workgroups itself (one record per
@@ -2635,8 +2712,13 @@ void BatchRun::tensor_level_decisions() {
     int red = 0, copy = 0;
     auto flush = [&]() {
         if (g.n == 0 || err != hipSuccess) { g.n = 0; red = 0; copy = 0; return; }
-        { ProfScope ps(prof, kKernScopeReduce, st); k_scope_reduce_group<<<dim3(red), dim3(256), 0, st>>>(g); }
-        { ProfScope ps(prof, kKernFallbackCopy, st); k_scope_copy_group<<<dim3(copy), dim3(256), 0, st>>>(g); }
+        bool direct = true;
+        for (int k = 0; k < g.n; ++k) direct &= g.op[k].n_part <= (g.op[k].stats ? kScopeDirectStats : kScopeDirect) && g.op[k].col.n_strips == 0;
+        if (direct) { ProfScope ps(prof, kKernFallbackCopy, st); k_scope_direct_group<<<dim3(copy), dim3(256), 0, st>>>(g); }
+        else {
+            { ProfScope ps(prof, kKernScopeReduce, st); k_scope_reduce_group<<<dim3(red), dim3(256), 0, st>>>(g); }
+            { ProfScope ps(prof, kKernFallbackCopy, st); k_scope_copy_group<<<dim3(copy), dim3(256), 0, st>>>(g); }
+        }
         g.n = 0; red = 0; copy = 0;
     };
     int64_t total_elems = 0, unproven_bytes = 0;
