@@ -2348,6 +2348,7 @@ bool taken_whole(const BatchItem& it) {
 }
 // The operands of linear layers under the per-channel strategy: rows and columns in common launches (see launch_channel_col_items).
 void BatchRun::paired_operands() {
+    if (n < 2) return;
     for (int fake = 0; fake < 2 && err == hipSuccess; ++fake) {
         PairRows rows;
         rows.n = 0;
@@ -2387,12 +2388,19 @@ void BatchRun::paired_operands() {
 void BatchRun::streamed_operands() {
     constexpr int kMost = 12;                    // operands of a launch
     bool beside = false;
-    for (int i = 0; i < n; ++i)
-        beside |= !streamed[i] && items[i].scaling == kScaleGam && items[i].gran != kGranTensor && items[i].gran != kGranCol && team_stream_kind(items[i]) < 0;
+    int kind[kBatchMax];
+    uint32_t kinds = 0u;
+    for (int i = 0; i < n; ++i) {
+        const int k = streamed[i] ? -1 : team_stream_kind(items[i]);
+        kind[i] = k < 0 ? -1 : 2 * k + (items[i].o.fake != nullptr ? 1 : 0);
+        if (k >= 0) kinds |= 1u << kind[i];
+        beside |= !streamed[i] && items[i].scaling == kScaleGam && items[i].gran != kGranTensor && items[i].gran != kGranCol && k < 0;
+    }
     for (int c = 0; c < 2 * kTeamKinds && err == hipSuccess; ++c) {
+        if ((kinds >> c & 1u) == 0u) continue;
         int idx[kBatchMax], cnt = 0;
         for (int i = 0; i < n; ++i)
-            if (!streamed[i] && team_stream_kind(items[i]) == c / 2 && (items[i].o.fake != nullptr) == (c % 2 != 0)) idx[cnt++] = i;
+            if (kind[i] == c) idx[cnt++] = i;
         for (int base = 0; base < cnt && err == hipSuccess; base += kMost) {
             TeamStreamItem ops[kMost];
             const int m = cnt - base < kMost ? cnt - base : kMost;
@@ -2961,6 +2969,7 @@ constexpr int64_t kFillAloneTiles = 128;
 // Which operands go along with the passes of per-tensor ones (see TensorFill): those decided block by block under Eq. 2 with two types, FP8
 // payload and no pre-pass, of which one may have 1 x 128 blocks; with statistics, up to what one workgroup counts of 128 x 128 blocks.
 void BatchRun::plan_fill() {
+    if (n < 2) return;
     for (int strided = 0; strided < 2 && fill_strided < 0; ++strided) {
         int cnt = 0;
         int64_t tiles = 0;
