@@ -484,10 +484,12 @@ def main() -> int:
         step(profiles)
         torch.cuda.synchronize()
         for o, pr in zip(ops, profiles):
-            # a small 1x128 operand rides in extra workgroups of the 128x128 team launch (no launch of its own): its bytes
-            # then belong to that launch
+            # the operands that have no launch of their own (a small 1x128 operand beside 128x128 blocks, both beside the passes of
+            # the per-tensor operands) go through in workgroups of another one's: their bytes then belong to that launch
             seen = {B.KERNEL_NAMES[pr.kernel[k]] for k in range(pr.count)}
-            sub_rides = not args.per_operand and "sub1x128" not in seen and "team_block" in seen
+            host = "team_block" if "team_block" in seen else "tensor_stream"
+            ride = {"sub1x128": "sub1x128", "block128": "team_block"}
+            riders = {g: k for g, k in ride.items() if not args.per_operand and k not in seen and host in seen}
             for k in range(pr.count):
                 kname = B.KERNEL_NAMES[pr.kernel[k]]
                 ms = ev.elapsed_ms(pr.start[k], pr.stop[k])
@@ -501,8 +503,8 @@ def main() -> int:
                     for q in ops:
                         if kname.startswith("stats"):
                             rec["bytes"] += algorithmic_bytes(kname, q["n"], q["P"], 0.0) / parts if q["gran"] != "tensor" else 0.0
-                        elif KERNEL_GRAN.get(kname) == q["gran"] or (sub_rides and kname == "team_block" and q["gran"] == "sub1x128"):
-                            rec["bytes"] += algorithmic_bytes(kname, q["n"], q["P"], q["fallback_frac"], q["fused_fallback"]) / parts
+                        elif KERNEL_GRAN.get(kname) == q["gran"] or (kname == host and q["gran"] in riders):
+                            rec["bytes"] += algorithmic_bytes(riders.get(q["gran"], kname), q["n"], q["P"], q["fallback_frac"], q["fused_fallback"]) / parts
             if not args.per_operand:
                 break
     ev.destroy()
