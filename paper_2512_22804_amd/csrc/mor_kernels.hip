@@ -2817,6 +2817,7 @@ bool tensor_stream_pays(int n, int64_t tiles, bool strided, bool ride) {
 template <bool STRIDED>
 hipError_t launch_tensor_stream(GroupTensor& g, const GroupStats& riders, int ride_partial, int c_end, int ride_final, bool fake, int polls, StreamFill& fill,
                                 hipStream_t st, KProf* prof) {
+    if (fill.form != kFillNone && (fake || (STRIDED && fill.form == kFillFlat))) return hipErrorInvalidValue;      // not instantiated below
     StreamClear clear;
     clear.n = g.n;
     uint32_t groups = 0u, largest = 0u;
@@ -2859,10 +2860,9 @@ hipError_t launch_tensor_stream(GroupTensor& g, const GroupStats& riders, int ri
         // (gradients of a layer 383.0 us per call uncapped, 382.5 at 5, 382.1 at 4, 382.4 at 3 workgroups per compute unit, kept lean 347.5, 347.7, 346.2,
         // 354.9; a slice of 4099 x 5000 28.6, 28.6, 30.1, 28.5)
         if (fake) k_tensor_stream<true, STRIDED, kFillNone><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
-        else if (fill.form == kFillRows) k_tensor_stream<false, STRIDED, kFillRows><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
-        else if (fill.form == kFillFlat) {
-            if constexpr (!STRIDED) k_tensor_stream<false, STRIDED, kFillFlat><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
-        } else k_tensor_stream<false, STRIDED, kFillNone><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
+        else if (fill.form == kFillNone) k_tensor_stream<false, STRIDED, kFillNone><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
+        else if (STRIDED || fill.form == kFillRows) k_tensor_stream<false, STRIDED, kFillRows><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
+        else k_tensor_stream<false, false, kFillFlat><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
     }
     ProfScope ps(prof, kKernFallbackCopy, st);
     k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end, fill.direct, fill.solo);
@@ -3005,7 +3005,7 @@ void BatchRun::plan_fill() {
 }
 void BatchRun::make_fill(StreamFill& f, GroupStats& riders, int& ride_final) {
     TensorFill& t = f.table;
-    f.form = kFillFlat;
+    f.form = fill_strided ? kFillRows : kFillFlat;      // (beside padded rows only the rows form exists; without a 1 x 128 operand nothing runs it)
     int64_t units = 0;
     t.team.n = n_fill_team;
     for (int k = 0; k < n_fill_team; ++k) {
