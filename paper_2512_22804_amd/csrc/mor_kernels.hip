@@ -2984,18 +2984,24 @@ void BatchRun::plan_fill() {
         bool counts = false;                               // the call counts statistics
         for (int i = 0; i < n; ++i) counts |= items[i].stats != nullptr;
         if (cnt == 0 || cnt > kMaxGroupTensor || !all || (cnt == 1 && !counts && tiles < kFillAloneTiles)) continue;
-        int others = 0, counted = 0, subs = 0;             // statistics of operands that do not go along, that do
+        int others = 0, counted = 0;                       // statistics of operands that do not go along, of blocks that do
+        int subs = 0, subs_counted = 0;
         for (int i = 0; i < n; ++i) {
             const BatchItem& it = items[i];
             if (it.gran == kGranTensor) continue;
             const Route own = route_of(it);
             const bool plain = it.crit == kCritEq2 && it.scope == 0 && !it.three && !it.o.fake && it.scaling != kScaleGam;
-            if (plain && (own == kRouteSubFlat || own == kRouteSubRows)) { ++subs; if (!strided || own == kRouteSubRows) fill_sub = i; }
+            if (plain && (own == kRouteSubFlat || own == kRouteSubRows)) {
+                ++subs;
+                subs_counted += it.stats != nullptr;
+                if (!strided || own == kRouteSubRows) fill_sub = i;
+            }
             else if (plain && own == kRouteTeam && team_kind_of(it) == kTeamWg128 && !team_needs_edge(it, kTeamWg128) && n_fill_team < kMaxTeamGroup &&
                      (!it.stats || item_parts(it) <= kStatsOneWg)) { fill_team[n_fill_team++] = i; counted += it.stats != nullptr; }
             else others += it.stats != nullptr;
         }
-        if (subs > 1) { fill_sub = -1; others += subs; }
+        if (subs > 1) fill_sub = -1;
+        if (fill_sub < 0) others += subs_counted;          // (the one that goes along leaves records of its own)
         if ((fill_sub < 0 && n_fill_team == 0) || others + counted > kMaxGroupStats) { fill_sub = -1; n_fill_team = 0; continue; }
         fill_strided = strided;
     }
@@ -3015,6 +3021,7 @@ void BatchRun::make_fill(StreamFill& f, GroupStats& riders, int& ride_final) {
         set_team_op(t.team.op[k], it, units_x, nullptr);
         t.team.unit_end[k] = units;
         if (!it.stats) continue;
+        if (riders.n == kMaxGroupStats) { err = hipErrorInvalidValue; return; }      // (not where plan_fill has counted right)
         StatsOp& s = riders.op[riders.n];
         s.err_sum = it.o.err_sum; s.nnz = it.o.nnz; s.mask = it.o.mask;
         s.geom = make_geom(it.gran, it.sh.rows, it.sh.cols);

@@ -82,7 +82,7 @@ static bool passes_follow() {
     }
     return true;
 }
-static const int T = MOR_GRAN_TENSOR, B128 = MOR_GRAN_BLOCK_128x128, S = MOR_GRAN_SUB_1x128;
+static const int T = MOR_GRAN_TENSOR, B128 = MOR_GRAN_BLOCK_128x128, S = MOR_GRAN_SUB_1x128, B64 = MOR_GRAN_BLOCK_64x64;
 
 // Per-tensor operands with padded rows take 128 x 128 blocks along, also without a 1 x 128 operand in a form that could share their launch.
 static bool padded_with_blocks() {
@@ -95,13 +95,27 @@ static bool padded_with_blocks() {
         }
     return true;
 }
+// Statistics that the finish pass takes: at most twelve operands' in its table, also where a dense 1 x 128 operand cannot share the launch.
+static bool statistics_fit() {
+    for (int64_t pad = 0; pad <= 2048; pad += 2048)
+        for (int subs = 0; subs < 3; ++subs)
+            for (int others = 8; others < 14; ++others) {
+                std::vector<Op> ops{{T, 1024, 2048, pad, true}, {B128, 1024, 1024, 0, true}};
+                for (int k = 0; k < subs; ++k) ops.push_back({S, 1024, 1024, 0, true});
+                for (int k = 0; k < others; ++k) ops.push_back({B64, 256, 256, 0, true});
+                if (run(ops) != MOR_OK || !passes_follow()) return false;
+                for (const Launch& l : log_)
+                    if (l.second < 0 || l.second > 12) return false;
+            }
+    return true;
+}
 
 int main(int, char** argv) {
     void* lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
     if (!lib) { fprintf(stderr, "%s\n", dlerror()); return 1; }
     ws_bytes = reinterpret_cast<decltype(ws_bytes)>(dlsym(lib, "mor_batch_workspace_bytes"));
     batch = reinterpret_cast<decltype(batch)>(dlsym(lib, "mor_analyze_quantize_batch"));
-    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}};
+    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"statistics_fit", statistics_fit}};
     printf("%d\n", checks.at(argv[2])() ? 1 : 0);
     return 0;
 }
@@ -121,6 +135,6 @@ def driver(tmp_path_factory):
     return lambda check: subprocess.run([str(exe), build.LIB, check], check=True, capture_output=True, text=True, timeout=120).stdout.strip()
 
 
-@pytest.mark.parametrize("check", ["padded_with_blocks"])
+@pytest.mark.parametrize("check", ["padded_with_blocks", "statistics_fit"])
 def test_plan(driver, check):
     assert driver(check) == "1"
