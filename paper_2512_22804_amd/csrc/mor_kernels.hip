@@ -2972,20 +2972,25 @@ void BatchRun::plan_fill() {
     if (n < 2) return;
     for (int strided = 0; strided < 2 && fill_strided < 0; ++strided) {
         int cnt = 0;
-        int64_t tiles = 0;
+        int64_t tiles = 0, pass_groups = 0;                // (groups of eight workgroups, see TensorFill)
         bool all = true;
         for (int i = 0; i < n; ++i) {
             const BatchItem& it = items[i];
             if (it.gran != kGranTensor || it.crit != kCritEq2 || it.o.fake || item_is_flat(it) != (strided == 0)) continue;
             all &= tensor_streams(it);
             ++cnt;
-            tiles += (it.sh.rows * (it.sh.cols / 8) + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
+            const int64_t own = (it.sh.rows * (it.sh.cols / 8) + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
+            tiles += own;
+            pass_groups += 2 * ((own + 7) / 8) + 1;
         }
         bool counts = false;                               // the call counts statistics
         for (int i = 0; i < n; ++i) counts |= items[i].stats != nullptr;
         if (cnt == 0 || cnt > kMaxGroupTensor || !all || (cnt == 1 && !counts && tiles < kFillAloneTiles)) continue;
         int others = 0, counted = 0;                       // statistics of operands that do not go along, of blocks that do
         int subs = 0, subs_counted = 0;
+        int64_t team_wgs = 0;
+        // Blocks beyond what the launch's order can be divided into (some 370 000, 12 GB) keep a launch of their own.
+        auto spread = [&](int64_t wgs) { return spread_fits((uint64_t)(wgs + 7) / 8, (uint64_t)(pass_groups + (wgs + 7) / 8)); };
         for (int i = 0; i < n; ++i) {
             const BatchItem& it = items[i];
             if (it.gran == kGranTensor) continue;
@@ -2997,8 +3002,11 @@ void BatchRun::plan_fill() {
                 if (!strided || own == kRouteSubRows) fill_sub = i;
             }
             else if (plain && own == kRouteTeam && team_kind_of(it) == kTeamWg128 && !team_needs_edge(it, kTeamWg128) && n_fill_team < kMaxTeamGroup &&
-                     (!it.stats || item_parts(it) <= kStatsOneWg)) { fill_team[n_fill_team++] = i; counted += it.stats != nullptr; }
-            else others += it.stats != nullptr;
+                     (!it.stats || item_parts(it) <= kStatsOneWg) && spread(team_wgs + item_parts(it))) {
+                fill_team[n_fill_team++] = i;
+                team_wgs += item_parts(it);
+                counted += it.stats != nullptr;
+            } else others += it.stats != nullptr;
         }
         if (subs > 1) fill_sub = -1;
         if (fill_sub < 0) others += subs_counted;          // (the one that goes along leaves records of its own)

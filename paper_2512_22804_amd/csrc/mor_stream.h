@@ -61,10 +61,11 @@ struct Spread {
     uint32_t n, mul, shift;       // that many among a number of groups; reciprocal of that number
 };
 __device__ __forceinline__ uint32_t spread_before(const Spread& s, uint32_t group) { return recip_div(group * s.n, s.mul, s.shift); }
+inline bool spread_fits(uint64_t n, uint64_t all) { return n <= all && all < 0x7FFFFFFFull && (all + 1) * n < 0x7FFFFFFFull; }      // (see recip_div)
 inline bool make_spread(Spread& s, uint32_t n, uint32_t all) {
     s.n = n;
     recip_of(all ? all : 1u, &s.mul, &s.shift);
-    return (uint64_t)(all + 1) * n < 0x7FFFFFFFull;
+    return spread_fits(n, all);
 }
 
 // `Tile`: count(tile, lane of the workgroup, amax, flushes) adds a lane's share of a tile to its figures, `amax` a pattern.

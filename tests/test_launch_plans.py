@@ -109,13 +109,46 @@ static bool statistics_fit() {
             }
     return true;
 }
+// Blocks of any number are accepted beside per-tensor operands; so many that the common launch cannot hold them have their own.
+static bool many_blocks() {
+    for (int64_t pad = 0; pad <= 4096; pad += 4096)
+        for (int64_t rows = 16384; rows <= 16384 * 64; rows *= 4) {
+            std::vector<Op> ops{{T, 4096, 4096, pad, false}};
+            for (int k = 0; k < 8; ++k) ops.push_back({B128, rows, 53248, 0, false});
+            if (run(ops) != MOR_OK || !passes_follow() || count("15k_tensor_streamI") != (rows <= 65536 ? 1 : 0) || count("k_team_group") != 1) return false;
+            if (run({{T, 4096, 4096, pad, true}, {B128, 1835008, 4096, 0, true}, {B128, 128, 128, 0, true}}) != MOR_OK || !passes_follow()) return false;
+        }
+    return true;
+}
+// Random mixes of what a batch takes.
+static bool mixes() {
+    uint64_t state = 1;
+    auto draw = [&](int n) { state = state * 6364136223846793005ull + 1442695040888963407ull; return (int)((state >> 33) % (uint64_t)n); };
+    for (int round = 0; round < 4000; ++round) {
+        std::vector<Op> ops;
+        const int n = 1 + draw(round % 4 ? 8 : 40), fakes = draw(4);
+        const bool stats = draw(2) != 0;
+        for (int k = 0; k < n; ++k) {
+            static const int grans[] = {T, T, B128, B128, S, B64, MOR_GRAN_CHANNEL_ROW, MOR_GRAN_CHANNEL_COL};
+            Op o{grans[draw(8)], 128ll << draw(6), 128ll << draw(6), draw(3) ? 0 : 128, stats && draw(4) != 0};
+            o.scaling = draw(3) ? MOR_SCALE_FP32_AMAX : (draw(2) ? MOR_SCALE_GAM : MOR_SCALE_E8M0);
+            if (o.gran != T && !draw(3)) o.scope = MOR_SCOPE_TENSOR;
+            o.fake = !fakes && draw(2);
+            ops.push_back(o);
+        }
+        if (run(ops) != MOR_OK || !passes_follow()) return false;
+        for (const Launch& l : log_)
+            if (l.second < 0 || l.second > 12) return false;
+    }
+    return true;
+}
 
 int main(int, char** argv) {
     void* lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
     if (!lib) { fprintf(stderr, "%s\n", dlerror()); return 1; }
     ws_bytes = reinterpret_cast<decltype(ws_bytes)>(dlsym(lib, "mor_batch_workspace_bytes"));
     batch = reinterpret_cast<decltype(batch)>(dlsym(lib, "mor_analyze_quantize_batch"));
-    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"statistics_fit", statistics_fit}};
+    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"statistics_fit", statistics_fit}, {"many_blocks", many_blocks}, {"mixes", mixes}};
     printf("%d\n", checks.at(argv[2])() ? 1 : 0);
     return 0;
 }
@@ -135,6 +168,6 @@ def driver(tmp_path_factory):
     return lambda check: subprocess.run([str(exe), build.LIB, check], check=True, capture_output=True, text=True, timeout=120).stdout.strip()
 
 
-@pytest.mark.parametrize("check", ["padded_with_blocks", "statistics_fit"])
+@pytest.mark.parametrize("check", ["padded_with_blocks", "statistics_fit", "many_blocks", "mixes"])
 def test_plan(driver, check):
     assert driver(check) == "1"
