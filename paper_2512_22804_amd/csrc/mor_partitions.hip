@@ -1522,7 +1522,9 @@ bool pair_takes_row(const BatchItem& it) {
     if (it.scaling == kScaleGam) return team_stream_kind(it) == kTeamWaveRow;
     return (kind == kTeamWaveRow || kind == kTeamWgRow) && it.sh.rows * it.sh.cols <= 0x7FFFFFFFll;
 }
-// Columns whose launches need no scales of their own (see k_col_scales) and are of one kind.
+// Does the amax pass count the certain flushes of single columns (Eq. 2), which prove their decisions?
+static bool proves_columns(const BatchItem& it) { return it.o.bf16 && !it.o.fake && !it.three && it.th > 0.0f && it.th < 0.9f; }
+// Columns under Eq. 2 whose launches need no scales of their own (see k_col_scales) and are of one kind.
 bool columns_pair(const BatchItem* items, const int* idx, int cnt) {
     int64_t total = 0;
     for (int k = 0; k < cnt; ++k) {
@@ -1533,7 +1535,7 @@ bool columns_pair(const BatchItem* items, const int* idx, int cnt) {
     }
     if (total > kColScaleWgs) return false;
     for (int k = 0; k < cnt; ++k)
-        if (!column_scales_folded(plan_columns(items[idx[k]].sh.rows, items[idx[k]].sh.cols).n_strips, total, items[idx[k]].scope != 1)) return false;
+        if (!column_scales_folded(plan_columns(items[idx[k]].sh.rows, items[idx[k]].sh.cols).n_strips, total, proves_columns(items[idx[k]]) && items[idx[k]].scope != 1)) return false;
     return true;
 }
 hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int cnt, int crit, const uint32_t* const* gam_of,
@@ -1617,7 +1619,7 @@ hipError_t launch_channel_col_items(const BatchItem* items, const int* idx, int 
             t.col_scale5 = reinterpret_cast<float*>(w + pl.off_scale5);
             t.col_amin = reinterpret_cast<uint16_t*>(w + pl.off_amin);
             t.col_proven = reinterpret_cast<uint8_t*>(w + pl.off_proven);
-            t.prove = (crit == kCritEq2 && it.o.bf16 && !it.o.fake && !it.three && it.th > 0.0f && it.th < 0.9f) ? 1 : 0;
+            t.prove = (crit == kCritEq2 && proves_columns(it)) ? 1 : 0;
             t.flush_need = (uint32_t)flush_need_of(it.th, it.sh.rows);
             t.tensor_need = it.scope == 1 ? flush_need_of(it.th, it.sh.rows * it.sh.cols) : 0ull;
             t.wg = reinterpret_cast<uint32_t*>(w + pl.off_wg);

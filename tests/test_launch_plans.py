@@ -78,7 +78,10 @@ static bool passes_follow() {
         auto then = [&](size_t k, const char* part) { return i + k < log_.size() && is(log_[i + k], part); };
         if (is(log_[i], "k_tensor_stream_clear") && !(then(1, "15k_tensor_streamI") && then(2, "k_tensor_finish_group"))) return false;
         if (is(log_[i], "14k_stream_clear") && !then(1, "k_team_streamI")) return false;
-        if (is(log_[i], "k_pair_clear") && !(then(1, "k_pair_firstI") && then(2, "k_pair_secondI"))) return false;
+        if (is(log_[i], "k_pair_clear") && !then(1, "k_pair_firstI")) return false;
+        if (is(log_[i], "k_pair_firstI") && !then(1, "k_pair_secondI")) return false;
+        // (columns that share a launch with rows form their scales in it)
+        if (is(log_[i], "k_pair_secondI") && !(i && (is(log_[i - 1], "k_pair_firstI") || is(log_[i - 1], "k_col_groupI")))) return false;
     }
     return true;
 }
@@ -120,6 +123,19 @@ static bool many_blocks() {
         }
     return true;
 }
+// Tall columns whose scales take a launch of their own stay apart from rows, whether or not columns are proven one by one.
+static bool tall_columns() {
+    const int R = MOR_GRAN_CHANNEL_ROW, C = MOR_GRAN_CHANNEL_COL;
+    for (int scaling : {MOR_SCALE_FP32_AMAX, MOR_SCALE_GAM})
+        for (int scope : {MOR_SCOPE_PARTITION, MOR_SCOPE_TENSOR})
+            for (int fake = 0; fake < 2; ++fake)
+                for (int64_t cols = 128; cols <= 256; cols += 128) {
+                    if (run({{C, 65536, cols, 0, false, scaling, scope, fake != 0}, {R, 128, 4096, 0, false, scaling, scope, fake != 0}}) != MOR_OK || !passes_follow()) return false;
+                    const int wgs = 4 * (int)cols, limit = fake || scope == MOR_SCOPE_TENSOR ? 512 : 1024;
+                    if (count("k_pair_secondI") != (wgs <= limit ? 1 : 0) || count("k_col_scales") != (wgs <= limit ? 0 : 1)) return false;
+                }
+    return true;
+}
 // Random mixes of what a batch takes.
 static bool mixes() {
     uint64_t state = 1;
@@ -148,7 +164,7 @@ int main(int, char** argv) {
     if (!lib) { fprintf(stderr, "%s\n", dlerror()); return 1; }
     ws_bytes = reinterpret_cast<decltype(ws_bytes)>(dlsym(lib, "mor_batch_workspace_bytes"));
     batch = reinterpret_cast<decltype(batch)>(dlsym(lib, "mor_analyze_quantize_batch"));
-    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"statistics_fit", statistics_fit}, {"many_blocks", many_blocks}, {"mixes", mixes}};
+    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"statistics_fit", statistics_fit}, {"many_blocks", many_blocks}, {"tall_columns", tall_columns}, {"mixes", mixes}};
     printf("%d\n", checks.at(argv[2])() ? 1 : 0);
     return 0;
 }
@@ -168,6 +184,6 @@ def driver(tmp_path_factory):
     return lambda check: subprocess.run([str(exe), build.LIB, check], check=True, capture_output=True, text=True, timeout=120).stdout.strip()
 
 
-@pytest.mark.parametrize("check", ["padded_with_blocks", "statistics_fit", "many_blocks", "mixes"])
+@pytest.mark.parametrize("check", ["padded_with_blocks", "statistics_fit", "many_blocks", "tall_columns", "mixes"])
 def test_plan(driver, check):
     assert driver(check) == "1"
