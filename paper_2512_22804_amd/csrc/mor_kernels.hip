@@ -1360,7 +1360,7 @@ __device__ __forceinline__ void tensor_stream_count(const TensorOp& t, int tile,
     if (t.flush_need != 0ull) flushes += certain_flushes<CH>(v, a | (a << 16));
 }
 struct TensorTold {
-    const uint32_t* copy;
+    uint32_t* words;
     int polls;
 };
 // STRIDED: operands with padded leading dimensions (see RowMap).  STREAM: pass A shares the launch, a tile per workgroup.
@@ -1368,7 +1368,8 @@ template <int CRIT, bool FAKE, bool STRIDED, bool STREAM>
 __device__ __forceinline__ void tensor_quant_body(const TensorOp& t, int b, const TensorTold& told_by) {
     constexpr int CH = kTensorChunksPerThread, kTile = 256 * CH;
     uint32_t told = 0u;
-    if constexpr (STREAM) told = agent_load(told_by.copy);      // (before the tile's loads, so that it is there before them)
+    const uint32_t* copy = STREAM ? stream_copy(told_by.words, b) : nullptr;
+    if constexpr (STREAM) told = agent_load(copy);      // (before the tile's loads, so that it is there before them)
     const uint16_t* __restrict__ x = t.x;
     uint8_t* __restrict__ fp8 = t.o.fp8;
     const int64_t n_chunks = t.n_chunks, n_tiles = t.n_tiles, n_slots = t.n_slots;
@@ -1408,9 +1409,9 @@ __device__ __forceinline__ void tensor_quant_body(const TensorOp& t, int b, cons
     bool proven;                                             // then the BF16 fallback is written in this sweep
     uint32_t abits;
     if constexpr (STREAM) {
-        told = stream_told(told_by.copy, told, told_by.polls);
-        if (!told) {
-            told = stream_scan((int)n_tiles, (uint32_t)t.flush_need, [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { tensor_stream_count<STRIDED>(t, k, tid, amax, flushes); });
+        told = stream_told(copy, told, told_by.polls);
+        if (__builtin_expect(told == 0u, 0)) {
+            told = stream_scan(told_by.words, (int)n_tiles, stream_scan_from((uint32_t)b, (int)n_tiles), (uint32_t)t.flush_need, [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { tensor_stream_count<STRIDED>(t, k, tid, amax, flushes); });
             asm volatile("" : "+s"(tl));                     // the tile is loaded again, so that its registers need not be kept meanwhile
             load_tile(bufA, tl);
         }
@@ -1619,7 +1620,7 @@ __global__ __launch_bounds__(256) void k_tensor_stream(GroupTensor g, GroupStats
     const TensorOp& t = g.op[op];
     const int b = wg - (op ? g.slot_end[op - 1] : 0);
     if (b >= (int)t.n_tiles) return;
-    tensor_quant_body<kCritEq2, FAKE, STRIDED, true>(t, b, TensorTold{stream_copy(stream_words(t), b), polls});
+    tensor_quant_body<kCritEq2, FAKE, STRIDED, true>(t, b, TensorTold{stream_words(t), polls});
 }
 // Decision on a per-tensor operand from its sums (se and se5 over n non-zero elements): every thread of the workgroup calls it and gets
 // the mask; with `emit`, thread 0 writes the outputs and the statistics.

@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256) void k_team_stream(StreamTeam g) {
     if (unit >= g.units[op]) return;
     const ProveOp& f = g.first.op[op];
     const StreamUnit su{stream_copy(f.amax_part, unit), g.polls};
-    auto scan = [&] { return stream_scan(stream_tiles(f), g.flush_need[op], [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { stream_count(f, k, tid, amax, flushes); }); };
+    auto scan = [&] { return stream_scan(f.amax_part, stream_tiles(f), stream_scan_from((uint32_t)unit, stream_tiles(f)), g.flush_need[op], [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { stream_count(f, k, tid, amax, flushes); }); };
     if (TEAM == kTeamWaveRow && g.team.op[op].cols > kWaveRowCols) team_block<kTeamWgRow, kCritEq2, FAKE, false, kTeamStream>(g.team.op[op], unit, sh, su, scan);
     else team_block<TEAM, kCritEq2, FAKE, false, kTeamStream>(g.team.op[op], unit, sh, su, scan);
 }
@@ -1003,7 +1003,7 @@ __global__ __launch_bounds__(256) void k_pair_first(PairFirst g, PairCols c) {
 }
 // GAM: the first launch has told the rows' figures.
 template <bool FAKE, bool EDGE, bool GAM>
-__global__ __launch_bounds__(256, 4) void k_pair_second(PairTeam t, PairFirst g, PairCols c, int col_wgs) {
+__global__ __launch_bounds__(256, 4) void k_pair_second(PairTeam t, PairCols c, int col_wgs) {
     __shared__ ColShared csh;
     __shared__ TeamShared sh;
     const int64_t wg = (int64_t)blockIdx.x - col_wgs;
@@ -1012,10 +1012,9 @@ __global__ __launch_bounds__(256, 4) void k_pair_second(PairTeam t, PairFirst g,
     const int op = group_find(t.unit_end, t.n, wg);
     const int64_t unit = wg - (op ? t.unit_end[op - 1] : 0);
     if (unit >= t.units[op]) return;
-    constexpr int kFrom = GAM ? kTeamStream : kTeamAlone;
-    const ProveOp& f = g.first.op[op];
-    const StreamUnit su{GAM ? stream_copy(t.words[op], unit) : nullptr, g.polls};
-    auto scan = [&] { return stream_scan(stream_tiles(f), g.flush_need[op], [&](int k, int tid, uint32_t& amax, uint32_t& flushes) { stream_count(f, k, tid, amax, flushes); }); };
+    constexpr int kFrom = GAM ? kTeamTold : kTeamAlone;
+    const StreamUnit su{GAM ? stream_copy(t.words[op], unit) : nullptr, 0};
+    auto scan = [] { return 0u; };
     if (t.op[op].cols > kWaveRowCols) team_block<kTeamWgRow, kCritEq2, FAKE, false, kFrom>(t.op[op], unit, sh, su, scan);
     else team_block<kTeamWaveRow, kCritEq2, FAKE, false, kFrom>(t.op[op], unit, sh, su, scan);
 }
@@ -1513,8 +1512,8 @@ template <bool FAKE, bool EDGE>
 void launch_pair_second(const PairLaunch& p, const PairCols& c, hipStream_t st) {
     const int col_wgs = (int)((c.unit_end[c.n - 1] + 7) / 8 * 8);
     const dim3 grid((unsigned)(col_wgs + p.wgs));
-    if (p.gam) k_pair_second<FAKE, EDGE, true><<<grid, dim3(256), 0, st>>>(p.team, p.first, c, col_wgs);
-    else k_pair_second<FAKE, EDGE, false><<<grid, dim3(256), 0, st>>>(p.team, p.first, c, col_wgs);
+    if (p.gam) k_pair_second<FAKE, EDGE, true><<<grid, dim3(256), 0, st>>>(p.team, c, col_wgs);
+    else k_pair_second<FAKE, EDGE, false><<<grid, dim3(256), 0, st>>>(p.team, c, col_wgs);
 }
 }  // namespace
 bool pair_takes_row(const BatchItem& it) {

@@ -3,8 +3,9 @@
 // The launch walks over the operands' tiles twice at once: the first pass (amax, elements certain to flush) leads, the blocks follow at a
 // distance of the largest operand and some more, so that what they read again lies in the Infinity Cache, and reads and writes are mixed
 // evenly all the way.  A workgroup of the first pass leaves its figures in a word of its own; one workgroup behind an operand's last tile
-// collects them and tells the blocks' workgroups.  Workgroups are dispatched in order, so what one waits for has always started before;
-// still no wait is without end: who is not told in time goes through the operand's tiles itself.
+// collects them and tells the blocks' workgroups.  Workgroups are dispatched in order, so what one waits for has as a rule started before; but
+// the XCDs start their shares each by itself, and one that other work holds up can lag behind those that wait already.  So no wait is
+// without end: who is not told in time takes the figures together itself, counting the tiles that are missing (see stream_scan).
 // Against one launch per pass over parts of 256 MB: a boundary between launches costs some 5 us (the last workgroups of one, the first
 // loads of the next), and a pass that only reads leaves the writes to the other.  Bare passes over 960 MB, 2 bytes read, then 2 read and
 // 2 written per element: 448 us in parts, 417 with one part's first pass beside the other's second, of 2 + 3 written 518 and 492.
@@ -69,6 +70,7 @@ inline bool make_spread(Spread& s, uint32_t n, uint32_t all) {
 }
 
 // `Tile`: count(tile, lane of the workgroup, amax, flushes) adds a lane's share of a tile to its figures, `amax` a pattern.
+__device__ __forceinline__ uint32_t stream_tile_word(uint32_t amax, uint32_t flushes) { return kThere | (flushes << kFlushShift) | amax; }
 template <class Tile>
 __device__ __forceinline__ void stream_first(uint32_t* words, int tile, uint32_t* sh8, Tile count) {
     uint32_t amax = 0u, flushes = 0u;
@@ -78,18 +80,51 @@ __device__ __forceinline__ void stream_first(uint32_t* words, int tile, uint32_t
     if ((threadIdx.x & 63) == 0) { sh8[threadIdx.x >> 6] = amax; sh8[4 + (threadIdx.x >> 6)] = flushes; }
     __syncthreads();
     if (threadIdx.x == 0)
-        agent_store(words + kStreamTiles + tile, kThere | (((sh8[4] + sh8[5]) + (sh8[6] + sh8[7])) << kFlushShift) | max(max(sh8[0], sh8[1]), max(sh8[2], sh8[3])));
+        agent_store(words + kStreamTiles + tile, stream_tile_word(max(max(sh8[0], sh8[1]), max(sh8[2], sh8[3])), (sh8[4] + sh8[5]) + (sh8[6] + sh8[7])));
 }
 __device__ __forceinline__ uint32_t stream_figures(uint32_t amax, uint32_t flushes, uint32_t flush_need) {
     return kThere | (flush_need != 0u && flushes >= flush_need ? kToldProven : 0u) | amax;
 }
-// The operand's figures by a wave of its own (an operand has less than 2^32 elements).
+// Where wave w of a unit's workgroup begins its scan: the waves of neighbouring units far from each other.
+__device__ __forceinline__ uint32_t stream_scan_from(uint32_t unit, int tiles) {
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(unit * 4u + (threadIdx.x >> 6)));
+    return __umulhi(wave * 0x9E3779B1u, (uint32_t)tiles);
+}
+// The operand's figures by a wave of its own, beginning at tile `from` (an operand has less than 2^32 elements).  A tile whose word is there is
+// not read; one that is not is counted and its word left, the same that its workgroup leaves, and the figures are told.  So however many
+// waves are here, together they read what of the operand has not been read yet, and little of it twice; each of them, its words.
+// us per call as it is / where no wave waits at all: per-tensor 8192 x 4096 42.5 / 260, 8192 x 14336 with padded rows 110 / 335, two of these
+// dense 189 / 502, 128 x 128 blocks of 8192 x 8192 69 / 327, twelve of 8192 x 4096 by rows 286 / 1116.  (Each wave going through all tiles, as
+// it was, would read 64 MB for each of 8192 waves in the first.)
 template <class Tile>
-__device__ __forceinline__ uint32_t stream_scan(int tiles, uint32_t flush_need, Tile count) {
+__device__ __forceinline__ uint32_t stream_scan(uint32_t* words, int tiles, uint32_t from, uint32_t flush_need, Tile count) {
+    const int lane = (int)(threadIdx.x & 63u), chunks = (tiles + 63) >> 6, turn = (int)(from & 63u);
     uint32_t amax = 0u, flushes = 0u;
+    int c = (int)(from >> 6);                              // chunks of 64 words, one per lane
 #pragma clang loop unroll(disable)
-    for (int part = 0; part < 4 * tiles; ++part) count(part >> 2, (part & 3) * 64 + (int)(threadIdx.x & 63), amax, flushes);
-    return stream_figures(wave_allmax_u32(amax), wave_allsum_u32(flushes), flush_need);
+    for (int k = 0; k < chunks; ++k) {
+        const int i = c * 64 + lane;
+        uint32_t v = i < tiles ? 0u : kThere;
+#pragma clang loop unroll(disable)
+        for (;;) {                                         // a turn adds a word at least
+            if (!(v & kThere)) v = agent_load(words + kStreamTiles + i);
+            const unsigned long long missing = __ballot(!(v & kThere));
+            if (missing == 0ull) break;
+            const unsigned long long turned = turn ? (missing >> turn) | (missing << (64 - turn)) : missing;
+            const int at = (__builtin_ctzll(turned) + turn) & 63;
+            uint32_t a = 0u, f = 0u;
+#pragma clang loop unroll(disable)
+            for (int part = 0; part < 4; ++part) count(c * 64 + at, part * 64 + lane, a, f);
+            const uint32_t word = stream_tile_word(wave_allmax_u32(a), wave_allsum_u32(f));
+            if (lane == at) { v = word; agent_store(words + kStreamTiles + i, word); }
+        }
+        amax = max(amax, v & kAmaxBits);                   // (lanes beyond the last tile: zeros)
+        flushes += (v & ~kThere) >> kFlushShift;
+        if (++c == chunks) c = 0;
+    }
+    const uint32_t figures = stream_figures(wave_allmax_u32(amax), wave_allsum_u32(flushes), flush_need);
+    if (lane < kToldCopies) agent_store(words + lane * kToldLine, figures);
+    return figures;
 }
 // By the workgroup that collects: from the tiles' words, which it tells; the same value in all lanes.
 template <class Tile>
@@ -115,8 +150,8 @@ __device__ __forceinline__ uint32_t stream_collect(uint32_t* words, int tiles, u
     flushes = wave_allsum_u32(flushes);
     if ((tid & 63) == 0) { sh8[tid >> 6] = amax; sh8[4 + (tid >> 6)] = flushes; }
     const bool every = __syncthreads_and(all ? 1 : 0) != 0;
-    uint32_t figures = stream_figures(max(max(sh8[0], sh8[1]), max(sh8[2], sh8[3])), (sh8[4] + sh8[5]) + (sh8[6] + sh8[7]), flush_need);
-    if (!every) figures = stream_scan(tiles, flush_need, count);
+    if (!every) return stream_scan(words, tiles, stream_scan_from(0u, tiles), flush_need, count);
+    const uint32_t figures = stream_figures(max(max(sh8[0], sh8[1]), max(sh8[2], sh8[3])), (sh8[4] + sh8[5]) + (sh8[6] + sh8[7]), flush_need);
     if (tid < kToldCopies) agent_store(words + tid * kToldLine, figures);
     return figures;
 }

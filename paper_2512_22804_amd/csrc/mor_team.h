@@ -132,7 +132,8 @@ struct StreamUnit {
     int polls;
 };
 enum { kTeamAlone = 0,         // the operand's figures come from earlier launches
-       kTeamStream = 1 };      // from the first pass in this launch; `scan` finds them out from the operand itself
+       kTeamStream = 1,        // from the first pass in this launch; `scan` finds them out from the operand itself
+       kTeamTold = 2 };        // from the first pass in an earlier launch
 
 // EDGE = false: the operand has no partial blocks (block teams), or its rows are a whole number of the
 // team's sweeps (row teams), so chunk validity is uniform over the team and costs no per-lane predicates.
@@ -197,7 +198,7 @@ __device__ __forceinline__ void team_block(const TeamOp& t, int64_t unit, TeamSh
     const BufRsrc rx = make_buf(t.x + r0 * t.ld + c0);
     const uint32_t xoff = (uint32_t)((trow * t.ld + tcol) * 2), xstep = (uint32_t)(src_step * 2);
     uint32_t told = 0u;
-    if constexpr (FROM == kTeamStream) told = agent_load(su.told);      // (before the block's loads, so that it is there before them)
+    if constexpr (PIPE) told = agent_load(su.told);      // (before the block's loads, so that it is there before them)
     u32x4 raw[NCH];
     auto load_block = [&](uint32_t off) {
 #pragma unroll
@@ -207,10 +208,11 @@ __device__ __forceinline__ void team_block(const TeamOp& t, int64_t unit, TeamSh
         }
     };
     load_block(xoff);
-    if constexpr (PIPE) {
+    if constexpr (FROM == kTeamTold) told = (uint32_t)__builtin_amdgcn_readfirstlane((int)told);
+    if constexpr (FROM == kTeamStream) {
         // The first pass ends well before the launch comes to the operand's blocks, so this is a look and no wait.
         told = stream_told(su.told, told, su.polls);
-        if (!told) {
+        if (__builtin_expect(told == 0u, 0)) {
             told = scan();
             uint32_t off = xoff;
             asm volatile("" : "+v"(off));                  // the block is loaded again, so that its registers need not be kept meanwhile

@@ -181,6 +181,36 @@ def test_per_tensor_operands(fake, lean, pad):
         assert int(out.mask[0]) == int(want.mask[0])
 
 
+@pytest.mark.parametrize("gran, rows, cols, pad", [("tensor", 8192, 4096, 0), ("tensor", 8192, 8192, 8), ("block128", 8192, 8192, 0)])
+def test_waves_that_are_not_told_share_the_operand(gran, rows, cols, pad):
+    """Where no wave waits, all of them go for the operand's figures themselves, and together read it about once: 0.26 to 0.33 ms for these
+    calls.  Each on its own, 8192 waves would read 64 MB in the smallest: more than 25 ms at 20 TB/s."""
+    from paper_2512_22804_amd import binding as B
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(5)
+    x = torch.randn((rows, cols + pad), generator=gen, device=dev)
+    x = (x * torch.where(torch.rand(x.shape, generator=gen, device=dev) < 0.1, 1e-8, 1.0)).to(torch.bfloat16)[:, :cols]
+    scaling = "fp32_amax" if gran == "tensor" else "gam"
+    entries = []
+    for polls in (None, 0):
+        p = B.make_params(rows, cols, gran, "partition" if gran == "tensor" else "tensor", ld=cols + pad, scaling=scaling)
+        out = B.alloc_outputs(p, dev, bf16_fill=0x1234)
+        out.workspace = None
+        out.fp8.view(torch.uint8).fill_(0x5A)
+        entries.append((p, x, out, None, None))
+    _run(B, entries[:1])
+    for _ in range(3):
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        print(f"[stream] untold {gran} {rows}x{cols}", flush=True)
+        start.record()
+        _run(B, entries[1:], 0)
+        stop.record()
+        stop.synchronize()
+        assert start.elapsed_time(stop) < 5.0
+        _same(entries[:1], entries[1:], (gran, rows, cols))
+
+
 # (granularity, rows, cols, row padding, scaling): per-tensor operands first, then what goes along; edges of the 1 x 128 operand's units of 32 blocks and
 # of the number that its waves take (one up to 6144 units, then two), of its two forms, and of groups of eight 128 x 128 blocks
 ALONG = [
