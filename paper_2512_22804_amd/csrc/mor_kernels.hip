@@ -2008,9 +2008,17 @@ __global__ __launch_bounds__(T, 4) void k_tensor_quant_one(OneTensor g, int poll
     }
 }
 // Workgroups from `stats_first` on combine the riders' partial statistics records (one workgroup per operand).
-// (`direct`: operands of the table, one bit each, whose statistics are still to be taken, by one workgroup; then the 1 x 128 operand of `solo`.)
 template <int CRIT, bool STRIDED>
-__global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, GroupStats riders, int stats_first, uint32_t direct, SoloStats solo) {
+__global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, GroupStats riders, int stats_first) {
+    if ((int)blockIdx.x >= stats_first) { stats_final_body(riders, (int)blockIdx.x - stats_first); return; }
+    tensor_finish_body<CRIT, STRIDED>(g, (int)blockIdx.x);
+}
+// The same where operands went along (see TensorFill).  `direct`: operands of the table, one bit each, whose statistics are still to be taken,
+// by one workgroup; then the 1 x 128 operand of `solo`.  A kernel of its own, since the additional branches' registers and LDS hold up the
+// other calls' some 2000 workgroups: per-tensor operands of 744 x 280 and 243 x 456 15.5 us per call without them, 16.4 with, three of 1024 x 1024
+// 16.1, 18.0, eight of 512 x 512 16.5, 18.5.
+template <bool STRIDED>
+__global__ __launch_bounds__(256) void k_tensor_finish_fill(GroupTensor g, GroupStats riders, int stats_first, uint32_t direct, SoloStats solo) {
     if ((int)blockIdx.x >= stats_first) {
         const int op = (int)blockIdx.x - stats_first;
         if (op >= riders.n) solo_final_body<256>(solo);
@@ -2018,7 +2026,7 @@ __global__ __launch_bounds__(256) void k_tensor_finish_group(GroupTensor g, Grou
         else stats_final_body(riders, op);
         return;
     }
-    tensor_finish_body<CRIT, STRIDED>(g, (int)blockIdx.x);
+    tensor_finish_body<kCritEq2, STRIDED>(g, (int)blockIdx.x);
 }
 // Group loop of Algorithm 1 for sub-tensor operands: the operand's amax (partials of pass A) gives the
 // group mantissas for E4M3 and E5M2, which the block kernels read; also written to the caller's output.
@@ -2866,7 +2874,8 @@ hipError_t launch_tensor_stream(GroupTensor& g, const GroupStats& riders, int ri
         else k_tensor_stream<false, false, kFillFlat><<<grid, dim3(256), kResidency5, st>>>(g, riders, order, ride_partial, polls, fo);
     }
     ProfScope ps(prof, kKernFallbackCopy, st);
-    k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end, fill.direct, fill.solo);
+    if (fill.form != kFillNone) k_tensor_finish_fill<STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end, fill.direct, fill.solo);
+    else k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
     return hipGetLastError();
 }
 template <bool STRIDED>
@@ -2891,8 +2900,8 @@ void launch_tensor_passes(const GroupTensor& g, const TensorPart* parts, int n_p
     }
     {
         ProfScope ps(prof, kKernFallbackCopy, st);
-        if (crit == kCritEq3) k_tensor_finish_group<kCritEq3, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end, 0u, SoloStats{});
-        else k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end, 0u, SoloStats{});
+        if (crit == kCritEq3) k_tensor_finish_group<kCritEq3, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
+        else k_tensor_finish_group<kCritEq2, STRIDED><<<dim3(c_end + ride_final), dim3(256), 0, st>>>(g, riders, c_end);
     }
 }
 // A small operand that is alone: two launches from a table of one operand.  Such a call is a chain of launches, so what counts is their

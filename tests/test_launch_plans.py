@@ -31,7 +31,7 @@ int __hipPushCallConfiguration(Dim3 grid, Dim3 block, size_t, void*) { call_grid
 int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* lds, void** stream) { *grid = call_grid; *block = call_block; *lds = 0; *stream = nullptr; return 0; }
 int hipLaunchKernel(const void* f, Dim3, Dim3, void** args, size_t, void*) {
     const std::string& n = names()[f];
-    const bool table = n.find("15k_tensor_streamI") != std::string::npos || n.find("k_tensor_finish_group") != std::string::npos;
+    const bool table = n.find("15k_tensor_streamI") != std::string::npos || n.find("k_tensor_finish_") != std::string::npos;
     log_.push_back({n, table ? *static_cast<const int*>(args[1]) : 0});
     return 0;
 }
@@ -76,7 +76,7 @@ static int count(const char* part) { int n = 0; for (const Launch& l : log_) n +
 static bool passes_follow() {
     for (size_t i = 0; i < log_.size(); ++i) {
         auto then = [&](size_t k, const char* part) { return i + k < log_.size() && is(log_[i + k], part); };
-        if (is(log_[i], "k_tensor_stream_clear") && !(then(1, "15k_tensor_streamI") && then(2, "k_tensor_finish_group"))) return false;
+        if (is(log_[i], "k_tensor_stream_clear") && !(then(1, "15k_tensor_streamI") && then(2, "k_tensor_finish_"))) return false;
         if (is(log_[i], "14k_stream_clear") && !then(1, "k_team_streamI")) return false;
         if (is(log_[i], "k_pair_clear") && !then(1, "k_pair_firstI")) return false;
         if (is(log_[i], "k_pair_firstI") && !then(1, "k_pair_secondI")) return false;
@@ -94,7 +94,16 @@ static bool padded_with_blocks() {
             std::vector<Op> ops{{T, 2048, 2048, 2048, stats != 0}, {B128, 1024, 1024, 0, stats != 0}};
             for (int k = 0; k < subs; ++k) ops.push_back({S, 1024, 1024, 0, stats != 0});
             if (run(ops) != MOR_OK || !passes_follow()) return false;
-            if (count("15k_tensor_streamI") != 1 || count("k_tensor_finish_group") != 1) return false;
+            if (count("15k_tensor_streamI") != 1 || count("k_tensor_finish_fillI") != 1 || count("k_tensor_finish_groupI") != 0) return false;
+        }
+    return true;
+}
+// The finish pass of operands that nothing goes along with is the one without the others' statistics.
+static bool nothing_along() {
+    for (int64_t rows = 256; rows <= 8192; rows *= 2)
+        for (int64_t pad = 0; pad <= 8; pad += 8) {
+            if (run({{T, rows, 4096, pad, true}, {T, rows, 2048, pad, true}, {B64, 256, 256, 0, true}}) != MOR_OK || !passes_follow()) return false;
+            if (count("k_tensor_finish_fillI") != 0 || count("k_tensor_finish_groupI") != 1) return false;
         }
     return true;
 }
@@ -164,7 +173,7 @@ int main(int, char** argv) {
     if (!lib) { fprintf(stderr, "%s\n", dlerror()); return 1; }
     ws_bytes = reinterpret_cast<decltype(ws_bytes)>(dlsym(lib, "mor_batch_workspace_bytes"));
     batch = reinterpret_cast<decltype(batch)>(dlsym(lib, "mor_analyze_quantize_batch"));
-    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"statistics_fit", statistics_fit}, {"many_blocks", many_blocks}, {"tall_columns", tall_columns}, {"mixes", mixes}};
+    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"nothing_along", nothing_along}, {"statistics_fit", statistics_fit}, {"many_blocks", many_blocks}, {"tall_columns", tall_columns}, {"mixes", mixes}};
     printf("%d\n", checks.at(argv[2])() ? 1 : 0);
     return 0;
 }
@@ -184,6 +193,6 @@ def driver(tmp_path_factory):
     return lambda check: subprocess.run([str(exe), build.LIB, check], check=True, capture_output=True, text=True, timeout=120).stdout.strip()
 
 
-@pytest.mark.parametrize("check", ["padded_with_blocks", "statistics_fit", "many_blocks", "tall_columns", "mixes"])
+@pytest.mark.parametrize("check", ["padded_with_blocks", "nothing_along", "statistics_fit", "many_blocks", "tall_columns", "mixes"])
 def test_plan(driver, check):
     assert driver(check) == "1"
