@@ -2993,8 +2993,8 @@ void BatchRun::plan_fill() {
             tiles += own;
             pass_groups += 2 * ((own + 7) / 8) + 1;
         }
-        bool counts = false;                               // the call counts statistics
-        for (int i = 0; i < n; ++i) counts |= items[i].stats != nullptr;
+        bool counts = false;                               // the call counts statistics (those of a per-tensor operand come with its decision)
+        for (int i = 0; i < n; ++i) counts |= items[i].stats != nullptr && items[i].gran != kGranTensor;
         if (cnt == 0 || cnt > kMaxGroupTensor || !all || (cnt == 1 && !counts && tiles < kFillAloneTiles)) continue;
         int others = 0, counted = 0;                       // statistics of operands that do not go along, of blocks that do
         int subs = 0, subs_counted = 0;

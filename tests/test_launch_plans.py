@@ -107,6 +107,15 @@ static bool nothing_along() {
         }
     return true;
 }
+// A small per-tensor operand alone keeps its own two launches beside a 1 x 128 operand, unless there are statistics of that to take along.
+static bool small_beside_sub() {
+    for (int64_t pad = 0; pad <= 8; pad += 8)
+        for (int counted = 0; counted < 4; ++counted) {
+            if (run({{T, 465, 3040, pad, (counted & 1) != 0}, {S, 106, 1024, pad, (counted & 2) != 0}}) != MOR_OK || !passes_follow()) return false;
+            if (count("15k_tensor_streamI") != counted / 2 || count("k_tensor_quant_oneI") != 1 - counted / 2) return false;
+        }
+    return true;
+}
 // Statistics that the finish pass takes: at most twelve operands' in its table, also where a dense 1 x 128 operand cannot share the launch.
 static bool statistics_fit() {
     for (int64_t pad = 0; pad <= 2048; pad += 2048)
@@ -173,7 +182,7 @@ int main(int, char** argv) {
     if (!lib) { fprintf(stderr, "%s\n", dlerror()); return 1; }
     ws_bytes = reinterpret_cast<decltype(ws_bytes)>(dlsym(lib, "mor_batch_workspace_bytes"));
     batch = reinterpret_cast<decltype(batch)>(dlsym(lib, "mor_analyze_quantize_batch"));
-    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"nothing_along", nothing_along}, {"statistics_fit", statistics_fit}, {"many_blocks", many_blocks}, {"tall_columns", tall_columns}, {"mixes", mixes}};
+    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"nothing_along", nothing_along}, {"small_beside_sub", small_beside_sub}, {"statistics_fit", statistics_fit}, {"many_blocks", many_blocks}, {"tall_columns", tall_columns}, {"mixes", mixes}};
     printf("%d\n", checks.at(argv[2])() ? 1 : 0);
     return 0;
 }
@@ -193,6 +202,6 @@ def driver(tmp_path_factory):
     return lambda check: subprocess.run([str(exe), build.LIB, check], check=True, capture_output=True, text=True, timeout=120).stdout.strip()
 
 
-@pytest.mark.parametrize("check", ["padded_with_blocks", "nothing_along", "statistics_fit", "many_blocks", "tall_columns", "mixes"])
+@pytest.mark.parametrize("check", ["padded_with_blocks", "nothing_along", "small_beside_sub", "statistics_fit", "many_blocks", "tall_columns", "mixes"])
 def test_plan(driver, check):
     assert driver(check) == "1"
