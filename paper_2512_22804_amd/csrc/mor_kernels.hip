@@ -2999,6 +2999,7 @@ void BatchRun::plan_fill() {
         int others = 0, counted = 0;                       // statistics of operands that do not go along, of blocks that do
         int subs = 0, subs_counted = 0;
         int64_t team_wgs = 0;
+        bool launch_stays = false;                         // of 128 x 128 blocks, for other operands
         // Blocks beyond what the launch's order can be divided into (some 370 000, 12 GB) keep a launch of their own.
         auto spread = [&](int64_t wgs) { return spread_fits((uint64_t)(wgs + 7) / 8, (uint64_t)(pass_groups + (wgs + 7) / 8)); };
         for (int i = 0; i < n; ++i) {
@@ -3016,11 +3017,19 @@ void BatchRun::plan_fill() {
                 fill_team[n_fill_team++] = i;
                 team_wgs += item_parts(it);
                 counted += it.stats != nullptr;
-            } else others += it.stats != nullptr;
+            } else {
+                others += it.stats != nullptr;
+                launch_stays |= own == kRouteTeam && wave_of[i] == 0 && it.crit == kCritEq2 && !it.o.fake && team_kind_of(it) == kTeamWg128 && !team_needs_edge(it, kTeamWg128);
+            }
         }
         if (subs > 1) fill_sub = -1;
         if (fill_sub < 0) others += subs_counted;          // (the one that goes along leaves records of its own)
-        if ((fill_sub < 0 && n_fill_team == 0) || others + counted > kMaxGroupStats) { fill_sub = -1; n_fill_team = 0; continue; }
+        // Blocks alone save nothing where their launch stays for others: then the passes have to pay by themselves, or be of several operands beside many
+        // blocks.  us per call apart / together, beside blocks of 2304 x 384 under GAM scales: one of 3681 x 1336 with blocks of 2048 x 4096 26.7 / 31.1,
+        // 8192 x 4096 39.5 / 41.6; that and 2059 x 1760 with 2048 x 4096 32.0 / 33.2, 4096 x 4096 37.7 / 36.8, 8192 x 4096 45.2 / 44.0 (where no launch
+        // stays 1408 x 1280 23.8 / 20.4).
+        const bool pays = fill_sub >= 0 || !launch_stays || (cnt > 1 && team_wgs >= 1024) || tensor_stream_pays(cnt, tiles, strided != 0, others > 0);
+        if ((fill_sub < 0 && n_fill_team == 0) || !pays || others + counted > kMaxGroupStats) { fill_sub = -1; n_fill_team = 0; continue; }
         fill_strided = strided;
     }
     if (fill_strided < 0) return;
