@@ -2971,11 +2971,15 @@ bool tensor_streams(const BatchItem& it) {
     if ((it.sh.rows * (it.sh.cols / 8) + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock > kTensorStreamMaxTiles) return false;
     return item_is_flat(it) || tensor_rows_fit(it.sh, it.o);
 }
-// A small per-tensor operand alone and without statistics has kernels of its own, which a 1 x 128 operand beside it does not outweigh: us per call
-// apart / together, slices of 64 x 1024 12.7 / 14.2, 512 x 2048 12.8 / 15.2, 1000 x 4096 18.0 / 17.2, 2500 x 5000 37.2 / 33.0; with statistics 18.5 / 14.5, 19.1 / 15.3,
-// 22.8 / 16.8, 37.9 / 32.7, 4099 x 5000 48.2 / 47.8, 8192 x 4096 66.2 / 62.3.  Layers with statistics: 8192 tokens x hidden 4096 382.9 / 373.6 (lean, without 347.2 /
-// 328.9), 4096 x 2048 107.5 / 102.1, 512 x 1024 37.1 / 33.6, 64 x 256 21.3 / 16.1.
-constexpr int64_t kFillAloneTiles = 128;
+// A small per-tensor operand alone has kernels of its own, whose two launches a 1 x 128 operand or blocks beside it do not outweigh unless they bring
+// statistics.  us per call apart / together, without: slices of 64 x 1024 12.7 / 14.2, 512 x 2048 12.8 / 15.2; 2000 x 4096 kept in E4M3 with a 1 x 128 operand
+// of 1000 x 4096 19.1 / 20.3, falling back without a proof 22.6 / 25.1, with one 20.8 / 19.8, in padded rows beside 64 x 4096 18.3 / 19.9, 20.4 / 26.1, 18.7 /
+// 18.3; beyond (see one_max_chunks) 4096 x 4096 27.1 / 24.5, 2500 x 5000 37.2 / 33.0.  With statistics 18.5 / 14.5, 19.1 / 15.3,
+// 1000 x 4096 22.8 / 16.8, 2500 x 5000 37.9 / 32.7, 4099 x 5000 48.2 / 47.8, 8192 x 4096 66.2 / 62.3.  Layers with statistics: 8192 tokens x hidden 4096 382.9 / 373.6 (lean,
+// without 347.2 / 328.9), 4096 x 2048 107.5 / 102.1, 512 x 1024 37.1 / 33.6, 64 x 256 21.3 / 16.1.
+bool takes_two_launches(const BatchItem& it) {
+    return it.sh.rows * (it.sh.cols / 8) <= one_max_chunks(it.crit) && (!item_is_flat(it) || tensor_rows_fit(it.sh, it.o));
+}
 // Which operands go along with the passes of per-tensor ones (see TensorFill): those decided block by block under Eq. 2 with two types, FP8
 // payload and no pre-pass, of which one may have 1 x 128 blocks; with statistics, up to what one workgroup counts of 128 x 128 blocks.
 void BatchRun::plan_fill() {
@@ -2983,11 +2987,12 @@ void BatchRun::plan_fill() {
     for (int strided = 0; strided < 2 && fill_strided < 0; ++strided) {
         int cnt = 0;
         int64_t tiles = 0, pass_groups = 0;                // (groups of eight workgroups, see TensorFill)
-        bool all = true;
+        bool all = true, small = false;                    // (`small`: of the last, where it is alone)
         for (int i = 0; i < n; ++i) {
             const BatchItem& it = items[i];
             if (it.gran != kGranTensor || it.crit != kCritEq2 || it.o.fake || item_is_flat(it) != (strided == 0)) continue;
             all &= tensor_streams(it);
+            small = takes_two_launches(it);
             ++cnt;
             const int64_t own = (it.sh.rows * (it.sh.cols / 8) + kTensorChunksPerBlock - 1) / kTensorChunksPerBlock;
             tiles += own;
@@ -2995,7 +3000,7 @@ void BatchRun::plan_fill() {
         }
         bool counts = false;                               // the call counts statistics (those of a per-tensor operand come with its decision)
         for (int i = 0; i < n; ++i) counts |= items[i].stats != nullptr && items[i].gran != kGranTensor;
-        if (cnt == 0 || cnt > kMaxGroupTensor || !all || (cnt == 1 && !counts && tiles < kFillAloneTiles)) continue;
+        if (cnt == 0 || cnt > kMaxGroupTensor || !all || (cnt == 1 && !counts && small)) continue;
         int others = 0, counted = 0;                       // statistics of operands that do not go along, of blocks that do
         int subs = 0, subs_counted = 0;
         int64_t team_wgs = 0;
@@ -3096,7 +3101,7 @@ void BatchRun::per_tensor_operands(int crit) {
             // (the kernels of the two launches address rows through a RowMap, so a dense operand whose rows are too long for it stays with the
             // dense kernels, which number chunks without it: 1 x 8 388 608 kept in BF16 45.2 us as one of these, without a proof, 17.6 with the dense kernels)
             const bool filled = fill_strided == (strided ? 1 : 0) && crit == kCritEq2 && !fake;
-            const bool one = cnt == 1 && !ride && !filled && it0.sh.rows * (it0.sh.cols / 8) <= one_max_chunks(crit) && (strided || tensor_rows_fit(it0.sh, it0.o));
+            const bool one = cnt == 1 && !ride && !filled && takes_two_launches(it0);
             int64_t all_tiles = 0;
             for (int k = 0; k < cnt; ++k) {
                 const BatchItem& it = items[idx[k]];

@@ -223,9 +223,9 @@ ALONG = [
     [("tensor", 4096, 4096, 0, "fp32_amax"), ("block128", 8192, 8192, 0, "fp32_amax")],
     [("tensor", 512, 2048, 0, "fp32_amax"), ("sub1x128", 64, 2048, 0, "fp32_amax"), ("sub1x128", 65, 2048, 0, "fp32_amax"), ("channel_col", 256, 384, 0, "fp32_amax")],
     # padded rows with blocks alone, and with 1 x 128 operands that keep their own launch: a dense one, two
-    [("tensor", 2048, 2048, 2048, "fp32_amax"), ("block128", 1024, 1024, 0, "fp32_amax"), ("block128", 128, 128, 0, "e8m0")],
+    [("tensor", 4200, 2048, 2048, "fp32_amax"), ("block128", 1024, 1024, 0, "fp32_amax"), ("block128", 128, 128, 0, "e8m0")],
     [("tensor", 1000, 4096, 4096, "gam"), ("tensor", 1100, 1000, 8, "fp32_amax"), ("sub1x128", 256, 1024, 0, "fp32_amax"), ("block128", 1152, 640, 0, "fp32_amax")],
-    [("tensor", 2100, 2048, 8, "fp32_amax"), ("sub1x128", 64, 2048, 0, "fp32_amax"), ("sub1x128", 65, 2056, 0, "fp32_amax"), ("block128", 256, 384, 0, "fp32_amax")],
+    [("tensor", 4200, 2048, 8, "fp32_amax"), ("sub1x128", 64, 2048, 0, "fp32_amax"), ("sub1x128", 65, 2056, 0, "fp32_amax"), ("block128", 256, 384, 0, "fp32_amax")],
     # as many operands with statistics as the finish pass has room for, and one more
     [("tensor", 300, 1000, 8, "fp32_amax"), ("sub1x128", 64, 256, 0, "fp32_amax"), ("block128", 256, 128, 0, "fp32_amax")] + [("block64", 64, 192, 0, "fp32_amax")] * 10,
     [("tensor", 300, 1000, 8, "fp32_amax"), ("sub1x128", 64, 256, 0, "fp32_amax"), ("block128", 256, 128, 0, "fp32_amax")] + [("block64", 64, 192, 0, "fp32_amax")] * 11,

@@ -91,7 +91,7 @@ static const int T = MOR_GRAN_TENSOR, B128 = MOR_GRAN_BLOCK_128x128, S = MOR_GRA
 static bool padded_with_blocks() {
     for (int stats = 0; stats < 2; ++stats)
         for (int subs = 0; subs < 3; ++subs) {
-            std::vector<Op> ops{{T, 2048, 2048, 2048, stats != 0}, {B128, 1024, 1024, 0, stats != 0}};
+            std::vector<Op> ops{{T, 4200, 2048, 2048, stats != 0}, {B128, 1024, 1024, 0, stats != 0}};
             for (int k = 0; k < subs; ++k) ops.push_back({S, 1024, 1024, 0, stats != 0});
             if (run(ops) != MOR_OK || !passes_follow()) return false;
             if (count("15k_tensor_streamI") != 1 || count("k_tensor_finish_fillI") != 1 || count("k_tensor_finish_groupI") != 0) return false;
@@ -107,13 +107,16 @@ static bool nothing_along() {
         }
     return true;
 }
-// A small per-tensor operand alone keeps its own two launches beside a 1 x 128 operand, unless there are statistics of that to take along.
-static bool small_beside_sub() {
+// A small per-tensor operand alone keeps its own two launches beside others, unless there are statistics of those to take along.
+static bool small_alone() {
     for (int64_t pad = 0; pad <= 8; pad += 8)
-        for (int counted = 0; counted < 4; ++counted) {
-            if (run({{T, 465, 3040, pad, (counted & 1) != 0}, {S, 106, 1024, pad, (counted & 2) != 0}}) != MOR_OK || !passes_follow()) return false;
-            if (count("15k_tensor_streamI") != counted / 2 || count("k_tensor_quant_oneI") != 1 - counted / 2) return false;
-        }
+        for (int counted = 0; counted < 4; ++counted)
+            for (int gran : {S, B128})
+                for (int64_t rows : {64, 465, 2048, 2560}) {
+                    if (run({{T, rows, 4096, pad, (counted & 1) != 0}, {gran, 128, 1024, pad, (counted & 2) != 0}}) != MOR_OK || !passes_follow()) return false;
+                    const int want = counted / 2 || rows > 2048 ? 1 : 0;
+                    if (count("15k_tensor_streamI") != want || count("k_tensor_quant_oneI") != 1 - want) return false;
+                }
     return true;
 }
 // Blocks go along with passes of some hundred tiles where that saves their launch, not where it stays for blocks that have a pre-pass.
@@ -191,7 +194,7 @@ int main(int, char** argv) {
     if (!lib) { fprintf(stderr, "%s\n", dlerror()); return 1; }
     ws_bytes = reinterpret_cast<decltype(ws_bytes)>(dlsym(lib, "mor_batch_workspace_bytes"));
     batch = reinterpret_cast<decltype(batch)>(dlsym(lib, "mor_analyze_quantize_batch"));
-    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"nothing_along", nothing_along}, {"small_beside_sub", small_beside_sub}, {"blocks_that_stay", blocks_that_stay}, {"statistics_fit", statistics_fit}, {"many_blocks", many_blocks}, {"tall_columns", tall_columns}, {"mixes", mixes}};
+    const std::map<std::string, bool (*)()> checks{{"padded_with_blocks", padded_with_blocks}, {"nothing_along", nothing_along}, {"small_alone", small_alone}, {"blocks_that_stay", blocks_that_stay}, {"statistics_fit", statistics_fit}, {"many_blocks", many_blocks}, {"tall_columns", tall_columns}, {"mixes", mixes}};
     printf("%d\n", checks.at(argv[2])() ? 1 : 0);
     return 0;
 }
@@ -211,6 +214,6 @@ def driver(tmp_path_factory):
     return lambda check: subprocess.run([str(exe), build.LIB, check], check=True, capture_output=True, text=True, timeout=120).stdout.strip()
 
 
-@pytest.mark.parametrize("check", ["padded_with_blocks", "nothing_along", "small_beside_sub", "blocks_that_stay", "statistics_fit", "many_blocks", "tall_columns", "mixes"])
+@pytest.mark.parametrize("check", ["padded_with_blocks", "nothing_along", "small_alone", "blocks_that_stay", "statistics_fit", "many_blocks", "tall_columns", "mixes"])
 def test_plan(driver, check):
     assert driver(check) == "1"
