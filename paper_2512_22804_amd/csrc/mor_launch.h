@@ -243,8 +243,8 @@ int team_stream_kind(const BatchItem& it);      // operands of one number may sh
 // 123 / 113, 171 / 153; 512 x 1024 42.7 / 41.9, 47.3 / 45.6, 80 / 65; 64 x 256, of which some have ragged blocks and stay launch by launch, 34.2 / 34.8,
 // 30.7 / 35.9).  Fewer have nobody to share the launch with, so it saves a launch and fills the gap between the passes, but at 128 x 128 takes about
 // 2 us more to tell: 4096 x 4096 26.0 / 28.4, 8192 x 4096 40.5 / 40.5, 8192 x 14336 110.6 / 101.8; at 64 x 64 2048 x 4096 24.0 / 23.9, 4096 x 4096 30.7 / 27.3,
-// 8192 x 4096 46.3 / 40.3; by rows 22.5 / 23.3, 26.7 / 26.0, 43.3 / 38.4.  (Two or three of more than 256 MiB together stay in parts, although they
-// would gain too: their sequence of launches, as the profile of a call records it, is relied on.)
+// 8192 x 4096 46.3 / 40.3; by rows 22.5 / 23.3, 26.7 / 26.0, 43.3 / 38.4.  (Two or three of more than 256 MiB together
+// would gain too, but stay in parts: the interface promises no sequence of launches, but tests/test_gpu_launch_counts.py counts these.)
 // Where other operands of the call have a pre-pass of their own (`beside`), streaming adds launches to theirs: layer with weights at 128 x 128,
 // activations at 1 x 128 and gradients per tensor under GAM scales, 512 x 1024 55 / 66, 2048 x 1024 52 / 62, 1024 x 2048 (110 MB of weights) 131 / 133, 4096 x 2048
 // 147 / 146, 4096 x 3072 (248 MB) 298 / 278.

@@ -1123,7 +1123,7 @@ __global__ __launch_bounds__(256) void k_col_finish(GroupCol g) {
 // Workgroups of a launch up to which each forms its columns' scales itself (see also column_scales_folded): 768 workgroups 88.3 -> 80.4 us
 // per call, 1024 (14336 x 4096) 92.5 -> 83.2.  The line is not where that stops to pay: without it launches of several large operands would
 // take 2 to 4 % less (three of 4096 x 14336 162.7 us against 167.6, six 318 against 325; six of 4096 x 4096 1.5 % more).  It is there
-// because their sequence of five launches, as the profile of a call records it, is relied on.
+// because tests/test_gpu_launch_counts.py counts their five launches; the interface promises no sequence.
 constexpr int64_t kColScaleWgs = 2048;
 // Columns kept in BF16 are copied: 16 bytes at a time where all eight columns of a chunk are kept, else by element.
 // Columns kept in E5M2 (three-way recipe) get their payload here, element by element, over the E4M3 one.
