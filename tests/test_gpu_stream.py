@@ -1,6 +1,5 @@
-"""Operands under GAM scales whose two passes share a launch (several of them in a call, or a large one): the same outputs, bit for bit, as
-each of them gives alone launch by launch; also where workgroups do not wait and leave their units to the launch that follows, and from
-a replayed graph."""
+"""Operands whose two passes share a launch, and operands that go along in one: the same outputs as each of them gives alone launch by launch; also where
+no wave waits to be told and all of them take the figures themselves, and from a replayed graph."""
 import ctypes as C
 
 import pytest
